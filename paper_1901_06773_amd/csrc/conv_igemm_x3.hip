@@ -1,0 +1,882 @@
+// Implicit-GEMM convolution for fp32 storage on the bf16 matrix cores (see split3.h for the
+// arithmetic), forward pass and data gradient of every layer with whole 16-channel chunks.
+//
+//   out[m][n] (+)= sum_k A[m][k] * W[n][k],   m = (img,p,q), k = (r,t,c), c fastest
+//
+// A workgroup of 4 waves (2 x 2) owns a 64*MB x 64*NB tile, each wave MB x NB blocks of 32 x 32.  The
+// operands travel global memory -> registers -> LDS: on the way every fp32 value is split into its three
+// bf16 parts, once per workgroup, and LDS holds three planes per operand, [row][KC bf16], from which a
+// fragment is one ds_read_b128 per lane.  Two LDS stages, two register sets: the loads of chunk kc+2 are
+// issued when chunk kc starts, chunk kc+1 is split and stored while chunk kc is multiplied.
+//
+// Bound: the matrix cores sustain 2.0-2.08 PFLOP/s in bf16 (their clock falls under load), a sixth of that, 333
+// TFLOP/s, in these products; the rest is LDS traffic, splitting (11 vector instructions per two values) and the
+// fixed cost of a tile.  Measured against the fp32-instruction kernel this replaces (154 TFLOP/s ceiling), forward,
+// minibatch 41: 256->256 3x3 at 14x14 75.2 -> 49.5 us, 128->128 3x3 at 28x28 74.7 -> 51.0, 512->512 3x3 at 7x7
+// 77.4 -> 65.6, 256->1024 1x1 at 14x14 38.6 -> 29.0, 1024->256 35.6 -> 30.0, 64->256 at 56x56 (minibatch 32) 38.8
+// -> 33; error against float64 5.9e-7 -> 3.5e-7 on the first of them, smaller on all.
+#include "kernels.h"
+#include "dtype.h"
+#include "igemm_side.h"
+#include "split3.h"
+
+namespace acc {
+namespace {
+
+struct RowPos {  // decoded GEMM row
+  int pix;       // img * h * wd (pixel index of the image origin)
+  int iy0, ix0;  // p*stride - pad, q*stride - pad
+  int ok;
+};
+
+__device__ __forceinline__ RowPos decode_row(const ConvGeom& g, int m, int M) {
+  RowPos rp;
+  rp.ok = m < M;
+  const int mm = rp.ok ? m : 0;
+  const int pq = g.p * g.q;
+  const int img = mm / pq;
+  const int rem = mm - img * pq;
+  const int p = rem / g.q;
+  const int q = rem - p * g.q;
+  rp.pix = img * g.h * g.wd;
+  rp.iy0 = p * g.stride - g.pad;
+  rp.ix0 = q * g.stride - g.pad - g.pad_dx;
+  return rp;
+}
+
+__device__ __forceinline__ size_t out_row_offset(const ConvGeom& g, int m) {
+  const int pq = g.p * g.q;
+  const int img = m / pq;
+  const int rem = m - img * pq;
+  const int p = rem / g.q;
+  const int q = rem - p * g.q;
+  return ((size_t)(img * g.out_h + g.out_y0 + p * g.out_stride) * g.out_w + g.out_x0 + q * g.out_stride) * g.n_out;
+}
+
+// One 32 x 32 block (rows from mr, columns from nr on) with the fp32 matrix instruction, operands straight from
+// memory: for blocks whose split products are not finite, where an infinity times the zero part of a value would
+// have made a NaN, or a finite value rounded to an infinite part.
+__device__ __forceinline__ x3_v16f plain_block(const ConvGeom& g, int mr, int nr, int M, int K, int lane) {
+  x3_v16f acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  const RowPos rp = decode_row(g, mr + (lane & 31), M);
+  const int n = nr + (lane & 31), k0 = (lane >> 5) * 4;
+  const bool col = n < g.n_out;
+  const float* w = static_cast<const float*>(g.w) + (size_t)(col ? n : 0) * K + k0;
+#pragma unroll 1
+  for (int kr = 0; kr < g.r; ++kr)
+#pragma unroll 1
+    for (int kt = 0; kt < g.s; ++kt) {
+      const int iy = rp.iy0 + kr, ix = rp.ix0 + kt;
+      const bool ok = rp.ok && (unsigned)iy < (unsigned)g.h && (unsigned)ix < (unsigned)g.wd;
+      const float* x = static_cast<const float*>(g.in) + (size_t)(ok ? rp.pix + iy * g.wd + ix : 0) * g.c + k0;
+#pragma unroll 1
+      for (int c = 0; c < g.c; c += 8) {
+        [[maybe_unused]] x3_v4f a = *reinterpret_cast<const x3_v4f*>(x + c), b = *reinterpret_cast<const x3_v4f*>(w + c);
+        if (!ok) a = x3_v4f{0.f, 0.f, 0.f, 0.f};
+        if (!col) b = x3_v4f{0.f, 0.f, 0.f, 0.f};
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc, 0, 0, 0);
+#endif
+      }
+      w += g.c;
+    }
+  return acc;
+}
+
+// Swizzled byte offset of 16-byte column `col` (0 or 1) of row `row` inside one plane: rows are 32 bytes (16 bf16),
+// and eight consecutive rows read at one column lie on different banks.
+[[maybe_unused]] __device__ __forceinline__ int plane_at(int row, int col) { return row * 32 + ((col ^ ((row >> 2) & 1)) << 4); }
+
+// What follows the products: a wave's MB x NB blocks, rows from mw and columns from nw on, are summed for a
+// batch norm, masked, added to, biased and stored as the launch asks.
+template <int MB, int NB, bool ACT>
+__device__ __forceinline__ void x3_finish(const ConvGeom& g, int M, int K, int mw, int nw, int lane, x3_v16f (&acc)[MB][NB]) {
+  const int half = lane >> 5;
+  if (x3_any_nonfinite<MB, NB>(acc)) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int jj = 0; jj < NB; ++jj) acc[i][jj] = plain_block(g, mw + 32 * i, nw + 32 * jj, M, K, lane);
+  }
+
+  // epilogue: accumulator register v of a lane holds row 8*(v/4) + 4*(lane/32) + v%4,
+  // column lane%32 of its 32x32 block
+  const bool dense = g.out_stride == 1 && g.out_h == g.p && g.out_w == g.q;
+#pragma unroll
+  for (int jj = 0; jj < NB; ++jj) {
+    const int n = nw + 32 * jj + (lane & 31);
+    const bool col = n < g.n_out;
+    float bias_n = 0.f;
+    if constexpr (ACT) bias_n = col && g.bias ? g.bias[n] : 0.f;
+    float mu = 0.f, is = 0.f;
+    if (!ACT && g.bnb.sums && col) { mu = g.bnb.mean[n]; is = g.bnb.istd[n]; }
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const int mr = mw + 32 * i;                  // first row of the block
+      if (mr >= ((M + 63) & ~63)) continue;              // (uniform) neither results nor sums: those come in pairs of blocks
+      x3_v16f& c = acc[i][jj];
+      const size_t slab = (size_t)(mr >> 5);             // 32-row block of the whole result
+      const int mb = mr + 4 * half;
+      const bool whole = mr + 32 <= M;
+      // the lane's first row; its other rows lie dr = 8*(v/4) + v%4 rows further on, a distance
+      // that is the same for every lane
+      const int left = !col ? 0 : whole ? 32 : M - mb;   // rows of the lane that exist, counted from mb
+      const size_t at0 = (size_t)(mb < M ? mb : 0) * g.n_out + (col ? n : 0);
+      if (!ACT && g.stats) {
+        // sums of the column and of its squares over the 32 rows (rows beyond M are exact zeros),
+        // for the batch norm that follows.  Fixed order: the lane's 16 values, then the partner lane.
+        float sum = 0.f, sq = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          sum += c[v];
+          sq = fmaf(c[v], c[v], sq);
+        }
+        sum += __shfl_xor(sum, 32);
+        sq += __shfl_xor(sq, 32);
+        if (lane < 32 && col) {
+          g.stats[slab * g.n_out + n] = sum;
+          g.stats[((size_t)g.stats_stride + slab) * g.n_out + n] = sq;
+        }
+      }
+      if (!ACT && g.bnb.sums) {
+        // Data gradient whose result is the gradient of a batch norm's ReLU output: mask it with
+        // [y > 0] and leave the sums of g and g * xhat over the 32 rows for that batch norm's backward pass.
+        const float* bx = static_cast<const float*>(g.bnb.x) + at0;
+        const float* by = static_cast<const float*>(g.bnb.y) + at0;
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int dr = 8 * (v >> 2) + (v & 3);
+          float gv = 0.f, xh = 0.f;
+          if (dr < left) {
+            const size_t at = (size_t)dr * g.n_out;
+            gv = by[at] > 0.f ? c[v] : 0.f;
+            xh = (bx[at] - mu) * is;
+          }
+          c[v] = gv;
+          s0 += gv;
+          s1 = fmaf(gv, xh, s1);
+        }
+        s0 += __shfl_xor(s0, 32);
+        s1 += __shfl_xor(s1, 32);
+        if (lane < 32 && col) {
+          g.bnb.sums[slab * g.n_out + n] = s0;
+          g.bnb.sums[((size_t)g.bnb.stride + slab) * g.n_out + n] = s1;
+        }
+      }
+      if (dense) {
+        float* o0 = static_cast<float*>(g.out) + at0;
+        if (!ACT && g.accumulate) {
+          float old[16];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int dr = 8 * (v >> 2) + (v & 3);
+            old[v] = dr < left ? o0[(size_t)dr * g.n_out] : 0.f;
+          }
+#pragma unroll
+          for (int v = 0; v < 16; ++v) c[v] += old[v];
+        }
+        if constexpr (ACT) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            c[v] += bias_n;
+            if (g.relu) c[v] = fmaxf(c[v], 0.f);
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int dr = 8 * (v >> 2) + (v & 3);
+          if (dr < left) o0[(size_t)dr * g.n_out] = c[v];
+        }
+        continue;
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = mb + 8 * (v >> 2) + (v & 3);
+        if (m >= M || !col) continue;
+        float* o = static_cast<float*>(g.out) + out_row_offset(g, m) + n;
+        float val = c[v];
+        if constexpr (ACT) {
+          val += bias_n;
+          if (g.relu) val = fmaxf(val, 0.f);
+        } else {
+          if (g.accumulate) val += *o;
+        }
+        *o = val;
+      }
+    }
+  }
+}
+
+template <int MB, int NB, bool ACT>
+__global__ __launch_bounds__(256, 2) void igemm_x3_kernel(ConvGeom g, int M, int K, int n_tiles_n,
+                                                                              int n_tiles, int main_grid) {
+  constexpr int BM = 64 * MB, BN = 64 * NB, KC = 16;
+  constexpr int ROWB = KC * 2;                           // bytes per row and plane
+  constexpr int A_PLANE = BM * ROWB, B_PLANE = BN * ROWB;
+  constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
+  static_assert(2 * STAGE >= 32 * 33 * 4, "side jobs");
+  __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE];
+
+  if ((int)blockIdx.x >= main_grid) {
+    igemm_side_jobs<float>(g, (int)blockIdx.x - main_grid, lds);
+    return;
+  }
+#if defined(__HIP_DEVICE_COMPILE__)
+  // Forward products and data gradients are the critical path of an iteration; a weight gradient may run
+  // beside them on a stream of its own at the default wave priority.
+  __builtin_amdgcn_s_setprio(3);
+  // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a
+  // contiguous range of tiles (neighbouring tiles share operand rows in its L2).
+  const int per_xcd = main_grid >> 3;
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (tile >= n_tiles) return;
+  const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm0 = (wave >> 1) * 32 * MB, wn0 = (wave & 1) * 32 * NB;
+
+  x3_v16f acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  const int n_chunks = K / KC;                           // whole chunks only (launcher)
+  constexpr int TPR = KC / 4;                            // threads per row (16 bytes of fp32 each)
+  constexpr int RPP = 256 / TPR;                         // rows per pass
+  constexpr int AI = BM / RPP, BI = BN / RPP;
+  const int lrow = tid / TPR, lk4 = tid & (TPR - 1);
+  const int margin = g.pad * g.wd + g.pad + g.pad_dx;    // pixels; the descriptor starts that far before the tensor
+  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;              // beyond any descriptor range: reads as zero
+  uint32_t a_voff[AI], a_mask[AI], b_voff[BI];
+  // 1x1, stride 1, no padding: GEMM row m is pixel m, nothing to decode
+  const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 && g.pad_dx == 0 && g.p == g.h && g.q == g.wd;
+#pragma unroll
+  for (int i = 0; i < AI; ++i) {
+    const int m = m0 + lrow + RPP * i;
+    if (plain) {
+      a_voff[i] = (uint32_t)(m < M ? m : 0) * (uint32_t)(g.c * 4) + lk4 * 16;
+      a_mask[i] = m < M ? 1u : 0u;
+      continue;
+    }
+    const RowPos rp = decode_row(g, m, M);
+    a_voff[i] = (uint32_t)(rp.pix + rp.iy0 * g.wd + rp.ix0 + margin) * (uint32_t)(g.c * 4) + lk4 * 16;
+    uint32_t mask = 0;
+    for (int kr = 0; kr < g.r; ++kr)
+      for (int kt = 0; kt < g.s; ++kt) {
+        const bool ok = rp.ok && (unsigned)(rp.iy0 + kr) < (unsigned)g.h && (unsigned)(rp.ix0 + kt) < (unsigned)g.wd;
+        mask |= (ok ? 1u : 0u) << (kr * g.s + kt);
+      }
+    a_mask[i] = mask;
+  }
+#pragma unroll
+  for (int i = 0; i < BI; ++i) {
+    const int n = n0 + lrow + RPP * i;
+    b_voff[i] = n < g.n_out ? (uint32_t)n * (uint32_t)(K * 4) + lk4 * 16 : OUTSIDE;
+  }
+  const size_t margin_bytes = (size_t)margin * g.c * 4;
+  const size_t a_bytes = margin_bytes + (size_t)g.n_img * g.h * g.wd * g.c * 4;
+  __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(reinterpret_cast<const char*>(g.in)) - margin_bytes, 0, (int)(uint32_t)a_bytes, 0x00020000);
+  __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(g.w), 0, (int)(uint32_t)((size_t)g.n_out * K * 4), 0x00020000);
+
+  struct Regs { x3_v4u a[AI], b[BI]; } R0, R1;
+  int kr = 0, kt = 0, c0 = 0, kb = 0;     // tap, channel offset and filter offset of the chunk whose loads are issued next (uniform)
+  auto advance = [&]() {
+    kb += KC * 4;
+    c0 += KC;
+    if (c0 == g.c) {
+      c0 = 0;
+      if (++kt == g.s) { kt = 0; ++kr; }
+    }
+  };
+  auto load = [&](Regs& R) {
+    const int tap = kr * g.s + kt;
+    const int soff_a = ((kr * g.wd + kt) * g.c + c0) * 4;
+#pragma unroll
+    for (int i = 0; i < AI; ++i)
+      R.a[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, ((a_mask[i] >> tap) & 1u) ? a_voff[i] : OUTSIDE, soff_a, 0);
+#pragma unroll
+    for (int i = 0; i < BI; ++i) R.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_b, b_voff[i], kb, 0);
+    advance();
+  };
+  const int st_at = plane_at(lrow, lk4 >> 1) + (lk4 & 1) * 8;   // rows RPP further on keep the swizzle
+  static_assert(RPP % 8 == 0, "swizzle period");
+  auto put = [&](const x3_v4u& x, char* at, int plane) {
+    uint32_t h0, m0_, l0, h1, m1_, l1;
+    x3_split(__uint_as_float(x[0]), __uint_as_float(x[1]), h0, m0_, l0);
+    x3_split(__uint_as_float(x[2]), __uint_as_float(x[3]), h1, m1_, l1);
+    *reinterpret_cast<x3_v2u*>(at) = x3_v2u{h0, h1};
+    *reinterpret_cast<x3_v2u*>(at + plane) = x3_v2u{m0_, m1_};
+    *reinterpret_cast<x3_v2u*>(at + 2 * plane) = x3_v2u{l0, l1};
+  };
+  auto store = [&](const Regs& R, int buf) {
+    char* as = lds + buf * STAGE + st_at;
+#pragma unroll
+    for (int i = 0; i < AI; ++i) put(R.a[i], as + i * RPP * ROWB, A_PLANE);
+    char* bs = as + 3 * A_PLANE;
+#pragma unroll
+    for (int i = 0; i < BI; ++i) put(R.b[i], bs + i * RPP * ROWB, B_PLANE);
+  };
+  const int fra = wm0 + (lane & 31), frb = wn0 + (lane & 31), half = lane >> 5;
+  // The largest product of a step, h*h, goes into one set of accumulators, the five small ones into another:
+  // an addition to the large sum rounds once per 16 products, and the small sums' roundings are 2^8 smaller.
+  x3_v16f accs[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) accs[i][j][v] = 0.f;
+  // One step: the chunk in LDS stage `buf` is multiplied, the chunk in registers R is split and stored into the
+  // other stage.  The h*h products of the chunk before are held back (ph_a, ph_b) until this chunk's fragments
+  // have been requested; the splitting is spread over the matrix instructions.
+  x3_v4u ph_a[1][MB], ph_b[1][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) ph_a[0][i] = x3_v4u{0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < NB; ++j) ph_b[0][j] = x3_v4u{0, 0, 0, 0};
+  auto held = [&]() {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int jj = 0; jj < NB; ++jj) acc[i][jj] = x3_mfma(ph_a[0][i], ph_b[0][jj], acc[i][jj]);
+  };
+  auto step = [&](int buf, const Regs* R, Regs* L) {
+    const char* as = lds + buf * STAGE + plane_at(fra, half);
+    const char* bs = lds + buf * STAGE + 3 * A_PLANE + plane_at(frb, half);
+    x3_v4u a[3][MB], b[3][NB];
+    auto rd_a = [&](int p) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) a[p][i] = *reinterpret_cast<const x3_v4u*>(as + p * A_PLANE + i * 32 * ROWB);
+    };
+    auto rd_b = [&](int p) {
+#pragma unroll
+      for (int jj = 0; jj < NB; ++jj) b[p][jj] = *reinterpret_cast<const x3_v4u*>(bs + p * B_PLANE + jj * 32 * ROWB);
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    rd_a(2); rd_b(0); rd_a(0); rd_b(2); rd_a(1); rd_b(1);
+    __builtin_amdgcn_sched_barrier(0);
+    held();
+    if (L) load(*L);
+    if (R) store(*R, buf ^ 1);
+    x3_product<2, 0, MB, NB>(a, b, accs);
+    x3_product<0, 2, MB, NB>(a, b, accs);
+    x3_product<1, 1, MB, NB>(a, b, accs);
+    x3_product<1, 0, MB, NB>(a, b, accs);
+    x3_product<0, 1, MB, NB>(a, b, accs);
+#pragma unroll
+    for (int i = 0; i < MB; ++i) ph_a[0][i] = a[0][i];
+#pragma unroll
+    for (int jj = 0; jj < NB; ++jj) ph_b[0][jj] = b[0][jj];
+    if (R) {
+      constexpr int V = (22 * (AI + BI) + 6 * MB * NB - 1) / (6 * MB * NB) + 1;     // vector instructions per matrix instruction
+#pragma unroll
+      for (int u = 0; u < 6 * MB * NB; ++u) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+        if (u == 0 && L) __builtin_amdgcn_sched_group_barrier(0x020, AI + BI, 0);
+        if (u % (2 * MB * NB) == 2 * MB * NB - 1) __builtin_amdgcn_sched_group_barrier(0x200, AI + BI, 0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // One barrier per chunk: it says that chunk kc+1 is in LDS and that everybody is done with chunk kc,
+  // whose stage chunk kc+2 may overwrite.
+  load(R0);
+  if (n_chunks > 1) load(R1);
+  store(R0, 0);
+  __syncthreads();
+  int j = 0;
+  for (; j + 4 <= n_chunks; j += 2) {        // steady state: every load and store unconditional
+    step(0, &R1, &R0);
+    __syncthreads();
+    step(1, &R0, &R1);
+    __syncthreads();
+  }
+  for (; j < n_chunks; j += 2) {
+    if (j + 2 < n_chunks) load(R0);
+    step(0, nullptr, nullptr);
+    if (j + 1 < n_chunks) store(R1, 1);
+    __syncthreads();
+    if (j + 1 >= n_chunks) break;
+    if (j + 3 < n_chunks) load(R1);
+    step(1, nullptr, nullptr);
+    if (j + 2 < n_chunks) store(R0, 0);
+    __syncthreads();
+  }
+  held();
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int jj = 0; jj < NB; ++jj) acc[i][jj] += accs[i][jj];
+  x3_finish<MB, NB, ACT>(g, M, K, m0 + wm0, n0 + wn0, lane, acc);
+#else
+  (void)&decode_row; (void)&out_row_offset; (void)&plain_block;
+#endif
+}
+
+
+// ---- long reductions: eight waves, each 64 x 64 (2 x 2 blocks), the steps of K dealt out to groups of waves
+//
+// What a step costs besides its 24 matrix instructions per wave is LDS traffic (12 KB read per wave, 96 bytes
+// per operand row written) and the splitting of the operand rows, so a wave's tile is as large as its
+// registers allow, and a tile of 64*WM x 64*WN is shared by KS = 8 / (WM*WN) groups that take every KS-th
+// step: the chip is filled by tiles x KS even where the minibatch gives few tiles.  Fragments are fetched one
+// step ahead: while step j is multiplied out of registers, step j+1 is read from LDS, step j+2 is split and
+// stored, later loads are issued.  Nothing in a step waits for anything else of that step.  At the end the groups exchange their sums through LDS, each adding
+// up and writing some of the blocks.
+//
+// WINDOW: stride-1 convolutions with r x r > 1 taps whose output has the size of the input.  GEMM row m is
+// pixel m there, and tap (kr, kt) reads pixel m + (kr - pad) * wd + (kt - pad): for the rows of a tile all taps
+// read one window of consecutive pixels.  The window's 16 channels of a step are fetched, split and stored
+// once, by the whole workgroup, and serve all r*r taps and all groups; a lane whose tap falls into the padding
+// is pointed at a row of zeros.
+template <int WM, int WN, bool WINDOW>
+struct Deep {
+  static constexpr int KS = 8 / (WM * WN), GT = 64 * WM * WN;        // groups, threads of a group
+  static constexpr int BM = 64 * WM, BN = 64 * WN;
+  static constexpr int WROWS = 256, WPLANE = (WROWS + 1) * 32, WBUF = WINDOW ? 3 * WPLANE : 0;   // largest window, a row of zeros
+  static constexpr int AP = WINDOW ? 0 : BM * 32, BP = BN * 32, STAGE = 3 * (AP + BP);
+  static constexpr int NST = GT == 64 ? 1 : 2;                       // a group of one wave needs no second stage: its LDS accesses keep their order
+  static constexpr int MAIN = 2 * WBUF + KS * NST * STAGE;
+  static constexpr int NQ = KS < 4 ? KS : 4, BPQ = 4 / NQ;           // groups that finish blocks, blocks each
+  static constexpr int RED = NQ * (KS - 1) * WM * WN * BPQ * 16 * 64 * 4;
+  static constexpr int LDS = MAIN > RED ? MAIN : RED;
+};
+
+template <int WM, int WN, bool WINDOW, bool ACT>
+__global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles, int main_grid) {
+  using D = Deep<WM, WN, WINDOW>;
+  [[maybe_unused]] constexpr int KS = D::KS, GT = D::GT;
+  __shared__ __attribute__((aligned(1024))) char lds[D::LDS];
+  if ((int)blockIdx.x >= main_grid) {
+    // the side jobs are written for 256 threads (a barrier counts the waves that are still there)
+    if (threadIdx.x < 256) igemm_side_jobs<float>(g, (int)blockIdx.x - main_grid, lds);
+    return;
+  }
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_s_setprio(3);
+  const int per_xcd = main_grid >> 3;
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (tile >= n_tiles) return;
+  const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
+  const int m0 = tile_m * D::BM, n0 = tile_n * D::BN;
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+  const int grp = __builtin_amdgcn_readfirstlane(tid / GT), gt = tid & (GT - 1);
+  const int gw = __builtin_amdgcn_readfirstlane((tid >> 6) & (WM * WN - 1));   // wave of the group
+  const int wm0 = (gw / WN) * 64, wn0 = (gw % WN) * 64;
+  const int taps = g.r * g.s, n_steps = K >> 4;
+  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;              // beyond any descriptor range: reads as zero
+  const int margin = WINDOW ? 0 : g.pad * g.wd + g.pad + g.pad_dx;   // pixels; the descriptor starts that far before the tensor
+  const size_t margin_bytes = (size_t)margin * g.c * 4;
+  __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(reinterpret_cast<const char*>(g.in)) - margin_bytes, 0,
+      (int)(uint32_t)(margin_bytes + (size_t)g.n_img * g.h * g.wd * g.c * 4), 0x00020000);
+  __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(g.w), 0, (int)(uint32_t)((size_t)g.n_out * K * 4), 0x00020000);
+  auto tap_mask = [&](const RowPos& rp) {
+    uint32_t mk = 0;
+    for (int kr = 0; kr < g.r; ++kr)
+      for (int kt = 0; kt < g.s; ++kt) {
+        const bool ok = rp.ok && (unsigned)(rp.iy0 + kr) < (unsigned)g.h && (unsigned)(rp.ix0 + kt) < (unsigned)g.wd;
+        mk |= (ok ? 1u : 0u) << (kr * g.s + kt);
+      }
+    return mk;
+  };
+
+  // ---- loads: 16 bytes (four values of K) per thread and row
+  constexpr int RPP = GT / 4, AI = WINDOW ? 0 : D::BM / RPP, BI = D::BN / RPP;   // rows per pass of the group; passes
+  constexpr int AN = AI > 0 ? AI : 1;
+  uint32_t a_voff[AN], a_mask[AN], b_voff[BI];
+  const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 && g.pad_dx == 0 && g.p == g.h && g.q == g.wd;
+#pragma unroll
+  for (int i = 0; i < AI; ++i) {
+    const int m = m0 + (gt >> 2) + RPP * i;
+    if (plain) {      // 1x1, stride 1, no padding: GEMM row m is pixel m
+      a_voff[i] = (uint32_t)(m < M ? m : 0) * (uint32_t)(g.c * 4) + (gt & 3) * 16;
+      a_mask[i] = m < M ? 1u : 0u;
+      continue;
+    }
+    const RowPos rp = decode_row(g, m, M);
+    a_voff[i] = (uint32_t)(rp.pix + rp.iy0 * g.wd + rp.ix0 + margin) * (uint32_t)(g.c * 4) + (gt & 3) * 16;
+    a_mask[i] = tap_mask(rp);
+  }
+#pragma unroll
+  for (int i = 0; i < BI; ++i) {
+    const int n = n0 + (gt >> 2) + RPP * i;
+    b_voff[i] = n < g.n_out ? (uint32_t)n * (uint32_t)(K * 4) + (gt & 3) * 16 : OUTSIDE;
+  }
+  // One register set where a thread loads eight vectors per step, else two.
+  constexpr int NR = AI + BI > 6 ? 1 : 2;
+  struct Regs { x3_v4u a[AN], b[BI]; } R0, R1_;
+  Regs& R1 = NR == 2 ? R1_ : R0;
+  // The group's steps.  WINDOW: every KS-th of the sequence in which the taps run fastest.  Else: a range of the
+  // sequence in which the channels run fastest (the next tap of a filter row continues where the channels of the
+  // one before end, so offsets only jump from one filter row to the next).
+  const int first = WINDOW ? grp : (int)((long)n_steps * grp / KS);
+  const int mine = WINDOW ? (n_steps - grp + KS - 1) / KS : (int)((long)n_steps * (grp + 1) / KS) - first;
+  const int rounds = (n_steps + KS - 1) / KS;            // the most steps of any group
+  int lw, ltap, lkt, lc, soff_a = 0, soff_b = 0;
+  if constexpr (WINDOW) {
+    lw = first / taps; ltap = first - lw * taps;
+    lkt = lc = 0;
+  } else {
+    const int spt = g.c >> 4;
+    ltap = first / spt; lc = (first - ltap * spt) * 16;
+    lkt = ltap % g.s; lw = 0;
+    soff_a = (((ltap / g.s) * g.wd + lkt) * g.c + lc) * 4;
+    soff_b = first * 64;
+  }
+  const int row_jump = (g.wd - g.s) * g.c * 4;
+  int cw = lw, ctap = ltap, ckr = ctap / g.s, ckt = ctap - (ctap / g.s) * g.s;   // WINDOW: the step that is read from LDS next
+  auto load = [&](Regs& R) {
+    if constexpr (WINDOW) {
+      const int so = (ltap * g.c + lw * 16) * 4;
+#pragma unroll
+      for (int i = 0; i < BI; ++i) R.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_b, b_voff[i], so, 0);
+      ltap += KS;                  // KS <= taps
+      const bool wrap = ltap >= taps;
+      ltap -= wrap ? taps : 0;
+      lw += wrap ? 1 : 0;
+    } else {
+#pragma unroll
+      for (int i = 0; i < AI; ++i)
+        R.a[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, ((a_mask[i] >> ltap) & 1u) ? a_voff[i] : OUTSIDE, soff_a, 0);
+#pragma unroll
+      for (int i = 0; i < BI; ++i) R.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_b, b_voff[i], soff_b, 0);
+      soff_b += 64;
+      lc += 16;
+      const bool wrap = lc == g.c;
+      lc = wrap ? 0 : lc;
+      ltap += wrap ? 1 : 0;
+      lkt += wrap ? 1 : 0;
+      const bool down = lkt == g.s;
+      lkt = down ? 0 : lkt;
+      soff_a += 64 + (down ? row_jump : 0);
+    }
+  };
+  // ---- split and store
+  auto put = [&](const x3_v4u& x, char* at, int plane) {
+    uint32_t h0, m0_, l0, h1, m1_, l1;
+    x3_split(__uint_as_float(x[0]), __uint_as_float(x[1]), h0, m0_, l0);
+    x3_split(__uint_as_float(x[2]), __uint_as_float(x[3]), h1, m1_, l1);
+    *reinterpret_cast<x3_v2u*>(at) = x3_v2u{h0, h1};
+    *reinterpret_cast<x3_v2u*>(at + plane) = x3_v2u{m0_, m1_};
+    *reinterpret_cast<x3_v2u*>(at + 2 * plane) = x3_v2u{l0, l1};
+  };
+  char* const lds_g = lds + 2 * D::WBUF + grp * (D::NST * D::STAGE);
+  static_assert(RPP % 8 == 0, "swizzle period");
+  const int st_at = plane_at(gt >> 2, (gt & 3) >> 1) + (gt & 1) * 8;
+  auto store = [&](const Regs& R, int buf) {
+    char* as = lds_g + (buf & (D::NST - 1)) * D::STAGE + st_at;
+#pragma unroll
+    for (int i = 0; i < AI; ++i) put(R.a[i], as + i * RPP * 32, D::AP);
+    char* bs = as + 3 * D::AP;
+#pragma unroll
+    for (int i = 0; i < BI; ++i) put(R.b[i], bs + i * RPP * 32, D::BP);
+  };
+  // ---- the window: thread -> 16 bytes of rows tid/4 and tid/4 + 128
+  x3_v4u W[2];
+  uint32_t w_voff[2], mask[2];
+  const int w_at = plane_at(tid >> 2, (tid & 3) >> 1) + (tid & 1) * 8;
+  if constexpr (WINDOW) {
+    const int reach = g.pad * g.wd + g.pad;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = (tid >> 2) + 128 * i, px = m0 - reach + row;
+      w_voff[i] = row < D::BM + 2 * reach && px >= 0 && px < M ? (uint32_t)px * (uint32_t)(g.c * 4) + (tid & 3) * 16 : OUTSIDE;
+      mask[i] = tap_mask(decode_row(g, m0 + wm0 + 32 * i + (lane & 31), M));
+    }
+    if (tid < 12)      // the rows of zeros, one per stage and plane
+      *reinterpret_cast<x3_v4u*>(lds + (tid / 6) * D::WBUF + ((tid % 6) >> 1) * D::WPLANE + D::WROWS * 32 + (tid & 1) * 16) = x3_v4u{0, 0, 0, 0};
+  }
+  auto load_window = [&](int w) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) W[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, w_voff[i], w * 64, 0);
+  };
+  auto store_window = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) put(W[i], lds + buf * D::WBUF + w_at + i * (128 * 32), D::WPLANE);
+  };
+  // ---- fragments and products
+  struct Frags { x3_v4u a[3][2], b[3][2]; } F0, F1;
+  const int fa_at = plane_at(wm0 + (lane & 31), half), fb_at = plane_at(wn0 + (lane & 31), half);
+  int at[2] = {fa_at, fa_at + 32 * 32};
+  const char* wb = lds;
+  auto aim = [&]() {               // WINDOW: where the next step's rows lie
+    if constexpr (WINDOW) {
+      const int shift = ckr * g.wd + ckt;
+      wb = lds + (cw & 1) * D::WBUF;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        at[i] = plane_at((mask[i] >> ctap) & 1u ? wm0 + (lane & 31) + 32 * i + shift : D::WROWS, half);
+      ctap += KS; ckt += KS;
+      while (ckt >= g.s) { ckt -= g.s; ++ckr; }
+      if (ctap >= taps) { ctap -= taps; ++cw; ckr -= g.r; }
+    }
+  };
+  auto read = [&](Frags& F, int buf) {
+    const char* st = lds_g + (buf & (D::NST - 1)) * D::STAGE;
+    const char* as = WINDOW ? wb : st;
+    const char* bs = st + 3 * D::AP + fb_at;
+    constexpr int APL = WINDOW ? D::WPLANE : D::AP;
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        F.a[p][i] = *reinterpret_cast<const x3_v4u*>(as + p * APL + at[i]);
+        F.b[p][i] = *reinterpret_cast<const x3_v4u*>(bs + p * D::BP + i * (32 * 32));
+      }
+  };
+  x3_v16f acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  auto multiply = [&](const Frags& F) {
+    x3_product<2, 0, 2, 2>(F.a, F.b, acc);
+    x3_product<0, 2, 2, 2>(F.a, F.b, acc);
+    x3_product<1, 1, 2, 2>(F.a, F.b, acc);
+    x3_product<1, 0, 2, 2>(F.a, F.b, acc);
+    x3_product<0, 1, 2, 2>(F.a, F.b, acc);
+    x3_product<0, 0, 2, 2>(F.a, F.b, acc);
+  };
+  auto sync = [&]() {              // a group of one wave shares nothing with the others but the window
+    if constexpr (D::NST == 2 || WINDOW) __syncthreads();
+  };
+  // Step j: fragments F multiplied, fragments of j+1 read from stage (j+1)&1 into G, step j+2 (in R) stored into
+  // stage j&1, whose last reader was step j-1's read of j; its registers are loaded with step j+2+NR.
+  auto step = [&](const Frags& F, Frags& G, Regs& R, int par) {
+    aim();
+    __builtin_amdgcn_sched_barrier(0);
+    read(G, par ^ 1);
+    store(R, par);
+    load(R);
+    multiply(F);
+    constexpr int V = (22 * (AI + BI) + 23) / 24 + (AI + BI) / 6;
+#pragma unroll
+    for (int u = 0; u < 24; ++u) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (u < 12) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+      if (u >= 12) __builtin_amdgcn_sched_group_barrier(0x200, (3 * (AI + BI) + 23) / 24, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Window w + 1 goes into the stage of window w - 1: from the round on after the last step of w - 1 has been
+  // read, one round before its own first step is read (taps >= 2 * KS - 1 steps per window).  Step s is read
+  // in round s / KS - 1.
+  const int n_win = g.c >> 4;
+  int w_next = 1, w_round = -1;
+  auto window = [&](int round) {
+    if constexpr (WINDOW) {
+      if (round == w_round && w_next < n_win) {
+        store_window(w_next & 1);
+        if (w_next + 1 < n_win) load_window(w_next + 1);
+        w_round = (taps * w_next - 1) / KS;
+        ++w_next;
+      }
+    }
+  };
+  if constexpr (WINDOW) load_window(0);
+  if (mine > 0) load(R0);
+  if (NR == 2 && mine > 1) load(R1);
+  if constexpr (WINDOW) {
+    store_window(0);
+    if (n_win > 1) load_window(1);
+  }
+  if (mine > 0) store(R0, 0);
+  if (mine > NR) load(R0);
+  sync();
+  window(-1);
+  aim();
+  if (mine > 0) read(F0, 0);
+  if (mine > 1) store(R1, 1);
+  if (mine > NR + 1) load(R1);
+  sync();
+  int j = 0;
+  for (; j + 4 + NR <= mine; j += 2) {   // steady state: every load and store unconditional
+    window(j);
+    step(F0, F1, R0, 0);
+    sync();
+    window(j + 1);
+    step(F1, F0, R1, 1);
+    sync();
+  }
+  for (; j < rounds; j += 2) {
+    window(j);
+    aim();
+    if (j + 1 < mine) read(F1, 1);
+    if (j + 2 < mine) store(R0, 0);
+    if (j + 2 + NR < mine) load(R0);
+    if (j < mine) multiply(F0);
+    sync();
+    if (j + 1 >= rounds) break;
+    window(j + 1);
+    aim();
+    if (j + 2 < mine) read(F0, 0);
+    if (j + 3 < mine) store(R1, 1);
+    if (j + 3 + NR < mine) load(R1);
+    if (j + 1 < mine) multiply(F1);
+    sync();
+  }
+  // ---- group q < NQ adds up the blocks BPQ*q ... of all wave positions, the groups' sums in their order after its own
+  constexpr int BLK = 16 * 64, PER = WM * WN * D::BPQ * BLK;      // floats of a block, of one (to, from) pair of groups
+  float* const red = reinterpret_cast<float*>(lds) + gw * (D::BPQ * BLK) + lane;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < D::NQ; ++q) {
+    if (q == grp) continue;
+    float* to = red + (q * (KS - 1) + (grp < q ? grp : grp - 1)) * PER;
+#pragma unroll
+    for (int b = 0; b < D::BPQ; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) to[b * BLK + v * 64] = acc[(q * D::BPQ + b) >> 1][(q * D::BPQ + b) & 1][v];
+  }
+  __syncthreads();
+  if (KS > D::NQ && grp >= D::NQ) return;
+  x3_v16f c[1][D::BPQ];            // BPQ = 2: one row block, two column blocks; BPQ = 1: one block
+#pragma unroll
+  for (int q = 0; q < D::NQ; ++q)
+    if (q == grp) {
+#pragma unroll
+      for (int b = 0; b < D::BPQ; ++b) c[0][b] = acc[(q * D::BPQ + b) >> 1][(q * D::BPQ + b) & 1];
+    }
+#pragma unroll
+  for (int u = 0; u < KS - 1; ++u)
+#pragma unroll
+    for (int b = 0; b < D::BPQ; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) c[0][b][v] += red[(grp * (KS - 1) + u) * PER + b * BLK + v * 64];
+  const int blk = grp * D::BPQ;
+  x3_finish<1, D::BPQ, ACT>(g, M, K, m0 + wm0 + 32 * (blk >> 1), n0 + wn0 + 32 * (blk & 1), lane, c);
+#else
+  (void)&decode_row;
+#endif
+}
+
+template <int WM, int WN, bool WINDOW>
+void launch_deep(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe, long side_blocks) {
+  using D = Deep<WM, WN, WINDOW>;
+  const int tm = (M + D::BM - 1) / D::BM, tn = (g.n_out + D::BN - 1) / D::BN;
+  const int tiles = tm * tn, main_grid = (tiles + 7) / 8 * 8;
+  const dim3 grid((unsigned)(main_grid + side_blocks));
+  if (probe->before) (void)hipEventRecord(probe->before, st);
+  if (g.bias || g.relu)
+    hipLaunchKernelGGL((igemm_x3_deep_kernel<WM, WN, WINDOW, true>), grid, dim3(512), 0, st, g, M, K, tn, tiles, main_grid);
+  else
+    hipLaunchKernelGGL((igemm_x3_deep_kernel<WM, WN, WINDOW, false>), grid, dim3(512), 0, st, g, M, K, tn, tiles, main_grid);
+  if (probe->after) (void)hipEventRecord(probe->after, st);
+}
+
+template <int MB, int NB>
+void launch_short(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe, long side_blocks) {
+  const int tm = (M + 64 * MB - 1) / (64 * MB), tn = (g.n_out + 64 * NB - 1) / (64 * NB);
+  const int tiles = tm * tn, main_grid = (tiles + 7) / 8 * 8;
+  const dim3 grid((unsigned)(main_grid + side_blocks));
+  if (probe->before) (void)hipEventRecord(probe->before, st);
+  if (g.bias || g.relu)
+    hipLaunchKernelGGL((igemm_x3_kernel<MB, NB, true>), grid, dim3(256), 0, st, g, M, K, tn, tiles, main_grid);
+  else
+    hipLaunchKernelGGL((igemm_x3_kernel<MB, NB, false>), grid, dim3(256), 0, st, g, M, K, tn, tiles, main_grid);
+  if (probe->after) (void)hipEventRecord(probe->after, st);
+}
+
+// Which kernel: a launch is predicted to take, on the compute unit with the most tiles,
+//   base + sum over rounds of max(alone + alone_step * steps, r * (shared + shared_step * steps))   [microseconds]
+// with steps = 16-element steps of K per group of waves and r <= per_cu tiles resident together, and the kernel with
+// the smallest prediction runs.  The constants are fitted to measured launches (124 shapes: the layers of the
+// ResNets at minibatches 4 to 128 and random ones, every kernel on each): median error 2-10 %, and the choice is
+// within 1.5 % of the best of the six on average.  A function of the shape and the alignment only, never of the
+// swap plan (pool offsets are multiples of 256).
+struct Kind {
+  int bm, bn, ks, per_cu;
+  double alone, alone_step, shared, shared_step, base;
+};
+enum { X3_128 = 0, X3_64, X3_WINDOW, X3_DEEP_2x1, X3_DEEP_2x2, X3_DEEP_1x1, X3_KINDS };
+constexpr Kind kKinds[X3_KINDS] = {
+    {128, 128, 1, 2, 3.54, 0.618, 2.90, 0.581, 2.7},   // igemm_x3_kernel<2, 2>
+    {64, 64, 1, 5, 1.75, 0.278, 0.40, 0.215, 3.6},     // igemm_x3_kernel<1, 1>
+    {128, 64, 4, 1, 8.39, 1.039, 8.39, 1.039, -1.8},   // igemm_x3_deep_kernel<2, 1, window>
+    {128, 64, 4, 1, 5.38, 1.315, 5.38, 1.315, 0.5},    // igemm_x3_deep_kernel<2, 1>
+    {128, 128, 2, 1, 6.74, 0.966, 6.74, 0.966, -0.1},  // igemm_x3_deep_kernel<2, 2>
+    {64, 64, 8, 1, 3.90, 1.704, 3.90, 1.704, 1.3},     // igemm_x3_deep_kernel<1, 1>
+};
+double predicted_us(const Kind& k, long M, long N, long K) {
+  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = (K / 16 + k.ks - 1) / k.ks;
+  const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
+  auto round = [&](long r) {
+    const double alone = k.alone + k.alone_step * steps, shared = r * (k.shared + k.shared_step * steps);
+    return r == 0 ? 0.0 : alone > shared ? alone : shared;
+  };
+  return k.base + (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu);
+}
+
+// the launches that read every tap from one window of consecutive pixels, if it fits
+bool window_takes(const ConvGeom& g) {
+  using D = Deep<2, 1, true>;
+  return g.r == g.s && g.r * g.s >= 2 * D::KS - 1 && g.stride == 1 && 2 * g.pad == g.r - 1 && g.pad_dx == 0 &&
+         g.p == g.h && g.q == g.wd && D::BM + 2 * (g.pad * g.wd + g.pad) <= D::WROWS;
+}
+
+}  // namespace
+
+bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K) {
+  if (g.dtype != DT_F32 || g.c % 16 != 0 || g.r * g.s > 32) return false;
+  // both operands within 32-bit byte ranges (the last bytes stay free for the offset that stands for
+  // "outside"), 16-byte aligned
+  const long margin_px = (long)g.pad * g.wd + g.pad + g.pad_dx;
+  if ((margin_px + (long)g.n_img * g.h * g.wd) * g.c * 4 > 0xFFFFFF00L || (long)g.n_out * K * 4 > 0xFFFFFF00L) return false;
+  if ((reinterpret_cast<uintptr_t>(g.in) & 15) || (reinterpret_cast<uintptr_t>(g.w) & 15)) return false;
+  return ((M + 63) / 64) * ((g.n_out + 63) / 64) <= (1L << 30);
+}
+
+hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
+  long side_blocks = 0;
+  if (g.side.count) {
+    if (!g.side.part || !g.side.dw || g.side.splits < 1) return hipErrorInvalidValue;
+    side_blocks = (long)((g.side.count + 1023) / 1024);
+  }
+  if ((g.bias || g.relu) && (g.accumulate || g.stats || g.bnb.sums)) return hipErrorInvalidValue;
+  const bool dense = g.out_stride == 1 && g.out_h == g.p && g.out_w == g.q;
+  if (g.stats && (g.accumulate || !dense || conv_stat_slabs(M) > g.stats_stride)) return hipErrorInvalidValue;
+  if (g.bnb.sums && (!g.bnb.x || !g.bnb.y || !g.bnb.mean || !g.bnb.istd || g.accumulate || !dense ||
+                     conv_stat_slabs(M) > g.bnb.stride))
+    return hipErrorInvalidValue;
+  if (g.flip.wt) {
+    if (!g.flip.w || g.flip.cout <= 0 || g.flip.cin <= 0 || g.flip.r <= 0 || g.flip.s <= 0) return hipErrorInvalidValue;
+    side_blocks += (long)((g.flip.cin + 31) / 32) * ((g.flip.cout + 31) / 32) * g.flip.r * g.flip.s;
+  }
+  const long tiles = (long)((M + 63) / 64) * ((g.n_out + 63) / 64);
+  if (tiles + 8 + side_blocks > (1L << 30)) return hipErrorInvalidValue;
+  const bool window = window_takes(g);
+  int best = -1;
+  double best_us = 0;
+  for (int v = 0; v < X3_KINDS; ++v) {
+    if (v == X3_WINDOW && !window) continue;
+    const double us = predicted_us(kKinds[v], M, g.n_out, K);
+    if (best < 0 || us < best_us) { best = v; best_us = us; }
+  }
+  probe->variant = best <= X3_64 ? V_IGEMM_X3 : best == X3_WINDOW ? V_IGEMM_X3_WINDOW : V_IGEMM_X3_DEEP;
+  switch (best) {
+    case X3_128: launch_short<2, 2>(g, M, K, st, probe, side_blocks); break;
+    case X3_64: launch_short<1, 1>(g, M, K, st, probe, side_blocks); break;
+    case X3_WINDOW: launch_deep<2, 1, true>(g, M, K, st, probe, side_blocks); break;
+    case X3_DEEP_2x1: launch_deep<2, 1, false>(g, M, K, st, probe, side_blocks); break;
+    case X3_DEEP_2x2: launch_deep<2, 2, false>(g, M, K, st, probe, side_blocks); break;
+    default: launch_deep<1, 1, false>(g, M, K, st, probe, side_blocks); break;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace acc

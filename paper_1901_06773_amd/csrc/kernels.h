@@ -101,8 +101,11 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe = nu
 // function of the shape and the alignment only), and the launch itself; conv_igemm() routes to it.
 bool conv_igemm_bf16_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe);
+// fp32 products on the bf16 matrix cores (conv_igemm_x3.hip): as above.
+bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
+hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
 enum { V_IGEMM_FAST = 0, V_IGEMM_GENERIC, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16,
-       V_IGEMM_BF16, V_IGEMM_DIRECT_2G, V_COUNT };
+       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_COUNT };
 const char* conv_variant_name(int v);
 
 // dw[co][(r,t,ci)] = sum_{img,p,q} dy[img,p,q,co] * x[img, p*stride+r-pad, q*stride+t-pad, ci]

@@ -1,0 +1,82 @@
+"""GPU parity of the fp32 convolutions on the bf16 matrix cores (every value split into three bf16 parts) at the
+sizes where their kernels can go wrong: ragged row and column tiles, reductions that deal unevenly to the groups
+of waves, windows of the largest width, one-chunk reductions; and values the split cannot represent.
+
+Tolerance: the parts left out of a product are below 2^-25 of it, and a result is rounded 6 times per 16 products,
+at most 6 * K / 16 * 2^-24 of the sum of magnitudes (K = 3024: 7e-5) if every rounding went the same way; they do
+not, and 2e-6 in the l2 norm is what the fp32 matrix instruction (up to 8e-7 measured) stays below as well."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from test_gpu_ops import B, close, dev, nchw, nhwc, ohwi, rnd
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # n, h, w, cin, cout, r, stride: which kernel the launcher picks
+    (41, 14, 14, 144, 1000, 1, 1),    # 128 x 128 tiles, ragged rows and columns, nine steps
+    (13, 31, 30, 112, 264, 1, 1),     # 64 x 64 tiles, seven steps
+    (7, 9, 9, 16, 24, 1, 1),          # a single step
+    (5, 61, 62, 64, 136, 3, 1),       # window of the largest width (61 x 62 map: 254 of 256 rows)
+    (23, 14, 14, 336, 260, 3, 1),     # window, 189 steps over four groups (48 + 47 + 47 + 47)
+    (30, 14, 14, 528, 136, 1, 1),     # 128 x 64 tiles, four groups of waves, 33 steps
+    (20, 28, 28, 272, 250, 1, 1),     # 128 x 128 tiles, two groups, 17 steps
+    (3, 62, 64, 64, 136, 3, 1),       # 3x3 on a map too wide for the window
+    (9, 31, 29, 80, 72, 3, 1),        # 64 x 64 tiles, eight groups of one wave, 45 steps
+    (6, 15, 17, 48, 40, 3, 2),        # strided: forward gathers, data gradient in four parts
+    (2, 11, 10, 16, 20, 5, 1),        # 5x5 taps, one window
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_split_conv(case):
+    n, h, w, cin, cout, r, stride = case
+    pad = r // 2
+    x = rnd(1, n, cin, h, w)
+    wt = rnd(2, cout, cin, r, r) * np.float32(np.sqrt(2.0 / (cin * r * r)))
+    ref = O.conv_fwd(x, wt, stride, pad)
+    y = torch.full((n, ref.shape[2], ref.shape[3], cout), float("nan"), device="cuda")
+    B().op_conv_fwd(dev(nhwc(x)), dev(ohwi(wt)), y, stride, pad)
+    torch.cuda.synchronize()
+    close(nchw(y.cpu().numpy()), ref, f"conv_fwd {case}", 2e-6 * 4)
+    err = np.linalg.norm(nchw(y.cpu().numpy()).astype(np.float64) - ref) / np.linalg.norm(ref.astype(np.float64))
+    assert err <= 2e-6, err
+    if cout % 16:
+        return      # the data gradient reduces over cout
+    dy = rnd(3, *ref.shape)
+    refd = O.conv_dgrad(dy, wt, x.shape, stride, pad)
+    ws = torch.empty(max(B().op_conv_workspace(n, h, w, cin, cout, r, stride, pad), 256), dtype=torch.uint8, device="cuda")
+    dx = torch.full((n, h, w, cin), float("nan"), device="cuda")
+    B().op_conv_dgrad(dev(nhwc(dy)), dev(ohwi(wt)), dx, stride, pad, ws)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(nchw(dx.cpu().numpy()).astype(np.float64) - refd) / np.linalg.norm(refd.astype(np.float64))
+    assert err <= 2e-6, err
+
+
+@pytest.mark.parametrize("case", [CASES[i] for i in (1, 4, 6, 8)])
+def test_split_conv_keeps_infinities_nan_and_the_largest_values(case):
+    """As the fp32 instruction: an infinity times a nonzero weight is an infinity (also where a part of the weight
+    is zero), a NaN stays in the outputs that read it, values next to the largest finite one do not overflow."""
+    n, h, w, cin, cout, r, stride = case
+    pad = r // 2
+    x = rnd(1, n, cin, h, w)
+    wt = rnd(2, cout, cin, r, r) * np.float32(np.sqrt(2.0 / (cin * r * r)))
+    wt[:, 3] = 0.5                                    # exact in one bf16: its other parts are zero
+    x[0, 3, 2, 1] = np.inf
+    x[n - 1, 3, h - 1, w - 1] = -np.inf
+    x[n // 2, cin - 1, 3, 4] = np.nan
+    x[n // 2, 3, h - 2, 2] = np.float32(3.4028e38)    # rounds to an infinite bf16; times 0.5 it is finite
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(wt).double(), stride=stride,
+                                         padding=pad).numpy()
+    y = torch.zeros((n, ref.shape[2], ref.shape[3], cout), device="cuda")
+    B().op_conv_fwd(dev(nhwc(x)), dev(ohwi(wt)), y, stride, pad)
+    torch.cuda.synchronize()
+    got = nchw(y.cpu().numpy()).astype(np.float64)
+    assert np.isinf(ref).any() and np.isnan(ref).any() and (np.abs(ref[np.isfinite(ref)]) > 1e38).any()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(ref), got, 0.0), np.where(np.isinf(ref), ref, 0.0))
+    ok = np.isfinite(ref)
+    scale = np.maximum(np.abs(ref[ok]), 1.0)
+    assert (np.abs(got[ok] - ref[ok]) / scale).max() <= 1e-4
