@@ -591,7 +591,8 @@ const char* conv_variant_name(int v) {
   static const char* names[V_COUNT] = {"igemm_kernel<fast>", "igemm_kernel<generic>", "wgrad_kernel<fast>",
                                        "wgrad_kernel<generic>", "igemm_kernel<direct>", "wgrad_kernel<direct>",
                                        "wgrad_bf16_kernel", "igemm_bf16_kernel", "igemm_x3_kernel",
-                                       "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel"};
+                                       "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel",
+                                       "wgrad_x3_kernel"};
   return (v >= 0 && v < V_COUNT) ? names[v] : "?";
 }
 

@@ -3,21 +3,18 @@
 //   dw[co][j] = sum_m dy[m][co] * X[m][j],   m = (img,p,q),  j = (r,t,ci), ci fastest,
 //   X[m][j] = x[img, p*stride+r-pad, q*stride+t-pad, ci]  (zero in the padding)
 //
-// Both operands are read along their contiguous channel axis and staged in LDS as
-// [m][channel]; the fp32 MFMA (v_mfma_f32_32x32x2_f32) takes k = m.  A workgroup of 4
-// waves owns a 64 x 64 tile of dw; the m range is cut into `splits` equal parts
-// (grid.y); each part writes its own partial tile and a second kernel adds the parts in
-// a fixed order, so the result is deterministic (no atomics).
-//
-// Pipeline as in the forward kernel: two chunks of 32 rows in LDS, two more in
-// registers, every steady-state load unconditional (rows beyond the range and padded taps
-// read a stand-in address and are zeroed on the way into LDS), one barrier per chunk.
-// 64x64 tiles measured best on MI355X (ResNet shapes, minibatch 32 / 256: 66 / 91
-// TFLOP/s against 48 / 86 with 128-wide tiles).
+// fp32 storage runs in conv_wgrad_x3.hip where its channel counts allow and the reduction is long enough; here are
+// the kernel for bf16 storage and one for the rest (the 3-channel stem, short reductions, odd channel counts).  In the
+// latter both operands are read along their contiguous channel axis and staged in LDS as [m][channel]; the fp32 MFMA
+// (v_mfma_f32_32x32x2_f32) takes k = m.  A workgroup of 4 waves owns a 64 x 64 tile of dw; the m range is cut into
+// `splits` equal parts; each part writes its own partial tile and the parts are added in a fixed order, so the result is
+// deterministic (no atomics).  Two chunks of 32 rows in LDS, two more in registers, every steady-state load unconditional
+// (rows beyond the range and padded taps read a stand-in address and are zeroed on the way into LDS), one barrier per chunk.
 #include <cstdlib>
 
 #include "kernels.h"
 #include "dtype.h"
+#include "wgrad_side.h"
 
 namespace acc {
 namespace {
@@ -71,86 +68,20 @@ __device__ __forceinline__ int gather_pixel(const WgradGeom& g, int m, int kr, i
   return (img * g.h + iy) * g.wd + ix;
 }
 
-// Side jobs of a weight-gradient launch (workgroups appended behind the tiles): first the
-// blocks that add up 1024 elements each of an earlier weight gradient's parts, in their fixed
-// order; then the blocks that write one 32 x 32 (co, ci) block each of one tap of the flipped,
-// transposed filter.  scratch: at least 32 x 33 elements of LDS.
-template <class T>
-__device__ __forceinline__ void side_jobs(const WgradGeom& g, int id, float* scratch) {
-  const ReduceJob& rj = g.side;
-  const int reduce_blocks = (int)((rj.count + 1023) / 1024);
-  if (id < reduce_blocks) {
-    const size_t i4 = ((size_t)id * 256 + threadIdx.x) * 4;
-    if (i4 >= rj.count) return;
-    if (i4 + 4 <= rj.count && (rj.count & 3) == 0) {
-      float4 sum = *reinterpret_cast<const float4*>(rj.part + i4);
-      // eight parts fetched at a time, added in their order: with hundreds of parts (few tiles, many
-      // cuts of the minibatch range) one load waiting for the sum before it is a chain of latencies
-      int k = 1;
-      for (; k + 8 <= rj.splits; k += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(rj.part + (size_t)(k + u) * rj.count + i4);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { sum.x += v[u].x; sum.y += v[u].y; sum.z += v[u].z; sum.w += v[u].w; }
-      }
-      for (; k < rj.splits; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(rj.part + (size_t)k * rj.count + i4);
-        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-      }
-      *reinterpret_cast<float4*>(rj.dw + i4) = sum;
-    } else {
-      for (size_t i = i4; i < rj.count && i < i4 + 4; ++i) {
-        float sum = rj.part[i];
-        for (int k = 1; k < rj.splits; ++k) sum += rj.part[(size_t)k * rj.count + i];
-        rj.dw[i] = sum;
-      }
-    }
-    return;
-  }
-  id -= reduce_blocks;
-  if (!g.flip_wt) return;
-  const int bx = (g.cin + 31) / 32, by = (g.cout + 31) / 32;
-  const int tap = id / (bx * by), rem = id - tap * (bx * by);
-  const int co0f = (rem / bx) * 32, ci0f = (rem - (rem / bx) * bx) * 32;
-  const int kr = g.r - 1 - tap / g.s, kt = g.s - 1 - tap % g.s;
-  const int src_tap = kr * g.s + kt;
-  T (*tile)[33] = reinterpret_cast<T (*)[33]>(scratch);
-  const T* fw = static_cast<const T*>(g.flip_w);
-  T* fwt = static_cast<T*>(g.flip_wt);
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < 32; i += 8) {
-    const int co = co0f + i, ci = ci0f + tx;
-    tile[i][tx] = (co < g.cout && ci < g.cin) ? fw[((size_t)co * g.r * g.s + src_tap) * g.cin + ci] : T(0);
-  }
-  __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int ci = ci0f + i, co = co0f + tx;
-    if (ci < g.cin && co < g.cout) fwt[((size_t)ci * g.r * g.s + tap) * g.cout + co] = tile[tx][i];
-  }
-}
-
-// L_FAST, L_DIRECT: cin % 64 == 0 (a tile's columns lie inside one tap), cout % 4 == 0, byte
-// offsets below 2^32.  L_DIRECT (fp32 storage only: bf16 operands are widened on their way
-// into LDS, which needs the registers) moves the chunks from global memory straight into LDS
-// (buffer_load_dwordx4 ... lds: a wave fills four 256-byte rows), rows beyond the range,
-// padded taps and columns beyond cout as offsets outside the buffer descriptor, which read as
-// zero.  Rows are unpadded; odd rows hold their two 128-byte halves swapped (the lane fetches
-// the half that belongs into its slot), so that the two rows one MFMA operand is read from
-// lie on different banks.  Two LDS stages, as in the forward kernel's direct loader.
-enum { L_GENERIC = 0, L_FAST = 1, L_DIRECT = 2 };
+// L_FAST: cin % 64 == 0 (a tile's columns lie inside one tap), cout % 4 == 0, byte offsets below 2^32.
+enum { L_GENERIC = 0, L_FAST = 1 };
 
 template <int LOADER, class T>
 __global__ __launch_bounds__(256) void wgrad_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles,
                                                      int splits, int chunks_per_split, float* out,
                                                      size_t split_stride, int main_grid) {
-  constexpr bool FAST = LOADER == L_FAST, DIRECT = LOADER == L_DIRECT;
-  constexpr int PITCH = DIRECT ? 64 : LDT;
+  constexpr bool FAST = LOADER == L_FAST;
+  constexpr int PITCH = LDT;
   __shared__ __attribute__((aligned(256))) float As[2 * BKM * PITCH];
   __shared__ __attribute__((aligned(256))) float Bs[2 * BKM * PITCH];
 
   if ((int)blockIdx.x >= main_grid) {
-    side_jobs<T>(g, (int)blockIdx.x - main_grid, As);
+    wgrad_side_jobs<T>(g, (int)blockIdx.x - main_grid, As);
     return;
   }
 
@@ -251,142 +182,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradGeom g, int Mrows, int 
     }
   };
 
-  if constexpr (DIRECT) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    static_assert(!DIRECT || sizeof(T) == 4, "the direct loader copies raw fp32 rows");
-    // lane -> LDS slot: row tid/16 (+16 on the second pass), 16-byte column tid%16; the slot of
-    // an odd row holds the column of the other half
-    const int row = tid >> 4;
-    const int col4 = (tid & 15) ^ ((row & 1) << 3);
-    const int tap = j0 / g.cin, ci0 = j0 - tap * g.cin;
-    const int kr = tap / g.s, kt = tap - kr * g.s;
-    const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0;
-    const bool a_col_ok = co0 + col4 * 4 < g.cout;
-    constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
-    uint32_t a_lane[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a_lane[i] = (uint32_t)(row + 16 * i) * (uint32_t)(g.cout * 4) + (uint32_t)(co0 + col4 * 4) * 4;
-    const uint32_t b_lane = (uint32_t)(ci0 + col4 * 4) * 4;
-    int r_org[2] = {0, 0}, r_p[2] = {0, 0}, r_q[2] = {0, 0};
-    const float inv_q = 1.0f / (float)g.q, inv_p = 1.0f / (float)g.p;
-    if (!plain) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int m = chunk_lo * BKM + row + 16 * i;
-        const int pq = g.p * g.q;
-        const int img = m / pq, rem = m - img * pq;
-        r_p[i] = rem / g.q;
-        r_q[i] = rem - r_p[i] * g.q;
-        r_org[i] = img * g.h * g.wd;
-      }
-    }
-    __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void*>(g.dy), 0, (int)(uint32_t)((size_t)Mrows * g.cout * 4), 0x00020000);
-    __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void*>(g.x), 0, (int)(uint32_t)((size_t)g.n_img * g.h * g.wd * g.cin * 4), 0x00020000);
-    typedef __attribute__((address_space(3))) void* lds_ptr;
-    const int uwave = __builtin_amdgcn_readfirstlane(wave);
-    const uint32_t lds_a = (uint32_t)(size_t)As + uwave * 1024, lds_b = (uint32_t)(size_t)Bs + uwave * 1024;
-    // loads of chunk kc (relative to chunk_lo) into stage buf; chunks are issued in order, so the
-    // gathered position advances by BKM rows per call without any division
-    auto issue = [&](int kc, int buf) {
-      const int mbase = (chunk_lo + kc) * BKM;
-      const int soff_a = (int)((uint32_t)mbase * (uint32_t)(g.cout * 4));   // below 2^32 (launcher)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int m = mbase + row + 16 * i;
-        const bool mok = m < Mrows;
-        const uint32_t va = (mok && a_col_ok) ? a_lane[i] : OUTSIDE;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(lds_a + buf * (BKM * 256) + i * (16 * 256)), 16, va,
-                                                 soff_a, 0, 0);
-        int pix = m;
-        if (!plain) {
-          const int iy = r_p[i] * g.stride + kr - g.pad, ix = r_q[i] * g.stride + kt - g.pad;
-          pix = ((unsigned)iy < (unsigned)g.h && (unsigned)ix < (unsigned)g.wd) ? r_org[i] + iy * g.wd + ix : -1;
-          // 32 positions on, without a loop that runs differently in every lane: the number of
-          // rows and of images passed are small quotients, exact in float with the half added
-          const int xq = r_q[i] + BKM;
-          const int wq = (int)(((float)xq + 0.5f) * inv_q);
-          r_q[i] = xq - wq * g.q;
-          const int xp = r_p[i] + wq;
-          const int wp = (int)(((float)xp + 0.5f) * inv_p);
-          r_p[i] = xp - wp * g.p;
-          r_org[i] += wp * (g.h * g.wd);
-        }
-        const uint32_t vb = (mok && pix >= 0) ? (uint32_t)pix * (uint32_t)(g.cin * 4) + b_lane : OUTSIDE;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(size_t)(lds_b + buf * (BKM * 256) + i * (16 * 256)), 16, vb,
-                                                 0, 0, 0);
-      }
-    };
-    // operand of MFMA step kk: lanes 0-31 row kk (even), lanes 32-63 row kk+1 (odd: halves swapped)
-    const int half = lane >> 5;
-    const float* a_rd = As + half * 64 + ((wm0 + (lane & 31)) ^ (half << 5));
-    const float* b_rd = Bs + half * 64 + ((wn0 + (lane & 31)) ^ (half << 5));
-    // Groups of four MFMAs (eight rows of the chunk): the operands of group g + 1 are read between the MFMAs
-    // of group g, and the last group's MFMAs are held back (pa, pb) until the next chunk's barrier has been
-    // passed and its first reads are on their way.  Same order of additions.
-    constexpr int NG = BKM / 8;
-    float pa[4] = {0.f, 0.f, 0.f, 0.f}, pb[4] = {0.f, 0.f, 0.f, 0.f};
-    auto mm4 = [&](const float (&a)[4], const float (&b)[4], int half) {
-      if (half != 1) {
-        acc = mfma32x32x2(a[0], b[0], acc);
-        acc = mfma32x32x2(a[1], b[1], acc);
-      }
-      if (half != 0) {
-        acc = mfma32x32x2(a[2], b[2], acc);
-        acc = mfma32x32x2(a[3], b[3], acc);
-      }
-    };
-    auto compute_direct = [&](int buf, bool prev) {
-      const float* as = a_rd + buf * (BKM * 64);
-      const float* bs = b_rd + buf * (BKM * 64);
-      float af[NG][4], bf[NG][4];
-      auto rd = [&](int g) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          af[g][u] = as[(g * 8 + u * 2) * 64];
-          bf[g][u] = bs[(g * 8 + u * 2) * 64];
-        }
-      };
-      rd(0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (prev) mm4(pa, pb, 2);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int g = 0; g + 1 < NG; ++g) {
-        mm4(af[g], bf[g], 0);
-        __builtin_amdgcn_sched_barrier(0);
-        rd(g + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mm4(af[g], bf[g], 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { pa[u] = af[NG - 1][u]; pb[u] = bf[NG - 1][u]; }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    if (n_chunks > 0) {
-      issue(0, 0);
-      int kc = 0;
-      for (; kc + 2 <= n_chunks; kc += 2) {     // whole pairs of chunks: stage 0, then stage 1
-        __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wave's part of chunk kc is in LDS
-        __syncthreads();                        // everybody's is, and chunk kc-1 has been read by all
-        issue(kc + 1, 1);
-        compute_direct(0, kc > 0);
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();
-        if (kc + 2 < n_chunks) issue(kc + 2, 0);
-        compute_direct(1, true);
-      }
-      if (kc < n_chunks) {                      // an odd number of chunks: the last one sits in stage 0
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();
-        compute_direct(0, kc > 0);
-      }
-      mm4(pa, pb, 2);
-    }
-#endif
-  } else if constexpr (FAST) {
+  if constexpr (FAST) {
     // 16 float4 per 64-wide row, 16 rows per pass, 2 passes per operand and chunk
     const int col4 = tid & 15, row = tid >> 4;
     const int tap = j0 / g.cin, ci0 = j0 - tap * g.cin;
@@ -573,7 +369,7 @@ __global__ __launch_bounds__(256) void wgrad_bf16_kernel(WgradGeom g, int Mrows,
   __shared__ __attribute__((aligned(1024))) v4u As[2 * 8 * WB_BM];
   __shared__ __attribute__((aligned(1024))) v4u Bs[2 * 8 * WB_BN];
   if ((int)blockIdx.x >= main_grid) {
-    side_jobs<bf16_t>(g, (int)blockIdx.x - main_grid, reinterpret_cast<float*>(As));
+    wgrad_side_jobs<bf16_t>(g, (int)blockIdx.x - main_grid, reinterpret_cast<float*>(As));
     return;
   }
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -762,6 +558,13 @@ struct WgradCfg {
 // bf16 storage on the bf16 matrix cores: channel counts the 128 x 128 tile of wgrad_bf16_kernel takes
 inline bool bf16_mfma_shape(int dtype, int cin, int cout) { return dtype == DT_BF16 && cin % 8 == 0 && cout % 8 == 0; }
 
+// fp32 storage: channel counts whose groups of four lie inside one filter tap, and more than ten steps of 16 positions
+// (the fully connected layer at minibatch 41, three steps: 10.5 us there, 7.7 here, where 512 small workgroups share
+// the chip and there are no sums to exchange)
+inline bool x3_shape(int dtype, long rows, int cin, int cout) {
+  return dtype == DT_F32 && cin % 4 == 0 && cout % 4 == 0 && rows > 160;
+}
+
 WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   WgradCfg c;
   const long J = (long)r * s * cin;
@@ -813,9 +616,17 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
     const size_t b = wgrad_workspace_bytes(n_img, p, q, cin, cout, r, s, DT_BF16);
     return a > b ? a : b;
   }
-  const WgradCfg c = choose((long)n_img * p * q, cin, cout, r, s, dtype);
-  if (c.splits <= 1) return 0;
-  return (size_t)c.splits * cout * r * s * cin * sizeof(float);
+  const long rows = (long)n_img * p * q;
+  int splits = choose(rows, cin, cout, r, s, dtype).splits;
+  if (x3_shape(dtype, rows, cin, cout)) {
+    // (the other kernel's count matters only where the operands may leave the 32-bit ranges; the input of a strided
+    // convolution has up to stride^2 <= 16 times the rows)
+    const int sx = wgrad_x3_choose(rows, cin, cout, r, s).splits;
+    const bool sure = p <= 4096 && q <= 4096 && rows * (cin > cout ? cin : cout) * 4 * 20 <= 0xFFFFFF00L;
+    splits = sure ? sx : sx > splits ? sx : splits;
+  }
+  if (splits <= 1) return 0;
+  return (size_t)splits * cout * r * s * cin * sizeof(float);
 }
 
 hipError_t reduce_parts(const ReduceJob& job, hipStream_t st) {
@@ -839,13 +650,21 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
     return hipErrorInvalidValue;
   if (g.dtype != DT_F32 && g.dtype != DT_BF16) return hipErrorInvalidValue;
   const WgradCfg c = choose(Mrows, g.cin, g.cout, g.r, g.s, g.dtype);
-  if (c.splits > 1 && !g.workspace) return hipErrorInvalidValue;
+  // fp32 storage on the bf16 matrix cores: both operands inside 32-bit buffer ranges (the last bytes stay free for
+  // the offset that stands for "outside") and 16-byte aligned; p, q <= 4096: the range over which the loader's float
+  // quotients are exact
+  const bool x3 = x3_shape(g.dtype, Mrows, g.cin, g.cout) && g.p <= 4096 && g.q <= 4096 && Mrows * g.cout * 4 <= 0xFFFFFF00L &&
+                  (long)g.n_img * g.h * g.wd * g.cin * 4 <= 0xFFFFFF00L &&
+                  (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
+  const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s) : WgradX3Cfg{};
+  const int splits = x3 ? cx.splits : c.splits;
+  if (splits > 1 && !g.workspace) return hipErrorInvalidValue;
   const long work = (long)c.tiles_co * c.tiles_j * c.splits;
   if (work > (1L << 30)) return hipErrorInvalidValue;
   const long es = (long)dt_size(g.dtype);
   const bool fast = (g.cout % 4 == 0) && (g.cin % 64 == 0) && Mrows * g.cout * es < (1L << 32) &&
                     (long)g.n_img * g.h * g.wd * g.cin * es < (1L << 32);
-  float* out = c.splits > 1 ? g.workspace : g.dw;
+  float* out = splits > 1 ? g.workspace : g.dw;
   const size_t count = (size_t)g.cout * J;
   const int main_grid = (int)((work + 7) / 8 * 8);
   const long flip_blocks = g.flip_wt ? (long)((g.cin + 31) / 32) * ((g.cout + 31) / 32) * g.r * g.s : 0;
@@ -856,14 +675,9 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   }
   if (main_grid + flip_blocks + reduce_blocks > (1L << 30)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(main_grid + reduce_blocks + flip_blocks));
+  hipError_t e = hipSuccess;
   const int tiles = c.tiles_co * c.tiles_j;
   if (probe && probe->before) (void)hipEventRecord(probe->before, st);
-  // direct loader: fp32 storage, both operands inside 32-bit buffer ranges (the last bytes stay
-  // free for the offset that stands for "outside") and 16-byte aligned
-  // (p, q <= 4096: the range over which the loader's float quotients were checked exhaustively)
-  const bool direct = fast && g.dtype == DT_F32 && g.p <= 4096 && g.q <= 4096 && Mrows * g.cout * es <= 0xFFFFFF00L &&
-                      (long)g.n_img * g.h * g.wd * g.cin * es <= 0xFFFFFF00L &&
-                      (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
 #define ACC_WGRAD_LAUNCH(F, T)                                                                             \
   hipLaunchKernelGGL((wgrad_kernel<F, T>), grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, \
                      c.splits, c.chunks_per_split, out, count, main_grid)
@@ -874,7 +688,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
     return hipErrorInvalidValue;   // (the split count, and with it the workspace, was sized for this kernel)
   if (g.dtype == DT_F32) {
-    if (direct) ACC_WGRAD_LAUNCH(L_DIRECT, float);
+    if (x3) e = conv_wgrad_x3(g, cx, (int)Mrows, (int)J, out, count, st);
     else if (fast) ACC_WGRAD_LAUNCH(L_FAST, float);
     else ACC_WGRAD_LAUNCH(L_GENERIC, float);
   } else if (mfma16) {
@@ -885,11 +699,11 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   }
 #undef ACC_WGRAD_LAUNCH
   if (probe && probe->after) (void)hipEventRecord(probe->after, st);
-  if (probe) probe->variant = mfma16 ? V_WGRAD_BF16 : direct ? V_WGRAD_DIRECT : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
-  hipError_t e = hipGetLastError();
+  if (probe) probe->variant = mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
+  if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (c.splits > 1) {
-    const ReduceJob job{g.workspace, g.dw, count, c.splits};
+  if (splits > 1) {
+    const ReduceJob job{g.workspace, g.dw, count, splits};
     if (deferred) *deferred = job;
     else e = reduce_parts(job, st);
   }

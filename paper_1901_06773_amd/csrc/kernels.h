@@ -105,7 +105,7 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, cons
 bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
 enum { V_IGEMM_FAST = 0, V_IGEMM_GENERIC, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16,
-       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_COUNT };
+       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_COUNT };
 const char* conv_variant_name(int v);
 
 // dw[co][(r,t,ci)] = sum_{img,p,q} dy[img,p,q,co] * x[img, p*stride+r-pad, q*stride+t-pad, ci]
@@ -134,6 +134,13 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
 // runs reduce_parts); otherwise dw is complete when the stream reaches the end of this call.
 hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe = nullptr,
                       ReduceJob* deferred = nullptr);
+// The kernel for fp32 storage on the bf16 matrix cores (conv_wgrad_x3.hip): how it cuts a shape (tile of 64*wt
+// squared, steps of 16 positions per part), and the launch; conv_wgrad() routes to it.
+struct WgradX3Cfg {
+  int wt, tiles_co, tiles_j, splits, steps_per_split;
+};
+WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s);
+hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st);
 hipError_t reduce_parts(const ReduceJob& job, hipStream_t st);
 
 // wt[ci][r'][t'][co] = w[co][R-1-r'][S-1-t'][ci]  (filter of the transposed convolution)

@@ -80,3 +80,59 @@ def test_split_conv_keeps_infinities_nan_and_the_largest_values(case):
     ok = np.isfinite(ref)
     scale = np.maximum(np.abs(ref[ok]), 1.0)
     assert (np.abs(got[ok] - ref[ok]) / scale).max() <= 1e-4
+
+
+WGRAD_CASES = [  # n, h, w, cin, cout, r, stride
+    (9, 13, 11, 132, 260, 1, 1),      # ragged tiles of 128 x 128
+    (7, 14, 14, 36, 44, 3, 1),        # channels that fill no block, taps that change inside one
+    (2, 9, 9, 64, 64, 1, 1),          # 162 positions: the fewest this kernel takes
+    (5, 21, 3, 32, 40, 3, 1),         # rows of three positions: several wraps inside a thread's four
+    (11, 2, 20, 32, 32, 3, 1),        # images of two rows
+    (6, 31, 29, 48, 20, 3, 2),        # strided gather
+    (4, 28, 28, 64, 256, 1, 2),       # strided 1x1
+    (23, 14, 14, 256, 256, 3, 1),     # several parts, a ragged last step
+]
+
+
+def wgrad(case, x, dy):
+    n, h, w, cin, cout, r, stride = case
+    ws = torch.empty(max(B().op_conv_workspace(n, h, w, cin, cout, r, stride, r // 2), 256), dtype=torch.uint8, device="cuda")
+    dw = torch.full((cout, r, r, cin), float("nan"), device="cuda")
+    B().op_conv_wgrad(dev(nhwc(x)), dev(nhwc(dy)), dw, stride, r // 2, ws)
+    torch.cuda.synchronize()
+    return dw.cpu().numpy().transpose(0, 3, 1, 2).astype(np.float64)
+
+
+@pytest.mark.parametrize("case", WGRAD_CASES)
+def test_split_wgrad(case):
+    n, h, w, cin, cout, r, stride = case
+    x = rnd(1, n, cin, h, w)
+    dy = rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2))
+    ref = O.conv_wgrad(x, dy, (cout, cin, r, r), stride, r // 2).astype(np.float64)
+    got = wgrad(case, x, dy)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("case", [WGRAD_CASES[i] for i in (0, 1, 7)])
+def test_split_wgrad_keeps_infinities_nan_and_the_largest_values(case):
+    n, h, w, cin, cout, r, stride = case
+    x = rnd(1, n, cin, h, w)
+    dy = rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2))
+    dy[0, 5] = 0.25                                   # exact in one bf16
+    x[0, 7, 1, 1] = np.inf
+    x[n - 1, 3, h - 1, 2] = np.nan
+    x[0, 9, 1, 2] = np.float32(3.4028e38)
+    dy[:, 8:] = np.where(np.abs(dy[:, 8:]) > 0.9, 0.9, dy[:, 8:])
+    xt, dt = torch.from_numpy(x).double(), torch.from_numpy(dy).double()
+    cols = torch.nn.functional.unfold(xt, r, padding=r // 2, stride=stride)          # [n, cin*r*r, positions]
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = torch.einsum("ncp,nkp->ck", dt.reshape(n, cout, -1), cols).reshape(cout, cin, r, r).numpy()
+    got = wgrad(case, x, dy)
+    fit = np.abs(np.where(np.isfinite(ref), ref, 0.0)) < 3.3e38                      # the others overflow or not by their order
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    assert np.array_equal(np.isnan(got[fit]), np.isnan(ref[fit]))
+    inf = np.isinf(ref) & fit
+    assert np.array_equal(got[inf], ref[inf])
+    ok = np.isfinite(ref) & fit & (np.abs(ref) < 1e30)
+    assert np.abs(got[ok] - ref[ok]).max() <= 1e-4 * np.abs(ref[ok]).max()
