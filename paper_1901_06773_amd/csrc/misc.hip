@@ -163,77 +163,154 @@ __global__ __launch_bounds__(THREADS) void maxpool_bwd_kernel(const T* __restric
 }
 
 // The same for 3x3 windows at stride 2 with padding 1 (the stem pool of the ResNets): one thread
-// per 2x2 block of input positions and four channels.  The block (rows 2a, 2a+1, columns 2b,
-// 2b+1) is covered by the windows p in {a, a+1}, q in {b, b+1} and by no other, so each
-// window's maximum is looked up once for the four positions instead of once per position
-// (36 loads for four results instead of 81).  Windows are visited in the same (p, q) order
-// and the same first maximum wins, so every sum has the same terms in the same order as in
-// the kernel above.
+// per column of 2x2 blocks of input positions (MP_STRIP of them, top to bottom) and four channels.  The block (rows
+// 2a, 2a+1, columns 2b, 2b+1) is covered by the windows p in {a, a+1}, q in {b, b+1} and by no other.  Going down, the
+// windows of row a+1 are the next block's row a, and their first input row is the last one of the windows above: ten
+// loads of x per block where every block on its own takes 36 (64 channels, 112x112, 32 images: 104.5 us before, 59 now;
+// the 232 MB it has to move take 50).  Windows are visited in the same (p, q) order and the same
+// first maximum wins, so every sum has the same terms in the same order as in the kernel above.
+constexpr int MP_STRIP = 8;
 template <class T>
 __global__ __launch_bounds__(THREADS) void maxpool3s2_bwd_kernel(const T* __restrict__ x,
-                                                                 const T* __restrict__ dy, T* dx, int n,
+                                                                 const T* __restrict__ dy, T* __restrict__ dx, int n,
                                                                  int h, int wd, int c, int ho, int wo,
                                                                  int accumulate) {
-  const int cg = c >> 2, hb = (h + 1) >> 1, wb = (wd + 1) >> 1;
-  const size_t total = (size_t)n * hb * wb * cg;
+  const int cg = c >> 2, hb = (h + 1) >> 1, wb = (wd + 1) >> 1, strips = (hb + MP_STRIP - 1) / MP_STRIP;
+  const size_t total = (size_t)n * strips * wb * cg;
   for (size_t i = (size_t)blockIdx.x * THREADS + threadIdx.x; i < total; i += (size_t)gridDim.x * THREADS) {
     const int g = (int)(i % cg);
     size_t rest = i / cg;
     const int b = (int)(rest % wb); rest /= wb;
-    const int a = (int)(rest % hb);
-    const int img = (int)(rest / hb);
-    float acc[2][2][4] = {};
-    for (int p = a; p <= a + 1 && p < ho; ++p)
-      for (int q = b; q <= b + 1 && q < wo; ++q) {
-        float best[4] = {0.f, 0.f, 0.f, 0.f};
-        int at[4] = {-1, -1, -1, -1};
+    const int a0 = (int)(rest % strips) * MP_STRIP;
+    const int img = (int)(rest / strips);
+    const T* xi = x + (size_t)img * h * wd * c + g * 4;
+    const T* dyi = dy + (size_t)img * ho * wo * c + g * 4;
+    T* dxi = dx + (size_t)img * h * wd * c + g * 4;
+    bool col_ok[5];
+    int col[5];
 #pragma unroll
-        for (int kr = 0; kr < 3; ++kr) {
-          const int yy = 2 * p + kr - 1;
-          if ((unsigned)yy >= (unsigned)h) continue;
+    for (int t = 0; t < 5; ++t) {
+      const int xx = 2 * b - 1 + t;
+      col_ok[t] = (unsigned)xx < (unsigned)wd;
+      col[t] = col_ok[t] ? xx : 0;
+    }
+    struct Row { float v[5][4]; bool ok; } r0, r1, r2;
+    auto load_row = [&](Row& r, int yy) {
+      r.ok = (unsigned)yy < (unsigned)h;
+      const T* p = xi + (size_t)(r.ok ? yy : 0) * wd * c;
 #pragma unroll
-          for (int kt = 0; kt < 3; ++kt) {
-            const int xx = 2 * q + kt - 1;
-            if ((unsigned)xx >= (unsigned)wd) continue;
-            float v[4];
-            Elem<T>::load4(x + ((size_t)(img * h + yy) * wd + xx) * c + g * 4, v);
+      for (int t = 0; t < 5; ++t) Elem<T>::load4(p + (size_t)col[t] * c, r.v[t]);
+    };
+    struct Win { int at[4]; float d[4]; };      // place of the first maximum (3 * row + column), gradient of the window
+    auto window = [&](Win& w, int p, int q, int t0) {
+      const bool exists = p < ho && q < wo;
+      float best[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (at[j] < 0 || v[j] > best[j]) { best[j] = v[j]; at[j] = yy * wd + xx; }
+      for (int j = 0; j < 4; ++j) w.at[j] = -1;
+#pragma unroll
+      for (int kr = 0; kr < 3; ++kr) {
+        const Row& r = kr == 0 ? r0 : kr == 1 ? r1 : r2;
+#pragma unroll
+        for (int kt = 0; kt < 3; ++kt) {
+          const bool ok = r.ok && col_ok[t0 + kt];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float v = r.v[t0 + kt][j];
+            const bool more = ok & ((w.at[j] < 0) | (v > best[j]));
+            best[j] = more ? v : best[j];
+            w.at[j] = more ? 3 * kr + kt : w.at[j];
           }
         }
-        float d[4];
-        Elem<T>::load4(dy + ((size_t)(img * ho + p) * wo + q) * c + g * 4, d);
+      }
+      Elem<T>::load4(dyi + (exists ? ((size_t)p * wo + q) * c : 0), w.d);
 #pragma unroll
-        for (int ry = 0; ry < 2; ++ry)
+      for (int j = 0; j < 4; ++j) w.at[j] = exists ? w.at[j] : -1;
+    };
+    Win u0, u1, l0, l1;                          // windows (a, b), (a, b+1) and (a+1, b), (a+1, b+1)
+    load_row(r0, 2 * a0 - 1);
+    load_row(r1, 2 * a0);
+    load_row(r2, 2 * a0 + 1);
+    window(u0, a0, b, 0);
+    window(u1, a0, b + 1, 2);
+    for (int a = a0; a < a0 + MP_STRIP && a < hb; ++a) {
+      r0 = r2;
+      load_row(r1, 2 * a + 2);
+      load_row(r2, 2 * a + 3);
+      window(l0, a + 1, b, 0);
+      window(l1, a + 1, b + 1, 2);
+      float o[2][2][4];
 #pragma unroll
-          for (int rx = 0; rx < 2; ++rx) {
-            const int me = (2 * a + ry) * wd + 2 * b + rx;
+      for (int j = 0; j < 4; ++j) {
+        auto take = [&](float acc, const Win& w, int at) { return w.at[j] == at ? acc + w.d[j] : acc; };
+        o[0][0][j] = take(0.f, u0, 4);
+        o[0][1][j] = take(take(0.f, u0, 5), u1, 3);
+        o[1][0][j] = take(take(0.f, u0, 7), l0, 1);
+        o[1][1][j] = take(take(take(take(0.f, u0, 8), u1, 6), l0, 2), l1, 0);
+      }
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (at[j] == me) acc[ry][rx][j] += d[j];
+      for (int ry = 0; ry < 2; ++ry)
+#pragma unroll
+        for (int rx = 0; rx < 2; ++rx) {
+          const int iy = 2 * a + ry, ix = 2 * b + rx;
+          if (iy >= h || ix >= wd) continue;
+          T* out = dxi + ((size_t)iy * wd + ix) * c;
+          if (accumulate) {
+            float old[4];
+            Elem<T>::load4(out, old);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[ry][rx][j] = old[j] + o[ry][rx][j];
           }
-      }
-#pragma unroll
-    for (int ry = 0; ry < 2; ++ry)
-#pragma unroll
-      for (int rx = 0; rx < 2; ++rx) {
-        const int iy = 2 * a + ry, ix = 2 * b + rx;
-        if (iy >= h || ix >= wd) continue;
-        T* out = dx + ((size_t)(img * h + iy) * wd + ix) * c + g * 4;
-        float o[4] = {acc[ry][rx][0], acc[ry][rx][1], acc[ry][rx][2], acc[ry][rx][3]};
-        if (accumulate) {
-          float old[4];
-          Elem<T>::load4(out, old);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) o[j] = old[j] + o[j];
+          Elem<T>::store4(out, o[ry][rx]);
         }
-        Elem<T>::store4(out, o);
-      }
+      u0 = l0;
+      u1 = l1;
+    }
   }
 }
 
-// y[n][c] = mean over hw of x[n][hw][c]
+// y[n][c] = mean over hw of x[n][hw][c].  A workgroup takes one image and up to 256 channels: tpr threads of four
+// channels each across a row, the other threads further rows (four in flight each); the row groups are added in order.
+// (One thread per channel and image, all rows one after the other, waited for every row in turn: 2 x 64 channels of
+// 16x16 67 us, 41 x 2048 of 7x7 16.5 us; now 5 and 6.)
+template <class T>
+__global__ __launch_bounds__(THREADS) void gap_fwd4_kernel(const T* __restrict__ x, T* __restrict__ y, int hw, int c, int tpr, int rpi) {
+  __shared__ float red[THREADS][4];
+  const int tid = threadIdx.x, lane_r = tid / tpr, lane_c = tid - lane_r * tpr;
+  const int ch = (blockIdx.y * tpr + lane_c) * 4, img = blockIdx.x;
+  const bool active = lane_r < rpi && ch < c;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  if (active) {
+    const T* p = x + (size_t)img * hw * c + ch;
+    int k = lane_r;
+    for (; k + 3 * rpi < hw; k += 4 * rpi) {
+      float v[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) Elem<T>::load4(p + (size_t)(k + u * rpi) * c, v[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] += v[u][j];
+    }
+    for (; k < hw; k += rpi) {
+      float v[4];
+      Elem<T>::load4(p + (size_t)k * c, v);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[j] += v[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) red[tid][j] = s[j];
+  __syncthreads();
+  if (lane_r != 0 || !active) return;
+  for (int r = 1; r < rpi; ++r)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] += red[r * tpr + lane_c][j];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) s[j] = s[j] / (float)hw;
+  Elem<T>::store4(y + (size_t)img * c + ch, s);
+}
+
+// the same for channel counts or addresses that do not allow four channels at a time
 template <class T>
 __global__ __launch_bounds__(THREADS) void gap_fwd_kernel(const T* __restrict__ x, T* __restrict__ y,
                                                           int n, int hw, int c) {
@@ -244,6 +321,33 @@ __global__ __launch_bounds__(THREADS) void gap_fwd_kernel(const T* __restrict__ 
     float sum = 0.f;
     for (int k = 0; k < hw; ++k) sum += Elem<T>::load(x + ((size_t)img * hw + k) * c + ch);
     Elem<T>::store(y + i, sum / (float)hw);
+  }
+}
+
+// dx[n][k][c] (+)= dy[n][c] / hw; four channels per thread, rows as in gap_fwd4_kernel, blockIdx.z a range of them
+template <class T>
+__global__ __launch_bounds__(THREADS) void gap_bwd4_kernel(const T* __restrict__ dy, T* __restrict__ dx, int hw, int c, int tpr, int rpi,
+                                                           int rows_per_block, int accumulate) {
+  const int tid = threadIdx.x, lane_r = tid / tpr, lane_c = tid - lane_r * tpr;
+  const int ch = (blockIdx.y * tpr + lane_c) * 4, img = blockIdx.x;
+  if (lane_r >= rpi || ch >= c) return;
+  const float inv = 1.f / (float)hw;
+  float v[4];
+  Elem<T>::load4(dy + (size_t)img * c + ch, v);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] *= inv;
+  const int lo = blockIdx.z * rows_per_block, hi = lo + rows_per_block < hw ? lo + rows_per_block : hw;
+  T* p = dx + (size_t)img * hw * c + ch;
+  for (int k = lo + lane_r; k < hi; k += rpi) {
+    if (accumulate) {
+      float o[4];
+      Elem<T>::load4(p + (size_t)k * c, o);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] += v[j];
+      Elem<T>::store4(p + (size_t)k * c, o);
+    } else {
+      Elem<T>::store4(p + (size_t)k * c, v);
+    }
   }
 }
 
@@ -419,7 +523,7 @@ __global__ __launch_bounds__(THREADS) void fill_zero_kernel(float* __restrict__ 
     p[i] = 0.f;
 }
 
-// y[n][hw][c] = x[n][c][hw]: reads coalesced along hw for each channel, one pixel per thread
+// y[n][hw][c] = x[n][c][hw]: reads coalesced along hw for each channel, one pixel per thread (few channels)
 template <class T>
 __global__ __launch_bounds__(THREADS) void nchw_to_nhwc_kernel(const float* __restrict__ x, T* __restrict__ y,
                                                                int n, int c, int hw) {
@@ -430,6 +534,22 @@ __global__ __launch_bounds__(THREADS) void nchw_to_nhwc_kernel(const float* __re
     T* dst = y + i * c;
     for (int ch = 0; ch < c; ++ch) Elem<T>::store(dst + ch, src[(size_t)ch * hw]);
   }
+}
+
+// many channels: 32 x 32 (channel, pixel) tiles through LDS, both sides coalesced (64 channels, 2 x 16x16 pixels: 22.8
+// -> 4 us, where a thread of the kernel above reads 64 values one after the other)
+template <class T>
+__global__ __launch_bounds__(THREADS) void nchw_to_nhwc_tile_kernel(const float* __restrict__ x, T* __restrict__ y,
+                                                                    int c, int hw, int tiles_p, int tiles_c) {
+  __shared__ float tile[32][33];
+  const int tp = blockIdx.x % tiles_p, rest = blockIdx.x / tiles_p, tc = rest % tiles_c, img = rest / tiles_c;
+  const int p0 = tp * 32, c0 = tc * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const float* src = x + (size_t)img * c * hw;
+  for (int i = ty; i < 32; i += 8) tile[i][tx] = c0 + i < c && p0 + tx < hw ? src[(size_t)(c0 + i) * hw + p0 + tx] : 0.f;
+  __syncthreads();
+  T* dst = y + (size_t)img * c * hw;
+  for (int i = ty; i < 32; i += 8)
+    if (p0 + i < hw && c0 + tx < c) Elem<T>::store(dst + (size_t)(p0 + i) * c + c0 + tx, tile[tx][i]);
 }
 
 }  // namespace
@@ -444,6 +564,12 @@ __global__ __launch_bounds__(THREADS) void nchw_to_nhwc_kernel(const float* __re
 
 hipError_t nchw_to_nhwc(const float* x, void* y, int n, int c, int hw, int dtype, hipStream_t st) {
   if (!x || !y || n <= 0 || c <= 0 || hw <= 0) return hipErrorInvalidValue;
+  const long tiles_p = (hw + 31L) / 32, tiles_c = (c + 31L) / 32;
+  if (c >= 8 && tiles_p * tiles_c * n <= (1L << 30)) {
+    ACC_DISPATCH(dtype, hipLaunchKernelGGL(nchw_to_nhwc_tile_kernel<T>, dim3((unsigned)(tiles_p * tiles_c * n)), dim3(THREADS), 0, st,
+                                           x, (T*)y, c, hw, (int)tiles_p, (int)tiles_c));
+    return hipGetLastError();
+  }
   ACC_DISPATCH(dtype, hipLaunchKernelGGL(nchw_to_nhwc_kernel<T>, dim3(grid_for((size_t)n * hw)), dim3(THREADS), 0, st,
                                          x, (T*)y, n, c, hw));
   return hipGetLastError();
@@ -494,7 +620,7 @@ hipError_t maxpool_backward(const void* x, const void* dy, void* dx, int n, int 
   const int ho = (h + 2 * pad - r) / stride + 1, wo = (wd + 2 * pad - s) / stride + 1;
   if (ho <= 0 || wo <= 0) return hipErrorInvalidValue;
   if (c % 4 == 0 && r == 3 && s == 3 && stride == 2 && pad == 1) {
-    const size_t total = (size_t)n * ((h + 1) / 2) * ((wd + 1) / 2) * (c / 4);
+    const size_t total = (size_t)n * (((h + 1) / 2 + MP_STRIP - 1) / MP_STRIP) * ((wd + 1) / 2) * (c / 4);
     ACC_DISPATCH(dtype, hipLaunchKernelGGL(maxpool3s2_bwd_kernel<T>, dim3(grid_for(total, 256 * 64)), dim3(THREADS), 0, st,
                                            (const T*)x, (const T*)dy, (T*)dx, n, h, wd, c, ho, wo, accumulate));
   } else if (c % 4 == 0) {
@@ -511,8 +637,21 @@ hipError_t maxpool_backward(const void* x, const void* dy, void* dx, int n, int 
   return hipGetLastError();
 }
 
+namespace {
+// four channels at a time: whole groups of four, addresses that allow the wide access, grid sizes within bounds
+inline bool gap_wide(const void* x, const void* y, int n, int c, int dtype) {
+  const uintptr_t mask = dtype == DT_BF16 ? 7 : 15;
+  return c % 4 == 0 && !((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & mask) && c / 4 <= 64 * 65535;
+}
+}  // namespace
+
 hipError_t gap_forward(const void* x, void* y, int n, int hw, int c, int dtype, hipStream_t st) {
   if (!x || !y || n <= 0 || hw <= 0 || c <= 0) return hipErrorInvalidValue;
+  if (gap_wide(x, y, n, c, dtype)) {
+    const int tpr = c / 4 < 64 ? c / 4 : 64, rpi = THREADS / tpr, slices = (c / 4 + tpr - 1) / tpr;
+    ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_fwd4_kernel<T>, dim3(n, slices), dim3(THREADS), 0, st, (const T*)x, (T*)y, hw, c, tpr, rpi));
+    return hipGetLastError();
+  }
   ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_fwd_kernel<T>, dim3(grid_for((size_t)n * c)), dim3(THREADS), 0, st,
                                          (const T*)x, (T*)y, n, hw, c));
   return hipGetLastError();
@@ -520,6 +659,17 @@ hipError_t gap_forward(const void* x, void* y, int n, int hw, int c, int dtype, 
 
 hipError_t gap_backward(const void* dy, void* dx, int n, int hw, int c, int accumulate, int dtype, hipStream_t st) {
   if (!dy || !dx || n <= 0 || hw <= 0 || c <= 0) return hipErrorInvalidValue;
+  if (gap_wide(dy, dx, n, c, dtype)) {
+    const int tpr = c / 4 < 64 ? c / 4 : 64, rpi = THREADS / tpr, slices = (c / 4 + tpr - 1) / tpr;
+    // rows in pieces of at least four trips of a workgroup, about 1024 workgroups
+    long pieces = 1024 / ((long)n * slices) + 1;
+    const long most = ((long)hw + 4 * rpi - 1) / (4 * rpi);
+    if (pieces > most) pieces = most;
+    const int per = (int)((hw + pieces - 1) / pieces);
+    ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_bwd4_kernel<T>, dim3(n, slices, (hw + per - 1) / per), dim3(THREADS), 0, st, (const T*)dy,
+                                           (T*)dx, hw, c, tpr, rpi, per, accumulate));
+    return hipGetLastError();
+  }
   ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_bwd_kernel<T>, dim3(grid_for((size_t)n * hw * c)), dim3(THREADS), 0, st,
                                          (const T*)dy, (T*)dx, n, hw, c, accumulate));
   return hipGetLastError();
