@@ -74,7 +74,9 @@ __device__ __forceinline__ x3_v16f plain_block(const ConvGeom& g, int mr, int nr
       const float* x = static_cast<const float*>(g.in) + (size_t)(ok ? rp.pix + iy * g.wd + ix : 0) * g.c + k0;
 #pragma unroll 1
       for (int c = 0; c < g.c; c += 8) {
-        [[maybe_unused]] x3_v4f a = *reinterpret_cast<const x3_v4f*>(x + c), b = *reinterpret_cast<const x3_v4f*>(w + c);
+        const bool k_ok = c + k0 < g.c;
+        [[maybe_unused]] x3_v4f a = *reinterpret_cast<const x3_v4f*>(x + (k_ok ? c : 0)), b = *reinterpret_cast<const x3_v4f*>(w + (k_ok ? c : 0));
+        if (!k_ok) a = b = x3_v4f{0.f, 0.f, 0.f, 0.f};
         if (!ok) a = x3_v4f{0.f, 0.f, 0.f, 0.f};
         if (!col) b = x3_v4f{0.f, 0.f, 0.f, 0.f};
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void igemm_x3_kernel(ConvGeom g, int M, int
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int n_chunks = K / KC;                           // whole chunks only (launcher)
+  const int n_chunks = (K + KC - 1) / KC;                // whole chunks but for 1x1 filters (launcher)
   constexpr int TPR = KC / 4;                            // threads per row (16 bytes of fp32 each)
   constexpr int RPP = 256 / TPR;                         // rows per pass
   constexpr int AI = BM / RPP, BI = BN / RPP;
@@ -307,9 +309,10 @@ __global__ __launch_bounds__(256, 2) void igemm_x3_kernel(ConvGeom g, int M, int
   auto load = [&](Regs& R) {
     const int tap = kr * g.s + kt;
     const int soff_a = ((kr * g.wd + kt) * g.c + c0) * 4;
+    const bool k_ok = c0 + lk4 * 4 < g.c;                // (1x1 filters: K need not be whole chunks)
 #pragma unroll
     for (int i = 0; i < AI; ++i)
-      R.a[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, ((a_mask[i] >> tap) & 1u) ? a_voff[i] : OUTSIDE, soff_a, 0);
+      R.a[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, ((((a_mask[i] >> tap) & 1u) != 0) & k_ok) ? a_voff[i] : OUTSIDE, soff_a, 0);
 #pragma unroll
     for (int i = 0; i < BI; ++i) R.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_b, b_voff[i], kb, 0);
     advance();
@@ -482,7 +485,7 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   const int grp = __builtin_amdgcn_readfirstlane(tid / GT), gt = tid & (GT - 1);
   const int gw = __builtin_amdgcn_readfirstlane((tid >> 6) & (WM * WN - 1));   // wave of the group
   const int wm0 = (gw / WN) * 64, wn0 = (gw % WN) * 64;
-  const int taps = g.r * g.s, n_steps = K >> 4;
+  const int taps = g.r * g.s, n_steps = (K + 15) >> 4;
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;              // beyond any descriptor range: reads as zero
   const int margin = WINDOW ? 0 : g.pad * g.wd + g.pad + g.pad_dx;   // pixels; the descriptor starts that far before the tensor
   const size_t margin_bytes = (size_t)margin * g.c * 4;
@@ -538,7 +541,7 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
     lw = first / taps; ltap = first - lw * taps;
     lkt = lc = 0;
   } else {
-    const int spt = g.c >> 4;
+    const int spt = (g.c + 15) >> 4;
     ltap = first / spt; lc = (first - ltap * spt) * 16;
     lkt = ltap % g.s; lw = 0;
     soff_a = (((ltap / g.s) * g.wd + lkt) * g.c + lc) * 4;
@@ -556,9 +559,10 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
       ltap -= wrap ? taps : 0;
       lw += wrap ? 1 : 0;
     } else {
+      const bool k_ok = lc + (gt & 3) * 4 < g.c;         // (1x1 filters: K need not be whole steps)
 #pragma unroll
       for (int i = 0; i < AI; ++i)
-        R.a[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, ((a_mask[i] >> ltap) & 1u) ? a_voff[i] : OUTSIDE, soff_a, 0);
+        R.a[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, ((((a_mask[i] >> ltap) & 1u) != 0) & k_ok) ? a_voff[i] : OUTSIDE, soff_a, 0);
 #pragma unroll
       for (int i = 0; i < BI; ++i) R.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_b, b_voff[i], soff_b, 0);
       soff_b += 64;
@@ -823,7 +827,7 @@ constexpr Kind kKinds[X3_KINDS] = {
     {64, 64, 8, 1, 3.90, 1.704, 3.90, 1.704, 1.3},     // igemm_x3_deep_kernel<1, 1>
 };
 double predicted_us(const Kind& k, long M, long N, long K) {
-  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = (K / 16 + k.ks - 1) / k.ks;
+  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + 15) / 16 + k.ks - 1) / k.ks;
   const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
   auto round = [&](long r) {
     const double alone = k.alone + k.alone_step * steps, shared = r * (k.shared + k.shared_step * steps);
@@ -842,7 +846,9 @@ bool window_takes(const ConvGeom& g) {
 }  // namespace
 
 bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K) {
-  if (g.dtype != DT_F32 || g.c % 16 != 0 || g.r * g.s > 32) return false;
+  // whole 16-channel steps inside one tap; a 1x1 filter may end inside a step (1000 classes: the fully connected layer's
+  // data gradient at minibatch 41 49 us in the per-element kernel, 27 here)
+  if (g.dtype != DT_F32 || g.c % (g.r * g.s == 1 ? 4 : 16) != 0 || g.c < 16 || g.r * g.s > 32) return false;
   // both operands within 32-bit byte ranges (the last bytes stay free for the offset that stands for
   // "outside"), 16-byte aligned
   const long margin_px = (long)g.pad * g.wd + g.pad + g.pad_dx;

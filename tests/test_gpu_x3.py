@@ -26,6 +26,9 @@ CASES = [  # n, h, w, cin, cout, r, stride: which kernel the launcher picks
     (9, 31, 29, 80, 72, 3, 1),        # 64 x 64 tiles, eight groups of one wave, 45 steps
     (6, 15, 17, 48, 40, 3, 2),        # strided: forward gathers, data gradient in four parts
     (2, 11, 10, 16, 20, 5, 1),        # 5x5 taps, one window
+    (41, 1, 1, 516, 1000, 1, 1),      # fully connected: both reductions end inside a step (516 = 32 * 16 + 4, 1000 = 62 * 16 + 8)
+    (9, 12, 11, 20, 260, 1, 1),       # the same with 64 x 64 tiles
+    (64, 14, 14, 148, 620, 1, 1),     # and with 128 x 128 tiles
 ]
 
 
@@ -42,7 +45,7 @@ def test_split_conv(case):
     close(nchw(y.cpu().numpy()), ref, f"conv_fwd {case}", 2e-6 * 4)
     err = np.linalg.norm(nchw(y.cpu().numpy()).astype(np.float64) - ref) / np.linalg.norm(ref.astype(np.float64))
     assert err <= 2e-6, err
-    if cout % 16:
+    if cout % (4 if r == 1 else 16):
         return      # the data gradient reduces over cout
     dy = rnd(3, *ref.shape)
     refd = O.conv_dgrad(dy, wt, x.shape, stride, pad)
@@ -54,7 +57,7 @@ def test_split_conv(case):
     assert err <= 2e-6, err
 
 
-@pytest.mark.parametrize("case", [CASES[i] for i in (1, 4, 6, 8)])
+@pytest.mark.parametrize("case", [CASES[i] for i in (1, 4, 6, 8, 12)])
 def test_split_conv_keeps_infinities_nan_and_the_largest_values(case):
     """As the fp32 instruction: an infinity times a nonzero weight is an infinity (also where a part of the weight
     is zero), a NaN stays in the outputs that read it, values next to the largest finite one do not overflow."""
