@@ -592,7 +592,7 @@ const char* conv_variant_name(int v) {
                                        "wgrad_kernel<generic>", "igemm_kernel<direct>", "wgrad_kernel<direct>",
                                        "wgrad_bf16_kernel", "igemm_bf16_kernel", "igemm_x3_kernel",
                                        "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel",
-                                       "wgrad_x3_kernel"};
+                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel"};
   return (v >= 0 && v < V_COUNT) ? names[v] : "?";
 }
 
@@ -618,6 +618,7 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
     probe->variant = V_IGEMM_BF16;
     return conv_igemm_bf16(g, (int)M, (int)K, st, probe);
   }
+  if (conv_smallc_takes(g, M)) return conv_smallc_fwd(g, st, probe);
   if (conv_igemm_x3_takes(g, M, K))        // fp32 storage, whole 16-channel steps: products on the bf16 matrix cores
     return conv_igemm_x3(g, (int)M, (int)K, st, probe);
   if (g.dtype == DT_F32) {

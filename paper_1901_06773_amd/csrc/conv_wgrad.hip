@@ -625,6 +625,7 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
     const bool sure = p <= 4096 && q <= 4096 && rows * (cin > cout ? cin : cout) * 4 * 20 <= 0xFFFFFF00L;
     splits = sure ? sx : sx > splits ? sx : splits;
   }
+  if (const int sc = wgrad_smallc_splits(rows, cin, cout, r, s); sc > splits) splits = sc;   // (either kernel may run)
   if (splits <= 1) return 0;
   return (size_t)splits * cout * r * s * cin * sizeof(float);
 }
@@ -657,7 +658,8 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
                   (long)g.n_img * g.h * g.wd * g.cin * 4 <= 0xFFFFFF00L &&
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
   const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s) : WgradX3Cfg{};
-  const int splits = x3 ? cx.splits : c.splits;
+  const bool small = !x3 && conv_wgrad_smallc_takes(g);
+  const int splits = x3 ? cx.splits : small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s) : c.splits;
   if (splits > 1 && !g.workspace) return hipErrorInvalidValue;
   const long work = (long)c.tiles_co * c.tiles_j * c.splits;
   if (work > (1L << 30)) return hipErrorInvalidValue;
@@ -687,7 +689,9 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   if (mfma16 && !(Mrows * g.cout * es <= 0xFFFFFF00L && (long)g.n_img * g.h * g.wd * g.cin * es <= 0xFFFFFF00L &&
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
     return hipErrorInvalidValue;   // (the split count, and with it the workspace, was sized for this kernel)
-  if (g.dtype == DT_F32) {
+  if (small) {
+    e = conv_wgrad_smallc(g, splits, out, count, st);
+  } else if (g.dtype == DT_F32) {
     if (x3) e = conv_wgrad_x3(g, cx, (int)Mrows, (int)J, out, count, st);
     else if (fast) ACC_WGRAD_LAUNCH(L_FAST, float);
     else ACC_WGRAD_LAUNCH(L_GENERIC, float);
@@ -699,7 +703,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   }
 #undef ACC_WGRAD_LAUNCH
   if (probe && probe->after) (void)hipEventRecord(probe->after, st);
-  if (probe) probe->variant = mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
+  if (probe) probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (splits > 1) {

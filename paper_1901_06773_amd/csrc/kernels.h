@@ -104,8 +104,11 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, cons
 // fp32 products on the bf16 matrix cores (conv_igemm_x3.hip): as above.
 bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
+// A handful of input channels (conv_smallc.hip): as above.
+bool conv_smallc_takes(const ConvGeom& g, long M);
+hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe);
 enum { V_IGEMM_FAST = 0, V_IGEMM_GENERIC, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16,
-       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_COUNT };
+       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD, V_COUNT };
 const char* conv_variant_name(int v);
 
 // dw[co][(r,t,ci)] = sum_{img,p,q} dy[img,p,q,co] * x[img, p*stride+r-pad, q*stride+t-pad, ci]
@@ -141,6 +144,11 @@ struct WgradX3Cfg {
 };
 WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s);
 hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st);
+// The kernel for a handful of input channels (conv_smallc.hip): parts it cuts the reduction into (0: the shape is not
+// its; a function of what wgrad_workspace_bytes() knows), whether it takes a launch, and the launch.
+int wgrad_smallc_splits(long Mrows, int cin, int cout, int r, int s);
+bool conv_wgrad_smallc_takes(const WgradGeom& g);
+hipError_t conv_wgrad_smallc(const WgradGeom& g, int splits, float* out, size_t count, hipStream_t st);
 hipError_t reduce_parts(const ReduceJob& job, hipStream_t st);
 
 // wt[ci][r'][t'][co] = w[co][R-1-r'][S-1-t'][ci]  (filter of the transposed convolution)
