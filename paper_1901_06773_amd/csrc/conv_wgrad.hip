@@ -363,7 +363,8 @@ __device__ __forceinline__ int wb_slot(int kg, int ch) {   // 16-byte slot of (r
   return kg * WB_BM + (o << 3) + ((ch & 7) ^ ((o >> 1) & 7));
 }
 
-__global__ __launch_bounds__(256) void wgrad_bf16_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles,
+template <bool PLAIN>
+__global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles,
                                                           int splits, int chunks_per_split, float* out,
                                                           size_t split_stride, int main_grid) {
   __shared__ __attribute__((aligned(1024))) v4u As[2 * 8 * WB_BM];
@@ -401,61 +402,76 @@ __global__ __launch_bounds__(256) void wgrad_bf16_kernel(WgradGeom g, int Mrows,
   const bool b_col_ok = jt < J;
   const int tap = (b_col_ok ? jt : 0) / g.cin, ci0 = (b_col_ok ? jt : 0) - tap * g.cin;
   const int kr = tap / g.s, kt = tap - kr * g.s;
-  const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0;
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;   // beyond the descriptor's range: reads as zero
   const bool a_col_ok = co0 + oct * 8 < g.cout;
   const uint32_t a_lane = (uint32_t)(co0 + oct * 8) * 2u, b_lane = (uint32_t)ci0 * 2u;
-  __amdgpu_buffer_rsrc_t rs = role_b
-      ? __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.x), 0, (int)(uint32_t)((size_t)g.n_img * g.h * g.wd * g.cin * 2), 0x00020000)
-      : __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(g.dy), 0, (int)(uint32_t)((size_t)Mrows * g.cout * 2), 0x00020000);
-  v4u R[8];
-  auto load = [&](int kc) {
-    const int m0 = (chunk_lo + kc) * WB_BK + kg * 8;
-    if (!role_b) {
+  // (the role is the same for a whole wave; said so explicitly, or the descriptor ends up in vector registers)
+  const uint64_t base = role_b ? reinterpret_cast<uint64_t>(g.x) : reinterpret_cast<uint64_t>(g.dy);
+  const int bytes = (int)(uint32_t)(role_b ? (size_t)g.n_img * g.h * g.wd * g.cin * 2 : (size_t)Mrows * g.cout * 2);
+  const uint32_t base_lo = __builtin_amdgcn_readfirstlane((uint32_t)base), base_hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)base_hi << 32 | base_lo), 0,
+                                                                __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+  // The eight rows of a thread, two register sets (one chunk is written to LDS while the loads of the next but one are on
+  // their way).  Offsets are moved on from chunk to chunk: adds and selects, dy as the input of a 1x1 convolution would be.
+  struct Regs { v4u r[8]; } R0, R1;
+  const int gh = role_b ? g.h : g.p, gwd = role_b ? g.wd : g.q, gs = role_b ? g.stride : 1;
+  const int gy = role_b ? kr - g.pad : 0, gx = role_b ? kt - g.pad : 0;
+  const uint32_t row_b = (uint32_t)(role_b ? g.cin : g.cout) * 2u;
+  const uint32_t wrap_q = (uint32_t)(gs * gwd - g.q * gs) * row_b, wrap_p = (uint32_t)((gh - g.p * gs) * gwd) * row_b;
+  const int m_lim = (role_b ? b_col_ok : a_col_ok) ? Mrows : 0;
+  int m_next = chunk_lo * WB_BK + kg * 8, p0, q0;
+  uint32_t off;
+  {
+    const int pq = g.p * g.q, img = m_next / pq, rem = m_next - img * pq;
+    p0 = rem / g.q;
+    q0 = rem - p0 * g.q;
+    off = (uint32_t)((img * gh + p0 * gs + gy) * gwd + q0 * gs + gx) * row_b + (role_b ? b_lane : a_lane);
+  }
+  const float inv_q = 1.0f / (float)g.q, inv_p = 1.0f / (float)g.p;
+  auto load = [&](Regs& R) {
+    uint32_t voff[8];
+    if (PLAIN) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int m = m0 + r;
-        const uint32_t voff = (m < Mrows && a_col_ok) ? (uint32_t)m * (uint32_t)(g.cout * 2) + a_lane : OUTSIDE;
-        R[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0);
-      }
+      for (int r = 0; r < 8; ++r) voff[r] = m_next + r < m_lim ? off + r * row_b : OUTSIDE;
+      off += WB_BK * row_b;
     } else {
-      int p = 0, q = 0, org = 0;
-      if (!plain) {
-        const int pq = g.p * g.q;
-        const int mm = m0 < Mrows ? m0 : 0;
-        const int img = mm / pq, rem = mm - img * pq;
-        p = rem / g.q;
-        q = rem - p * g.q;
-        org = img * g.h * g.wd;
-      }
+      int p = p0, q = q0;
+      uint32_t o = off;
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
-        const int m = m0 + r;
-        int pix = m;
-        if (!plain) {
-          const int iy = p * g.stride + kr - g.pad, ix = q * g.stride + kt - g.pad;
-          pix = ((unsigned)iy < (unsigned)g.h && (unsigned)ix < (unsigned)g.wd) ? org + iy * g.wd + ix : -1;
-          if (++q == g.q) { q = 0; if (++p == g.p) { p = 0; org += g.h * g.wd; } }
-        }
-        const uint32_t voff = (m < Mrows && pix >= 0 && b_col_ok) ? (uint32_t)pix * (uint32_t)(g.cin * 2) + b_lane : OUTSIDE;
-        R[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0);
+        const bool wq = q + 1 == g.q, wp = wq & (p + 1 == g.p);
+        const int iy = __mul24(p, gs) + gy, ix = __mul24(q, gs) + gx;
+        const bool in = ((unsigned)iy < (unsigned)gh) & ((unsigned)ix < (unsigned)gwd) & (m_next + r < m_lim);
+        voff[r] = in ? o : OUTSIDE;
+        o += gs * row_b + (wq ? wrap_q : 0u) + (wp ? wrap_p : 0u);
+        q = wq ? 0 : q + 1;
+        p = wp ? 0 : p + (wq ? 1 : 0);
       }
+      // 64 rows on: small quotients, exact in float with the half added (p, q <= 4096)
+      const int xq = q0 + WB_BK, nq = (int)(((float)xq + 0.5f) * inv_q);
+      q0 = xq - nq * g.q;
+      const int xp = p0 + nq, np = (int)(((float)xp + 0.5f) * inv_p);
+      p0 = xp - np * g.p;
+      off += WB_BK * gs * row_b + (uint32_t)nq * wrap_q + (uint32_t)np * wrap_p;
     }
+    m_next += WB_BK;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) R.r[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[r], 0, 0);
   };
   // 8 x 8 transpose of 16-bit values: vector c = channel c of the thread's eight, rows 0..7
   v4u* stage_base = (role_b ? Bs : As);
   const int slot0 = kg * WB_BM + (oct << 3);
   const int sw = (oct >> 1) & 7;
-  auto transpose_store = [&](int buf) {
+  auto transpose_store = [&](const Regs& R, int buf) {
     v4u* dst = stage_base + buf * (8 * WB_BM) + slot0;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
       v4u v;
-      v.x = __builtin_amdgcn_perm(R[1][c >> 1], R[0][c >> 1], sel);
-      v.y = __builtin_amdgcn_perm(R[3][c >> 1], R[2][c >> 1], sel);
-      v.z = __builtin_amdgcn_perm(R[5][c >> 1], R[4][c >> 1], sel);
-      v.w = __builtin_amdgcn_perm(R[7][c >> 1], R[6][c >> 1], sel);
+      v.x = __builtin_amdgcn_perm(R.r[1][c >> 1], R.r[0][c >> 1], sel);
+      v.y = __builtin_amdgcn_perm(R.r[3][c >> 1], R.r[2][c >> 1], sel);
+      v.z = __builtin_amdgcn_perm(R.r[5][c >> 1], R.r[4][c >> 1], sel);
+      v.w = __builtin_amdgcn_perm(R.r[7][c >> 1], R.r[6][c >> 1], sel);
       dst[c ^ sw] = v;
     }
   };
@@ -484,20 +500,33 @@ __global__ __launch_bounds__(256) void wgrad_bf16_kernel(WgradGeom g, int Mrows,
         for (int j = 0; j < 2; ++j) acc[i][j] = mfma32x32x16bf(a[i], b[j], acc[i][j]);
     }
   };
-  if (n_chunks > 0) {
-    load(0);
-    transpose_store(0);
+  if (n_chunks > 0) load(R0);
+  if (n_chunks > 1) load(R1);
+  if (n_chunks > 0) transpose_store(R0, 0);
+  __syncthreads();
+  int kc = 0;
+  for (; kc + 4 <= n_chunks; kc += 2) {      // steady state: every load and store unconditional
+    load(R0);
+    compute(0);
+    transpose_store(R1, 1);
     __syncthreads();
-    for (int kc = 0; kc < n_chunks; ++kc) {
-      const bool more = kc + 1 < n_chunks;
-      if (more) load(kc + 1);
-      compute(kc & 1);
-      if (more) transpose_store((kc + 1) & 1);
-      __syncthreads();
-    }
+    load(R1);
+    compute(1);
+    transpose_store(R0, 0);
+    __syncthreads();
+  }
+  for (; kc < n_chunks; kc += 2) {
+    if (kc + 2 < n_chunks) load(R0);
+    compute(0);
+    if (kc + 1 < n_chunks) transpose_store(R1, 1);
+    __syncthreads();
+    if (kc + 1 >= n_chunks) break;
+    if (kc + 3 < n_chunks) load(R1);
+    compute(1);
+    if (kc + 2 < n_chunks) transpose_store(R0, 0);
+    __syncthreads();
   }
   float* dst = out + (size_t)split * split_stride;
-  (void)ci0;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -696,8 +725,12 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
     else if (fast) ACC_WGRAD_LAUNCH(L_FAST, float);
     else ACC_WGRAD_LAUNCH(L_GENERIC, float);
   } else if (mfma16) {
-    hipLaunchKernelGGL(wgrad_bf16_kernel, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, c.splits,
-                       c.chunks_per_split, out, count, main_grid);
+    if (g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0)
+      hipLaunchKernelGGL(wgrad_bf16_kernel<true>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, c.splits,
+                         c.chunks_per_split, out, count, main_grid);
+    else
+      hipLaunchKernelGGL(wgrad_bf16_kernel<false>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, c.splits,
+                         c.chunks_per_split, out, count, main_grid);
   } else {
     if (fast) ACC_WGRAD_LAUNCH(L_FAST, bf16_t); else ACC_WGRAD_LAUNCH(L_GENERIC, bf16_t);
   }
