@@ -20,116 +20,129 @@ constexpr int ROWS_PER_THREAD = 4;  // rows a thread of the reduction sums at le
 constexpr int THREADS = 256;
 constexpr int FIN_CH = THREADS / 64;  // the finishing kernels give every channel one wave
 
+// How the threads of a workgroup cover the channels: tpr threads of V channels each across a row, rpi rows per trip;
+// col_slices workgroups (grid.y) where a row is wider than one covers.
 struct ReduceShape {
-  int tpr;        // threads across one row (each owns 4 channels), at most 64
-  int rpi;        // rows per iteration of a block
-  int col_slices; // grid.y: slices of 4 * tpr channels
+  int tpr, rpi, col_slices;
 };
 
-__host__ __device__ inline ReduceShape reduce_shape(int c) {
+__host__ __device__ inline ReduceShape reduce_shape(int groups) {   // groups of V channels
   ReduceShape s;
-  const int cg = c / 4;
-  s.tpr = cg < 64 ? cg : 64;
+  s.tpr = groups < 64 ? groups : 64;
   // tpr need not divide 256: the leftover threads idle
   s.rpi = THREADS / s.tpr;
-  s.col_slices = (cg + s.tpr - 1) / s.tpr;
+  s.col_slices = (groups + s.tpr - 1) / s.tpr;
   return s;
 }
 
-// Sums over the rows of one slab, per channel, of up to two quantities.
+// A tensor, how a workgroup covers its channels, and the rows of one workgroup.
+struct Span {
+  long rows;
+  int c, tpr, rpi;
+  long rows_per_wg;
+};
+
+// Sums over the rows of one slab, per channel, of up to two quantities.  Bound by memory: x (and dy, y) read once, V channels
+// = 16 bytes per thread and load, U rows in flight.  With the passes below, bf16 512 channels, 256 images of 28x28, residual:
+// forward 198 -> 170 us, backward 358 -> 333 (8-byte loads, coefficients fetched per element before); what is left of
+// the way to 134 / 223 us of traffic at 4.6 TB/s is the second read of x, dy and y, which the caches don't hold: in slices of
+// 1/2 or 1/4 of the channels, one after the other, the rows become too short (862 us both ways), and walking back from the
+// end in the second pass gives nothing (170.4 / 333.3).
 // MODE 0: (x, x*x).   MODE 1: (g, g*xhat) with g = dy * [y > 0] (y optional).
-template <int MODE, class T>
+template <int MODE, class T, int V>
 __global__ __launch_bounds__(THREADS) void bn_reduce_kernel(const T* __restrict__ x,
                                                             const T* __restrict__ dy,
                                                             const T* __restrict__ y,
                                                             const float* __restrict__ mean,
                                                             const float* __restrict__ istd,
-                                                            double* __restrict__ part, long rows,
-                                                            int c, int tpr, int rpi, int slabs) {
-  __shared__ double red[2][THREADS][4];
+                                                            double* __restrict__ part, Span sp) {
+  __shared__ double red[2][THREADS][V];
   const int tid = threadIdx.x;
-  const int lane_r = tid / tpr;            // which row of the iteration
-  const int lane_c = tid - lane_r * tpr;   // which channel group
-  const int cg = blockIdx.y * tpr + lane_c;
-  const bool active = lane_r < rpi && cg * 4 < c;
-  const long rows_per_slab = (rows + slabs - 1) / slabs;
-  const long r_lo = (long)blockIdx.x * rows_per_slab;
-  const long r_hi = r_lo + rows_per_slab < rows ? r_lo + rows_per_slab : rows;
+  const int lane_r = tid / sp.tpr;            // which row of the iteration
+  const int lane_c = tid - lane_r * sp.tpr;   // which channel group
+  const int ch = (blockIdx.y * sp.tpr + lane_c) * V;
+  const bool active = lane_r < sp.rpi && ch < sp.c;
+  const long r_lo = (long)blockIdx.x * sp.rows_per_wg;
+  const long r_hi = r_lo + sp.rows_per_wg < sp.rows ? r_lo + sp.rows_per_wg : sp.rows;
+  const int c = sp.c, rpi = sp.rpi;
 
-  double s0[4] = {0, 0, 0, 0}, s1[4] = {0, 0, 0, 0};
+  double s0[V], s1[V];
+#pragma unroll
+  for (int j = 0; j < V; ++j) s0[j] = s1[j] = 0.0;
   if (active) {
-    float mu[4] = {0, 0, 0, 0}, is[4] = {0, 0, 0, 0};
+    float mu[V], is[V];
     if (MODE == 1) {
-      const float4 m4 = *reinterpret_cast<const float4*>(mean + cg * 4);
-      const float4 i4 = *reinterpret_cast<const float4*>(istd + cg * 4);
-      mu[0] = m4.x; mu[1] = m4.y; mu[2] = m4.z; mu[3] = m4.w;
-      is[0] = i4.x; is[1] = i4.y; is[2] = i4.z; is[3] = i4.w;
+#pragma unroll
+      for (int j = 0; j < V; ++j) { mu[j] = mean[ch + j]; is[j] = istd[ch + j]; }
     }
-    auto add_row = [&](const float (&xs)[4], const float (&gv)[4], const float (&ys)[4]) {
+    auto add_row = [&](const float (&xs)[V], const float (&gv)[V], const float (&ys)[V]) {
       if (MODE == 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < V; ++j) {
           const double d = (double)xs[j];
           s0[j] += d;
           s1[j] += d * d;
         }
       } else {
-        float gs[4] = {gv[0], gv[1], gv[2], gv[3]};
-        if (y) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) gs[j] = ys[j] > 0.f ? gs[j] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double gd = (double)gs[j];
+        for (int j = 0; j < V; ++j) {
+          const double gd = (double)(!y || ys[j] > 0.f ? gv[j] : 0.f);
           s0[j] += gd;
           s1[j] += gd * (double)((xs[j] - mu[j]) * is[j]);
         }
       }
     };
-    // four rows per trip: all their loads are issued before the first sum needs one
-    constexpr int U = 4;
+    // several rows per trip: all their loads are issued before the first sum needs one
+    constexpr int U = V == 8 && MODE == 1 ? 2 : 4;
+    const T* px = x + (size_t)(r_lo + lane_r) * c + ch;
+    const T* pd = MODE == 1 ? dy + (size_t)(r_lo + lane_r) * c + ch : nullptr;
+    const T* py = MODE == 1 && y ? y + (size_t)(r_lo + lane_r) * c + ch : nullptr;
+    const size_t hop = (size_t)rpi * c;
     long r = r_lo + lane_r;
     for (; r + (long)(U - 1) * rpi < r_hi; r += (long)U * rpi) {
-      float xv[U][4], gv[U][4] = {}, yv[U][4] = {};
+      float xv[U][V], gv[U][V], yv[U][V];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const size_t off = (size_t)(r + (long)u * rpi) * c + (size_t)cg * 4;
-        Elem<T>::load4(x + off, xv[u]);
-        if (MODE == 1) Elem<T>::load4(dy + off, gv[u]);
-        if (MODE == 1 && y) Elem<T>::load4(y + off, yv[u]);
+        ElemV<T, V>::load(px + u * hop, xv[u]);
+        if (MODE == 1) ElemV<T, V>::load(pd + u * hop, gv[u]);
+        if (MODE == 1 && y) ElemV<T, V>::load(py + u * hop, yv[u]);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) add_row(xv[u], gv[u], yv[u]);
+      px += U * hop;
+      if (MODE == 1) pd += U * hop;
+      if (MODE == 1 && y) py += U * hop;
     }
     for (; r < r_hi; r += rpi) {
-      const size_t off = (size_t)r * c + (size_t)cg * 4;
-      float xv[4], gv[4] = {}, yv[4] = {};
-      Elem<T>::load4(x + off, xv);
-      if (MODE == 1) Elem<T>::load4(dy + off, gv);
-      if (MODE == 1 && y) Elem<T>::load4(y + off, yv);
+      float xv[V], gv[V], yv[V];
+      ElemV<T, V>::load(px, xv);
+      if (MODE == 1) ElemV<T, V>::load(pd, gv);
+      if (MODE == 1 && y) ElemV<T, V>::load(py, yv);
       add_row(xv, gv, yv);
+      px += hop;
+      if (MODE == 1) pd += hop;
+      if (MODE == 1 && y) py += hop;
     }
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < V; ++j) {
     red[0][tid][j] = s0[j];
     red[1][tid][j] = s1[j];
   }
   __syncthreads();
   // the first row of threads adds the other rows in order
-  if (lane_r == 0 && cg * 4 < c) {
+  if (lane_r == 0 && active) {
     for (int rr = 1; rr < rpi; ++rr) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        s0[j] += red[0][rr * tpr + lane_c][j];
-        s1[j] += red[1][rr * tpr + lane_c][j];
+      for (int j = 0; j < V; ++j) {
+        s0[j] += red[0][rr * sp.tpr + lane_c][j];
+        s1[j] += red[1][rr * sp.tpr + lane_c][j];
       }
     }
-    double* p0 = part + ((size_t)0 * MAX_SLABS + blockIdx.x) * c + (size_t)cg * 4;
-    double* p1 = part + ((size_t)1 * MAX_SLABS + blockIdx.x) * c + (size_t)cg * 4;
+    double* p0 = part + ((size_t)0 * MAX_SLABS + blockIdx.x) * c + ch;
+    double* p1 = part + ((size_t)1 * MAX_SLABS + blockIdx.x) * c + ch;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < V; ++j) {
       p0[j] = s0[j];
       p1[j] = s1[j];
     }
@@ -213,69 +226,104 @@ __global__ __launch_bounds__(THREADS) void bn_bwd_finish_kernel(
   coef[2 * c + ch] = (float)(dg / m);
 }
 
-// y = relu?((x-mean)*scale + beta (+ res)), float4 per thread, grid-stride.  Subtracting the
-// mean first keeps the result exact where x equals the mean (a channel of constant values).
-template <class T>
+// y = relu?((x-mean)*scale + beta (+ res)): a thread keeps its V channels and walks down the rows of its workgroup, the
+// coefficients in registers.  Subtracting the mean first keeps the result exact where x equals the mean (a channel of
+// constant values).
+template <class T, int V>
 __global__ __launch_bounds__(THREADS) void bn_apply_kernel(const T* __restrict__ x,
                                                            const T* __restrict__ res,
                                                            const float* __restrict__ coef,
-                                                           T* __restrict__ y, size_t n4, int c,
-                                                           int relu) {
-  const int cg = c >> 2;
-  for (size_t i = (size_t)blockIdx.x * THREADS + threadIdx.x; i < n4; i += (size_t)gridDim.x * THREADS) {
-    const int g = (int)(i % cg);
-    float xv[4], o[4];
-    Elem<T>::load4(x + i * 4, xv);
-    const float4 sc = reinterpret_cast<const float4*>(coef)[g];
-    const float4 mu = reinterpret_cast<const float4*>(coef + c)[g];
-    const float4 be = reinterpret_cast<const float4*>(coef + 2 * c)[g];
-    o[0] = fmaf(xv[0] - mu.x, sc.x, be.x);
-    o[1] = fmaf(xv[1] - mu.y, sc.y, be.y);
-    o[2] = fmaf(xv[2] - mu.z, sc.z, be.z);
-    o[3] = fmaf(xv[3] - mu.w, sc.w, be.w);
-    if (res) {
-      float rv[4];
-      Elem<T>::load4(res + i * 4, rv);
+                                                           T* __restrict__ y, int relu, Span sp) {
+  const int tid = threadIdx.x, lane_r = tid / sp.tpr, lane_c = tid - lane_r * sp.tpr;
+  const int ch = (blockIdx.y * sp.tpr + lane_c) * V;
+  if (lane_r >= sp.rpi || ch >= sp.c) return;
+  const int c = sp.c, rpi = sp.rpi;
+  float sc[V], mu[V], be[V];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] += rv[j];
-    }
-    if (relu) {
+  for (int j = 0; j < V; ++j) { sc[j] = coef[ch + j]; mu[j] = coef[c + ch + j]; be[j] = coef[2 * c + ch + j]; }
+  const long r_lo = (long)blockIdx.x * sp.rows_per_wg;
+  const long r_hi = r_lo + sp.rows_per_wg < sp.rows ? r_lo + sp.rows_per_wg : sp.rows;
+  constexpr int U = 4;
+  const size_t hop = (size_t)rpi * c;
+  size_t at = (size_t)(r_lo + lane_r) * c + ch;
+  auto one = [&](const float (&xv)[V], const float (&rv)[V], size_t to) {
+    float o[V];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] = fmaxf(o[j], 0.f);
+    for (int j = 0; j < V; ++j) {
+      o[j] = fmaf(xv[j] - mu[j], sc[j], be[j]);
+      if (res) o[j] += rv[j];
+      if (relu) o[j] = fmaxf(o[j], 0.f);
     }
-    Elem<T>::store4(y + i * 4, o);
+    ElemV<T, V>::store(y + to, o);
+  };
+  long r = r_lo + lane_r;
+  for (; r + (long)(U - 1) * rpi < r_hi; r += (long)U * rpi, at += U * hop) {
+    float xv[U][V], rv[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ElemV<T, V>::load(x + at + u * hop, xv[u]);
+      if (res) ElemV<T, V>::load(res + at + u * hop, rv[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) one(xv[u], rv[u], at + u * hop);
+  }
+  for (; r < r_hi; r += rpi, at += hop) {
+    float xv[V], rv[V];
+    ElemV<T, V>::load(x + at, xv);
+    if (res) ElemV<T, V>::load(res + at, rv);
+    one(xv, rv, at);
   }
 }
 
 // dx = a*(g - dbeta/m - xhat*dgamma/m), g = dy*[y>0]; optionally stores g (may alias dy)
-template <class T>
+template <class T, int V>
 __global__ __launch_bounds__(THREADS) void bn_bwd_apply_kernel(
     const T* __restrict__ x, const T* dy, const T* __restrict__ y,
     const float* __restrict__ mean, const float* __restrict__ istd, const float* __restrict__ coef,
-    T* __restrict__ dx, T* g_out, size_t n4, int c) {
-  const int cg = c >> 2;
-  for (size_t i = (size_t)blockIdx.x * THREADS + threadIdx.x; i < n4; i += (size_t)gridDim.x * THREADS) {
-    const int g = (int)(i % cg);
-    float xv[4], gv[4], o[4];
-    Elem<T>::load4(x + i * 4, xv);
-    Elem<T>::load4(dy + i * 4, gv);
-    if (y) {
-      float yv[4];
-      Elem<T>::load4(y + i * 4, yv);
+    T* __restrict__ dx, T* g_out, Span sp) {
+  const int tid = threadIdx.x, lane_r = tid / sp.tpr, lane_c = tid - lane_r * sp.tpr;
+  const int ch = (blockIdx.y * sp.tpr + lane_c) * V;
+  if (lane_r >= sp.rpi || ch >= sp.c) return;
+  const int c = sp.c, rpi = sp.rpi;
+  float mu[V], is[V], a[V], c1[V], c2[V];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) gv[j] = yv[j] > 0.f ? gv[j] : 0.f;
+  for (int j = 0; j < V; ++j) {
+    mu[j] = mean[ch + j]; is[j] = istd[ch + j];
+    a[j] = coef[ch + j]; c1[j] = coef[c + ch + j]; c2[j] = coef[2 * c + ch + j];
+  }
+  const long r_lo = (long)blockIdx.x * sp.rows_per_wg;
+  const long r_hi = r_lo + sp.rows_per_wg < sp.rows ? r_lo + sp.rows_per_wg : sp.rows;
+  constexpr int U = V == 8 ? 2 : 4;
+  const size_t hop = (size_t)rpi * c;
+  size_t at = (size_t)(r_lo + lane_r) * c + ch;
+  auto one = [&](const float (&xv)[V], float (&gv)[V], const float (&yv)[V], size_t to) {
+    float o[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      gv[j] = !y || yv[j] > 0.f ? gv[j] : 0.f;
+      o[j] = a[j] * (gv[j] - c1[j] - (xv[j] - mu[j]) * is[j] * c2[j]);
     }
-    const float4 mu = reinterpret_cast<const float4*>(mean)[g];
-    const float4 is = reinterpret_cast<const float4*>(istd)[g];
-    const float4 a = reinterpret_cast<const float4*>(coef)[g];
-    const float4 c1 = reinterpret_cast<const float4*>(coef + c)[g];
-    const float4 c2 = reinterpret_cast<const float4*>(coef + 2 * c)[g];
-    o[0] = a.x * (gv[0] - c1.x - (xv[0] - mu.x) * is.x * c2.x);
-    o[1] = a.y * (gv[1] - c1.y - (xv[1] - mu.y) * is.y * c2.y);
-    o[2] = a.z * (gv[2] - c1.z - (xv[2] - mu.z) * is.z * c2.z);
-    o[3] = a.w * (gv[3] - c1.w - (xv[3] - mu.w) * is.w * c2.w);
-    Elem<T>::store4(dx + i * 4, o);
-    if (g_out) Elem<T>::store4(g_out + i * 4, gv);
+    ElemV<T, V>::store(dx + to, o);
+    if (g_out) ElemV<T, V>::store(g_out + to, gv);
+  };
+  long r = r_lo + lane_r;
+  for (; r + (long)(U - 1) * rpi < r_hi; r += (long)U * rpi, at += U * hop) {
+    float xv[U][V], gv[U][V], yv[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ElemV<T, V>::load(x + at + u * hop, xv[u]);
+      ElemV<T, V>::load(dy + at + u * hop, gv[u]);
+      if (y) ElemV<T, V>::load(y + at + u * hop, yv[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) one(xv[u], gv[u], yv[u], at + u * hop);
+  }
+  for (; r < r_hi; r += rpi, at += hop) {
+    float xv[V], gv[V], yv[V];
+    ElemV<T, V>::load(x + at, xv);
+    ElemV<T, V>::load(dy + at, gv);
+    if (y) ElemV<T, V>::load(y + at, yv);
+    one(xv, gv, yv, at);
   }
 }
 
@@ -535,10 +583,11 @@ inline int slab_count(long rows, const ReduceShape& rs) {
   return (int)s;
 }
 
-inline unsigned apply_grid(size_t n4) {
-  const size_t blocks = (n4 + THREADS - 1) / THREADS;
-  const size_t cap = 256 * 16;   // 16 workgroups per CU keep every XCD busy
-  return (unsigned)(blocks < cap ? (blocks ? blocks : 1) : cap);
+// rows of an apply workgroup: about 16 workgroups per compute unit over all column slices, whole trips of four rows per thread
+inline long apply_rows(long rows, const ReduceShape& rs) {
+  const long wgs = 4096 / rs.col_slices > 0 ? 4096 / rs.col_slices : 1, trip = 4L * rs.rpi;
+  const long per = (rows + wgs - 1) / wgs;
+  return (per + trip - 1) / trip * trip;
 }
 
 }  // namespace
@@ -550,78 +599,97 @@ size_t bn_workspace_bytes(int c) {
 namespace {
 
 // finish + apply of the forward pass from `slabs` partial sums of type P
-template <class T, class P>
-void bn_forward_tail(const T* x, const float* gamma, const float* beta, const T* res, T* y, float* mean, float* istd,
-                     long rows, int c, int relu, float eps, const P* sums, int slabs, int stride, float* coef,
-                     hipStream_t st) {
-  if (slice_takes<T>(rows, slabs)) {
-    long per;
-    const dim3 grid = slice_grid(rows, c, &per);
-    hipLaunchKernelGGL((bn_fwd_slice_kernel<T, P>), grid, dim3(THREADS), 0, st, x, res, sums, gamma, beta, mean, istd,
-                       y, rows, c, relu, eps, slabs, stride, per);
-    return;
-  }
+template <class T, int V, class P>
+void bn_forward_finish(const T* x, const float* gamma, const float* beta, const T* res, T* y, float* mean, float* istd,
+                       long rows, int c, int relu, float eps, const P* sums, int slabs, int stride,
+                       float* coef, hipStream_t st) {
   hipLaunchKernelGGL(bn_fwd_finish_kernel<P>, dim3((c + FIN_CH - 1) / FIN_CH), dim3(THREADS), 0, st, sums, gamma,
                      beta, mean, istd, coef, rows, c, eps, slabs, stride);
-  const size_t n4 = (size_t)rows * c / 4;
-  hipLaunchKernelGGL(bn_apply_kernel<T>, dim3(apply_grid(n4)), dim3(THREADS), 0, st, x, res, coef, y, n4, c, relu);
+  const ReduceShape rs = reduce_shape(c / V);
+  const long per = apply_rows(rows, rs);
+  hipLaunchKernelGGL((bn_apply_kernel<T, V>), dim3((unsigned)((rows + per - 1) / per), rs.col_slices), dim3(THREADS), 0, st, x, res,
+                     coef, y, relu, Span{rows, c, rs.tpr, rs.rpi, per});
 }
 
-template <class T>
-hipError_t bn_forward_t(const T* x, const float* gamma, const float* beta, const T* res, T* y, float* mean,
+template <class T, class P>
+void bn_forward_slices(const T* x, const float* gamma, const float* beta, const T* res, T* y, float* mean, float* istd,
+                       long rows, int c, int relu, float eps, const P* sums, int slabs, int stride, hipStream_t st) {
+  long per;
+  const dim3 grid = slice_grid(rows, c, &per);
+  hipLaunchKernelGGL((bn_fwd_slice_kernel<T, P>), grid, dim3(THREADS), 0, st, x, res, sums, gamma, beta, mean, istd,
+                     y, rows, c, relu, eps, slabs, stride, per);
+}
+
+template <class T, int V>
+hipError_t bn_forward_v(const T* x, const float* gamma, const float* beta, const T* res, T* y, float* mean,
                         float* istd, long rows, int c, int relu, float eps, void* workspace, hipStream_t st,
                         const BnSums& ready) {
   double* part = static_cast<double*>(workspace);
   float* coef = reinterpret_cast<float*>(part + (size_t)2 * MAX_SLABS * c);
   if (ready.part) {   // the producer of x left the sums
-    bn_forward_tail(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, ready.part, ready.slabs, ready.stride,
-                    coef, st);
-  } else {
-    const ReduceShape rs = reduce_shape(c);
-    const int slabs = slab_count<T>(rows, rs);
-    hipLaunchKernelGGL((bn_reduce_kernel<0, T>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, (const T*)nullptr,
-                       (const T*)nullptr, nullptr, nullptr, part, rows, c, rs.tpr, rs.rpi, slabs);
-    bn_forward_tail(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, (const double*)part, slabs, MAX_SLABS,
-                    coef, st);
+    if (slice_takes<T>(rows, ready.slabs))
+      bn_forward_slices(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, ready.part, ready.slabs, ready.stride, st);
+    else
+      bn_forward_finish<T, V>(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, ready.part, ready.slabs, ready.stride,
+                              coef, st);
+    return hipGetLastError();
   }
+  const ReduceShape rs = reduce_shape(c / V);
+  const int slabs = slab_count<T>(rows, rs);
+  hipLaunchKernelGGL((bn_reduce_kernel<0, T, V>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, (const T*)nullptr,
+                     (const T*)nullptr, nullptr, nullptr, part, Span{rows, c, rs.tpr, rs.rpi, (rows + slabs - 1) / slabs});
+  if (slice_takes<T>(rows, slabs))
+    bn_forward_slices(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, (const double*)part, slabs, MAX_SLABS, st);
+  else
+    bn_forward_finish<T, V>(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, (const double*)part, slabs, MAX_SLABS, coef, st);
   return hipGetLastError();
 }
 
-template <class T, class P>
-void bn_backward_tail(const T* x, const T* dy, const T* y, const float* gamma, const float* mean, const float* istd,
-                      T* dx, float* dgamma, float* dbeta, T* g_out, long rows, int c, const P* sums, int slabs,
-                      int stride, float* coef, hipStream_t st) {
-  if (slice_takes<T>(rows, slabs)) {
-    long per;
-    const dim3 grid = slice_grid(rows, c, &per);
-    hipLaunchKernelGGL((bn_bwd_slice_kernel<T, P>), grid, dim3(THREADS), 0, st, x, dy, y, sums, gamma, mean, istd,
-                       dgamma, dbeta, dx, g_out, rows, c, slabs, stride, per);
-    return;
-  }
+template <class T, int V, class P>
+void bn_backward_finish(const T* x, const T* dy, const T* y, const float* gamma, const float* mean, const float* istd,
+                        T* dx, float* dgamma, float* dbeta, T* g_out, long rows, int c, const P* sums, int slabs,
+                        int stride, float* coef, hipStream_t st) {
   hipLaunchKernelGGL(bn_bwd_finish_kernel<P>, dim3((c + FIN_CH - 1) / FIN_CH), dim3(THREADS), 0, st, sums, gamma,
                      istd, dgamma, dbeta, coef, rows, c, slabs, stride);
-  const size_t n4 = (size_t)rows * c / 4;
-  hipLaunchKernelGGL(bn_bwd_apply_kernel<T>, dim3(apply_grid(n4)), dim3(THREADS), 0, st, x, dy, y, mean, istd,
-                     coef, dx, g_out, n4, c);
+  const ReduceShape rs = reduce_shape(c / V);
+  const long per = apply_rows(rows, rs);
+  hipLaunchKernelGGL((bn_bwd_apply_kernel<T, V>), dim3((unsigned)((rows + per - 1) / per), rs.col_slices), dim3(THREADS), 0, st, x, dy, y,
+                     mean, istd, coef, dx, g_out, Span{rows, c, rs.tpr, rs.rpi, per});
 }
 
-template <class T>
-hipError_t bn_backward_t(const T* x, const T* dy, const T* y, const float* gamma, const float* mean,
+template <class T, class P>
+void bn_backward_slices(const T* x, const T* dy, const T* y, const float* gamma, const float* mean, const float* istd,
+                        T* dx, float* dgamma, float* dbeta, T* g_out, long rows, int c, const P* sums, int slabs,
+                        int stride, hipStream_t st) {
+  long per;
+  const dim3 grid = slice_grid(rows, c, &per);
+  hipLaunchKernelGGL((bn_bwd_slice_kernel<T, P>), grid, dim3(THREADS), 0, st, x, dy, y, sums, gamma, mean, istd,
+                     dgamma, dbeta, dx, g_out, rows, c, slabs, stride, per);
+}
+
+template <class T, int V>
+hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma, const float* mean,
                          const float* istd, T* dx, float* dgamma, float* dbeta, T* g_out, long rows, int c,
                          void* workspace, hipStream_t st, const BnSums& ready) {
   double* part = static_cast<double*>(workspace);
   float* coef = reinterpret_cast<float*>(part + (size_t)2 * MAX_SLABS * c);
   if (ready.part) {   // the data gradient left the sums
-    bn_backward_tail(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, ready.part, ready.slabs,
-                     ready.stride, coef, st);
-  } else {
-    const ReduceShape rs = reduce_shape(c);
-    const int slabs = slab_count<T>(rows, rs);
-    hipLaunchKernelGGL((bn_reduce_kernel<1, T>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, dy, y, mean,
-                       istd, part, rows, c, rs.tpr, rs.rpi, slabs);
-    bn_backward_tail(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, (const double*)part, slabs,
-                     MAX_SLABS, coef, st);
+    if (slice_takes<T>(rows, ready.slabs))
+      bn_backward_slices(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, ready.part, ready.slabs, ready.stride, st);
+    else
+      bn_backward_finish<T, V>(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, ready.part, ready.slabs,
+                               ready.stride, coef, st);
+    return hipGetLastError();
   }
+  const ReduceShape rs = reduce_shape(c / V);
+  const int slabs = slab_count<T>(rows, rs);
+  hipLaunchKernelGGL((bn_reduce_kernel<1, T, V>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, dy, y, mean,
+                     istd, part, Span{rows, c, rs.tpr, rs.rpi, (rows + slabs - 1) / slabs});
+  if (slice_takes<T>(rows, slabs))
+    bn_backward_slices(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, (const double*)part, slabs, MAX_SLABS, st);
+  else
+    bn_backward_finish<T, V>(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, (const double*)part, slabs,
+                             MAX_SLABS, coef, st);
   return hipGetLastError();
 }
 
@@ -635,10 +703,15 @@ hipError_t bn_forward(const void* x, const float* gamma, const float* beta, cons
   const BnSums ready = ready_sums ? *ready_sums : BnSums{nullptr, 0, 0};
   if (ready.part && (ready.slabs <= 0 || ready.slabs > MAX_SLABS || ready.stride < ready.slabs)) return hipErrorInvalidValue;
   if (dtype == DT_F32)
-    return bn_forward_t((const float*)x, gamma, beta, (const float*)res, (float*)y, mean, istd, rows, c, relu, eps,
+    return bn_forward_v<float, 4>((const float*)x, gamma, beta, (const float*)res, (float*)y, mean, istd, rows, c, relu, eps,
                         workspace, st, ready);
+  // eight channels per thread where the channels come in eights: every row then starts on a 16-byte address, as every tensor
+  // does (bf16 512 channels, 256 images of 28x28, both ways: 510 us against 556 with four)
+  if (dtype == DT_BF16 && c % 8 == 0)
+    return bn_forward_v<bf16_t, 8>((const bf16_t*)x, gamma, beta, (const bf16_t*)res, (bf16_t*)y, mean, istd, rows, c, relu,
+                                   eps, workspace, st, ready);
   if (dtype == DT_BF16)
-    return bn_forward_t((const bf16_t*)x, gamma, beta, (const bf16_t*)res, (bf16_t*)y, mean, istd, rows, c, relu,
+    return bn_forward_v<bf16_t, 4>((const bf16_t*)x, gamma, beta, (const bf16_t*)res, (bf16_t*)y, mean, istd, rows, c, relu,
                         eps, workspace, st, ready);
   return hipErrorInvalidValue;
 }
@@ -653,10 +726,13 @@ hipError_t bn_backward(const void* x, const void* dy, const void* y, const float
   if (ready.part && (y || ready.slabs <= 0 || ready.slabs > MAX_SLABS || ready.stride < ready.slabs))
     return hipErrorInvalidValue;
   if (dtype == DT_F32)
-    return bn_backward_t((const float*)x, (const float*)dy, (const float*)y, gamma, mean, istd, (float*)dx, dgamma,
+    return bn_backward_v<float, 4>((const float*)x, (const float*)dy, (const float*)y, gamma, mean, istd, (float*)dx, dgamma,
                          dbeta, (float*)g_out, rows, c, workspace, st, ready);
+  if (dtype == DT_BF16 && c % 8 == 0)
+    return bn_backward_v<bf16_t, 8>((const bf16_t*)x, (const bf16_t*)dy, (const bf16_t*)y, gamma, mean, istd, (bf16_t*)dx,
+                                    dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready);
   if (dtype == DT_BF16)
-    return bn_backward_t((const bf16_t*)x, (const bf16_t*)dy, (const bf16_t*)y, gamma, mean, istd, (bf16_t*)dx,
+    return bn_backward_v<bf16_t, 4>((const bf16_t*)x, (const bf16_t*)dy, (const bf16_t*)y, gamma, mean, istd, (bf16_t*)dx,
                          dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready);
   return hipErrorInvalidValue;
 }
