@@ -55,28 +55,4 @@ template <> struct Elem<bf16_t> {
   }
 };
 
-// One 16-byte access per thread: four fp32 or eight bf16 channels; or four bf16 channels (8 bytes).
-template <class T, int V> struct ElemV;
-template <class T> struct ElemV<T, 4> {
-  static __device__ __forceinline__ void load(const T* p, float (&v)[4]) { Elem<T>::load4(p, v); }
-  static __device__ __forceinline__ void store(T* p, const float (&v)[4]) { Elem<T>::store4(p, v); }
-};
-template <> struct ElemV<bf16_t, 8> {
-  static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
-    const uint4 q = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[2 * i] = __uint_as_float(w[i] << 16);
-      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) {
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = (uint32_t)float_to_bf16(v[2 * i]) | ((uint32_t)float_to_bf16(v[2 * i + 1]) << 16);
-    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-};
-
 }  // namespace acc
