@@ -596,9 +596,39 @@ const char* conv_variant_name(int v) {
   return (v >= 0 && v < V_COUNT) ? names[v] : "?";
 }
 
+// A strided data gradient as a whole: one stride-1 convolution per residue class of the output position, each with its own
+// sub-filter; the first launch carries the side job.  A probe spans all of them and names the first one's kernel.
+static hipError_t conv_igemm_split(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
+  const DgradSplit& d = *g.split;
+  if (!g.w || g.bias || g.relu || g.stats || g.bnb.sums) return hipErrorInvalidValue;
+  hipError_t e = filter_gather_transpose(d, const_cast<void*>(g.w), g.dtype, st);
+  if (e != hipSuccess) return e;
+  ConvGeom parts[kMaxDgradParts];
+  for (int i = 0; i < d.count; ++i) {
+    const DgradPart& pt = d.parts[i];
+    ConvGeom& c = parts[i] = g;
+    c.split = nullptr;
+    c.w = static_cast<const char*>(g.w) + pt.wt_offset;
+    c.p = pt.p; c.q = pt.q; c.r = pt.nr; c.s = pt.ns; c.stride = 1;
+    c.pad = pt.pad_y; c.pad_dx = pt.pad_x - pt.pad_y;
+    c.out_stride = d.stride; c.out_y0 = pt.y0; c.out_x0 = pt.x0;
+    if (i > 0) { c.side = ReduceJob{}; c.flip = FlipJob{}; }
+  }
+  if (conv_igemm_x3_parts_takes(parts, d.count)) return conv_igemm_x3_parts(parts, d.count, st, probe);
+  if (probe->before) (void)hipEventRecord(probe->before, st);
+  for (int i = 0; i < d.count; ++i) {
+    LaunchProbe one;
+    if ((e = conv_igemm(parts[i], st, &one)) != hipSuccess) return e;
+    if (i == 0) probe->variant = one.variant;
+  }
+  if (probe->after) (void)hipEventRecord(probe->after, st);
+  return hipSuccess;
+}
+
 hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
   LaunchProbe local;
   if (!probe) probe = &local;
+  if (g.split) return conv_igemm_split(g, st, probe);
   if (!g.in || !g.w || !g.out) return hipErrorInvalidValue;
   if (g.n_img <= 0 || g.h <= 0 || g.wd <= 0 || g.c <= 0 || g.p <= 0 || g.q <= 0 || g.n_out <= 0 ||
       g.r <= 0 || g.s <= 0 || g.stride <= 0 || g.pad < 0 || g.pad + g.pad_dx < 0 || g.out_stride <= 0 ||

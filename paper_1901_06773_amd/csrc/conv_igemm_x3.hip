@@ -210,41 +210,61 @@ __device__ __forceinline__ void x3_finish(const ConvGeom& g, int M, int K, int m
       }
       continue;
     }
+    // A strided result: the pixel of the lane's first row by division, the others by counting on, one carry at most per
+    // step of 1 or 5 rows (sixteen divisions per block: 57 us for the data gradient of 128 channels of 55x55
+    // from stride 2, 19 images; 48 so).  Old values are requested together.
+    float* const first = static_cast<float*>(g.out) + out_row_offset(g, mb) + n;
+    const ptrdiff_t dx = (ptrdiff_t)g.out_stride * g.n_out, dy = ((ptrdiff_t)g.out_stride * g.out_w - (ptrdiff_t)g.q * g.out_stride) * g.n_out;
+    const ptrdiff_t di = ((ptrdiff_t)g.out_h * g.out_w - (ptrdiff_t)g.p * g.out_stride * g.out_w) * g.n_out;
+    const bool count_on = g.q >= 5;                      // (uniform)
+    const int row0 = mb / g.q, q0 = mb - row0 * g.q, p0 = row0 % g.p;
+    auto rows = [&](auto&& use) {
+      float* o = first;
+      int q = q0, p = p0;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int m = mb + 8 * (v >> 2) + (v & 3);
-      if (m >= M || !col) continue;
-      float* o = static_cast<float*>(g.out) + out_row_offset(g, m) + n;
-      *o = !ACT && g.accumulate ? c[v] + *o : c[v];
+      for (int v = 0; v < 16; ++v) {
+        const int dr = 8 * (v >> 2) + (v & 3);
+        if (v > 0) {
+          if (count_on) {
+            const int d = (v & 3) ? 1 : 5;
+            q += d;
+            o += d * dx;
+            if (q >= g.q) {
+              q -= g.q;
+              o += dy;
+              if (++p == g.p) { p = 0; o += di; }
+            }
+          } else {
+            o = static_cast<float*>(g.out) + out_row_offset(g, mb + dr) + n;
+          }
+        }
+        if (dr < left) use(o, v);
+      }
+    };
+    if (!ACT && g.accumulate) {
+      float old[16];
+      rows([&](const float* o, int v) { old[v] = *o; });
+      rows([&](float* o, int v) { *o = c[v] + old[v]; });
+    } else {
+      rows([&](float* o, int v) { *o = c[v]; });
     }
   }
 }
 
-template <int MB, int NB, bool ACT>
-__global__ __launch_bounds__(256, 2) void igemm_x3_kernel(ConvGeom g, int M, int K, int n_tiles_n,
-                                                                              int n_tiles, int main_grid) {
-  constexpr int BM = 64 * MB, BN = 64 * NB, KC = 16;
-  constexpr int ROWB = KC * 2;                           // bytes per row and plane
-  constexpr int A_PLANE = BM * ROWB, B_PLANE = BN * ROWB;
-  constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
+// One tile of 64*MB x 64*NB, its operands staged in `lds`.
+template <int MB, int NB> struct Short {
+  static constexpr int BM = 64 * MB, BN = 64 * NB, KC = 16;
+  static constexpr int ROWB = KC * 2;                    // bytes per row and plane
+  static constexpr int A_PLANE = BM * ROWB, B_PLANE = BN * ROWB;
+  static constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
   static_assert(2 * STAGE >= 32 * 33 * 4, "side jobs");
-  __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE];
+};
 
-  if ((int)blockIdx.x >= main_grid) {
-    igemm_side_jobs<float>(g, (int)blockIdx.x - main_grid, lds);
-    return;
-  }
+template <int MB, int NB, bool ACT>
+__device__ __forceinline__ void short_tile(const ConvGeom& g, int M, int K, int m0, int n0, char* lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  // Forward products and data gradients are the critical path of an iteration; a weight gradient may run
-  // beside them on a stream of its own at the default wave priority.
-  __builtin_amdgcn_s_setprio(3);
-  // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a
-  // contiguous range of tiles (neighbouring tiles share operand rows in its L2).
-  const int per_xcd = main_grid >> 3;
-  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (tile >= n_tiles) return;
-  const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  using S = Short<MB, NB>;
+  constexpr int BM = S::BM, BN = S::BN, KC = S::KC, ROWB = S::ROWB, A_PLANE = S::A_PLANE, B_PLANE = S::B_PLANE, STAGE = S::STAGE;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave >> 1) * 32 * MB, wn0 = (wave & 1) * 32 * NB;
 
@@ -433,6 +453,54 @@ __global__ __launch_bounds__(256, 2) void igemm_x3_kernel(ConvGeom g, int M, int
 #endif
 }
 
+template <int MB, int NB, bool ACT>
+__global__ __launch_bounds__(256, 2) void igemm_x3_kernel(ConvGeom g, int M, int K, int n_tiles_n,
+                                                                              int n_tiles, int main_grid) {
+  using S = Short<MB, NB>;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * S::STAGE];
+  if ((int)blockIdx.x >= main_grid) {
+    igemm_side_jobs<float>(g, (int)blockIdx.x - main_grid, lds);
+    return;
+  }
+  // Forward products and data gradients are the critical path of an iteration; a weight gradient may run
+  // beside them on a stream of its own at the default wave priority.
+  __builtin_amdgcn_s_setprio(3);
+  // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a
+  // contiguous range of tiles (neighbouring tiles share operand rows in its L2).
+  const int per_xcd = main_grid >> 3;
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (tile >= n_tiles) return;
+  const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
+  short_tile<MB, NB, ACT>(g, M, K, tile_m * S::BM, tile_n * S::BN, lds);
+}
+
+// The parts of a strided data gradient in one launch.  Alone, a part of a 3x3 stride-2 filter is a quarter of the rows
+// and one to four taps: too few tiles and too short a K to fill the chip or to pay for a launch.  Together their tiles
+// even out, the parts with the longest K first, and each XCD keeps the same range of rows of every part: the parts
+// read the same rows of the gradient.  128 -> 128 3x3 stride 2 on 55x55,
+// 19 images, with the sub-filters' launches: 79 us apart, 57 together, 48 with the counted rows of the epilogue above.
+constexpr int kX3Parts = 4;
+struct X3Parts {
+  ConvGeom g[kX3Parts];
+  int M[kX3Parts], K[kX3Parts], tiles[kX3Parts], per_xcd[kX3Parts];
+};
+
+template <int MB, int NB>
+__global__ __launch_bounds__(256, 2) void igemm_x3_parts_kernel(X3Parts ps, int n_tiles_n, int main_grid) {
+  using S = Short<MB, NB>;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * S::STAGE];
+  if ((int)blockIdx.x >= main_grid) {
+    igemm_side_jobs<float>(ps.g[0], (int)blockIdx.x - main_grid, lds);
+    return;
+  }
+  __builtin_amdgcn_s_setprio(3);
+  int i = 0, at = blockIdx.x >> 3;             // place in the XCD's list: its tiles of part 0, of part 1, ...
+  for (; i < kX3Parts - 1 && at >= ps.per_xcd[i]; ++i) at -= ps.per_xcd[i];
+  const int tile = (blockIdx.x & 7) * ps.per_xcd[i] + at;
+  if (tile >= ps.tiles[i]) return;
+  const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
+  short_tile<MB, NB, false>(ps.g[i], ps.M[i], ps.K[i], tile_m * S::BM, tile_n * S::BN, lds);
+}
 
 // ---- long reductions: eight waves, each 64 x 64 (2 x 2 blocks), the steps of K dealt out to groups of waves
 //
@@ -836,6 +904,40 @@ double predicted_us(const Kind& k, long M, long N, long K) {
   return k.base + (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu);
 }
 
+// The same for the parts of a strided data gradient in one launch of a short kernel: the longest tile alone, or the compute
+// units' share of all tiles, the last tiles half filling the chip; strided rows and tiles of unlike length add a part.
+double predicted_parts_us(bool wide, const ConvGeom* parts, int n) {
+  const Kind& k = kKinds[wide ? X3_128 : X3_64];
+  double work = 0, longest = 0, last = 0;
+  for (int i = 0; i < n; ++i) {
+    const ConvGeom& g = parts[i];
+    const long M = (long)g.n_img * g.p * g.q, steps = ((long)g.r * g.s * g.c + 15) / 16;
+    const long tiles = ((M + k.bm - 1) / k.bm) * ((g.n_out + k.bn - 1) / k.bn);
+    const double shared = k.shared + k.shared_step * steps, alone = k.alone + k.alone_step * steps;
+    work += tiles * shared;
+    if (alone > longest) longest = alone;
+    if (shared > last) last = shared;
+  }
+  const double share = work / 256 + last / 2;
+  const double us = k.base + (share > longest ? share : longest);
+  return wide ? us * 1.10 + 8 : us * 1.05 + 6;
+}
+
+template <int MB, int NB>
+void launch_parts(X3Parts& ps, int n, hipStream_t st, const LaunchProbe* probe, long side_blocks) {
+  const int tn = (ps.g[0].n_out + 64 * NB - 1) / (64 * NB);
+  long per_xcd = 0;
+  for (int i = 0; i < n; ++i) {
+    ps.tiles[i] = (ps.M[i] + 64 * MB - 1) / (64 * MB) * tn;
+    ps.per_xcd[i] = (ps.tiles[i] + 7) / 8;
+    per_xcd += ps.per_xcd[i];
+  }
+  const int main_grid = (int)(per_xcd * 8);
+  if (probe->before) (void)hipEventRecord(probe->before, st);
+  hipLaunchKernelGGL((igemm_x3_parts_kernel<MB, NB>), dim3((unsigned)(main_grid + side_blocks)), dim3(256), 0, st, ps, tn, main_grid);
+  if (probe->after) (void)hipEventRecord(probe->after, st);
+}
+
 // the launches that read every tap from one window of consecutive pixels, if it fits
 bool window_takes(const ConvGeom& g) {
   using D = Deep<2, 1, true>;
@@ -886,6 +988,68 @@ hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, Launch
     case X3_DEEP_2x2: launch_deep<2, 2, false>(g, M, K, st, probe); break;
     default: launch_deep<1, 1, false>(g, M, K, st, probe); break;
   }
+  return hipGetLastError();
+}
+
+// The parts go into one launch where that is predicted to take less than the parts one after the other, with a launch's
+// gap between them.  Of 21 shapes measured (2 to 256 images, 32 to 1024 channels, 3x3 to 7x7, stride 2) 19 go into one launch:
+// 128 channels of 56x56, 32 images 92 -> 71 us, 512 of 14x14, 256 images 392 -> 346; not 1024 channels of 14x14, 64 images
+// (366 us apart, 396 together) and 256 of 28x28 with 5x5 filters, 64 images (261, 276), which the deep kernels do better.
+static double best_alone_us(const ConvGeom& g) {
+  double best = 1e30;
+  for (int v = 0; v < X3_KINDS; ++v) {
+    if (v == X3_WINDOW && !window_takes(g)) continue;
+    const double us = predicted_us(kKinds[v], (long)g.n_img * g.p * g.q, g.n_out, (long)g.r * g.s * g.c);
+    if (us < best) best = us;
+  }
+  return best;
+}
+
+bool conv_igemm_x3_parts_takes(const ConvGeom* parts, int n) {
+  if (n < 2 || n > kX3Parts) return false;
+  double apart = (n - 1) * 1.5;
+  for (int i = 0; i < n; ++i) {
+    const ConvGeom& g = parts[i];
+    const long M = (long)g.n_img * g.p * g.q, K = (long)g.r * g.s * g.c;
+    if (g.p <= 0 || g.q <= 0 || g.r <= 0 || g.s <= 0 || M >= (1L << 28) || K >= (1L << 31) || !conv_igemm_x3_takes(g, M, K)) return false;
+    apart += best_alone_us(g);
+  }
+  const double a = predicted_parts_us(true, parts, n), b = predicted_parts_us(false, parts, n);
+  return (a < b ? a : b) < apart * 1.08;            // (1.08: strided rows)
+}
+
+hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, LaunchProbe* probe) {
+  const ConvGeom& g = parts[0];
+  if (n < 1 || n > kX3Parts || !g.in || !g.out || g.n_img <= 0 || g.h <= 0 || g.wd <= 0 || (long)g.n_img * g.h * g.wd >= (1L << 31)) return hipErrorInvalidValue;
+  if (g.side.count && (!g.side.part || !g.side.dw || g.side.splits < 1)) return hipErrorInvalidValue;
+  if (g.flip.wt && (!g.flip.w || g.flip.cout <= 0 || g.flip.cin <= 0 || g.flip.r <= 0 || g.flip.s <= 0)) return hipErrorInvalidValue;
+  int order[kX3Parts];
+  for (int i = 0; i < n; ++i) {                   // the longest K first
+    int j = i;
+    for (; j > 0 && parts[order[j - 1]].r * parts[order[j - 1]].s < parts[i].r * parts[i].s; --j) order[j] = order[j - 1];
+    order[j] = i;
+  }
+  X3Parts ps{};
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    const ConvGeom& c = parts[order[i]];
+    if (!c.w || c.pad < 0 || c.pad + c.pad_dx < 0 || c.out_y0 < 0 || c.out_x0 < 0 ||
+        c.out_y0 + (long)(c.p - 1) * c.out_stride >= c.out_h || c.out_x0 + (long)(c.q - 1) * c.out_stride >= c.out_w)
+      return hipErrorInvalidValue;
+    ps.g[i] = c;
+    ps.M[i] = c.n_img * c.p * c.q;
+    ps.K[i] = c.r * c.s * c.c;
+    tiles += (long)((ps.M[i] + 63) / 64) * ((c.n_out + 63) / 64) + 8;
+  }
+  ps.g[0].side = g.side;                          // the side jobs are read from the first part of the launch
+  ps.g[0].flip = g.flip;
+  const long narrow = (long)((g.side.count + 1023) / 1024) + (g.flip.wt ? flip_tiles(g.flip.cout, g.flip.cin, g.flip.r, g.flip.s) : 0);
+  if (tiles + narrow > (1L << 30)) return hipErrorInvalidValue;
+  probe->variant = V_IGEMM_X3;
+  if (predicted_parts_us(true, parts, n) < predicted_parts_us(false, parts, n))
+    launch_parts<2, 2>(ps, n, st, probe, narrow);
+  else
+    launch_parts<1, 1>(ps, n, st, probe, narrow);
   return hipGetLastError();
 }
 

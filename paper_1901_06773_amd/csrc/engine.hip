@@ -848,7 +848,7 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       cg.out_h = h; cg.out_w = wd;
       if (split) {
         // strided and larger than 1x1: one stride-1 convolution per residue class of the dx
-        // position, each with its own sub-filter; the first launch carries the side job
+        // position, each with its own sub-filter
         DgradPart parts[kMaxDgradParts];
         bool covers_all = false;
         size_t wt_bytes = 0;
@@ -859,21 +859,9 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
           e = fill_zero(ptr(s.dx), (size_t)k * h * wd * l->cin * es / 4, st);
           if (e != hipSuccess) return e;
         }
-        double work = 0;
-        for (int i = 0; i < np; ++i) work += (double)parts[i].p * parts[i].q * parts[i].nr * parts[i].ns;
-        for (int i = 0; i < np; ++i) {
-          const DgradPart& pt = parts[i];
-          e = filter_gather_transpose(wk, ptr(s.ws), l->cout, l->cin, l->r, l->s, l->stride, pt, dt, st);
-          if (e != hipSuccess) return e;
-          cg.w = (const char*)ptr(s.ws) + pt.wt_offset;
-          cg.p = pt.p; cg.q = pt.q; cg.r = pt.nr; cg.s = pt.ns;
-          cg.pad = pt.pad_y; cg.pad_dx = pt.pad_x - pt.pad_y;
-          cg.out_stride = l->stride; cg.out_y0 = pt.y0; cg.out_x0 = pt.x0;
-          e = igemm(cg, conv_flops * ((double)pt.p * pt.q * pt.nr * pt.ns / work));
-          if (e != hipSuccess) return e;
-          cg.flip = FlipJob{};         // the side job went with the first part
-        }
-        return hipSuccess;
+        const DgradSplit whole{wk, l->cout, l->cin, l->r, l->s, l->stride, parts, np};
+        cg.split = &whole;
+        return igemm(cg, conv_flops);
       }
       if (l->stride == 1) {
         cg.p = h; cg.q = wd; cg.pad = l->r - 1 - l->pad; cg.out_stride = 1;

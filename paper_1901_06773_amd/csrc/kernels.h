@@ -46,6 +46,14 @@ struct BnBackwardSums {
   int stride;
 };
 
+// A strided data gradient: the residue classes of dgrad_split(), and the filter w[cout][r][s][cin] their sub-filters come from.
+struct DgradSplit {
+  const void* w;
+  int cout, cin, r, s, stride;
+  const DgradPart* parts;
+  int count;
+};
+
 // Implicit-GEMM view of a convolution-like gather:
 //   out[m][n] (+)= sum_{r,t,c} in[img, p*stride+r-pad, q*stride+t-pad, c] * w[n][(r,t,c)]
 // with row m = (img, p, q) over a P x Q grid (columns use pad + pad_dx).  The result row is
@@ -78,6 +86,10 @@ struct ConvGeom {
   float* stats;
   int stats_stride;
   BnBackwardSums bnb;   // fp32 storage, plain dense output, no accumulation
+  // Optional (host memory, read by conv_igemm only): the launch is a strided data gradient as a whole.  conv_igemm writes
+  // the sub-filter of every part to w + its wt_offset (w is then a workspace) and runs the parts; p .. pad_dx, the
+  // output's stride and first pixel come from them.
+  const DgradSplit* split;
 };
 // Largest number of row slabs a batch-norm statistics pass adds up.
 constexpr int kBnMaxSlabs = 1024;
@@ -104,6 +116,9 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, cons
 // fp32 products on the bf16 matrix cores (conv_igemm_x3.hip): as above.
 bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
+// The parts of a strided data gradient in one launch, where that is the faster way (a function of the shapes only).
+bool conv_igemm_x3_parts_takes(const ConvGeom* parts, int n);
+hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, LaunchProbe* probe);
 // A handful of input channels (conv_smallc.hip): as above.
 bool conv_smallc_takes(const ConvGeom& g, long M);
 hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe);
@@ -155,10 +170,8 @@ hipError_t reduce_parts(const ReduceJob& job, hipStream_t st);
 hipError_t filter_flip_transpose(const void* w, void* wt, int cout, int cin, int r, int s, int dtype,
                                  hipStream_t st);
 
-// Sub-filter of one residue class of a strided data gradient (see dgrad_split.h), written at
-// wt + part.wt_offset.
-hipError_t filter_gather_transpose(const void* w, void* wt, int cout, int cin, int r, int s, int stride,
-                                   const DgradPart& part, int dtype, hipStream_t st);
+// The sub-filters of all residue classes of a strided data gradient (dgrad_split.h), each written at wt + its wt_offset.
+hipError_t filter_gather_transpose(const DgradSplit& d, void* wt, int dtype, hipStream_t st);
 
 // Batch norm over rows x c (NHWC flattened).  workspace: bn_workspace_bytes(c).
 // x, res, y, dy, dx, g_out: dtype; gamma, beta, mean, istd, dgamma, dbeta: fp32.

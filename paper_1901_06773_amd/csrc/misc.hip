@@ -40,27 +40,42 @@ __global__ __launch_bounds__(256) void flip_transpose_kernel(const T* __restrict
   }
 }
 
-// wt[ci][r'][t'][co] = w[co][r0 + (nr-1-r')*step][t0 + (ns-1-t')*step][ci]: the sub-filter of one
-// residue class of a strided data gradient; same tiling as above.
+// wt[ci][r'][t'][co] = w[co][r0 + (nr-1-r')*step][t0 + (ns-1-t')*step][ci]: the sub-filters of all residue classes of a
+// strided data gradient in one launch (a tap of w belongs to at most one of them; grid.z = taps); same tiling as above.
+struct GatherParts {
+  int r0[kMaxDgradParts], t0[kMaxDgradParts], nr[kMaxDgradParts], ns[kMaxDgradParts];
+  size_t offset[kMaxDgradParts];
+  int count;
+};
+
 template <class T>
-__global__ __launch_bounds__(256) void gather_transpose_kernel(const T* __restrict__ w,
-                                                               T* __restrict__ wt, int cout, int cin,
-                                                               int r, int s, int nr, int ns, int r0,
-                                                               int t0, int step) {
+__global__ __launch_bounds__(256) void gather_transpose_kernel(const T* __restrict__ w, char* __restrict__ out, int cout, int cin,
+                                                               int r, int s, int step, GatherParts gp) {
   __shared__ T tile[32][33];
-  const int tap = blockIdx.z;                       // r'*ns + t' of the output
-  const int kr = r0 + (nr - 1 - tap / ns) * step, kt = t0 + (ns - 1 - tap % ns) * step;
-  const int src_tap = kr * s + kt;
   const int co0 = blockIdx.y * 32, ci0 = blockIdx.x * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-  for (int i = ty; i < 32; i += 8) {
-    const int co = co0 + i, ci = ci0 + tx;
-    tile[i][tx] = (co < cout && ci < cin) ? w[((size_t)co * r * s + src_tap) * cin + ci] : T(0);
-  }
-  __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int ci = ci0 + i, co = co0 + tx;
-    if (ci < cin && co < cout) wt[((size_t)ci * nr * ns + tap) * cout + co] = tile[tx][i];
+  for (int src_tap = blockIdx.z; src_tap < r * s; src_tap += gridDim.z) {
+    const int kr = src_tap / s, kt = src_tap - kr * s;
+    int part = -1, jr = 0, jt = 0;                  // the class of the tap, and the tap's place in it
+    for (int i = 0; i < gp.count; ++i) {
+      const int dr = kr - gp.r0[i], dt = kt - gp.t0[i];
+      if (dr >= 0 && dt >= 0 && dr % step == 0 && dt % step == 0 && dr / step < gp.nr[i] && dt / step < gp.ns[i]) {
+        part = i; jr = dr / step; jt = dt / step;
+      }
+    }
+    if (part < 0) continue;                         // (the same for the whole workgroup)
+    const int nr = gp.nr[part], ns = gp.ns[part], tap = (nr - 1 - jr) * ns + (ns - 1 - jt);
+    T* wt = reinterpret_cast<T*>(out + gp.offset[part]);
+    __syncthreads();
+    for (int i = ty; i < 32; i += 8) {
+      const int co = co0 + i, ci = ci0 + tx;
+      tile[i][tx] = (co < cout && ci < cin) ? w[((size_t)co * r * s + src_tap) * cin + ci] : T(0);
+    }
+    __syncthreads();
+    for (int i = ty; i < 32; i += 8) {
+      const int ci = ci0 + i, co = co0 + tx;
+      if (ci < cin && co < cout) wt[((size_t)ci * nr * ns + tap) * cout + co] = tile[tx][i];
+    }
   }
 }
 
@@ -585,17 +600,23 @@ hipError_t filter_flip_transpose(const void* w, void* wt, int cout, int cin, int
   return hipGetLastError();
 }
 
-hipError_t filter_gather_transpose(const void* w, void* wt, int cout, int cin, int r, int s, int stride,
-                                   const DgradPart& pt, int dtype, hipStream_t st) {
-  if (!w || !wt || cout <= 0 || cin <= 0 || r <= 0 || s <= 0 || stride <= 0 || pt.nr <= 0 || pt.ns <= 0 ||
-      pt.r0 < 0 || pt.t0 < 0 || pt.r0 + (pt.nr - 1) * stride >= r || pt.t0 + (pt.ns - 1) * stride >= s ||
-      pt.nr * pt.ns > 65535)
+hipError_t filter_gather_transpose(const DgradSplit& d, void* wt, int dtype, hipStream_t st) {
+  if (!d.w || !wt || !d.parts || d.count <= 0 || d.count > kMaxDgradParts || d.cout <= 0 || d.cin <= 0 || d.r <= 0 || d.s <= 0 ||
+      d.stride <= 0 || (long)d.r * d.s >= (1L << 31))
     return hipErrorInvalidValue;
-  const dim3 grid((cin + 31) / 32, (cout + 31) / 32, pt.nr * pt.ns);
+  GatherParts gp{};
+  gp.count = d.count;
+  for (int i = 0; i < d.count; ++i) {
+    const DgradPart& pt = d.parts[i];
+    if (pt.nr <= 0 || pt.ns <= 0 || pt.r0 < 0 || pt.t0 < 0 || pt.r0 + (pt.nr - 1) * d.stride >= d.r ||
+        pt.t0 + (pt.ns - 1) * d.stride >= d.s)
+      return hipErrorInvalidValue;
+    gp.r0[i] = pt.r0; gp.t0[i] = pt.t0; gp.nr[i] = pt.nr; gp.ns[i] = pt.ns; gp.offset[i] = pt.wt_offset;
+  }
+  const dim3 grid((d.cin + 31) / 32, (d.cout + 31) / 32, d.r * d.s < 65535 ? d.r * d.s : 65535);
   if (grid.y > 65535) return hipErrorInvalidValue;
-  ACC_DISPATCH(dtype, hipLaunchKernelGGL(gather_transpose_kernel<T>, grid, dim3(256), 0, st, (const T*)w,
-                                         (T*)((char*)wt + pt.wt_offset), cout, cin, r, s, pt.nr, pt.ns, pt.r0,
-                                         pt.t0, stride));
+  ACC_DISPATCH(dtype, hipLaunchKernelGGL(gather_transpose_kernel<T>, grid, dim3(256), 0, st, (const T*)d.w, (char*)wt, d.cout,
+                                         d.cin, d.r, d.s, d.stride, gp));
   return hipGetLastError();
 }
 

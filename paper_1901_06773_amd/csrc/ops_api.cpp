@@ -68,18 +68,14 @@ extern "C" int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n,
       if (bytes % 4) return ACC_EINVAL;
       if ((e = fill_zero((float*)dx, bytes / 4, st)) != hipSuccess) return status(e);
     }
-    for (int i = 0; i < np; ++i) {
-      const DgradPart& pt = parts[i];
-      if ((e = filter_gather_transpose(w, workspace, cout, cin, r, s, stride, pt, dtype, st)) != hipSuccess) return status(e);
-      ConvGeom g{};
-      g.in = dy; g.w = (const char*)workspace + pt.wt_offset; g.out = dx; g.dtype = dtype;
-      g.n_img = n; g.h = ho; g.wd = wo; g.c = cout; g.n_out = cin;
-      g.p = pt.p; g.q = pt.q; g.r = pt.nr; g.s = pt.ns; g.stride = 1; g.pad = pt.pad_y; g.pad_dx = pt.pad_x - pt.pad_y;
-      g.out_h = h; g.out_w = wd; g.out_stride = stride; g.out_y0 = pt.y0; g.out_x0 = pt.x0;
-      g.accumulate = accumulate;
-      if ((e = conv_igemm(g, st)) != hipSuccess) return status(e);
-    }
-    return ACC_OK;
+    if (np == 0) return ACC_OK;      // no position of dx has a tap
+    const DgradSplit split{w, cout, cin, r, s, stride, parts, np};
+    ConvGeom g{};
+    g.in = dy; g.w = workspace; g.out = dx; g.dtype = dtype;
+    g.n_img = n; g.h = ho; g.wd = wo; g.c = cout; g.n_out = cin;
+    g.out_h = h; g.out_w = wd; g.accumulate = accumulate;
+    g.split = &split;
+    return status(conv_igemm(g, st));
   }
   const size_t filt = al256((size_t)cout * cin * r * s * sizeof(float));
   if (!workspace || workspace_bytes < filt) return ACC_EINVAL;
