@@ -25,34 +25,30 @@ struct SmallGeom {
   int h, wd, c, p, q, r, s, stride, pad;
   int row_words;                                       // LDS words per input row: (wd + 2 * pad) * c, plus what the last group of eight overhangs, even
   int rows;                                            // output rows per group, at most
+  uint32_t row_inv;                                    // i / row_words = (i * row_inv) >> 32 for the words of a group
 };
 
 // input rows of the output rows [p0, p0 + n_rows) of image img; waits for nothing, the caller synchronises
-template <class T>
+template <int U, class T>                              // U words of a thread on their way at once
 __device__ __forceinline__ void stage_rows(const T* __restrict__ x, const SmallGeom& sg, int img, int p0, int n_rows, float* lds) {
   const int in_rows = (n_rows - 1) * sg.stride + sg.r, len = sg.wd * sg.c, lead = sg.pad * sg.c;
-  const T* src = x + (size_t)img * sg.h * len;
-  for (int col = threadIdx.x; col < sg.row_words; col += SC_THREADS) {
-    const int at = col - lead;
-    const bool in = at >= 0 && at < len;
-    int row = 0;
-    for (; row + 8 <= in_rows; row += 8) {
-      float v[8];
+  const int total = in_rows * sg.row_words, iy0 = p0 * sg.stride - sg.pad;
+  // addresses count from the group's first row; a word outside the image reads the nearest row's first value and is dropped
+  const T* src = x + ((ptrdiff_t)img * sg.h + iy0) * len;
+  const int spare = (min(max(iy0, 0), sg.h - 1) - iy0) * len;
+#pragma unroll 1
+  for (int i0 = threadIdx.x; i0 < total; i0 += U * SC_THREADS) {
+    float v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int iy = p0 * sg.stride - sg.pad + row + u;
-        const bool ok = in && (unsigned)iy < (unsigned)sg.h;
-        const float t = Elem<T>::load(src + (ok ? (size_t)iy * len + at : 0));
-        v[u] = ok ? t : 0.f;
-      }
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * SC_THREADS, row = (int)__umulhi((uint32_t)i, sg.row_inv), at = i - row * sg.row_words - lead, iy = iy0 + row;
+      const bool ok = (i < total) & ((unsigned)at < (unsigned)len) & ((unsigned)iy < (unsigned)sg.h);
+      const float t = Elem<T>::load(src + (ok ? row * len + at : spare));
+      v[u] = ok ? t : 0.f;
+    }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) lds[(row + u) * sg.row_words + col] = v[u];
-    }
-    for (; row < in_rows; ++row) {
-      const int iy = p0 * sg.stride - sg.pad + row;
-      const bool ok = in && (unsigned)iy < (unsigned)sg.h;
-      lds[row * sg.row_words + col] = ok ? Elem<T>::load(src + (size_t)iy * len + at) : 0.f;
-    }
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * SC_THREADS < total) lds[i0 + u * SC_THREADS] = v[u];
   }
 }
 
@@ -122,7 +118,7 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_fwd_kernel(ConvGeom g, S
     const int img = grp / groups_per_img, p0 = (grp - img * groups_per_img) * sg.rows;
     const int n_rows = min(sg.rows, sg.p - p0), pairs = (n_rows + 1) >> 1;
     __syncthreads();                                   // the rows of the group before are no longer read
-    stage_rows(static_cast<const T*>(g.in), sg, img, p0, n_rows, rows);
+    stage_rows<16>(static_cast<const T*>(g.in), sg, img, p0, n_rows, rows);
     __syncthreads();
     for (int unit = wave; unit < pairs * qb; unit += SC_WAVES) {
       const int pr = (unit / qb) * 2, q0 = (unit % qb) * 32;
@@ -204,6 +200,9 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_fwd_kernel(ConvGeom g, S
 // workgroup column.  A step is 16 positions of one output row: dy comes straight from memory (eight positions per lane), X
 // from the rows in LDS, every lane at its own columns' places.  The waves take every eighth step of a group of rows and keep
 // the whole 64 x 160 block (2 x 5 blocks of 32 x 32); the workgroup adds them up at the end and writes one part.
+// Bound by trips to memory that nothing hides (the sums take 160 registers, so few loads can be on their way): the rows of a group
+// staged many words at a time instead of a row's, and the first dy values asked for before them, 124 -> 106 us (3->64 7x7/2
+// at 224x224, fp32, 32 images) and 278 -> 247 us (bf16, 128 images); sixteen words at a time spill and take 159 and 338.
 template <class T>
 __global__ __launch_bounds__(SC_THREADS, 1) void smallc_wgrad_kernel(WgradGeom g, SmallGeom sg, int rows_total, int rows_per_split,
                                                                       float* out, size_t split_stride) {
@@ -244,11 +243,11 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_wgrad_kernel(WgradGeom g
           v[i][e] = ok ? t : 0.f;
         }
     };
-    __syncthreads();
-    stage_rows(static_cast<const T*>(g.x), sg, img, p0, n_rows, rows);
     const int n_steps = n_rows * spr;
     float nv[2][8];
-    if (wave < n_steps) load(wave, nv);
+    if (wave < n_steps) load(wave, nv);                // on its way while the rows are staged
+    __syncthreads();
+    stage_rows<NP == 1 ? 8 : 4>(static_cast<const T*>(g.x), sg, img, p0, n_rows, rows);   // (the sums hold 160 registers)
     __syncthreads();
     for (int s = wave; s < n_steps; s += SC_WAVES) {
       x3_v4u a[2][NP];
@@ -317,10 +316,11 @@ static_assert(SC_WAVES * 64 * 32 <= SC_ROW_WORDS, "the waves' sums");
 
 // Rows per group (0: the shape is not taken): as many as their input rows fit in LDS, at most eight
 SmallGeom small_geom(int h, int wd, int c, int p, int q, int r, int s, int stride, int pad) {
-  SmallGeom sg{h, wd, c, p, q, r, s, stride, pad, 0, 0};
+  SmallGeom sg{h, wd, c, p, q, r, s, stride, pad, 0, 0, 0};
   const long words = (long)(wd + 2 * pad) * c + 8;
   if (words > SC_ROW_WORDS) return sg;
   sg.row_words = (int)((words + 1) & ~1L);
+  sg.row_inv = (uint32_t)(((1ull << 32) + sg.row_words - 1) / sg.row_words);   // exact while i * row_words < 2^32
   for (int n = 8; n >= 1; --n)
     if ((long)((n - 1) * stride + r) * sg.row_words <= SC_ROW_WORDS) { sg.rows = n < p ? n : p; break; }
   return sg;
