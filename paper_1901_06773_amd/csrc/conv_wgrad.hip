@@ -579,11 +579,8 @@ struct WgradCfg {
   int tiles_co, tiles_j, splits, chunks_per_split;
 };
 
-// Depends on the shape only (never on addresses or on the swap plan).  The m range is cut into
-// as many parts as keep the launch within 768 workgroups, three per CU (what the
-// register-staged loader's LDS allows; measured with the direct loader at minibatch 41:
-// 512 -> 86, 768 -> 96, 1024 -> 99, 1280 -> 88 TFLOP/s, and the larger part count of 1024
-// costs the reduction what it gains here), at least 8 chunks of 32 rows each.
+// The choices below depend on the shape only, never on addresses or on the swap plan.
+//
 // bf16 storage on the bf16 matrix cores: channel counts the 128 x 128 tile of wgrad_bf16_kernel takes
 inline bool bf16_mfma_shape(int dtype, int cin, int cout) { return dtype == DT_BF16 && cin % 8 == 0 && cout % 8 == 0; }
 
@@ -617,15 +614,10 @@ WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   c.tiles_j = (int)((J + BN - 1) / BN);
   const long tiles = (long)c.tiles_co * c.tiles_j;
   const long chunks = (Mrows + BKM - 1) / BKM;
-  // One round of workgroups.  Alone the kernel is fastest with 768 (three per CU: measured 86 / 96 / 99 / 88
-  // TFLOP/s at 512 / 768 / 1024 / 1280 when the choice was first made; 93 against 102 now), but in the step it
-  // runs on a stream of its own beside the data gradient and the next batch norm.  Those are the critical
-  // path, and at small minibatches, where their fixed costs weigh most, two weight-gradient workgroups per CU
-  // leave them the larger share of the matrix cores; at large minibatches the weight gradient itself becomes
-  // the longer chain.  ResNet-152, images/s with 512 / 768 everywhere: minibatch 32 1099 / 1110, 36 1159 / 1135,
-  // 41 1233 / 1194, 48 1177 / 1154, 52 1184 / 1199, 56 1186 / 1220, 64 1208 / 1205, 128 1263 / 1314; the
-  // row count below (14 x 14 maps up to minibatch 50) takes the better of the two everywhere but at 32.
-  // The per-element loader (3-channel stem, nothing beside it) keeps 768.
+  // What is left here is small (at most 160 positions) or has channels the matrix-core kernels don't take.  One round of
+  // workgroups, at least 8 chunks of 32 rows each: three per CU, or two where whole groups of 64 channels meet few positions
+  // (512 / 768 / 1024 / 1280 workgroups on the 3x3 layers at minibatch 41: 86 / 96 / 99 / 88 TFLOP/s, and beside a data
+  // gradient two per CU leave that the larger share).
   const long target = cin % 64 ? 768 : Mrows <= 9800 ? 512 : 768;
   long splits = target / tiles;
   const long max_splits = chunks / 8 > 0 ? chunks / 8 : 1;
@@ -648,11 +640,10 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
   const long rows = (long)n_img * p * q;
   int splits = choose(rows, cin, cout, r, s, dtype).splits;
   if (x3_shape(dtype, rows, cin, cout)) {
-    // (the other kernel's count matters only where the operands may leave the 32-bit ranges; the input of a strided
-    // convolution has up to stride^2 <= 16 times the rows)
+    // never less than the other kernel's parts: it runs where the operands leave the 32-bit ranges, and a size that grows
+    // with the minibatch the way it does keeps plans under a budget as they were
     const int sx = wgrad_x3_choose(rows, cin, cout, r, s).splits;
-    const bool sure = p <= 4096 && q <= 4096 && rows * (cin > cout ? cin : cout) * 4 * 20 <= 0xFFFFFF00L;
-    splits = sure ? sx : sx > splits ? sx : splits;
+    if (sx > splits) splits = sx;
   }
   if (const int sc = wgrad_smallc_splits(rows, cin, cout, r, s); sc > splits) splits = sc;   // (either kernel may run)
   if (splits <= 1) return 0;

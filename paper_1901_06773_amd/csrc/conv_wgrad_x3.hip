@@ -351,7 +351,8 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
 // the number of parts with the smallest predicted time,
 //   rounds of 256 workgroups x (fixed + per step of a group) + 3 us for the reduction + 1 byte / 4 TB/s for every part
 // written and read, with 7.0 + 1.05 us (128 x 128 tile) and 4.5 + 1.75 us (64 x 64, eight groups) as measured.  At least
-// two steps per group and part; the parts together take at most 32 MiB.
+// 16 steps per part, as the kernels before (more parts of small layers gain little alone and made the scratch memory jump from one
+// minibatch to the next, so that plans no longer fitted under budgets they had fitted under); at most 32 MiB together.
 WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s) {
   const long J = (long)r * s * cin, steps = (Mrows + 15) / 16;
   WgradX3Cfg best{};
@@ -364,7 +365,7 @@ WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s) {
     for (long want = 1; want <= 256; ++want) {
       const long per = (steps + want - 1) / want, splits = (steps + per - 1) / per;
       if (splits != want) continue;
-      if (splits > 1 && (per < 2 * ks || splits * cout * J * 4 > (32L << 20))) break;
+      if (splits > 1 && (per < 16 || splits * cout * J * 4 > (32L << 20))) break;
       const long rounds = (tiles * splits + 255) / 256;
       const double us = rounds * (wt == 2 ? 7.0 + 1.05 * ((per + ks - 1) / ks) : 4.5 + 1.75 * ((per + ks - 1) / ks)) +
                         (splits > 1 ? 3.0 + splits * part_us : 0.0);

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(THREADS) void maxpool_bwd_kernel(const T* __restric
 // per column of 2x2 blocks of input positions (MP_STRIP of them, top to bottom) and four channels.  The block (rows
 // 2a, 2a+1, columns 2b, 2b+1) is covered by the windows p in {a, a+1}, q in {b, b+1} and by no other.  Going down, the
 // windows of row a+1 are the next block's row a, and their first input row is the last one of the windows above: ten
-// loads of x per block where every block on its own takes 36 (64 channels, 112x112, 32 images: 104.5 us before, 59 now;
+// loads of x per block where every block on its own takes 36 (64 channels, 112x112, 32 images: 104.5 us before, 56 now;
 // the 232 MB it has to move take 50).  Windows are visited in the same (p, q) order and the same
 // first maximum wins, so every sum has the same terms in the same order as in the kernel above.
 constexpr int MP_STRIP = 8;
