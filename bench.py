@@ -7,7 +7,7 @@ budget on one MI355X (benchmark configs[3]), synthetic ImageNet-shaped data.
 Prints ONE JSON line.  `value` = images/s over exactly K timed steps at the headline
 minibatch, inputs resident in HBM (`pcie_inclusive` gives the same run with the batch handed
 over in pinned host memory, the first layer's prefetch of Algorithm 1).  `roofline` prices
-the dominant convolution kernel (by total time in a step) against the fp32 MFMA peak;
+the dominant convolution kernel (by total time in a step) against the matrix-core peak;
 `conv.by_shape` every distinct convolution shape and role; `swap_points` the swap engine
 where it has work to do (link GB/s, hidden fraction of the copy time, no-swap reference at
 the same minibatch); `cpu_baseline` times the CPU oracle on a bounded sample of the workload.
@@ -23,8 +23,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 GiB = 1 << 30
-PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X, dense fp32 matrix
-PEAK_BF16_MFMA_TFLOPS = 2500.0    # dense bf16 matrix
+PEAK_BF16_MFMA_TFLOPS = 2500.0    # MI355X, dense bf16 matrix
+PEAK_FP32_MFMA_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6   # an fp32 product is six bf16 products (the fp32 matrix cores: 157.3)
 PEAK_HBM_GBS = 8000.0
 MAX_TIMED_SWAP_BYTES = 24 << 30   # the library refuses event timing of plans that swap more
 MAX_TIMED_POINT_BYTES = 16 << 30  # swap points above this are not event-timed here (copy time from the calibrated rate)
@@ -57,11 +57,11 @@ def parse():
     return ap.parse_args()
 
 
-# HBM bytes per launch of the dominant kernel (igemm_kernel<direct>), from rocprofv3 --pmc FETCH_SIZE /
-# WRITE_SIZE runs of this script, scaled by what the same counters read for sgd_kernel
+# HBM bytes per launch of the dominant kernel, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script, scaled
+# by what the same counters read for sgd_kernel
 # (profiles/resnet152_k41_hbm_traffic_pmc.txt).  A figure of that profile, not of this run: counters
-# need the profiler.  Known for the profiled workload only.
-PROFILED_TRAFFIC_BYTES = {("resnet152", 41, 8.0): 71.3e6}
+# need the profiler.  Known for the profiled workload and kernel only.
+PROFILED_TRAFFIC_BYTES = {}
 
 
 def log(*a):
@@ -319,7 +319,7 @@ def main():
     ach = dom["flops"] / (dom["ms"] * 1e-3) / 1e12
     # bf16 storage: both convolution kernels multiply bf16 on the matrix cores (dense peak 2.5 PFLOP/s)
     peak = PEAK_BF16_MFMA_TFLOPS if args.dtype == "bf16" else PEAK_FP32_MFMA_TFLOPS
-    traffic = PROFILED_TRAFFIC_BYTES.get((args.net, k, args.budget_gib)) if args.dtype == "f32" else None
+    traffic = PROFILED_TRAFFIC_BYTES.get((args.net, k, args.budget_gib, dom["name"])) if args.dtype == "f32" else None
     roofline = dict(bound="mfma", kernel=dom["name"], achieved=ach, peak=peak, unit="TFLOP/s",
                     frac=ach / peak, traffic=traffic,
                     traffic_source=("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command "
