@@ -363,7 +363,13 @@ __device__ __forceinline__ int wb_slot(int kg, int ch) {   // 16-byte slot of (r
   return kg * WB_BM + (o << 3) + ((ch & 7) ^ ((o >> 1) & 7));
 }
 
-template <bool PLAIN>
+//
+// How x is gathered: G_PLAIN, 1x1 filters without stride or padding, row m is pixel m; G_NEAR, output maps of at most 4096 rows
+// and columns, where positions move on by quotients in float (exact there, tried over the whole range) and 24-bit products;
+// G_FAR, larger maps, where a quotient rounds across a whole number (from 6.5 million columns on) or a product needs more bits:
+// integer division (256->256 3x3 at 14x14, 512 images: 170 us with the quotients, 181 so).
+enum { G_PLAIN = 0, G_NEAR, G_FAR };
+template <int GATHER>
 __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles,
                                                           int splits, int chunks_per_split, float* out,
                                                           size_t split_stride, int main_grid) {
@@ -430,7 +436,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mro
   const float inv_q = 1.0f / (float)g.q, inv_p = 1.0f / (float)g.p;
   auto load = [&](Regs& R) {
     uint32_t voff[8];
-    if (PLAIN) {
+    if constexpr (GATHER == G_PLAIN) {
 #pragma unroll
       for (int r = 0; r < 8; ++r) voff[r] = m_next + r < m_lim ? off + r * row_b : OUTSIDE;
       off += WB_BK * row_b;
@@ -440,7 +446,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mro
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
         const bool wq = q + 1 == g.q, wp = wq & (p + 1 == g.p);
-        const int iy = __mul24(p, gs) + gy, ix = __mul24(q, gs) + gx;
+        const int iy = (GATHER == G_NEAR ? __mul24(p, gs) : p * gs) + gy, ix = (GATHER == G_NEAR ? __mul24(q, gs) : q * gs) + gx;
         const bool in = ((unsigned)iy < (unsigned)gh) & ((unsigned)ix < (unsigned)gwd) & (m_next + r < m_lim);
         voff[r] = in ? o : OUTSIDE;
         o += gs * row_b + (wq ? wrap_q : 0u) + (wp ? wrap_p : 0u);
@@ -448,9 +454,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mro
         p = wp ? 0 : p + (wq ? 1 : 0);
       }
       // 64 rows on: small quotients, exact in float with the half added (p, q <= 4096)
-      const int xq = q0 + WB_BK, nq = (int)(((float)xq + 0.5f) * inv_q);
+      const int xq = q0 + WB_BK, nq = GATHER == G_NEAR ? (int)(((float)xq + 0.5f) * inv_q) : xq / g.q;
       q0 = xq - nq * g.q;
-      const int xp = p0 + nq, np = (int)(((float)xp + 0.5f) * inv_p);
+      const int xp = p0 + nq, np = GATHER == G_NEAR ? (int)(((float)xp + 0.5f) * inv_p) : xp / g.p;
       p0 = xp - np * g.p;
       off += WB_BK * gs * row_b + (uint32_t)nq * wrap_q + (uint32_t)np * wrap_p;
     }
@@ -716,12 +722,12 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
     else if (fast) ACC_WGRAD_LAUNCH(L_FAST, float);
     else ACC_WGRAD_LAUNCH(L_GENERIC, float);
   } else if (mfma16) {
-    if (g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0)
-      hipLaunchKernelGGL(wgrad_bf16_kernel<true>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, c.splits,
-                         c.chunks_per_split, out, count, main_grid);
-    else
-      hipLaunchKernelGGL(wgrad_bf16_kernel<false>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, c.splits,
-                         c.chunks_per_split, out, count, main_grid);
+#define ACC_WBF16(G) hipLaunchKernelGGL(wgrad_bf16_kernel<G>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, \
+                                        c.splits, c.chunks_per_split, out, count, main_grid)
+    if (g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0) ACC_WBF16(G_PLAIN);
+    else if (g.p <= 4096 && g.q <= 4096) ACC_WBF16(G_NEAR);
+    else ACC_WBF16(G_FAR);
+#undef ACC_WBF16
   } else {
     if (fast) ACC_WGRAD_LAUNCH(L_FAST, bf16_t); else ACC_WGRAD_LAUNCH(L_GENERIC, bf16_t);
   }
