@@ -10,7 +10,7 @@
 // issued when chunk kc starts, chunk kc+1 is split and stored while chunk kc is multiplied.
 //
 // Bound: the matrix cores sustain 2.0-2.08 PFLOP/s in bf16 (their clock falls under load), a sixth of that, 333
-// TFLOP/s, in these products; the rest is LDS traffic, splitting (11 vector instructions per two values) and the
+// TFLOP/s, in these products; the rest is LDS traffic, splitting (13 vector instructions per two values) and the
 // fixed cost of a tile.  Measured against the fp32-instruction kernel this replaces (154 TFLOP/s ceiling), forward,
 // minibatch 41: 256->256 3x3 at 14x14 75.2 -> 49.5 us, 128->128 3x3 at 28x28 74.7 -> 51.0, 512->512 3x3 at 7x7
 // 77.4 -> 65.6, 256->1024 1x1 at 14x14 38.6 -> 29.0, 1024->256 35.6 -> 30.0, 64->256 at 56x56 (minibatch 32) 38.8
@@ -103,6 +103,11 @@ __device__ __forceinline__ void x3_finish(const ConvGeom& g, int M, int K, int m
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int jj = 0; jj < NB; ++jj) acc[i][jj] = plain_block(g, mw + 32 * i, nw + 32 * jj, M, K, lane);
+  } else {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int jj = 0; jj < NB; ++jj) acc[i][jj] *= kX3Unscale;
   }
 
   // epilogue: accumulator register v of a lane holds row 8*(v/4) + 4*(lane/32) + v%4,
@@ -407,7 +412,7 @@ __device__ __forceinline__ void short_tile(const ConvGeom& g, int M, int K, int 
 #pragma unroll
     for (int jj = 0; jj < NB; ++jj) ph_b[0][jj] = b[0][jj];
     if (R) {
-      constexpr int V = (22 * (AI + BI) + 6 * MB * NB - 1) / (6 * MB * NB) + 1;     // vector instructions per matrix instruction
+      constexpr int V = (26 * (AI + BI) + 6 * MB * NB - 1) / (6 * MB * NB) + 1;     // vector instructions per matrix instruction
 #pragma unroll
       for (int u = 0; u < 6 * MB * NB; ++u) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -744,7 +749,7 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
     store(R, par);
     load(R);
     multiply(F);
-    constexpr int V = (22 * (AI + BI) + 23) / 24 + (AI + BI) / 6;
+    constexpr int V = (26 * (AI + BI) + 23) / 24 + (AI + BI) / 6;
 #pragma unroll
     for (int u = 0; u < 24; ++u) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);

@@ -173,6 +173,8 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_fwd_kernel(ConvGeom g, S
               if (k + half >= K) av = bv = 0.f;
               acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
             }
+          } else if constexpr (NP == 3) {
+            acc[i][j] *= kX3Unscale;
           }
           if (n >= g.n_out) continue;
           const float bias_n = ACT && g.bias ? g.bias[n] : 0.f;
@@ -303,6 +305,8 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_wgrad_kernel(WgradGeom g
           }
         }
         sum = t;
+      } else if constexpr (NP == 3) {
+        sum *= kX3Unscale;
       }
       dst[(size_t)(co0 + co) * J + j] = sum;
     }

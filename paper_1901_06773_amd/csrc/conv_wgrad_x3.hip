@@ -13,7 +13,7 @@
 // stored.  Pipeline as in conv_igemm_x3.hip: step j multiplied out of registers, j+1 read from LDS, j+2 split and
 // stored, later loads issued.
 //
-// Bound as there (333 TFLOP/s in these products); what is lost goes to the gather and the splitting (about 150 vector
+// Bound as there (333 TFLOP/s in these products); what is lost goes to the gather and the splitting (about 170 vector
 // instructions per wave and step beside 24 matrix instructions) and to the parts, which are written and read once.
 // Measured against the fp32-instruction kernel this replaces, minibatch 41, reduction of the parts included:
 // 256->256 3x3 at 14x14 115.7 -> 63.8 us, 128->128 3x3 at 28x28 96.1 -> 63.7, 512->512 3x3 at 7x7 117.8 -> 79.6, 256->1024
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
     store(R, par);
     load(R);
     multiply(F);
-    constexpr int V = (88 * BPW + (PLAIN ? 12 : 60) * BPW + 23) / 24;
+    constexpr int V = (104 * BPW + (PLAIN ? 12 : 60) * BPW + 23) / 24;
 #pragma unroll
     for (int u = 0; u < 24; ++u) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -328,6 +328,9 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
 #pragma unroll
     for (int b = 0; b < D::BPQ; ++b)
       c[0][b] = plain_wgrad_block(g, co0 + wm0 + channel_of(32 * bi + (lane & 31)), j0 + wn0 + channel_of(32 * (bj + b) + (lane & 31)), J, m_lo, m_hi, lane);
+  } else {
+#pragma unroll
+    for (int b = 0; b < D::BPQ; ++b) c[0][b] *= kX3Unscale;
   }
   float* dst = out + (size_t)split * split_stride;
 #pragma unroll

@@ -6,8 +6,13 @@
 // six v_mfma_f32_32x32x16_bf16 (32 cycles each) where the fp32 instruction needs eight of 64 cycles
 // (v_mfma_f32_32x32x2_f32) for the same 32 x 32 x 16 products, with the same fp32 accumulators.
 // The terms left out are smaller than the rounding of one fp32 addition, and the sum is rounded 6 times per
-// 16 products instead of 16 times.  Values whose parts leave the bf16 range (infinities, NaN, magnitudes that
-// round to infinity) end up non-finite in the accumulator; the kernels then redo the tile in fp32.
+// 16 products instead of 16 times.
+//
+// The parts are taken of the value times 2^24.  bf16 has the exponents of fp32 but 16 bits less: below 2^-110 the lowest part of a
+// value would fall under the smallest bf16 (2^-133) and the value be held in fewer than 24 bits (2e-3 of it lost at
+// 2^-125); times 2^24 every part of every fp32 value, subnormal ones included, is a normal bf16.  The sums come out times
+// 2^48 and are taken back when they are finished.  Values and sums that leave the range at the other end (infinities, NaN,
+// values from 2^104 and sums from 2^80 on) end up non-finite in the accumulator; the kernels then redo the tile in fp32.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -25,8 +30,13 @@ __device__ __forceinline__ uint32_t x3_pack(float a, float b) {   // two bf16, r
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));
 }
 
-// the three parts of two values, packed in pairs
+constexpr float kX3Scale = 16777216.f;                                // 2^24, of every value
+constexpr float kX3Unscale = 1.f / (kX3Scale * kX3Scale);             // of the sums of products
+
+// the three parts of two values (times kX3Scale), packed in pairs
 __device__ __forceinline__ void x3_split(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  a *= kX3Scale;
+  b *= kX3Scale;
   h = x3_pack(a, b);
   const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
   m = x3_pack(ra, rb);

@@ -115,3 +115,25 @@ def test_pooling_mean_wide_and_narrow(case, offset):
     ref = O.gap_fwd(x)
     close(y.cpu().numpy(), ref, f"gap_fwd {case}", 1e-6 * 4)
     close(nchw(dx.cpu().numpy()), O.gap_bwd(ref.reshape(n, c), x.shape).astype(np.float64) + 2.0, f"gap_bwd {case}", 1e-6)
+
+
+@pytest.mark.parametrize("scales", [(-116, 90), (-140, 110), (90, -116), (100, -130)])
+@pytest.mark.parametrize("case", CASES[:2])
+def test_small_channel_conv_tiny_operands(case, scales):
+    """fp32 operands whose lowest bits lie below the smallest bf16 are held in all their bits."""
+    n, h, w, cin, cout, r, stride, pad = case
+    ho, wo = O.out_dim(h, r, stride, pad), O.out_dim(w, r, stride, pad)
+    small = lambda a, e: torch.from_numpy(np.ldexp(a.astype(np.float64), e).astype(np.float32))
+    x, wt, dy = small(rnd(1, n, cin, h, w), scales[0]), small(rnd(2, cout, cin, r, r), scales[1]), small(rnd(3, n, cout, ho, wo), scales[1])
+    y = torch.full((n, ho, wo, cout), float("nan"), device="cuda")
+    B().op_conv_fwd(dev(nhwc(x.numpy())), dev(ohwi(wt.numpy())), y, stride, pad)
+    ws = torch.empty(max(B().op_conv_workspace(n, h, w, cin, cout, r, stride, pad), 256), dtype=torch.uint8, device="cuda")
+    dw = torch.full((cout, r, r, cin), float("nan"), device="cuda")
+    B().op_conv_wgrad(dev(nhwc(x.numpy())), dev(nhwc(dy.numpy())), dw, stride, pad, ws)
+    torch.cuda.synchronize()
+    ref = torch.nn.functional.conv2d(x.double(), wt.double(), stride=stride, padding=pad)
+    cols = torch.nn.functional.unfold(x.double(), r, padding=pad, stride=stride)
+    refw = sum(d @ c.t() for d, c in zip(dy.double().reshape(n, cout, -1), cols)).reshape(wt.shape)
+    got, gotw = torch.from_numpy(nchw(y.cpu().numpy())).double(), dw.cpu().double().permute(0, 3, 1, 2)
+    assert ((got - ref).norm() / ref.norm()).item() <= 2e-6
+    assert ((gotw - refw).norm() / refw.norm()).item() <= 2e-6

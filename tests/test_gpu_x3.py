@@ -139,3 +139,35 @@ def test_split_wgrad_keeps_infinities_nan_and_the_largest_values(case):
     assert np.array_equal(got[inf], ref[inf])
     ok = np.isfinite(ref) & fit & (np.abs(ref) < 1e30)
     assert np.abs(got[ok] - ref[ok]).max() <= 1e-4 * np.abs(ref[ok]).max()
+
+
+# Operands whose lowest bits lie below the smallest bf16 (2^-133), subnormal ones among them, against others that bring the result
+# back into range: held in all their bits as before.  One operand at a time, then results far below one.
+TINY = [(-116, 90), (-124, 100), (-140, 110), (90, -116), (100, -130), (-50, -60)]
+
+
+@pytest.mark.parametrize("scales", TINY)
+@pytest.mark.parametrize("case", [CASES[i] for i in (0, 1, 4, 5, 6, 8, 9)])
+def test_split_conv_tiny_operands(case, scales):
+    n, h, w, cin, cout, r, stride = case
+    n, pad = min(n, 12), r // 2
+    x = torch.ldexp(torch.from_numpy(rnd(1, n, cin, h, w)).double(), torch.tensor(scales[0])).float()
+    wt = torch.ldexp(torch.from_numpy(rnd(2, cout, cin, r, r)).double() * (2.0 / (cin * r * r)) ** 0.5, torch.tensor(scales[1])).float()
+    ref = torch.nn.functional.conv2d(x.double(), wt.double(), stride=stride, padding=pad)
+    y = torch.full((n, ref.shape[2], ref.shape[3], cout), float("nan"), device="cuda")
+    B().op_conv_fwd(dev(nhwc(x.numpy())), dev(ohwi(wt.numpy())), y, stride, pad)
+    torch.cuda.synchronize()
+    got = torch.from_numpy(nchw(y.cpu().numpy())).double()
+    assert ((got - ref).norm() / ref.norm()).item() <= 2e-6
+
+
+@pytest.mark.parametrize("scales", TINY)
+@pytest.mark.parametrize("case", [WGRAD_CASES[i] for i in (0, 1, 7)])
+def test_split_wgrad_tiny_operands(case, scales):
+    n, h, w, cin, cout, r, stride = case
+    x = np.ldexp(rnd(1, n, cin, h, w).astype(np.float64), scales[0]).astype(np.float32)
+    dy = np.ldexp(rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2)).astype(np.float64), scales[1]).astype(np.float32)
+    cols = torch.nn.functional.unfold(torch.from_numpy(x).double(), r, padding=r // 2, stride=stride)
+    ref = sum(d @ c.t() for d, c in zip(torch.from_numpy(dy).double().reshape(n, cout, -1), cols)).reshape(cout, cin, r, r).numpy()
+    got = wgrad(case, x, dy)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
