@@ -283,46 +283,54 @@ __global__ __launch_bounds__(THREADS) void maxpool3s2_bwd_kernel(const T* __rest
   }
 }
 
-// y[n][c] = mean over hw of x[n][hw][c].  A workgroup takes one image and up to 256 channels: tpr threads of four
+// Workgroups along the images of the two kernels below at most; they walk on from there (a launch may have fewer than 2^32
+// threads in a dimension).
+constexpr int kGapImages = 1 << 20;
+
+// y[n][c] = mean over hw of x[n][hw][c].  A workgroup takes one image at a time and up to 256 channels: tpr threads of four
 // channels each across a row, the other threads further rows (four in flight each); the row groups are added in order.
 // (One thread per channel and image, all rows one after the other, waited for every row in turn: 2 x 64 channels of
 // 16x16 67 us, 41 x 2048 of 7x7 16.5 us; now 5 and 6.)
 template <class T>
-__global__ __launch_bounds__(THREADS) void gap_fwd4_kernel(const T* __restrict__ x, T* __restrict__ y, int hw, int c, int tpr, int rpi) {
+__global__ __launch_bounds__(THREADS) void gap_fwd4_kernel(const T* __restrict__ x, T* __restrict__ y, int n, int hw, int c, int tpr, int rpi) {
   __shared__ float red[THREADS][4];
   const int tid = threadIdx.x, lane_r = tid / tpr, lane_c = tid - lane_r * tpr;
-  const int ch = (blockIdx.y * tpr + lane_c) * 4, img = blockIdx.x;
+  const int ch = (blockIdx.y * tpr + lane_c) * 4;
   const bool active = lane_r < rpi && ch < c;
-  float s[4] = {0.f, 0.f, 0.f, 0.f};
-  if (active) {
-    const T* p = x + (size_t)img * hw * c + ch;
-    int k = lane_r;
-    for (; k + 3 * rpi < hw; k += 4 * rpi) {
-      float v[4][4];
+  for (int img = blockIdx.x; img < n; img += gridDim.x) {
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (active) {
+      const T* p = x + (size_t)img * hw * c + ch;
+      int k = lane_r;
+      for (; k + 3 * rpi < hw; k += 4 * rpi) {
+        float v[4][4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) Elem<T>::load4(p + (size_t)(k + u * rpi) * c, v[u]);
+        for (int u = 0; u < 4; ++u) Elem<T>::load4(p + (size_t)(k + u * rpi) * c, v[u]);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s[j] += v[u][j];
+          for (int j = 0; j < 4; ++j) s[j] += v[u][j];
+      }
+      for (; k < hw; k += rpi) {
+        float v[4];
+        Elem<T>::load4(p + (size_t)k * c, v);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] += v[j];
+      }
     }
-    for (; k < hw; k += rpi) {
-      float v[4];
-      Elem<T>::load4(p + (size_t)k * c, v);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) s[j] += v[j];
+    for (int j = 0; j < 4; ++j) red[tid][j] = s[j];
+    __syncthreads();
+    if (lane_r == 0 && active) {
+      for (int r = 1; r < rpi; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] += red[r * tpr + lane_c][j];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[j] = s[j] / (float)hw;
+      Elem<T>::store4(y + (size_t)img * c + ch, s);
     }
+    __syncthreads();                                   // the sums are no longer read
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) red[tid][j] = s[j];
-  __syncthreads();
-  if (lane_r != 0 || !active) return;
-  for (int r = 1; r < rpi; ++r)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s[j] += red[r * tpr + lane_c][j];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) s[j] = s[j] / (float)hw;
-  Elem<T>::store4(y + (size_t)img * c + ch, s);
 }
 
 // the same for channel counts or addresses that do not allow four channels at a time
@@ -341,27 +349,29 @@ __global__ __launch_bounds__(THREADS) void gap_fwd_kernel(const T* __restrict__ 
 
 // dx[n][k][c] (+)= dy[n][c] / hw; four channels per thread, rows as in gap_fwd4_kernel, blockIdx.z a range of them
 template <class T>
-__global__ __launch_bounds__(THREADS) void gap_bwd4_kernel(const T* __restrict__ dy, T* __restrict__ dx, int hw, int c, int tpr, int rpi,
+__global__ __launch_bounds__(THREADS) void gap_bwd4_kernel(const T* __restrict__ dy, T* __restrict__ dx, int n, int hw, int c, int tpr, int rpi,
                                                            int rows_per_block, int accumulate) {
   const int tid = threadIdx.x, lane_r = tid / tpr, lane_c = tid - lane_r * tpr;
-  const int ch = (blockIdx.y * tpr + lane_c) * 4, img = blockIdx.x;
+  const int ch = (blockIdx.y * tpr + lane_c) * 4;
   if (lane_r >= rpi || ch >= c) return;
   const float inv = 1.f / (float)hw;
-  float v[4];
-  Elem<T>::load4(dy + (size_t)img * c + ch, v);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) v[j] *= inv;
   const int lo = blockIdx.z * rows_per_block, hi = lo + rows_per_block < hw ? lo + rows_per_block : hw;
-  T* p = dx + (size_t)img * hw * c + ch;
-  for (int k = lo + lane_r; k < hi; k += rpi) {
-    if (accumulate) {
-      float o[4];
-      Elem<T>::load4(p + (size_t)k * c, o);
+  for (int img = blockIdx.x; img < n; img += gridDim.x) {
+    float v[4];
+    Elem<T>::load4(dy + (size_t)img * c + ch, v);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] += v[j];
-      Elem<T>::store4(p + (size_t)k * c, o);
-    } else {
-      Elem<T>::store4(p + (size_t)k * c, v);
+    for (int j = 0; j < 4; ++j) v[j] *= inv;
+    T* p = dx + (size_t)img * hw * c + ch;
+    for (int k = lo + lane_r; k < hi; k += rpi) {
+      if (accumulate) {
+        float o[4];
+        Elem<T>::load4(p + (size_t)k * c, o);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] += v[j];
+        Elem<T>::store4(p + (size_t)k * c, o);
+      } else {
+        Elem<T>::store4(p + (size_t)k * c, v);
+      }
     }
   }
 }
@@ -580,7 +590,7 @@ __global__ __launch_bounds__(THREADS) void nchw_to_nhwc_tile_kernel(const float*
 hipError_t nchw_to_nhwc(const float* x, void* y, int n, int c, int hw, int dtype, hipStream_t st) {
   if (!x || !y || n <= 0 || c <= 0 || hw <= 0) return hipErrorInvalidValue;
   const long tiles_p = (hw + 31L) / 32, tiles_c = (c + 31L) / 32;
-  if (c >= 8 && tiles_p * tiles_c * n <= (1L << 30)) {
+  if (c >= 8 && tiles_p * tiles_c * n < (1L << 24)) {        // (a launch has fewer than 2^32 threads)
     ACC_DISPATCH(dtype, hipLaunchKernelGGL(nchw_to_nhwc_tile_kernel<T>, dim3((unsigned)(tiles_p * tiles_c * n)), dim3(THREADS), 0, st,
                                            x, (T*)y, c, hw, (int)tiles_p, (int)tiles_c));
     return hipGetLastError();
@@ -660,7 +670,7 @@ hipError_t maxpool_backward(const void* x, const void* dy, void* dx, int n, int 
 
 namespace {
 // four channels at a time: whole groups of four, addresses that allow the wide access, grid sizes within bounds
-inline bool gap_wide(const void* x, const void* y, int n, int c, int dtype) {
+inline bool gap_wide(const void* x, const void* y, int c, int dtype) {
   const uintptr_t mask = dtype == DT_BF16 ? 7 : 15;
   return c % 4 == 0 && !((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & mask) && c / 4 <= 64 * 65535;
 }
@@ -668,9 +678,10 @@ inline bool gap_wide(const void* x, const void* y, int n, int c, int dtype) {
 
 hipError_t gap_forward(const void* x, void* y, int n, int hw, int c, int dtype, hipStream_t st) {
   if (!x || !y || n <= 0 || hw <= 0 || c <= 0) return hipErrorInvalidValue;
-  if (gap_wide(x, y, n, c, dtype)) {
+  if (gap_wide(x, y, c, dtype)) {
     const int tpr = c / 4 < 64 ? c / 4 : 64, rpi = THREADS / tpr, slices = (c / 4 + tpr - 1) / tpr;
-    ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_fwd4_kernel<T>, dim3(n, slices), dim3(THREADS), 0, st, (const T*)x, (T*)y, hw, c, tpr, rpi));
+    ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_fwd4_kernel<T>, dim3(n < kGapImages ? n : kGapImages, slices), dim3(THREADS), 0, st, (const T*)x,
+                                           (T*)y, n, hw, c, tpr, rpi));
     return hipGetLastError();
   }
   ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_fwd_kernel<T>, dim3(grid_for((size_t)n * c)), dim3(THREADS), 0, st,
@@ -680,15 +691,15 @@ hipError_t gap_forward(const void* x, void* y, int n, int hw, int c, int dtype, 
 
 hipError_t gap_backward(const void* dy, void* dx, int n, int hw, int c, int accumulate, int dtype, hipStream_t st) {
   if (!dy || !dx || n <= 0 || hw <= 0 || c <= 0) return hipErrorInvalidValue;
-  if (gap_wide(dy, dx, n, c, dtype)) {
+  if (gap_wide(dy, dx, c, dtype)) {
     const int tpr = c / 4 < 64 ? c / 4 : 64, rpi = THREADS / tpr, slices = (c / 4 + tpr - 1) / tpr;
     // rows in pieces of at least four trips of a workgroup, about 1024 workgroups
     long pieces = 1024 / ((long)n * slices) + 1;
     const long most = ((long)hw + 4 * rpi - 1) / (4 * rpi);
     if (pieces > most) pieces = most;
     const int per = (int)((hw + pieces - 1) / pieces);
-    ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_bwd4_kernel<T>, dim3(n, slices, (hw + per - 1) / per), dim3(THREADS), 0, st, (const T*)dy,
-                                           (T*)dx, hw, c, tpr, rpi, per, accumulate));
+    ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_bwd4_kernel<T>, dim3(n < kGapImages ? n : kGapImages, slices, (hw + per - 1) / per), dim3(THREADS),
+                                           0, st, (const T*)dy, (T*)dx, n, hw, c, tpr, rpi, per, accumulate));
     return hipGetLastError();
   }
   ACC_DISPATCH(dtype, hipLaunchKernelGGL(gap_bwd_kernel<T>, dim3(grid_for((size_t)n * hw * c)), dim3(THREADS), 0, st,

@@ -137,3 +137,18 @@ def test_small_channel_conv_tiny_operands(case, scales):
     got, gotw = torch.from_numpy(nchw(y.cpu().numpy())).double(), dw.cpu().double().permute(0, 3, 1, 2)
     assert ((got - ref).norm() / ref.norm()).item() <= 2e-6
     assert ((gotw - refw).norm() / refw.norm()).item() <= 2e-6
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,hw", [(2 ** 24 + 3, 1), (2 ** 20 + 1, 2)])
+def test_pooling_mean_of_many_images(n, hw, dtype):
+    """More images than a launch may have workgroups; whole numbers, exact."""
+    x = torch.randint(-8, 9, (n, 1, hw, 4), device="cuda").to(dtype) * hw
+    y = torch.full((n, 4), float("nan"), device="cuda", dtype=dtype)
+    B().op_gap_fwd(x, y)
+    dx = torch.full_like(x, 2.0)
+    B().op_gap_bwd(y * hw, dx, accumulate=True)
+    torch.cuda.synchronize()
+    mean = (x.float().sum((1, 2)) / hw).to(dtype)
+    assert torch.equal(y, mean)
+    assert torch.equal(dx, (2.0 + mean.float())[:, None, None, :].expand(n, 1, hw, 4).to(dtype))
