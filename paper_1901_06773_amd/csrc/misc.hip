@@ -178,25 +178,34 @@ __global__ __launch_bounds__(THREADS) void maxpool_bwd_kernel(const T* __restric
 }
 
 // The same for 3x3 windows at stride 2 with padding 1 (the stem pool of the ResNets): one thread
-// per column of 2x2 blocks of input positions (MP_STRIP of them, top to bottom) and four channels.  The block (rows
+// per column of 2x2 blocks of input positions (`strip` of them, top to bottom) and four channels.  The block (rows
 // 2a, 2a+1, columns 2b, 2b+1) is covered by the windows p in {a, a+1}, q in {b, b+1} and by no other.  Going down, the
 // windows of row a+1 are the next block's row a, and their first input row is the last one of the windows above: ten
-// loads of x per block where every block on its own takes 36 (64 channels, 112x112, 32 images: 104.5 us before, 56 now;
-// the 232 MB it has to move take 50).  Windows are visited in the same (p, q) order and the same
+// loads of x per block where every block on its own takes 36 (64 channels, 112x112, 32 images: 103 us a block at a time in
+// the kernel before, 48 now; the 232 MB it has to move take 50 at the rate of a large copy).  Windows are visited in the same (p, q) order and the same
 // first maximum wins, so every sum has the same terms in the same order as in the kernel above.
-constexpr int MP_STRIP = 8;
+//
+// Longer strips load less and leave fewer threads, each a longer chain of trips to memory.  Measured at strips of 1 / 2 / 4 / 8
+// (and the kernel before), 64 channels: fp32, 2 images of 112x112 (100 thousand blocks) 7.7 / 9.0 / 14.4 / 22.9 (11.5) us; 4 images
+// (200 thousand) 12.9 / 11.8 / 15.5 / 25.1 (18.8); 16 images (0.8 million) 37 / 31 / 28 / 31 (52); 32 images 66 / 54 / 49.5 /
+// 47.9 (103); bf16 at 32 images 62 / 49 / 45 / 50 (75).
+inline int maxpool_strip(size_t blocks, size_t elem_bytes) {
+  if (blocks < 160 << 10) return 1;
+  if (blocks < 512 << 10) return 2;
+  return elem_bytes == 2 || blocks < 1280 << 10 ? 4 : 8;
+}
 template <class T>
 __global__ __launch_bounds__(THREADS) void maxpool3s2_bwd_kernel(const T* __restrict__ x,
                                                                  const T* __restrict__ dy, T* __restrict__ dx, int n,
                                                                  int h, int wd, int c, int ho, int wo,
-                                                                 int accumulate) {
-  const int cg = c >> 2, hb = (h + 1) >> 1, wb = (wd + 1) >> 1, strips = (hb + MP_STRIP - 1) / MP_STRIP;
+                                                                 int accumulate, int strip) {
+  const int cg = c >> 2, hb = (h + 1) >> 1, wb = (wd + 1) >> 1, strips = (hb + strip - 1) / strip;
   const size_t total = (size_t)n * strips * wb * cg;
   for (size_t i = (size_t)blockIdx.x * THREADS + threadIdx.x; i < total; i += (size_t)gridDim.x * THREADS) {
     const int g = (int)(i % cg);
     size_t rest = i / cg;
     const int b = (int)(rest % wb); rest /= wb;
-    const int a0 = (int)(rest % strips) * MP_STRIP;
+    const int a0 = (int)(rest % strips) * strip;
     const int img = (int)(rest / strips);
     const T* xi = x + (size_t)img * h * wd * c + g * 4;
     const T* dyi = dy + (size_t)img * ho * wo * c + g * 4;
@@ -247,7 +256,7 @@ __global__ __launch_bounds__(THREADS) void maxpool3s2_bwd_kernel(const T* __rest
     load_row(r2, 2 * a0 + 1);
     window(u0, a0, b, 0);
     window(u1, a0, b + 1, 2);
-    for (int a = a0; a < a0 + MP_STRIP && a < hb; ++a) {
+    for (int a = a0; a < a0 + strip && a < hb; ++a) {
       r0 = r2;
       load_row(r1, 2 * a + 2);
       load_row(r2, 2 * a + 3);
@@ -651,9 +660,11 @@ hipError_t maxpool_backward(const void* x, const void* dy, void* dx, int n, int 
   const int ho = (h + 2 * pad - r) / stride + 1, wo = (wd + 2 * pad - s) / stride + 1;
   if (ho <= 0 || wo <= 0) return hipErrorInvalidValue;
   if (c % 4 == 0 && r == 3 && s == 3 && stride == 2 && pad == 1) {
-    const size_t total = (size_t)n * (((h + 1) / 2 + MP_STRIP - 1) / MP_STRIP) * ((wd + 1) / 2) * (c / 4);
+    const size_t blocks = (size_t)n * ((h + 1) / 2) * ((wd + 1) / 2) * (c / 4);
+    const int strip = maxpool_strip(blocks, dt_size(dtype));
+    const size_t total = (size_t)n * (((h + 1) / 2 + strip - 1) / strip) * ((wd + 1) / 2) * (c / 4);
     ACC_DISPATCH(dtype, hipLaunchKernelGGL(maxpool3s2_bwd_kernel<T>, dim3(grid_for(total, 256 * 64)), dim3(THREADS), 0, st,
-                                           (const T*)x, (const T*)dy, (T*)dx, n, h, wd, c, ho, wo, accumulate));
+                                           (const T*)x, (const T*)dy, (T*)dx, n, h, wd, c, ho, wo, accumulate, strip));
   } else if (c % 4 == 0) {
     const size_t total = (size_t)n * h * wd * (c / 4);
     ACC_DISPATCH(dtype, hipLaunchKernelGGL((maxpool_bwd_kernel<T, 4>), dim3(grid_for(total, 256 * 64)), dim3(THREADS), 0,

@@ -84,7 +84,9 @@ def test_small_channel_conv_keeps_infinities_and_nan(dtype):
         assert np.abs(got[ok] - want[ok]).max() <= 2e-2 * np.abs(want[ok]).max()
 
 
-@pytest.mark.parametrize("shape", [(2, 8, 33, 17), (1, 4, 3, 3), (3, 20, 16, 31), (2, 4, 1, 6), (1, 64, 37, 2)])
+# n, c, h, w; then strips of two, four, eight (fp32) blocks: 200 thousand, 0.55 million, 1.4 million blocks of 2 x 2
+@pytest.mark.parametrize("shape", [(2, 8, 33, 17), (1, 4, 3, 3), (3, 20, 16, 31), (2, 4, 1, 6), (1, 64, 37, 2),
+                                   (42, 128, 33, 17), (121, 128, 35, 15), (290, 128, 33, 17), (1300, 64, 3, 31)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_maxpool_gradient_in_strips(shape, accumulate):
     """Heights around the length of a strip, maps of one row or column of blocks, ties."""
@@ -98,6 +100,13 @@ def test_maxpool_gradient_in_strips(shape, accumulate):
     torch.cuda.synchronize()
     ref = O.maxpool_bwd(dy, arg, x.shape).astype(np.float64) + (base if accumulate else 0.0)
     close(nchw(dx.cpu().numpy()), ref, f"maxpool_bwd {shape}", 1e-6)
+    if not accumulate:      # bf16: sums of up to four values, rounded once
+        x16, dy16 = dev(nhwc(x)).bfloat16(), dev(nhwc(dy)).bfloat16()
+        dx16 = torch.full((n, h, w, c), float("nan"), device="cuda", dtype=torch.bfloat16)
+        B().op_maxpool_bwd(x16, dy16, dx16, 3, 2, 1)
+        ref = O.maxpool_bwd(nchw(dy16.float().cpu().numpy()), arg, x.shape)      # (the halves of x are exact in bf16)
+        torch.cuda.synchronize()
+        assert np.abs(nchw(dx16.float().cpu().numpy()) - ref).max() <= 2.0 ** -8 * np.abs(ref).max()
 
 
 @pytest.mark.parametrize("offset", [0, 1])
