@@ -366,6 +366,10 @@ int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int
 int acc_op_conv_wgrad(const void* x, const void* dy, float* dw, int n, int h, int wd, int cin,
                       int cout, int r, int s, int stride, int pad, void* workspace,
                       size_t workspace_bytes, int dtype, void* stream);
+/* Name of the kernel (with its tile) that acc_op_conv_fwd (role 0), _dgrad (1) or _wgrad (2) runs for a shape, "none" if
+ * there is nothing to run, NULL if the call refuses it.  The choice is a function of the shape; nothing is launched. */
+const char* acc_op_conv_kernel(int role, int n, int h, int wd, int cin, int cout, int r, int s,
+                               int stride, int pad, int dtype);
 /* y = relu?(gamma*(x-mean)*istd + beta (+ res)); saves mean / istd (c floats each).
  * workspace: acc_op_bn_workspace(c) bytes. */
 size_t acc_op_bn_workspace(int c);

@@ -152,6 +152,7 @@ _PROTOS = {
     "acc_op_conv_fwd": (_I, [_VP, _VP, _VP] + [_I] * 9 + [_I, _VP]),
     "acc_op_conv_dgrad": (_I, [_VP, _VP, _VP] + [_I] * 10 + [_VP, _SZ, _I, _VP]),
     "acc_op_conv_wgrad": (_I, [_VP, _VP, _VP] + [_I] * 9 + [_VP, _SZ, _I, _VP]),
+    "acc_op_conv_kernel": (C.c_char_p, [_I] * 11),
     "acc_op_bn_workspace": (_SZ, [_I]),
     "acc_op_bn_fwd": (_I, [_VP] * 7 + [_I, _I, _I, _F, _VP, _I, _VP]),
     "acc_op_bn_bwd": (_I, [_VP] * 10 + [_I, _I, _VP, _I, _VP]),
@@ -452,6 +453,12 @@ def _stream_ptr(torch):
 
 def op_conv_workspace(n, h, w, cin, cout, r, stride, pad) -> int:
     return int(_lib.acc_op_conv_workspace(n, h, w, cin, cout, r, r, stride, pad))
+
+
+def op_conv_kernel(role: str, n, h, w, cin, cout, r, stride, pad, dtype: int = F32) -> Optional[str]:
+    """Kernel (with its tile) that op_conv_fwd / op_conv_dgrad / op_conv_wgrad runs for a shape; None: the call refuses it."""
+    name = _lib.acc_op_conv_kernel(("fwd", "dgrad", "wgrad").index(role), n, h, w, cin, cout, r, r, stride, pad, int(dtype))
+    return name.decode() if name else None
 
 
 def _dtype_of(t) -> int:

@@ -576,6 +576,9 @@ hipError_t launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* 
   }
   if (main_grid + side_blocks > (1L << 30)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(main_grid + side_blocks));
+  probe->variant = LOADER == L_DIRECT ? V_IGEMM_DIRECT : V_IGEMM_GENERIC;
+  probe->kernel = LOADER == L_DIRECT ? "igemm direct 64x64" : "igemm generic 64x64";
+  if (probe->dry) return hipSuccess;
   if (probe->before) (void)hipEventRecord(probe->before, st);
   if (g.bias || g.relu)
     hipLaunchKernelGGL((igemm_kernel<LOADER, T, true>), grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
@@ -601,8 +604,8 @@ const char* conv_variant_name(int v) {
 static hipError_t conv_igemm_split(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
   const DgradSplit& d = *g.split;
   if (!g.w || g.bias || g.relu || g.stats || g.bnb.sums) return hipErrorInvalidValue;
-  hipError_t e = filter_gather_transpose(d, const_cast<void*>(g.w), g.dtype, st);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (!probe->dry && (e = filter_gather_transpose(d, const_cast<void*>(g.w), g.dtype, st)) != hipSuccess) return e;
   ConvGeom parts[kMaxDgradParts];
   for (int i = 0; i < d.count; ++i) {
     const DgradPart& pt = d.parts[i];
@@ -618,8 +621,9 @@ static hipError_t conv_igemm_split(const ConvGeom& g, hipStream_t st, LaunchProb
   if (probe->before) (void)hipEventRecord(probe->before, st);
   for (int i = 0; i < d.count; ++i) {
     LaunchProbe one;
+    one.dry = probe->dry;
     if ((e = conv_igemm(parts[i], st, &one)) != hipSuccess) return e;
-    if (i == 0) probe->variant = one.variant;
+    if (i == 0) { probe->variant = one.variant; probe->kernel = one.kernel; }
   }
   if (probe->after) (void)hipEventRecord(probe->after, st);
   return hipSuccess;
@@ -644,17 +648,12 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
     return hipErrorInvalidValue;
   if (g.dtype != DT_F32 && g.dtype != DT_BF16) return hipErrorInvalidValue;
   if ((g.bias || g.relu) && (g.accumulate || g.stats || g.bnb.sums)) return hipErrorInvalidValue;
-  if (conv_igemm_bf16_takes(g, M, K)) {    // bf16 storage, large layers: 128 x 128 tiles
-    probe->variant = V_IGEMM_BF16;
+  if (conv_igemm_bf16_takes(g, M, K))      // bf16 storage, large layers: 128 x 128 tiles
     return conv_igemm_bf16(g, (int)M, (int)K, st, probe);
-  }
   if (conv_smallc_takes(g, M)) return conv_smallc_fwd(g, st, probe);
   if (conv_igemm_x3_takes(g, M, K))        // fp32 storage, whole 16-channel steps: products on the bf16 matrix cores
     return conv_igemm_x3(g, (int)M, (int)K, st, probe);
-  if (g.dtype == DT_F32) {
-    probe->variant = V_IGEMM_GENERIC;
-    return launch<L_GENERIC, float>(g, (int)M, (int)K, st, probe);
-  }
+  if (g.dtype == DT_F32) return launch<L_GENERIC, float>(g, (int)M, (int)K, st, probe);
   // bf16 storage below the 128 x 128 kernel's sizes.  The direct loader addresses both operands through buffer
   // descriptors: 32-bit ranges, the last bytes kept free for the offset that stands for "outside"; 16-byte loads
   // want aligned tensors.  The choice depends on the shape and the alignment only, never on the swap plan
@@ -664,7 +663,6 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
                       (margin_px + (long)g.n_img * g.h * g.wd) * g.c * 2 <= 0xFFFFFF00L &&
                       (long)g.n_out * K * 2 <= 0xFFFFFF00L &&
                       (reinterpret_cast<uintptr_t>(g.in) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.w) & 15) == 0;
-  probe->variant = direct ? V_IGEMM_DIRECT : V_IGEMM_GENERIC;
   return direct ? launch<L_DIRECT, bf16_t>(g, (int)M, (int)K, st, probe) : launch<L_GENERIC, bf16_t>(g, (int)M, (int)K, st, probe);
 }
 

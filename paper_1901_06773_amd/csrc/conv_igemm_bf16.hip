@@ -334,7 +334,7 @@ bool conv_igemm_bf16_takes(const ConvGeom& g, long M, long K) {
   return tiles >= 256;
 }
 
-hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe) {
+hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
   const int tm = (M + TM - 1) / TM, tn = (g.n_out + TN - 1) / TN;
   const long tiles = (long)tm * tn;
   if (tiles <= 0 || tiles > (1L << 30) || K % BKE != 0) return hipErrorInvalidValue;
@@ -350,13 +350,16 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, cons
     side_blocks += (long)((g.flip.cin + 31) / 32) * ((g.flip.cout + 31) / 32) * g.flip.r * g.flip.s;
   }
   if (main_grid + side_blocks > (1L << 30)) return hipErrorInvalidValue;
-  if (probe && probe->before) (void)hipEventRecord(probe->before, st);
+  probe->variant = V_IGEMM_BF16;
+  probe->kernel = "igemm_bf16 128x128";
+  if (probe->dry) return hipSuccess;
+  if (probe->before) (void)hipEventRecord(probe->before, st);
   const dim3 grid((unsigned)(main_grid + side_blocks));
   if (g.bias || g.relu)
     hipLaunchKernelGGL(igemm_bf16_kernel<true>, grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
   else
     hipLaunchKernelGGL(igemm_bf16_kernel<false>, grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
-  if (probe && probe->after) (void)hipEventRecord(probe->after, st);
+  if (probe->after) (void)hipEventRecord(probe->after, st);
   return hipGetLastError();
 }
 

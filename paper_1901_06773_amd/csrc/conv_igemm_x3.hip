@@ -852,7 +852,11 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
 }
 
 template <int WM, int WN, bool WINDOW>
-void launch_deep(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe) {
+void launch_deep(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
+  probe->variant = WINDOW ? V_IGEMM_X3_WINDOW : V_IGEMM_X3_DEEP;
+  probe->kernel = WINDOW ? "igemm_x3_deep window 128x64" : WM * WN == 4 ? "igemm_x3_deep 128x128" : WM * WN == 2 ? "igemm_x3_deep 128x64"
+                                                                                                              : "igemm_x3_deep 64x64";
+  if (probe->dry) return;
   const long side_blocks = wide_reduce_blocks(g.side.count) + (g.flip.wt ? wide_flip_blocks(g.flip.cout, g.flip.cin, g.flip.r, g.flip.s) : 0);
   using D = Deep<WM, WN, WINDOW>;
   const int tm = (M + D::BM - 1) / D::BM, tn = (g.n_out + D::BN - 1) / D::BN;
@@ -867,7 +871,10 @@ void launch_deep(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchPr
 }
 
 template <int MB, int NB>
-void launch_short(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe, long side_blocks) {
+void launch_short(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe, long side_blocks) {
+  probe->variant = V_IGEMM_X3;
+  probe->kernel = MB == 2 ? "igemm_x3 128x128" : "igemm_x3 64x64";
+  if (probe->dry) return;
   const int tm = (M + 64 * MB - 1) / (64 * MB), tn = (g.n_out + 64 * NB - 1) / (64 * NB);
   const int tiles = tm * tn, main_grid = (tiles + 7) / 8 * 8;
   const dim3 grid((unsigned)(main_grid + side_blocks));
@@ -929,7 +936,10 @@ double predicted_parts_us(bool wide, const ConvGeom* parts, int n) {
 }
 
 template <int MB, int NB>
-void launch_parts(X3Parts& ps, int n, hipStream_t st, const LaunchProbe* probe, long side_blocks) {
+void launch_parts(X3Parts& ps, int n, hipStream_t st, LaunchProbe* probe, long side_blocks) {
+  probe->variant = V_IGEMM_X3;
+  probe->kernel = MB == 2 ? "igemm_x3_parts 128x128" : "igemm_x3_parts 64x64";
+  if (probe->dry) return;
   const int tn = (ps.g[0].n_out + 64 * NB - 1) / (64 * NB);
   long per_xcd = 0;
   for (int i = 0; i < n; ++i) {
@@ -984,7 +994,6 @@ hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, Launch
     const double us = predicted_us(kKinds[v], M, g.n_out, K);
     if (best < 0 || us < best_us) { best = v; best_us = us; }
   }
-  probe->variant = best <= X3_64 ? V_IGEMM_X3 : best == X3_WINDOW ? V_IGEMM_X3_WINDOW : V_IGEMM_X3_DEEP;
   switch (best) {
     case X3_128: launch_short<2, 2>(g, M, K, st, probe, narrow); break;
     case X3_64: launch_short<1, 1>(g, M, K, st, probe, narrow); break;
@@ -1050,7 +1059,6 @@ hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, Lau
   ps.g[0].flip = g.flip;
   const long narrow = (long)((g.side.count + 1023) / 1024) + (g.flip.wt ? flip_tiles(g.flip.cout, g.flip.cin, g.flip.r, g.flip.s) : 0);
   if (tiles + narrow > (1L << 30)) return hipErrorInvalidValue;
-  probe->variant = V_IGEMM_X3;
   if (predicted_parts_us(true, parts, n) < predicted_parts_us(false, parts, n))
     launch_parts<2, 2>(ps, n, st, probe, narrow);
   else

@@ -67,7 +67,7 @@ __device__ __forceinline__ void to_parts(const float (&v)[8], x3_v4u (&f)[NP]) {
   }
 }
 
-// the products of two fragments: six with three parts (small terms into accs), one with one
+// the products of two fragments: six with three parts (small terms first), one with one
 template <int NP>
 __device__ __forceinline__ void product(const x3_v4u (&a)[NP], const x3_v4u (&b)[NP], x3_v16f& acc) {
   if constexpr (NP == 3) {
@@ -332,15 +332,24 @@ SmallGeom small_geom(int h, int wd, int c, int p, int q, int r, int s, int strid
 
 }  // namespace
 
-// Few channels, a filter whose padded rows fit the LDS image, a plain dense result, and enough positions for one workgroup
-// per compute unit (below, the per-element kernel's many small workgroups finish first).
+// Few channels, a filter whose padded rows fit the LDS image, a plain dense result, and enough groups of output rows: a workgroup
+// takes one at a time (times 64 output channels), and with few of them the per-element kernel's many small workgroups
+// finish first.  Where the line lies, workgroups: per-element -> this kernel.  fp32: 7x7/2 at 224x224 84: 31 -> 38 us,
+// 112: 41 -> 39, 224: 69 -> 41; 3x3 at 224x224 112: 27 -> 29, 168: 37 -> 30; 3->128 at 128x128 128: 19 -> 19, 256: 33 -> 21.
+// bf16: 7x7/2 42: 21 -> 22, 56: 24 -> 23, 84: 31 -> 23; 3x3 28: 15 -> 23, 56: 25 -> 24, 84: 33 -> 24; 3->128 64: 16 -> 16, 128: 27 -> 17.
+// And enough units of two rows by 32 columns in a group for its eight waves (32x32 maps have four: fp32 3->64 3x3, 256 images
+// 31 -> 33); in fp32, filters that read values more than once (4x4/4 at 224x224, 48 images 29 -> 31).
 bool conv_smallc_takes(const ConvGeom& g, long M) {
   if (g.c > 4 || g.c % 4 == 0 || g.r * ((g.s * g.c + 7) / 8) * 8 > SC_KPAD - 8 || g.stats || g.bnb.sums || g.accumulate || g.side.count || g.flip.wt ||
-      g.out_stride != 1 || g.out_h != g.p || g.out_w != g.q || g.pad_dx != 0 || M < 16384)
+      g.out_stride != 1 || g.out_h != g.p || g.out_w != g.q || g.pad_dx != 0 || M < 16384 || (g.dtype == DT_F32 && g.stride >= g.r))
     return false;
   // every place the rows in LDS are read at lies inside the padded input: (q-1)*stride + s <= wd + 2*pad, likewise rows
   if ((g.q - 1) * (long)g.stride + g.s > g.wd + 2L * g.pad || (g.p - 1) * (long)g.stride + g.r > g.h + 2L * g.pad) return false;
-  return small_geom(g.h, g.wd, g.c, g.p, g.q, g.r, g.s, g.stride, g.pad).rows > 0 && (g.n_out + 63) / 64 <= 65535;
+  const SmallGeom sg = small_geom(g.h, g.wd, g.c, g.p, g.q, g.r, g.s, g.stride, g.pad);
+  const long cols = (g.n_out + 63) / 64;
+  if (sg.rows < 1 || cols > 65535) return false;
+  const long groups = (long)g.n_img * ((g.p + sg.rows - 1) / sg.rows), units = (sg.rows + 1) / 2 * ((g.q + 31L) / 32);
+  return units >= SC_WAVES && (groups < 256 ? groups : 256) * cols >= (g.dtype == DT_F32 ? 144 : 72);
 }
 
 hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
@@ -350,6 +359,8 @@ hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe
   if (sg.rows < 1 || groups > (1L << 30)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(groups < 256 ? groups : 256), (g.n_out + 63) / 64);
   probe->variant = V_SMALLC_FWD;
+  probe->kernel = "smallc";
+  if (probe->dry) return hipSuccess;
   if (probe->before) (void)hipEventRecord(probe->before, st);
   const bool act = g.bias || g.relu;
 #define ACC_SC(T, A) hipLaunchKernelGGL((smallc_fwd_kernel<T, A>), grid, dim3(SC_THREADS), 0, st, g, sg, per_img, (int)groups)
@@ -360,20 +371,24 @@ hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe
   return hipGetLastError();
 }
 
-int wgrad_smallc_splits(long Mrows, int cin, int cout, int r, int s) {
+// In fp32 the six products of all 160 columns are made however few of them exist, and the per-element kernel is the faster one for
+// short filter rows and for few positions: 3x3 of 3 channels at 224x224, 4 / 16 / 32 / 64 images 71 / 155 / 267 / 488 us there,
+// 63 / 142 / 317 / 613 here; 7x7/2, 4 (50 thousand positions) / 6 / 8 (100 thousand) / 32 images 49 / 57 / 67 / 189, 49 / 57 / 63 / 94.
+int wgrad_smallc_splits(long Mrows, int cin, int cout, int r, int s, int dtype) {
   if (cin > 4 || cin % 4 == 0 || r * s * cin > SC_J || Mrows < 16384) return 0;
+  if (dtype == DT_F32 && (r * s * cin <= 96 || Mrows < 80000)) return 0;
   const long want = Mrows / 1024;
   return (int)(want < 256 ? want : 256);
 }
 
 bool conv_wgrad_smallc_takes(const WgradGeom& g) {
   const long M = (long)g.n_img * g.p * g.q;
-  if (!wgrad_smallc_splits(M, g.cin, g.cout, g.r, g.s) || g.side.count || g.flip_wt || (g.cout + 63) / 64 > 65535) return false;
+  if (!wgrad_smallc_splits(M, g.cin, g.cout, g.r, g.s, g.dtype) || g.side.count || g.flip_wt || (g.cout + 63) / 64 > 65535) return false;
   if ((g.q - 1) * (long)g.stride + g.s > g.wd + 2L * g.pad || (g.p - 1) * (long)g.stride + g.r > g.h + 2L * g.pad) return false;
   return small_geom(g.h, g.wd, g.cin, g.p, g.q, g.r, g.s, g.stride, g.pad).rows > 0;
 }
 
-// out: `splits` parts of cout * r*s*cin elements (or dw itself if one); returns how many were written
+// out: `splits` parts of cout * r*s*cin elements (or dw itself if one)
 hipError_t conv_wgrad_smallc(const WgradGeom& g, int splits, float* out, size_t count, hipStream_t st) {
   const SmallGeom sg = small_geom(g.h, g.wd, g.cin, g.p, g.q, g.r, g.s, g.stride, g.pad);
   const int total = g.n_img * g.p, per = (total + splits - 1) / splits;

@@ -651,7 +651,7 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
     const int sx = wgrad_x3_choose(rows, cin, cout, r, s).splits;
     if (sx > splits) splits = sx;
   }
-  if (const int sc = wgrad_smallc_splits(rows, cin, cout, r, s); sc > splits) splits = sc;   // (either kernel may run)
+  if (const int sc = wgrad_smallc_splits(rows, cin, cout, r, s, dtype); sc > splits) splits = sc;   // (either kernel may run)
   if (splits <= 1) return 0;
   return (size_t)splits * cout * r * s * cin * sizeof(float);
 }
@@ -685,7 +685,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
   const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s) : WgradX3Cfg{};
   const bool small = !x3 && conv_wgrad_smallc_takes(g);
-  const int splits = x3 ? cx.splits : small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s) : c.splits;
+  const int splits = x3 ? cx.splits : small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s, g.dtype) : c.splits;
   if (splits > 1 && !g.workspace) return hipErrorInvalidValue;
   const long work = (long)c.tiles_co * c.tiles_j * c.splits;
   if (work > (1L << 30)) return hipErrorInvalidValue;
@@ -705,16 +705,23 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   const dim3 grid((unsigned)(main_grid + reduce_blocks + flip_blocks));
   hipError_t e = hipSuccess;
   const int tiles = c.tiles_co * c.tiles_j;
+  const bool mfma16 = bf16_mfma_shape(g.dtype, g.cin, g.cout);
+  const int gather = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 ? G_PLAIN : g.p <= 4096 && g.q <= 4096 ? G_NEAR : G_FAR;
+  // bf16 matrix cores: the shapes choose() cut into 128 x 128 tiles; byte offsets inside 32-bit buffer
+  // ranges (the last bytes stay free for the offset that stands for "outside"), 16-byte aligned operands
+  if (mfma16 && !(Mrows * g.cout * es <= 0xFFFFFF00L && (long)g.n_img * g.h * g.wd * g.cin * es <= 0xFFFFFF00L &&
+                  (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
+    return hipErrorInvalidValue;   // (the split count, and with it the workspace, was sized for this kernel)
+  if (probe) {
+    probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
+    probe->kernel = small ? "smallc" : mfma16 ? (gather == G_PLAIN ? "wgrad_bf16 plain" : gather == G_NEAR ? "wgrad_bf16 near" : "wgrad_bf16 far")
+                    : x3 ? (cx.wt == 2 ? "wgrad_x3 128x128" : "wgrad_x3 64x64") : fast ? "wgrad fast 64x64" : "wgrad generic 64x64";
+    if (probe->dry) return hipSuccess;
+  }
   if (probe && probe->before) (void)hipEventRecord(probe->before, st);
 #define ACC_WGRAD_LAUNCH(F, T)                                                                             \
   hipLaunchKernelGGL((wgrad_kernel<F, T>), grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, \
                      c.splits, c.chunks_per_split, out, count, main_grid)
-  // bf16 matrix cores: the shapes choose() cut into 128 x 128 tiles; byte offsets inside 32-bit buffer
-  // ranges (the last bytes stay free for the offset that stands for "outside"), 16-byte aligned operands
-  const bool mfma16 = bf16_mfma_shape(g.dtype, g.cin, g.cout);
-  if (mfma16 && !(Mrows * g.cout * es <= 0xFFFFFF00L && (long)g.n_img * g.h * g.wd * g.cin * es <= 0xFFFFFF00L &&
-                  (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
-    return hipErrorInvalidValue;   // (the split count, and with it the workspace, was sized for this kernel)
   if (small) {
     e = conv_wgrad_smallc(g, splits, out, count, st);
   } else if (g.dtype == DT_F32) {
@@ -724,8 +731,8 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   } else if (mfma16) {
 #define ACC_WBF16(G) hipLaunchKernelGGL(wgrad_bf16_kernel<G>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, \
                                         c.splits, c.chunks_per_split, out, count, main_grid)
-    if (g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0) ACC_WBF16(G_PLAIN);
-    else if (g.p <= 4096 && g.q <= 4096) ACC_WBF16(G_NEAR);
+    if (gather == G_PLAIN) ACC_WBF16(G_PLAIN);
+    else if (gather == G_NEAR) ACC_WBF16(G_NEAR);
     else ACC_WBF16(G_FAR);
 #undef ACC_WBF16
   } else {
@@ -733,7 +740,6 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   }
 #undef ACC_WGRAD_LAUNCH
   if (probe && probe->after) (void)hipEventRecord(probe->after, st);
-  if (probe) probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (splits > 1) {

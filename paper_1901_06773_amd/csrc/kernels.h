@@ -102,17 +102,20 @@ struct BnSums {
   int slabs, stride;
 };
 
-// Optional probe of one launch: which template instance ran (index into conv_variant_name())
-// and, when the two events are set, timestamps recorded directly around the main kernel.
+// Optional probe of one launch: which template instance ran (index into conv_variant_name(); `kernel` names it with its
+// tile) and, when the two events are set, timestamps recorded directly around the main kernel.  dry: every check and choice
+// is made, nothing is launched.
 struct LaunchProbe {
   int variant = -1;
   hipEvent_t before = nullptr, after = nullptr;
+  const char* kernel = nullptr;
+  bool dry = false;
 };
 hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe = nullptr);
 // The 128 x 128 kernel for bf16 storage (conv_igemm_bf16.hip): whether it takes this launch (a
 // function of the shape and the alignment only), and the launch itself; conv_igemm() routes to it.
 bool conv_igemm_bf16_takes(const ConvGeom& g, long M, long K);
-hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, const LaunchProbe* probe);
+hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
 // fp32 products on the bf16 matrix cores (conv_igemm_x3.hip): as above.
 bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
@@ -161,7 +164,7 @@ WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s);
 hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st);
 // The kernel for a handful of input channels (conv_smallc.hip): parts it cuts the reduction into (0: the shape is not
 // its; a function of what wgrad_workspace_bytes() knows), whether it takes a launch, and the launch.
-int wgrad_smallc_splits(long Mrows, int cin, int cout, int r, int s);
+int wgrad_smallc_splits(long Mrows, int cin, int cout, int r, int s, int dtype);
 bool conv_wgrad_smallc_takes(const WgradGeom& g);
 hipError_t conv_wgrad_smallc(const WgradGeom& g, int splits, float* out, size_t count, hipStream_t st);
 hipError_t reduce_parts(const ReduceJob& job, hipStream_t st);

@@ -35,8 +35,9 @@ extern "C" size_t acc_op_conv_workspace(int n, int h, int w, int cin, int cout, 
          (stride > 1 ? kMaxDgradParts * 256 : 0);
 }
 
-extern "C" int acc_op_conv_fwd(const void* x, const void* w, void* y, int n, int h, int wd, int cin, int cout,
-                               int r, int s, int stride, int pad, int dtype, void* stream) {
+namespace {
+int conv_fwd(const void* x, const void* w, void* y, int n, int h, int wd, int cin, int cout, int r, int s, int stride, int pad,
+             int dtype, hipStream_t st, LaunchProbe* probe) {
   if (!x || !w || !y || !dtype_ok(dtype) || !conv_ok(n, h, wd, cin, cout, r, s, stride, pad)) return ACC_EINVAL;
   if (!al16({x, w, y})) return ACC_EINVAL;
   ConvGeom g{};
@@ -45,15 +46,14 @@ extern "C" int acc_op_conv_fwd(const void* x, const void* w, void* y, int n, int
   g.p = out_dim(h, r, stride, pad); g.q = out_dim(wd, s, stride, pad); g.n_out = cout;
   g.r = r; g.s = s; g.stride = stride; g.pad = pad;
   g.out_h = g.p; g.out_w = g.q; g.out_stride = 1;
-  return status(conv_igemm(g, (hipStream_t)stream));
+  return status(conv_igemm(g, st, probe));
 }
 
-extern "C" int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, int cin, int cout,
-                                 int r, int s, int stride, int pad, int accumulate, void* workspace,
-                                 size_t workspace_bytes, int dtype, void* stream) {
+int conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, int cin, int cout, int r, int s, int stride, int pad,
+               int accumulate, void* workspace, size_t workspace_bytes, int dtype, hipStream_t st, LaunchProbe* probe) {
   if (!dy || !w || !dx || !dtype_ok(dtype) || !conv_ok(n, h, wd, cin, cout, r, s, stride, pad)) return ACC_EINVAL;
   if (!al16({dy, w, dx, workspace})) return ACC_EINVAL;
-  hipStream_t st = (hipStream_t)stream;
+  const bool dry = probe && probe->dry;
   const int ho = out_dim(h, r, stride, pad), wo = out_dim(wd, s, stride, pad);
   hipError_t e;
   if (stride > 1 && (r > 1 || pad > 0)) {
@@ -66,7 +66,7 @@ extern "C" int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n,
     if (!covers_all && !accumulate) {
       const size_t bytes = (size_t)n * h * wd * cin * dt_size(dtype);
       if (bytes % 4) return ACC_EINVAL;
-      if ((e = fill_zero((float*)dx, bytes / 4, st)) != hipSuccess) return status(e);
+      if (!dry && (e = fill_zero((float*)dx, bytes / 4, st)) != hipSuccess) return status(e);
     }
     if (np == 0) return ACC_OK;      // no position of dx has a tap
     const DgradSplit split{w, cout, cin, r, s, stride, parts, np};
@@ -75,13 +75,12 @@ extern "C" int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n,
     g.n_img = n; g.h = ho; g.wd = wo; g.c = cout; g.n_out = cin;
     g.out_h = h; g.out_w = wd; g.accumulate = accumulate;
     g.split = &split;
-    return status(conv_igemm(g, st));
+    return status(conv_igemm(g, st, probe));
   }
   const size_t filt = al256((size_t)cout * cin * r * s * sizeof(float));
   if (!workspace || workspace_bytes < filt) return ACC_EINVAL;
   void* wt = workspace;
-  e = filter_flip_transpose(w, wt, cout, cin, r, s, dtype, st);
-  if (e != hipSuccess) return status(e);
+  if (!dry && (e = filter_flip_transpose(w, wt, cout, cin, r, s, dtype, st)) != hipSuccess) return status(e);
   ConvGeom g{};
   g.in = dy; g.w = wt; g.out = dx; g.dtype = dtype;
   g.n_img = n; g.h = ho; g.wd = wo; g.c = cout; g.n_out = cin;
@@ -94,16 +93,14 @@ extern "C" int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n,
     if (!accumulate) {
       const size_t bytes = (size_t)n * h * wd * cin * dt_size(dtype);
       if (bytes % 4) return ACC_EINVAL;
-      e = fill_zero((float*)dx, bytes / 4, st);
-      if (e != hipSuccess) return status(e);
+      if (!dry && (e = fill_zero((float*)dx, bytes / 4, st)) != hipSuccess) return status(e);
     }
   }
-  return status(conv_igemm(g, st));
+  return status(conv_igemm(g, st, probe));
 }
 
-extern "C" int acc_op_conv_wgrad(const void* x, const void* dy, float* dw, int n, int h, int wd, int cin, int cout,
-                                 int r, int s, int stride, int pad, void* workspace, size_t workspace_bytes,
-                                 int dtype, void* stream) {
+int conv_wgrad_op(const void* x, const void* dy, float* dw, int n, int h, int wd, int cin, int cout, int r, int s, int stride, int pad,
+                  void* workspace, size_t workspace_bytes, int dtype, hipStream_t st, LaunchProbe* probe) {
   if (!x || !dy || !dw || !dtype_ok(dtype) || !conv_ok(n, h, wd, cin, cout, r, s, stride, pad)) return ACC_EINVAL;
   if (!al16({x, dy, dw, workspace})) return ACC_EINVAL;
   const int ho = out_dim(h, r, stride, pad), wo = out_dim(wd, s, stride, pad);
@@ -113,8 +110,42 @@ extern "C" int acc_op_conv_wgrad(const void* x, const void* dy, float* dw, int n
   g.x = x; g.dy = dy; g.dw = dw; g.dtype = dtype;
   g.n_img = n; g.h = h; g.wd = wd; g.cin = cin; g.p = ho; g.q = wo; g.cout = cout;
   g.r = r; g.s = s; g.stride = stride; g.pad = pad; g.workspace = (float*)workspace;
-  return status(conv_wgrad(g, (hipStream_t)stream));
+  return status(conv_wgrad(g, st, probe));
 }
+}  // namespace
+
+extern "C" int acc_op_conv_fwd(const void* x, const void* w, void* y, int n, int h, int wd, int cin, int cout,
+                               int r, int s, int stride, int pad, int dtype, void* stream) {
+  return conv_fwd(x, w, y, n, h, wd, cin, cout, r, s, stride, pad, dtype, (hipStream_t)stream, nullptr);
+}
+
+extern "C" int acc_op_conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, int cin, int cout,
+                                 int r, int s, int stride, int pad, int accumulate, void* workspace,
+                                 size_t workspace_bytes, int dtype, void* stream) {
+  return conv_dgrad(dy, w, dx, n, h, wd, cin, cout, r, s, stride, pad, accumulate, workspace, workspace_bytes, dtype,
+                    (hipStream_t)stream, nullptr);
+}
+
+extern "C" int acc_op_conv_wgrad(const void* x, const void* dy, float* dw, int n, int h, int wd, int cin, int cout,
+                                 int r, int s, int stride, int pad, void* workspace, size_t workspace_bytes,
+                                 int dtype, void* stream) {
+  return conv_wgrad_op(x, dy, dw, n, h, wd, cin, cout, r, s, stride, pad, workspace, workspace_bytes, dtype,
+                       (hipStream_t)stream, nullptr);
+}
+
+extern "C" const char* acc_op_conv_kernel(int role, int n, int h, int wd, int cin, int cout, int r, int s, int stride, int pad,
+                                          int dtype) {
+  LaunchProbe probe;
+  probe.dry = true;
+  float* const p = reinterpret_cast<float*>((uintptr_t)4096);      // any aligned address: nothing reads it
+  const size_t all = ~(size_t)0;
+  const int rc = role == 0 ? conv_fwd(p, p, p, n, h, wd, cin, cout, r, s, stride, pad, dtype, nullptr, &probe)
+                 : role == 1 ? conv_dgrad(p, p, p, n, h, wd, cin, cout, r, s, stride, pad, 0, p, all, dtype, nullptr, &probe)
+                 : role == 2 ? conv_wgrad_op(p, p, p, n, h, wd, cin, cout, r, s, stride, pad, p, all, dtype, nullptr, &probe)
+                             : ACC_EINVAL;
+  return rc != ACC_OK ? nullptr : probe.kernel ? probe.kernel : "none";
+}
+
 
 extern "C" size_t acc_op_bn_workspace(int c) { return c > 0 ? al256(bn_workspace_bytes(c)) : 0; }
 

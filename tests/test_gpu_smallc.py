@@ -22,6 +22,17 @@ CASES = [  # n, h, w, cin, cout, r, stride, pad: at least 16384 output positions
     (300, 8, 9, 3, 24, 3, 1, 1),       # images of one group of rows
     (3, 150, 600, 3, 32, 5, 2, 2),     # wide rows: fewer of them fit
 ]
+# the same where the kernels for few channels take both storage types: f = forward, w = weight gradient in fp32 too (bf16: always)
+TAKEN = [
+    (26, 112, 112, 3, 64, 7, 2, 3, "fw"),
+    (20, 131, 123, 3, 72, 7, 2, 3, "fw"),
+    (12, 97, 93, 3, 64, 3, 1, 1, "f"),
+    (29, 33, 40, 1, 40, 5, 1, 2, "f"),
+    (18, 64, 70, 2, 16, 4, 1, 0, "f"),
+    (150, 8, 41, 3, 24, 3, 1, 1, "f"),
+    (8, 150, 600, 3, 32, 5, 2, 2, "f"),
+    (34, 50, 49, 2, 40, 7, 1, 3, "fw"),
+]
 
 
 def bf16(a):
@@ -29,9 +40,12 @@ def bf16(a):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("case", CASES + TAKEN)
 def test_small_channel_conv(case, dtype):
-    n, h, w, cin, cout, r, stride, pad = case
+    n, h, w, cin, cout, r, stride, pad = case[:8]
+    if len(case) > 8:
+        kernel = lambda role: B().op_conv_kernel(role, *case[:8], B().F32 if dtype == "f32" else B().BF16)
+        assert kernel("fwd") == "smallc" and (kernel("wgrad") == "smallc") == (dtype == "bf16" or "w" in case[8])
     x = rnd(1, n, cin, h, w)
     wt = rnd(2, cout, cin, r, r) * np.float32(np.sqrt(2.0 / (cin * r * r)))
     ho, wo = O.out_dim(h, r, stride, pad), O.out_dim(w, r, stride, pad)
@@ -55,10 +69,11 @@ def test_small_channel_conv(case, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_small_channel_conv_keeps_infinities_and_nan(dtype):
+@pytest.mark.parametrize("case", [CASES[0], TAKEN[0]])
+def test_small_channel_conv_keeps_infinities_and_nan(case, dtype):
     """A non-finite input reaches exactly the outputs and the filter gradients that read it (the kernels also touch the
     values beside a window, times zeros)."""
-    n, h, w, cin, cout, r, stride, pad = CASES[0]
+    n, h, w, cin, cout, r, stride, pad = case[:8]
     x, wt = bf16(rnd(1, n, cin, h, w)), bf16(rnd(2, cout, cin, r, r))
     dy = bf16(rnd(3, n, cout, 56, 56))
     wt[:, 1] = 0.5
@@ -127,10 +142,10 @@ def test_pooling_mean_wide_and_narrow(case, offset):
 
 
 @pytest.mark.parametrize("scales", [(-116, 90), (-140, 110), (90, -116), (100, -130)])
-@pytest.mark.parametrize("case", CASES[:2])
+@pytest.mark.parametrize("case", TAKEN[:2])
 def test_small_channel_conv_tiny_operands(case, scales):
     """fp32 operands whose lowest bits lie below the smallest bf16 are held in all their bits."""
-    n, h, w, cin, cout, r, stride, pad = case
+    n, h, w, cin, cout, r, stride, pad = case[:8]
     ho, wo = O.out_dim(h, r, stride, pad), O.out_dim(w, r, stride, pad)
     small = lambda a, e: torch.from_numpy(np.ldexp(a.astype(np.float64), e).astype(np.float32))
     x, wt, dy = small(rnd(1, n, cin, h, w), scales[0]), small(rnd(2, cout, cin, r, r), scales[1]), small(rnd(3, n, cout, ho, wo), scales[1])
