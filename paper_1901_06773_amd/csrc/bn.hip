@@ -3,9 +3,9 @@
 //
 // The work is bandwidth bound, so every kernel reads whole float4 channel groups of
 // consecutive rows (a wave covers 1 KiB of contiguous memory per load).  Reductions
-// over rows run in two fixed-order stages (per-slab partials in double, then one
-// wave per channel adds the slabs in a fixed order): no atomics, results do not depend
-// on timing or addresses.
+// over rows run in two fixed-order stages (per-slab partials in double, then a
+// workgroup adds the slabs of eight channels in a fixed order): no atomics, results do
+// not depend on timing or addresses.
 //
 // workspace layout (bn_workspace_bytes): double part[2][MAX_SLABS][c] | float coef[4][c]
 // (partial sums a convolution launch hands over instead are floats: fp32 sums over 32 rows each)
@@ -53,12 +53,14 @@ struct ReduceShape {
   int tpr, rpi, col_slices;
 };
 
-__host__ __device__ inline ReduceShape reduce_shape(int groups) {   // groups of V channels
+__host__ __device__ inline ReduceShape reduce_shape(int groups, bool even) {   // groups of V channels
   ReduceShape s;
-  s.tpr = groups < 64 ? groups : 64;
+  s.col_slices = (groups + 63) / 64;
+  // even: slices of like width (65 groups as 33 + 32; bf16 520 channels, 41 images of 28x28 backward 53 -> 47 us), else as
+  // wide as can be (65 as 64 + 1; fp32 516 channels 107 us against 110)
+  s.tpr = even ? (groups + s.col_slices - 1) / s.col_slices : groups < 64 ? groups : 64;
   // tpr need not divide 256: the leftover threads idle
   s.rpi = THREADS / s.tpr;
-  s.col_slices = (groups + s.tpr - 1) / s.tpr;
   return s;
 }
 
@@ -70,11 +72,11 @@ struct Span {
 };
 
 // Sums over the rows of one slab, per channel, of up to two quantities.  Bound by memory: x (and dy, y) read once, V channels
-// = 16 bytes per thread and load, U rows in flight.  With the passes below, bf16 512 channels, 256 images of 28x28, residual:
-// forward 198 -> 170 us, backward 358 -> 333 (8-byte loads, coefficients fetched per element before); what is left of
+// = 16 bytes per thread and load, U rows in flight.  With the apply passes below, bf16 512 channels, 256 images of 28x28, residual:
+// forward 196 -> 153 us, backward 354 -> 313 (8-byte loads, coefficients fetched per element before); what is left of
 // the way to 134 / 223 us of traffic at 4.6 TB/s is the second read of x, dy and y, which the caches don't hold: in slices of
 // 1/2 or 1/4 of the channels, one after the other, the rows become too short (862 us both ways), and walking back from the
-// end in the second pass gives nothing (170.4 / 333.3).
+// end in the second pass gives nothing.
 // MODE 0: (x, x*x).   MODE 1: (g, g*xhat) with g = dy * [y > 0] (y optional).
 template <int MODE, class T, int V>
 __global__ __launch_bounds__(THREADS) void bn_reduce_kernel(const T* __restrict__ x,
@@ -262,52 +264,42 @@ __global__ __launch_bounds__(FIN_THREADS) void bn_bwd_finish_kernel(
   coef[2 * c + ch] = (float)(dg / m);
 }
 
-// y = relu?((x-mean)*scale + beta (+ res)): a thread keeps its V channels and walks down the rows of its workgroup, the
-// coefficients in registers.  Subtracting the mean first keeps the result exact where x equals the mean (a channel of
-// constant values).
+// The apply passes: the groups of V channels of the tensor in memory order, thread i of the first `stride` taking groups i,
+// i + stride, ...; stride is a multiple of the groups of a row, so a thread keeps its channels (`tpc` groups a row), the
+// coefficients stay in registers and the launch as a whole reads and writes one contiguous window after the other,
+// whatever the channel count.  bf16, both directions (coefficients fetched per element / a workgroup walking down rows of its
+// own, four or two in flight / so): 512 channels, 256 images of 28x28, residual 550 / 482 / 466 us; 760, 38 of 51x51,
+// residual 416 / 427 / 343; 1028, 41 of 28x28 133 / 148 / 124.  Several loads of a thread in flight gain nothing here (four: 491, 349, 129).
+struct Flat {
+  size_t groups, stride;
+  int c, tpc;
+};
+
+// y = relu?((x-mean)*scale + beta (+ res)).  Subtracting the mean first keeps the result exact where x equals the mean (a channel
+// of constant values).
 template <class T, int V>
 __global__ __launch_bounds__(THREADS) void bn_apply_kernel(const T* __restrict__ x,
                                                            const T* __restrict__ res,
                                                            const float* __restrict__ coef,
-                                                           T* __restrict__ y, int relu, Span sp) {
-  const int tid = threadIdx.x, lane_r = tid / sp.tpr, lane_c = tid - lane_r * sp.tpr;
-  const int ch = (blockIdx.y * sp.tpr + lane_c) * V;
-  if (lane_r >= sp.rpi || ch >= sp.c) return;
-  const int c = sp.c, rpi = sp.rpi;
+                                                           T* __restrict__ y, int relu, Flat fl) {
+  const size_t i0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
+  if (i0 >= fl.stride) return;
+  const int c = fl.c, ch = (int)(i0 % fl.tpc) * V;
   float sc[V], mu[V], be[V];
 #pragma unroll
   for (int j = 0; j < V; ++j) { sc[j] = coef[ch + j]; mu[j] = coef[c + ch + j]; be[j] = coef[2 * c + ch + j]; }
-  const long r_lo = (long)blockIdx.x * sp.rows_per_wg;
-  const long r_hi = r_lo + sp.rows_per_wg < sp.rows ? r_lo + sp.rows_per_wg : sp.rows;
-  constexpr int U = 4;
-  const size_t hop = (size_t)rpi * c;
-  size_t at = (size_t)(r_lo + lane_r) * c + ch;
-  auto one = [&](const float (&xv)[V], const float (&rv)[V], size_t to) {
-    float o[V];
+  const size_t hop = fl.stride * V, end = fl.groups * V;
+  for (size_t at = i0 * V; at < end; at += hop) {
+    float xv[V], rv[V], o[V];
+    ElemV<T, V>::load(x + at, xv);
+    if (res) ElemV<T, V>::load(res + at, rv);
 #pragma unroll
     for (int j = 0; j < V; ++j) {
       o[j] = fmaf(xv[j] - mu[j], sc[j], be[j]);
       if (res) o[j] += rv[j];
       if (relu) o[j] = fmaxf(o[j], 0.f);
     }
-    ElemV<T, V>::store(y + to, o);
-  };
-  long r = r_lo + lane_r;
-  for (; r + (long)(U - 1) * rpi < r_hi; r += (long)U * rpi, at += U * hop) {
-    float xv[U][V], rv[U][V];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      ElemV<T, V>::load(x + at + u * hop, xv[u]);
-      if (res) ElemV<T, V>::load(res + at + u * hop, rv[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) one(xv[u], rv[u], at + u * hop);
-  }
-  for (; r < r_hi; r += rpi, at += hop) {
-    float xv[V], rv[V];
-    ElemV<T, V>::load(x + at, xv);
-    if (res) ElemV<T, V>::load(res + at, rv);
-    one(xv, rv, at);
+    ElemV<T, V>::store(y + at, o);
   }
 }
 
@@ -316,50 +308,29 @@ template <class T, int V>
 __global__ __launch_bounds__(THREADS) void bn_bwd_apply_kernel(
     const T* __restrict__ x, const T* dy, const T* __restrict__ y,
     const float* __restrict__ mean, const float* __restrict__ istd, const float* __restrict__ coef,
-    T* __restrict__ dx, T* g_out, Span sp) {
-  const int tid = threadIdx.x, lane_r = tid / sp.tpr, lane_c = tid - lane_r * sp.tpr;
-  const int ch = (blockIdx.y * sp.tpr + lane_c) * V;
-  if (lane_r >= sp.rpi || ch >= sp.c) return;
-  const int c = sp.c, rpi = sp.rpi;
+    T* __restrict__ dx, T* g_out, Flat fl) {
+  const size_t i0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
+  if (i0 >= fl.stride) return;
+  const int c = fl.c, ch = (int)(i0 % fl.tpc) * V;
   float mu[V], is[V], a[V], c1[V], c2[V];
 #pragma unroll
   for (int j = 0; j < V; ++j) {
     mu[j] = mean[ch + j]; is[j] = istd[ch + j];
     a[j] = coef[ch + j]; c1[j] = coef[c + ch + j]; c2[j] = coef[2 * c + ch + j];
   }
-  const long r_lo = (long)blockIdx.x * sp.rows_per_wg;
-  const long r_hi = r_lo + sp.rows_per_wg < sp.rows ? r_lo + sp.rows_per_wg : sp.rows;
-  constexpr int U = V == 8 ? 2 : 4;
-  const size_t hop = (size_t)rpi * c;
-  size_t at = (size_t)(r_lo + lane_r) * c + ch;
-  auto one = [&](const float (&xv)[V], float (&gv)[V], const float (&yv)[V], size_t to) {
-    float o[V];
+  const size_t hop = fl.stride * V, end = fl.groups * V;
+  for (size_t at = i0 * V; at < end; at += hop) {
+    float xv[V], gv[V], yv[V], o[V];
+    ElemV<T, V>::load(x + at, xv);
+    ElemV<T, V>::load(dy + at, gv);
+    if (y) ElemV<T, V>::load(y + at, yv);
 #pragma unroll
     for (int j = 0; j < V; ++j) {
       gv[j] = !y || yv[j] > 0.f ? gv[j] : 0.f;
       o[j] = a[j] * (gv[j] - c1[j] - (xv[j] - mu[j]) * is[j] * c2[j]);
     }
-    ElemV<T, V>::store(dx + to, o);
-    if (g_out) ElemV<T, V>::store(g_out + to, gv);
-  };
-  long r = r_lo + lane_r;
-  for (; r + (long)(U - 1) * rpi < r_hi; r += (long)U * rpi, at += U * hop) {
-    float xv[U][V], gv[U][V], yv[U][V];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      ElemV<T, V>::load(x + at + u * hop, xv[u]);
-      ElemV<T, V>::load(dy + at + u * hop, gv[u]);
-      if (y) ElemV<T, V>::load(y + at + u * hop, yv[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) one(xv[u], gv[u], yv[u], at + u * hop);
-  }
-  for (; r < r_hi; r += rpi, at += hop) {
-    float xv[V], gv[V], yv[V];
-    ElemV<T, V>::load(x + at, xv);
-    ElemV<T, V>::load(dy + at, gv);
-    if (y) ElemV<T, V>::load(y + at, yv);
-    one(xv, gv, yv, at);
+    ElemV<T, V>::store(dx + at, o);
+    if (g_out) ElemV<T, V>::store(g_out + at, gv);
   }
 }
 
@@ -619,11 +590,15 @@ inline int slab_count(long rows, const ReduceShape& rs) {
   return (int)s;
 }
 
-// rows of an apply workgroup: about 16 workgroups per compute unit over all column slices, whole trips of four rows per thread
-inline long apply_rows(long rows, const ReduceShape& rs) {
-  const long wgs = 4096 / rs.col_slices > 0 ? 4096 / rs.col_slices : 1, trip = 4L * rs.rpi;
-  const long per = (rows + wgs - 1) / wgs;
-  return (per + trip - 1) / trip * trip;
+// about 16 workgroups per compute unit at most, and threads for a whole number of rows
+inline Flat apply_flat(long rows, int c, int v, unsigned* blocks) {
+  Flat f{(size_t)rows * (c / v), 0, c, c / v};
+  const size_t want = (f.groups + THREADS - 1) / THREADS, cap = 256 * 16;
+  size_t b = want < cap ? want : cap;
+  if (b * THREADS < (size_t)f.tpc) b = ((size_t)f.tpc + THREADS - 1) / THREADS;      // at least one row
+  f.stride = b * THREADS / f.tpc * f.tpc;
+  *blocks = (unsigned)b;
+  return f;
 }
 
 }  // namespace
@@ -641,10 +616,9 @@ void bn_forward_finish(const T* x, const float* gamma, const float* beta, const 
                        float* coef, hipStream_t st) {
   hipLaunchKernelGGL(bn_fwd_finish_kernel<P>, dim3((c + FIN_CH - 1) / FIN_CH), dim3(FIN_THREADS), 0, st, sums, gamma,
                      beta, mean, istd, coef, rows, c, eps, slabs, stride);
-  const ReduceShape rs = reduce_shape(c / V);
-  const long per = apply_rows(rows, rs);
-  hipLaunchKernelGGL((bn_apply_kernel<T, V>), dim3((unsigned)((rows + per - 1) / per), rs.col_slices), dim3(THREADS), 0, st, x, res,
-                     coef, y, relu, Span{rows, c, rs.tpr, rs.rpi, per});
+  unsigned blocks;
+  const Flat fl = apply_flat(rows, c, V, &blocks);
+  hipLaunchKernelGGL((bn_apply_kernel<T, V>), dim3(blocks), dim3(THREADS), 0, st, x, res, coef, y, relu, fl);
 }
 
 template <class T, class P>
@@ -670,7 +644,7 @@ hipError_t bn_forward_v(const T* x, const float* gamma, const float* beta, const
                               coef, st);
     return hipGetLastError();
   }
-  const ReduceShape rs = reduce_shape(c / V);
+  const ReduceShape rs = reduce_shape(c / V, V == 8);
   const int slabs = slab_count<T>(rows, rs);
   hipLaunchKernelGGL((bn_reduce_kernel<0, T, V>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, (const T*)nullptr,
                      (const T*)nullptr, nullptr, nullptr, part, Span{rows, c, rs.tpr, rs.rpi, (rows + slabs - 1) / slabs});
@@ -687,10 +661,9 @@ void bn_backward_finish(const T* x, const T* dy, const T* y, const float* gamma,
                         int stride, float* coef, hipStream_t st) {
   hipLaunchKernelGGL(bn_bwd_finish_kernel<P>, dim3((c + FIN_CH - 1) / FIN_CH), dim3(FIN_THREADS), 0, st, sums, gamma,
                      istd, dgamma, dbeta, coef, rows, c, slabs, stride);
-  const ReduceShape rs = reduce_shape(c / V);
-  const long per = apply_rows(rows, rs);
-  hipLaunchKernelGGL((bn_bwd_apply_kernel<T, V>), dim3((unsigned)((rows + per - 1) / per), rs.col_slices), dim3(THREADS), 0, st, x, dy, y,
-                     mean, istd, coef, dx, g_out, Span{rows, c, rs.tpr, rs.rpi, per});
+  unsigned blocks;
+  const Flat fl = apply_flat(rows, c, V, &blocks);
+  hipLaunchKernelGGL((bn_bwd_apply_kernel<T, V>), dim3(blocks), dim3(THREADS), 0, st, x, dy, y, mean, istd, coef, dx, g_out, fl);
 }
 
 template <class T, class P>
@@ -717,7 +690,7 @@ hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma
                                ready.stride, coef, st);
     return hipGetLastError();
   }
-  const ReduceShape rs = reduce_shape(c / V);
+  const ReduceShape rs = reduce_shape(c / V, V == 8);
   const int slabs = slab_count<T>(rows, rs);
   hipLaunchKernelGGL((bn_reduce_kernel<1, T, V>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, dy, y, mean,
                      istd, part, Span{rows, c, rs.tpr, rs.rpi, (rows + slabs - 1) / slabs});
@@ -731,6 +704,12 @@ hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma
 
 }  // namespace
 
+// bf16, eight channels per thread: the channels come in eights (every row then starts on a 16-byte address, as every tensor does)
+// and there are rows enough for the threads left (512 channels, 256 images of 28x28, both ways 510 us against 556 with four;
+// 40 channels, 200 images of 14x14, half the workgroups: 32 against 27; smaller tensors run the slice kernels: 512 channels,
+// 49 images of 9x9 31 against 26).
+static bool wide_bf16(long rows, int c) { return c % 8 == 0 && rows > kSliceMaxRows && rows * c >= (4L << 20); }
+
 hipError_t bn_forward(const void* x, const float* gamma, const float* beta, const void* res, void* y,
                       float* mean, float* istd, long rows, int c, int relu, float eps, void* workspace,
                       int dtype, hipStream_t st, const BnSums* ready_sums) {
@@ -741,9 +720,7 @@ hipError_t bn_forward(const void* x, const float* gamma, const float* beta, cons
   if (dtype == DT_F32)
     return bn_forward_v<float, 4>((const float*)x, gamma, beta, (const float*)res, (float*)y, mean, istd, rows, c, relu, eps,
                         workspace, st, ready);
-  // eight channels per thread where the channels come in eights: every row then starts on a 16-byte address, as every tensor
-  // does (bf16 512 channels, 256 images of 28x28, both ways: 510 us against 556 with four)
-  if (dtype == DT_BF16 && c % 8 == 0)
+  if (dtype == DT_BF16 && wide_bf16(rows, c))
     return bn_forward_v<bf16_t, 8>((const bf16_t*)x, gamma, beta, (const bf16_t*)res, (bf16_t*)y, mean, istd, rows, c, relu,
                                    eps, workspace, st, ready);
   if (dtype == DT_BF16)
@@ -764,7 +741,7 @@ hipError_t bn_backward(const void* x, const void* dy, const void* y, const float
   if (dtype == DT_F32)
     return bn_backward_v<float, 4>((const float*)x, (const float*)dy, (const float*)y, gamma, mean, istd, (float*)dx, dgamma,
                          dbeta, (float*)g_out, rows, c, workspace, st, ready);
-  if (dtype == DT_BF16 && c % 8 == 0)
+  if (dtype == DT_BF16 && wide_bf16(rows, c))
     return bn_backward_v<bf16_t, 8>((const bf16_t*)x, (const bf16_t*)dy, (const bf16_t*)y, gamma, mean, istd, (bf16_t*)dx,
                                     dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready);
   if (dtype == DT_BF16)

@@ -9,14 +9,15 @@ ROWS = 16384 + 1 + 2 * 23      # one row more than the slice kernels' last, and 
 
 
 def _tensor(flat):
-    return flat.to(torch.bfloat16).cuda().view(1, 1, ROWS, flat.shape[-1])
+    return flat.to(torch.bfloat16).cuda().view(1, 1, *flat.shape)
 
 
-# 8 and 24: eight channels per thread, one and three threads across a row; 520: 65 threads, a second column slice of one;
-# 12: channels not in eights
-@pytest.mark.parametrize("c", [8, 24, 520, 12])
+# Eight channels per thread from 4 Mi elements on: 520 (65 threads across a row, in slices of 33 and 32), 8 and 24 (one and three
+# threads), 256 (a last workgroup that is not full).  Four: fewer elements; 12, 260 and 1028: channels not in eights.
+@pytest.mark.parametrize("ROWS,c", [(ROWS, 8), (ROWS, 24), (ROWS, 520), (ROWS, 12), (ROWS, 260), (ROWS, 1028), (524288 + 47, 8),
+                                    (174763, 24), (16385, 256)])
 @pytest.mark.parametrize("relu", [False, True])
-def test_bn_bf16_many_rows(c, relu):
+def test_bn_bf16_many_rows(ROWS, c, relu):
     from paper_1901_06773_amd import binding as b
     g = torch.Generator().manual_seed(c)
     x, dy, res = ((torch.randn(ROWS, c, generator=g) * 1.5 + 0.3).to(torch.bfloat16) for _ in range(3))
