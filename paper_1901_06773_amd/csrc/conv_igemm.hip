@@ -80,7 +80,7 @@ __device__ __forceinline__ size_t out_row_offset(const ConvGeom& g, int m) {
   return ((size_t)(img * g.out_h + g.out_y0 + p * g.out_stride) * g.out_w + g.out_x0 + q * g.out_stride) * g.n_out;
 }
 
-// Loaders.  L_DIRECT: bf16, c a multiple of the chunk's 64 channels, NHWC input, at
+// Loaders.  L_DIRECT: c a multiple of the chunk (32 fp32 / 64 bf16 channels), NHWC input, at
 // most 32 filter taps, both operands within 32-bit byte ranges.  L_GENERIC: every element is
 // decoded on its own and staged through registers (any c, K tail); used for the 3-channel
 // stem and for tiny layers.
@@ -95,21 +95,30 @@ __device__ __forceinline__ size_t out_row_offset(const ConvGeom& g, int m) {
 // stages: the loads of chunk kc+1 are issued right after the barrier that opens chunk kc
 // and have its whole MFMA work to land.
 enum { L_GENERIC = 0, L_DIRECT = 2 };
-template <int LOADER, class T, bool ACT>
-__global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles,
+// KS = 2: a workgroup of 8 waves, two groups of 4 that each keep the whole 64 x 64 tile and take every
+// second K-chunk (own LDS stages, 64 KB per workgroup); group 1 hands its accumulators over through LDS
+// at the end and group 0 writes the tile.  For launches with at most one tile per compute unit (the 7 x 7
+// layers of a ResNet at small minibatches), where the 4-wave kernel leaves every SIMD with a single wave:
+// 512->512 3x3 at 7 x 7, minibatch 41 (256 tiles) 98 -> 85 us, 2048->512 1x1 47 -> 42 us.  With two tiles
+// per compute unit it gains nothing (256->256 3x3 at 14 x 14: 82.7 -> 82.3 us; 1024->256 1x1 40.5 -> 41.7):
+// the two groups pass the same barriers, so they wait together where two workgroups would not.
+template <int LOADER, class T, bool ACT, int KS = 1>
+__global__ __launch_bounds__(256 * KS) void igemm_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles,
                                                           int main_grid) {
   constexpr bool DIRECT = LOADER == L_DIRECT;
+  static_assert(KS == 1 || (KS == 2 && DIRECT && !ACT), "the split serves the direct loader only");
   constexpr int ES = sizeof(T);
-  static_assert(!DIRECT || ES == 2, "fp32 layers with whole 16-channel steps run elsewhere");
   constexpr int DCHUNK = CHUNK_BYTES;
-  constexpr int BK = (DIRECT ? DCHUNK : CHUNK_BYTES) / ES;       // elements of K per chunk
+  constexpr int BK = CHUNK_BYTES / ES;       // elements of K per chunk
   constexpr int LDD = DCHUNK / 4;            // LDS row pitch of L_DIRECT in words
   constexpr int PITCH = DIRECT ? LDD : LD;
-  __shared__ __attribute__((aligned(1024))) float As[2 * BM * PITCH];
-  __shared__ __attribute__((aligned(1024))) float Bs[2 * BN * PITCH];
+  __shared__ __attribute__((aligned(1024))) float As[KS * 2 * BM * PITCH];
+  __shared__ __attribute__((aligned(1024))) float Bs[KS * 2 * BN * PITCH];
 
   if ((int)blockIdx.x >= main_grid) {
-    igemm_side_jobs<T>(g, (int)blockIdx.x - main_grid, As);
+    // the side jobs are written for 256 threads (the second group's waves leave; a barrier counts
+    // the waves that are still there)
+    if (KS == 1 || threadIdx.x < 256) igemm_side_jobs<T>(g, (int)blockIdx.x - main_grid, As);
     return;
   }
 
@@ -129,8 +138,15 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
   const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // thread, wave: within the group of 4 waves; ugrp: the group (wave-uniform)
+  const int tid = KS == 1 ? (int)threadIdx.x : (int)(threadIdx.x & 255), lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int ugrp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8));
+#else
+  const int ugrp = 0;
+#endif
+
   v16f acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -249,7 +265,7 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
   bool have_old = false;
   if constexpr (DIRECT && !ACT) {
     const int n_pre = n0 + wn0 + (lane & 31);
-    if (g.accumulate && g.out_stride == 1 && g.out_h == g.p && g.out_w == g.q && n_pre < g.n_out) {
+    if (g.accumulate && g.out_stride == 1 && g.out_h == g.p && g.out_w == g.q && n_pre < g.n_out && ugrp == 0) {
       have_old = true;
       const int mb = m0 + wm0 + 4 * (lane >> 5);
       const int left = m0 + BM <= M ? 64 : M - mb;
@@ -304,8 +320,8 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
         const_cast<void*>(g.w), 0, (int)(uint32_t)((size_t)g.n_out * K * ES), 0x00020000);
     typedef __attribute__((address_space(3))) void* lds_ptr;
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
-    const uint32_t lds_a = (uint32_t)(size_t)As + uwave * 1024;
-    const uint32_t lds_b = (uint32_t)(size_t)Bs + uwave * 1024;
+    const uint32_t lds_a = (uint32_t)(size_t)As + ugrp * (2 * BM * DCHUNK) + uwave * 1024;
+    const uint32_t lds_b = (uint32_t)(size_t)Bs + ugrp * (2 * BN * DCHUNK) + uwave * 1024;
     int kr = 0, kt = 0, c0 = 0;     // tap and channel offset of the chunk whose loads are issued next (uniform)
     auto advance = [&]() {
       c0 += BK;
@@ -328,19 +344,39 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
       for (int i = 0; i < BI; ++i)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(size_t)(lds_b + buf * (BN * DCHUNK) + i * 4096),
                                                  16, b_voff[i], soff_b, 0, 0);
-      advance();
+#pragma unroll
+      for (int s = 0; s < KS; ++s) advance();   // a group's next chunk is KS further on
     };
     // fragment of a row: 16-byte column c16 sits in slot c16 ^ (row % CPR)
     const int ra_ = wm0 + (lane & 31), rb_ = wn0 + (lane & 31);
-    // One chunk out of LDS stage `buf`.  A group = two 16-byte columns of a row (lanes 0-31 / 32-63) = one MFMA.
-    // The reads of group g + 1 are issued behind group g, and the last group's MFMA is held back (pa, pb) until
-    // the next chunk's barrier has been passed and its first reads are on their way: the matrix cores have work
-    // queued while the wave waits at the barrier and for LDS.  The next chunk's global loads follow.
+    // One chunk out of LDS stage `buf`.  A group = two 16-byte columns of a row (lanes 0-31 / 32-63) = four
+    // MFMAs.  The reads of group g + 1 are issued between the MFMAs of group g, and the last group's MFMAs are
+    // held back (pa, pb) until the next chunk's barrier has been passed and its first reads are on their way:
+    // the matrix cores have work queued while the wave waits at the barrier and for LDS.  The products are
+    // added in the same order as ever.  The next chunk's global loads are issued after the held-back MFMAs, so
+    // that nothing stands between the barrier and queued matrix work.  (Measured against "all eight reads
+    // first, then sixteen MFMAs", 256->256 3x3 at 14 x 14, minibatch 41: 82.6 -> 79.8 us with the interleaved
+    // reads, 79.4 with the held-back group, 78.6 with the loads behind it; two held-back groups: 79.7; the four loads
+    // spread over the four groups instead of issued together: 82.3.  With no loads at all after the second chunk
+    // the same launch takes 71.3 us: the global -> LDS traffic costs a tenth of the kernel.)
     float4 pa = make_float4(0.f, 0.f, 0.f, 0.f), pb = pa;
-    auto mm = [&](const float4& a, const float4& b) { acc = mfma32x32x16bf(a, b, acc); };
+    auto mm = [&](const float4& a, const float4& b, int half) {
+      if constexpr (ES == 4) {
+        if (half != 1) {
+          acc = mfma32x32x2(a.x, b.x, acc);
+          acc = mfma32x32x2(a.y, b.y, acc);
+        }
+        if (half != 0) {
+          acc = mfma32x32x2(a.z, b.z, acc);
+          acc = mfma32x32x2(a.w, b.w, acc);
+        }
+      } else {
+        if (half != 0) acc = mfma32x32x16bf(a, b, acc);
+      }
+    };
     auto compute_direct = [&](int buf, bool prev, int next_kc = -1) {
-      const float* as = As + buf * (BM * LDD) + ra_ * LDD;
-      const float* bs = Bs + buf * (BN * LDD) + rb_ * LDD;
+      const float* as = As + (ugrp * 2 + buf) * (BM * LDD) + ra_ * LDD;
+      const float* bs = Bs + (ugrp * 2 + buf) * (BN * LDD) + rb_ * LDD;
       constexpr int NG = CPR / 2;
       float4 af[NG], bf[NG];
       auto rd = [&](int g8) {
@@ -350,15 +386,17 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
       };
       rd(0);
       __builtin_amdgcn_sched_barrier(0);
-      if (prev) mm(pa, pb);
+      if (prev) mm(pa, pb, 2);
       __builtin_amdgcn_sched_barrier(0);
       if (next_kc >= 0) issue(next_kc, buf ^ 1);   // the next chunk's loads, once the matrix cores have work queued
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int g8 = 0; g8 + 1 < NG; ++g8) {
+        mm(af[g8], bf[g8], 0);
+        __builtin_amdgcn_sched_barrier(0);
         rd(g8 + 1);
         __builtin_amdgcn_sched_barrier(0);
-        mm(af[g8], bf[g8]);
+        mm(af[g8], bf[g8], 1);
         __builtin_amdgcn_sched_barrier(0);
       }
       pa = af[NG - 1];
@@ -368,6 +406,39 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
     // The barrier that opens chunk kc says two things: every wave's part of chunk kc has
     // landed in LDS (each wave waits for its own loads first), and every wave is done with
     // chunk kc-1, whose stage the loads of chunk kc+1 may now overwrite.
+    if constexpr (KS == 2) {
+      // group u takes the chunks u, u + 2, ...: `mine` of them; both groups pass the same barriers
+      // (those of group 0, which has the odd chunk), a group without a chunk left only waits
+      const int mine = (n_chunks + 1 - ugrp) >> 1, rounds = (n_chunks + 1) >> 1;
+      if (ugrp) advance();
+      if (mine > 0) issue(ugrp, 0);
+      int j = 0;
+      for (; j + 2 <= rounds; j += 2) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (j < mine) compute_direct(0, j > 0, j + 1 < mine ? ugrp + 2 * (j + 1) : -1);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (j + 1 < mine) compute_direct(1, true, j + 2 < mine ? ugrp + 2 * (j + 2) : -1);
+      }
+      if (j < rounds) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (j < mine) compute_direct(0, j > 0);
+      }
+      if (mine > 0) mm(pa, pb, 2);
+      // group 1's sums go to group 0 through LDS (16 KB over stage 0 of As, which nobody reads any more)
+      __syncthreads();
+      float* red = As + (wave * 16) * 64 + lane;
+      if (ugrp == 1) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[v * 64] = acc[v];
+      }
+      __syncthreads();
+      if (ugrp == 1) return;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] += red[v * 64];
+    } else {
     issue(0, 0);
     int kc = 0;
     for (; kc + 2 <= n_chunks; kc += 2) {     // whole pairs of chunks: stage 0, then stage 1
@@ -383,7 +454,8 @@ __global__ __launch_bounds__(256) void igemm_kernel(ConvGeom g, int M, int K, in
       __syncthreads();
       compute_direct(0, kc > 0);
     }
-    mm(pa, pb);                               // n_chunks >= 1
+    mm(pa, pb, 2);                            // n_chunks >= 1
+    }
 #endif
   } else {
     // one element per load: thread -> k column tid % BK, rows tid / BK + RP * i
@@ -576,13 +648,19 @@ hipError_t launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* 
   }
   if (main_grid + side_blocks > (1L << 30)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(main_grid + side_blocks));
-  probe->variant = LOADER == L_DIRECT ? V_IGEMM_DIRECT : V_IGEMM_GENERIC;
-  probe->kernel = LOADER == L_DIRECT ? "igemm direct 64x64" : "igemm generic 64x64";
+  const bool split = LOADER == L_DIRECT && sizeof(T) == 4 && conv_igemm_two_groups(g, M, K);
+  probe->variant = split ? V_IGEMM_DIRECT_2G : LOADER == L_DIRECT ? V_IGEMM_DIRECT : V_IGEMM_GENERIC;
+  probe->kernel = split ? "igemm direct 64x64, two groups" : LOADER == L_DIRECT ? "igemm direct 64x64" : "igemm generic 64x64";
   if (probe->dry) return hipSuccess;
   if (probe->before) (void)hipEventRecord(probe->before, st);
   if (g.bias || g.relu)
     hipLaunchKernelGGL((igemm_kernel<LOADER, T, true>), grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
-  else
+  else if constexpr (LOADER == L_DIRECT && sizeof(T) == 4) {
+    if (split)
+      hipLaunchKernelGGL((igemm_kernel<LOADER, T, false, 2>), grid, dim3(512), 0, st, g, M, K, tn, (int)tiles, main_grid);
+    else
+      hipLaunchKernelGGL((igemm_kernel<LOADER, T, false>), grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
+  } else
     hipLaunchKernelGGL((igemm_kernel<LOADER, T, false>), grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
   if (probe->after) (void)hipEventRecord(probe->after, st);
   return hipGetLastError();
@@ -595,7 +673,8 @@ const char* conv_variant_name(int v) {
                                        "wgrad_kernel<generic>", "igemm_kernel<direct>", "wgrad_kernel<direct>",
                                        "wgrad_bf16_kernel", "igemm_bf16_kernel", "igemm_x3_kernel",
                                        "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel",
-                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel"};
+                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel",
+                                       "igemm_kernel<direct, two groups>"};
   return (v >= 0 && v < V_COUNT) ? names[v] : "?";
 }
 
@@ -651,19 +730,19 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
   if (conv_igemm_bf16_takes(g, M, K))      // bf16 storage, large layers: 128 x 128 tiles
     return conv_igemm_bf16(g, (int)M, (int)K, st, probe);
   if (conv_smallc_takes(g, M)) return conv_smallc_fwd(g, st, probe);
-  if (conv_igemm_x3_takes(g, M, K))        // fp32 storage, whole 16-channel steps: products on the bf16 matrix cores
-    return conv_igemm_x3(g, (int)M, (int)K, st, probe);
-  if (g.dtype == DT_F32) return launch<L_GENERIC, float>(g, (int)M, (int)K, st, probe);
-  // bf16 storage below the 128 x 128 kernel's sizes.  The direct loader addresses both operands through buffer
-  // descriptors: 32-bit ranges, the last bytes kept free for the offset that stands for "outside"; 16-byte loads
-  // want aligned tensors.  The choice depends on the shape and the alignment only, never on the swap plan
-  // (pool offsets are multiples of 256).
-  const long margin_px = (long)g.pad * g.wd + g.pad + g.pad_dx;
-  const bool direct = g.c % (CHUNK_BYTES / 2) == 0 && g.r * g.s <= 32 &&
-                      (margin_px + (long)g.n_img * g.h * g.wd) * g.c * 2 <= 0xFFFFFF00L &&
-                      (long)g.n_out * K * 2 <= 0xFFFFFF00L &&
+  // The direct loader addresses both operands through buffer descriptors: 32-bit ranges, the last bytes kept free for the
+  // offset that stands for "outside"; 16-byte loads want aligned tensors.  The choice depends on the shape and the
+  // alignment only, never on the swap plan (pool offsets are multiples of 256).
+  const long es = (long)dt_size(g.dtype), margin_px = (long)g.pad * g.wd + g.pad + g.pad_dx;
+  const bool direct = g.c % (CHUNK_BYTES / es) == 0 && g.r * g.s <= 32 &&
+                      (margin_px + (long)g.n_img * g.h * g.wd) * g.c * es <= 0xFFFFFF00L &&
+                      (long)g.n_out * K * es <= 0xFFFFFF00L &&
                       (reinterpret_cast<uintptr_t>(g.in) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.w) & 15) == 0;
-  return direct ? launch<L_DIRECT, bf16_t>(g, (int)M, (int)K, st, probe) : launch<L_GENERIC, bf16_t>(g, (int)M, (int)K, st, probe);
+  if (g.dtype == DT_BF16)      // below the 128 x 128 kernel's sizes
+    return direct ? launch<L_DIRECT, bf16_t>(g, (int)M, (int)K, st, probe) : launch<L_GENERIC, bf16_t>(g, (int)M, (int)K, st, probe);
+  // fp32 storage, whole 16-channel steps: products on the bf16 matrix cores, but for small launches
+  if (conv_igemm_x3_takes(g, M, K) && !(direct && conv_igemm_x3_slower(g, M, K))) return conv_igemm_x3(g, (int)M, (int)K, st, probe);
+  return direct ? launch<L_DIRECT, float>(g, (int)M, (int)K, st, probe) : launch<L_GENERIC, float>(g, (int)M, (int)K, st, probe);
 }
 
 }  // namespace acc

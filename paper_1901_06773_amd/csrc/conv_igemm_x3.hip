@@ -15,6 +15,8 @@
 // minibatch 41: 256->256 3x3 at 14x14 75.2 -> 49.5 us, 128->128 3x3 at 28x28 74.7 -> 51.0, 512->512 3x3 at 7x7
 // 77.4 -> 65.6, 256->1024 1x1 at 14x14 38.6 -> 29.0, 1024->256 35.6 -> 30.0, 64->256 at 56x56 (minibatch 32) 38.8
 // -> 33; error against float64 5.9e-7 -> 3.5e-7 on the first of them, smaller on all.
+#include <cmath>
+
 #include "kernels.h"
 #include "dtype.h"
 #include "igemm_side.h"
@@ -886,38 +888,72 @@ void launch_short(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* 
   if (probe->after) (void)hipEventRecord(probe->after, st);
 }
 
-// Which kernel: a launch is predicted to take, on the compute unit with the most tiles,
-//   base + sum over rounds of max(alone + alone_step * steps, r * (shared + shared_step * steps))   [microseconds]
-// with steps = 16-element steps of K per group of waves and r <= per_cu tiles resident together, and the kernel with
-// the smallest prediction runs.  The constants are fitted to measured launches (124 shapes: the layers of the
-// ResNets at minibatches 4 to 128 and random ones, every kernel on each): median error 2-10 %, and the choice is
-// within 1.5 % of the best of the six on average.  A function of the shape and the alignment only, never of the
-// swap plan (pool offsets are multiples of 256).
+// Which kernel: the one with the smallest predicted time, in microseconds.  With steps = steps of K (16 values; 32 in the direct
+// kernel with the fp32 instruction) per group of waves, and tiles counted on the compute unit with the most,
+//   one workgroup per compute unit:  base + first + first_step * steps + (tiles - 1) * (next + next_step * steps) + memory,
+//   several (r <= per_cu resident):  base + (compute^2 + memory^2)^(1/2),  compute = the sum over rounds of
+//                                    max(first + first_step * steps, r * (next + next_step * steps)),
+// taps more per tile for filters larger than 1x1, and memory = per_mb * MB + per_mb_far * (MB beyond 200) of both operands
+// and the result, each once.  The constants are fitted to 481 measured launches (the layers of the ResNets at minibatches
+// 1 to 128 and random ones, every kernel on each; profiles/conv_f32_kernels_by_shape.txt): median errors of 1-4 %, the
+// choice is within 0.4 % of the best on average, 18 % at most.  The fp32 instruction's kernel is kept for the launches where it is
+// still the faster one, small ones above all (256->64 1x1 at 56x56, 4 images 7.6 against 8.9 us; 64->256, 128 images, 514 MB 165
+// against 176); it wins ties within 5 %.  A function of the shape and the alignment only, never of the swap plan (pool
+// offsets are multiples of 256).
 struct Kind {
-  int bm, bn, ks, per_cu;
-  double alone, alone_step, shared, shared_step, base;
+  int bm, bn, ks, kc, per_cu;
+  double base, first, first_step, next, next_step, taps, per_mb, per_mb_far;
 };
-enum { X3_128 = 0, X3_64, X3_WINDOW, X3_DEEP_2x1, X3_DEEP_2x2, X3_DEEP_1x1, X3_KINDS };
-constexpr Kind kKinds[X3_KINDS] = {
-    {128, 128, 1, 2, 3.54, 0.618, 2.90, 0.581, 2.7},   // igemm_x3_kernel<2, 2>
-    {64, 64, 1, 5, 1.75, 0.278, 0.40, 0.215, 3.6},     // igemm_x3_kernel<1, 1>
-    {128, 64, 4, 1, 8.39, 1.039, 8.39, 1.039, -1.8},   // igemm_x3_deep_kernel<2, 1, window>
-    {128, 64, 4, 1, 5.38, 1.315, 5.38, 1.315, 0.5},    // igemm_x3_deep_kernel<2, 1>
-    {128, 128, 2, 1, 6.74, 0.966, 6.74, 0.966, -0.1},  // igemm_x3_deep_kernel<2, 2>
-    {64, 64, 8, 1, 3.90, 1.704, 3.90, 1.704, 1.3},     // igemm_x3_deep_kernel<1, 1>
+enum { X3_128 = 0, X3_64, X3_WINDOW, X3_DEEP_2x1, X3_DEEP_2x2, X3_DEEP_1x1, X3_KINDS, F32_ONE = X3_KINDS, F32_TWO, KINDS };
+constexpr Kind kKinds[KINDS] = {
+    {128, 128, 1, 16, 2, 3.36, 3.81, 0.744, 2.87, 0.596, 0.68, 0.130, 0.139},   // igemm_x3_kernel<2, 2>
+    {64, 64, 1, 16, 5, 4.19, 0.04, 0.369, 0.475, 0.220, 0.35, 0.028, 0.316},    // igemm_x3_kernel<1, 1>
+    {128, 64, 4, 16, 1, 2.96, 4.17, 0.959, 4.47, 1.154, 0.52, 0.133, 0},        // igemm_x3_deep_kernel<2, 1, window>
+    {128, 64, 4, 16, 1, 5.35, 0.69, 1.156, 3.34, 1.662, 1.93, 0.092, 0.076},    // igemm_x3_deep_kernel<2, 1>
+    {128, 128, 2, 16, 1, 5.92, 1.61, 0.844, 4.67, 1.203, 1.34, 0.063, 0.034},   // igemm_x3_deep_kernel<2, 2>
+    {64, 64, 8, 16, 1, 4.30, 1.37, 1.411, 3.33, 1.820, 1.85, 0.063, 0.089},     // igemm_x3_deep_kernel<1, 1>
+    {64, 64, 1, 32, 4, 2.65, 4.49, 0.034, 0.521, 0.506, 0.11, 0.047, 0.104},    // igemm_kernel<direct>, fp32
+    {64, 64, 2, 32, 1, 3.04, 0.21, 1.002, 0.21, 1.002, 1.50, 0.029, 0},         // igemm_kernel<direct, two groups>: one tile at most
 };
-double predicted_us(const Kind& k, long M, long N, long K) {
-  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + 15) / 16 + k.ks - 1) / k.ks;
+double predicted_us(const Kind& k, long M, long N, long K, bool taps, double mb) {
+  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
   const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
-  auto round = [&](long r) {
-    const double alone = k.alone + k.alone_step * steps, shared = r * (k.shared + k.shared_step * steps);
-    return r == 0 ? 0.0 : alone > shared ? alone : shared;
-  };
-  return k.base + (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu);
+  const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = taps ? k.taps * most : 0;
+  const double memory = k.per_mb * mb + k.per_mb_far * (mb > 200 ? mb - 200 : 0);
+  if (k.per_cu == 1) return k.base + first + (most - 1) * next + more + memory;
+  auto round = [&](long r) { return r == 0 ? 0.0 : first > r * next ? first : r * next; };
+  const double compute = (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu) + more;
+  return k.base + std::sqrt(compute * compute + memory * memory);
+}
+double megabytes(const ConvGeom& g, long M, long K) { return 4e-6 * ((double)g.n_img * g.h * g.wd * g.c + (double)M * g.n_out + (double)g.n_out * K); }
+
+// the launches that read every tap from one window of consecutive pixels, if it fits
+bool window_takes(const ConvGeom& g) {
+  using D = Deep<2, 1, true>;
+  return g.r == g.s && g.r * g.s >= 2 * D::KS - 1 && g.stride == 1 && 2 * g.pad == g.r - 1 && g.pad_dx == 0 &&
+         g.p == g.h && g.q == g.wd && D::BM + 2 * (g.pad * g.wd + g.pad) <= D::WROWS;
+}
+
+// the fastest of the kernels in this file, and its prediction
+int best_x3(const ConvGeom& g, long M, long K, double* us) {
+  const double mb = megabytes(g, M, K);
+  const bool window = window_takes(g);
+  int best = -1;
+  for (int v = 0; v < X3_KINDS; ++v) {
+    if (v == X3_WINDOW && !window) continue;
+    const double t = predicted_us(kKinds[v], M, g.n_out, K, g.r * g.s > 1, mb);
+    if (best < 0 || t < *us) { best = v; *us = t; }
+  }
+  return best;
+}
+double fp32_us(const ConvGeom& g, long M, long K) {
+  return predicted_us(kKinds[conv_igemm_two_groups(g, M, K) ? F32_TWO : F32_ONE], M, g.n_out, K, g.r * g.s > 1, megabytes(g, M, K));
 }
 
 // The same for the parts of a strided data gradient in one launch of a short kernel: the longest tile alone, or the compute
-// units' share of all tiles, the last tiles half filling the chip; strided rows and tiles of unlike length add a part.
+// units' share of all tiles and part of a last one.  These constants and those of conv_igemm_x3_parts_takes() are fitted to
+// 45 shapes (2 to 256 images, 32 to 1024 channels, 3x3 and 5x5, stride 2), the sub-filters' launch included: median errors of
+// 3 to 5 %, and on average the choice is within 0.2 % of the best of the three ways, 7 % at most.
 double predicted_parts_us(bool wide, const ConvGeom* parts, int n) {
   const Kind& k = kKinds[wide ? X3_128 : X3_64];
   double work = 0, longest = 0, last = 0;
@@ -925,14 +961,13 @@ double predicted_parts_us(bool wide, const ConvGeom* parts, int n) {
     const ConvGeom& g = parts[i];
     const long M = (long)g.n_img * g.p * g.q, steps = ((long)g.r * g.s * g.c + 15) / 16;
     const long tiles = ((M + k.bm - 1) / k.bm) * ((g.n_out + k.bn - 1) / k.bn);
-    const double shared = k.shared + k.shared_step * steps, alone = k.alone + k.alone_step * steps;
-    work += tiles * shared;
-    if (alone > longest) longest = alone;
-    if (shared > last) last = shared;
+    const double next = k.next + k.next_step * steps, first = k.first + k.first_step * steps;
+    work += tiles * next;
+    if (first > longest) longest = first;
+    if (next > last) last = next;
   }
-  const double share = work / 256 + last / 2;
-  const double us = k.base + (share > longest ? share : longest);
-  return wide ? us * 1.10 + 8 : us * 1.05 + 6;
+  const double share = work / 256 + last * (wide ? 0.51 : 0.27), alone = longest * (wide ? 0.965 : 1.12);
+  return (wide ? 13.1 : 9.6) + 1.08 * (share > alone ? share : alone);
 }
 
 template <int MB, int NB>
@@ -951,13 +986,6 @@ void launch_parts(X3Parts& ps, int n, hipStream_t st, LaunchProbe* probe, long s
   if (probe->before) (void)hipEventRecord(probe->before, st);
   hipLaunchKernelGGL((igemm_x3_parts_kernel<MB, NB>), dim3((unsigned)(main_grid + side_blocks)), dim3(256), 0, st, ps, tn, main_grid);
   if (probe->after) (void)hipEventRecord(probe->after, st);
-}
-
-// the launches that read every tap from one window of consecutive pixels, if it fits
-bool window_takes(const ConvGeom& g) {
-  using D = Deep<2, 1, true>;
-  return g.r == g.s && g.r * g.s >= 2 * D::KS - 1 && g.stride == 1 && 2 * g.pad == g.r - 1 && g.pad_dx == 0 &&
-         g.p == g.h && g.q == g.wd && D::BM + 2 * (g.pad * g.wd + g.pad) <= D::WROWS;
 }
 
 }  // namespace
@@ -986,14 +1014,8 @@ hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, Launch
   const long narrow = (long)((g.side.count + 1023) / 1024) + (g.flip.wt ? flip_tiles(g.flip.cout, g.flip.cin, g.flip.r, g.flip.s) : 0);
   const long tiles = (long)((M + 63) / 64) * ((g.n_out + 63) / 64);
   if (tiles + 8 + narrow > (1L << 30)) return hipErrorInvalidValue;
-  const bool window = window_takes(g);
-  int best = -1;
-  double best_us = 0;
-  for (int v = 0; v < X3_KINDS; ++v) {
-    if (v == X3_WINDOW && !window) continue;
-    const double us = predicted_us(kKinds[v], M, g.n_out, K);
-    if (best < 0 || us < best_us) { best = v; best_us = us; }
-  }
+  double us = 0;
+  const int best = best_x3(g, M, K, &us);
   switch (best) {
     case X3_128: launch_short<2, 2>(g, M, K, st, probe, narrow); break;
     case X3_64: launch_short<1, 1>(g, M, K, st, probe, narrow); break;
@@ -1002,34 +1024,32 @@ hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, Launch
     case X3_DEEP_2x2: launch_deep<2, 2, false>(g, M, K, st, probe); break;
     default: launch_deep<1, 1, false>(g, M, K, st, probe); break;
   }
-  return hipGetLastError();
+  return probe->dry ? hipSuccess : hipGetLastError();
 }
 
-// The parts go into one launch where that is predicted to take less than the parts one after the other, with a launch's
-// gap between them.  Of 21 shapes measured (2 to 256 images, 32 to 1024 channels, 3x3 to 7x7, stride 2) 19 go into one launch:
-// 128 channels of 56x56, 32 images 92 -> 71 us, 512 of 14x14, 256 images 392 -> 346; not 1024 channels of 14x14, 64 images
-// (366 us apart, 396 together) and 256 of 28x28 with 5x5 filters, 64 images (261, 276), which the deep kernels do better.
-static double best_alone_us(const ConvGeom& g) {
-  double best = 1e30;
-  for (int v = 0; v < X3_KINDS; ++v) {
-    if (v == X3_WINDOW && !window_takes(g)) continue;
-    const double us = predicted_us(kKinds[v], (long)g.n_img * g.p * g.q, g.n_out, (long)g.r * g.s * g.c);
-    if (us < best) best = us;
-  }
-  return best;
+bool conv_igemm_x3_slower(const ConvGeom& g, long M, long K) {
+  double us = 0;
+  best_x3(g, M, K, &us);
+  return fp32_us(g, M, K) < us * 1.05;
 }
 
+// The parts go into one launch where that is predicted to take less than the parts one after the other: 128 channels of 56x56, 32
+// images 93 -> 71 us, 512 of 14x14, 256 images 396 -> 350; not 1024 channels of 14x14, 64 images (366 us apart, 391 together) and
+// 256 of 28x28 with 5x5 filters, 64 images (261, 276), which the deep kernels do better.
 bool conv_igemm_x3_parts_takes(const ConvGeom* parts, int n) {
   if (n < 2 || n > kX3Parts) return false;
-  double apart = (n - 1) * 1.5;
+  double apart = 0;
   for (int i = 0; i < n; ++i) {
     const ConvGeom& g = parts[i];
     const long M = (long)g.n_img * g.p * g.q, K = (long)g.r * g.s * g.c;
     if (g.p <= 0 || g.q <= 0 || g.r <= 0 || g.s <= 0 || M >= (1L << 28) || K >= (1L << 31) || !conv_igemm_x3_takes(g, M, K)) return false;
-    apart += best_alone_us(g);
+    double us = 0;
+    best_x3(g, M, K, &us);
+    if (g.c % 32 == 0 && fp32_us(g, M, K) < us) us = fp32_us(g, M, K);
+    apart += us;
   }
   const double a = predicted_parts_us(true, parts, n), b = predicted_parts_us(false, parts, n);
-  return (a < b ? a : b) < apart * 1.08;            // (1.08: strided rows)
+  return (a < b ? a : b) < 6.4 + 1.19 * apart;
 }
 
 hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, LaunchProbe* probe) {
@@ -1063,7 +1083,7 @@ hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, Lau
     launch_parts<2, 2>(ps, n, st, probe, narrow);
   else
     launch_parts<1, 1>(ps, n, st, probe, narrow);
-  return hipGetLastError();
+  return probe->dry ? hipSuccess : hipGetLastError();
 }
 
 }  // namespace acc

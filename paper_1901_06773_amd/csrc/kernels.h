@@ -119,6 +119,13 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, Laun
 // fp32 products on the bf16 matrix cores (conv_igemm_x3.hip): as above.
 bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
+// Whether the direct kernel with the fp32 instruction is predicted to be the faster one for a launch that both take.
+bool conv_igemm_x3_slower(const ConvGeom& g, long M, long K);
+// The direct fp32 kernel runs two groups of waves per tile: at most one tile per compute unit and at least eight chunks of 32
+// values of K (a function of the shape only).
+inline bool conv_igemm_two_groups(const ConvGeom& g, long M, long K) {
+  return !(g.bias || g.relu) && ((M + 63) / 64) * ((g.n_out + 63) / 64) <= 256 && K >= 256;
+}
 // The parts of a strided data gradient in one launch, where that is the faster way (a function of the shapes only).
 bool conv_igemm_x3_parts_takes(const ConvGeom* parts, int n);
 hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, LaunchProbe* probe);
@@ -126,7 +133,7 @@ hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, Lau
 bool conv_smallc_takes(const ConvGeom& g, long M);
 hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe);
 enum { V_IGEMM_FAST = 0, V_IGEMM_GENERIC, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16,
-       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD, V_COUNT };
+       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD, V_IGEMM_DIRECT_2G, V_COUNT };
 const char* conv_variant_name(int v);
 
 // dw[co][(r,t,ci)] = sum_{img,p,q} dy[img,p,q,co] * x[img, p*stride+r-pad, q*stride+t-pad, ci]

@@ -43,3 +43,30 @@ def test_bf16_weight_gradient_gathers():
     assert kernel("wgrad", 1, 4096, 4, 8, 8, 3, 1, 1, BF16) == "wgrad_bf16 near"
     assert kernel("wgrad", 1, 4097, 4, 8, 8, 3, 1, 1, BF16) == "wgrad_bf16 far"
     assert kernel("wgrad", 1, 4, 4097, 8, 8, 3, 1, 1, BF16) == "wgrad_bf16 far"
+
+
+def test_fp32_layers_reach_the_kernels_their_parity_tests_name():
+    from test_gpu_x3 import CASES
+    for n, h, w, cin, cout, r, stride, fwd, dgrad in CASES:
+        shape = (n, h, w, cin, cout, r, stride, r // 2, F32)
+        assert (kernel("fwd", *shape), kernel("dgrad", *shape)) == (fwd, dgrad), shape
+
+
+# fp32: launches too small for the split products to pay, or bound by the result they write, stay with the fp32 instruction
+@pytest.mark.parametrize("shape,name", [
+    ((4, 56, 56, 256, 64, 1, 1, 0, F32), "igemm direct 64x64, two groups"),
+    ((1, 128, 129, 256, 64, 1, 1, 0, F32), "igemm direct 64x64"),          # 258 tiles
+    ((2, 8, 8, 224, 64, 1, 1, 0, F32), "igemm direct 64x64"),              # seven chunks of K: too short for two groups
+    ((128, 56, 56, 64, 256, 1, 1, 0, F32), "igemm direct 64x64"),          # 411 MB of result, K of 64
+    ((41, 14, 14, 256, 256, 3, 1, 1, F32), "igemm_x3_deep window 128x64"),
+    ((32, 56, 56, 64, 256, 1, 1, 0, F32), "igemm_x3 64x64"),
+    ((2, 9, 7, 288, 40, 1, 1, 0, F32), "igemm direct 64x64, two groups"),
+    ((41, 14, 14, 100, 256, 3, 1, 1, F32), "igemm generic 64x64"),         # channels not in 16s, r > 1
+])
+def test_fp32_forward(shape, name):
+    assert kernel("fwd", *shape) == name
+
+
+def test_fp32_strided_data_gradients_reach_the_kernels_their_parity_tests_name():
+    from test_gpu_strided_dgrad import CASES, KERNELS
+    assert [kernel("dgrad", *c, F32) for c in CASES] == KERNELS

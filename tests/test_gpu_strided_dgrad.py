@@ -8,12 +8,18 @@ pytestmark = pytest.mark.gpu
 CASES = [  # n, h, w, cin, cout, r, stride, pad
     (3, 7, 8, 48, 32, 3, 2, 1),         # one launch; four positions a row: a division per row
     (5, 13, 11, 80, 48, 3, 2, 1),       # one launch; rows of six and five, ragged tiles both ways
-    (96, 28, 27, 192, 256, 3, 2, 1),    # one launch, 128-wide tiles
+    (96, 28, 27, 192, 256, 3, 2, 1),    # one launch, 64-wide tiles, many of them
+    (45, 55, 54, 116, 112, 3, 2, 1),    # one launch, 128-wide tiles, ragged both ways
     (64, 14, 13, 960, 960, 3, 2, 1),    # long reductions: the parts on their own
     (4, 13, 14, 32, 32, 5, 3, 2),       # nine parts
     (2, 10, 9, 16, 32, 2, 3, 0),        # four parts, five classes of positions without a tap
     (4, 9, 9, 32, 20, 3, 2, 1),         # reductions that are not whole steps of 16: the per-element kernel
 ]
+
+
+# the kernel of the fp32 calls (of the first part, where the parts run one by one)
+KERNELS = ["igemm_x3_parts 64x64", "igemm_x3_parts 64x64", "igemm_x3_parts 64x64", "igemm_x3_parts 128x128", "igemm_x3_deep 128x128",
+           "igemm_x3 64x64", "igemm_x3_parts 64x64", "igemm_x3 64x64"]
 
 
 @pytest.mark.parametrize("accumulate", [False, True])

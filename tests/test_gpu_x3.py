@@ -1,4 +1,4 @@
-"""GPU parity of the fp32 convolutions on the bf16 matrix cores (every value split into three bf16 parts) at the
+"""GPU parity of the fp32 convolutions on the bf16 matrix cores (every value split into three bf16 parts, see split3.h) at the
 sizes where their kernels can go wrong: ragged row and column tiles, reductions that deal unevenly to the groups
 of waves, windows of the largest width, one-chunk reductions; and values the split cannot represent.
 
@@ -14,27 +14,37 @@ from test_gpu_ops import B, close, dev, nchw, nhwc, ohwi, rnd
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # n, h, w, cin, cout, r, stride: which kernel the launcher picks
-    (41, 14, 14, 144, 1000, 1, 1),    # 128 x 128 tiles, ragged rows and columns, nine steps
-    (13, 31, 30, 112, 264, 1, 1),     # 64 x 64 tiles, seven steps
-    (7, 9, 9, 16, 24, 1, 1),          # a single step
-    (5, 61, 62, 64, 136, 3, 1),       # window of the largest width (61 x 62 map: 254 of 256 rows)
-    (23, 14, 14, 336, 260, 3, 1),     # window, 189 steps over four groups (48 + 47 + 47 + 47)
-    (30, 14, 14, 528, 136, 1, 1),     # 128 x 64 tiles, four groups of waves, 33 steps
-    (20, 28, 28, 272, 250, 1, 1),     # 128 x 128 tiles, two groups, 17 steps
-    (3, 62, 64, 64, 136, 3, 1),       # 3x3 on a map too wide for the window
-    (9, 31, 29, 80, 72, 3, 1),        # 64 x 64 tiles, eight groups of one wave, 45 steps
-    (6, 15, 17, 48, 40, 3, 2),        # strided: forward gathers, data gradient in four parts
-    (2, 11, 10, 16, 20, 5, 1),        # 5x5 taps, one window
-    (41, 1, 1, 516, 1000, 1, 1),      # fully connected: both reductions end inside a step (516 = 32 * 16 + 4, 1000 = 62 * 16 + 8)
-    (9, 12, 11, 20, 260, 1, 1),       # the same with 64 x 64 tiles
-    (64, 14, 14, 148, 620, 1, 1),     # and with 128 x 128 tiles
+X128, X64, D2x1, D2x2, D1x1 = "igemm_x3 128x128", "igemm_x3 64x64", "igemm_x3_deep 128x64", "igemm_x3_deep 128x128", "igemm_x3_deep 64x64"
+WINDOW, PARTS, GENERIC = "igemm_x3_deep window 128x64", "igemm_x3_parts 64x64", "igemm generic 64x64"
+DIRECT, DIRECT2 = "igemm direct 64x64", "igemm direct 64x64, two groups"
+# n, h, w, cin, cout, r, stride, the kernels of the forward pass and of the data gradient (test_conv_routes.py holds them to it)
+CASES = [
+    (41, 14, 14, 144, 1000, 1, 1, X128, D2x1),     # ragged rows and columns, nine steps
+    (13, 31, 30, 112, 264, 1, 1, X64, X64),        # seven steps
+    (7, 9, 9, 16, 24, 1, 1, X64, X64),             # a single step
+    (5, 61, 62, 64, 144, 3, 1, WINDOW, WINDOW),    # window of the largest width (61 x 62 map: 254 of 256 rows)
+    (23, 14, 14, 336, 272, 3, 1, WINDOW, WINDOW),  # window, 189 steps over four groups (48 + 47 + 47 + 47)
+    (30, 14, 14, 528, 136, 1, 1, D2x1, D2x2),      # four groups of waves, 33 steps
+    (20, 28, 28, 272, 250, 1, 1, D2x2, GENERIC),   # two groups of waves, 17 steps
+    (3, 62, 64, 64, 144, 3, 1, D2x2, D1x1),        # 3x3 on a map too wide for the window
+    (9, 31, 29, 80, 80, 3, 1, D1x1, D1x1),         # eight groups of one wave, 45 steps
+    (6, 15, 17, 48, 48, 3, 2, D1x1, PARTS),        # strided: forward gathers, data gradient in four parts
+    (2, 11, 10, 16, 48, 5, 1, D1x1, D1x1),         # 5x5 taps
+    (41, 1, 1, 516, 1000, 1, 1, D1x1, D1x1),       # fully connected: both reductions end inside a step (516 = 32 * 16 + 4, 1000 = 62 * 16 + 8)
+    (9, 12, 11, 20, 260, 1, 1, X64, D1x1),         # the same with 64 x 64 tiles
+    (64, 14, 14, 148, 620, 1, 1, X128, D2x2),      # and with 128 x 128 tiles
+    (60, 28, 27, 144, 272, 3, 2, D2x1, PARTS),     # strided gather in four groups of waves
+    (11, 20, 20, 272, 144, 3, 1, D1x1, WINDOW),
+    # launches that stay with the fp32 instruction
+    (2, 56, 55, 256, 72, 1, 1, DIRECT2, X64),      # ragged rows and columns, two groups of waves
+    (13, 40, 40, 96, 64, 1, 1, DIRECT, DIRECT),
+    (1, 9, 9, 64, 64, 3, 1, DIRECT2, DIRECT2),
 ]
 
 
 @pytest.mark.parametrize("case", CASES)
 def test_split_conv(case):
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     pad = r // 2
     x = rnd(1, n, cin, h, w)
     wt = rnd(2, cout, cin, r, r) * np.float32(np.sqrt(2.0 / (cin * r * r)))
@@ -45,15 +55,22 @@ def test_split_conv(case):
     close(nchw(y.cpu().numpy()), ref, f"conv_fwd {case}", 2e-6 * 4)
     err = np.linalg.norm(nchw(y.cpu().numpy()).astype(np.float64) - ref) / np.linalg.norm(ref.astype(np.float64))
     assert err <= 2e-6, err
-    if cout % (4 if r == 1 else 16):
-        return      # the data gradient reduces over cout
-    dy = rnd(3, *ref.shape)
-    refd = O.conv_dgrad(dy, wt, x.shape, stride, pad)
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("case", CASES)
+def test_split_dgrad(case, accumulate):
+    n, h, w, cin, cout, r, stride = case[:7]
+    pad = r // 2
+    wt = rnd(2, cout, cin, r, r) * np.float32(np.sqrt(2.0 / (cin * r * r)))
+    dy = rnd(3, n, cout, O.out_dim(h, r, stride, pad), O.out_dim(w, r, stride, pad))
+    base = rnd(4, n, cin, h, w) if accumulate else np.zeros((n, cin, h, w), np.float32)
+    refd = O.conv_dgrad(dy, wt, (n, cin, h, w), stride, pad).astype(np.float64) + base
     ws = torch.empty(max(B().op_conv_workspace(n, h, w, cin, cout, r, stride, pad), 256), dtype=torch.uint8, device="cuda")
-    dx = torch.full((n, h, w, cin), float("nan"), device="cuda")
-    B().op_conv_dgrad(dev(nhwc(dy)), dev(ohwi(wt)), dx, stride, pad, ws)
+    dx = dev(nhwc(base)) if accumulate else torch.full((n, h, w, cin), float("nan"), device="cuda")
+    B().op_conv_dgrad(dev(nhwc(dy)), dev(ohwi(wt)), dx, stride, pad, ws, accumulate)
     torch.cuda.synchronize()
-    err = np.linalg.norm(nchw(dx.cpu().numpy()).astype(np.float64) - refd) / np.linalg.norm(refd.astype(np.float64))
+    err = np.linalg.norm(nchw(dx.cpu().numpy()).astype(np.float64) - refd) / np.linalg.norm(refd)
     assert err <= 2e-6, err
 
 
@@ -61,7 +78,7 @@ def test_split_conv(case):
 def test_split_conv_keeps_infinities_nan_and_the_largest_values(case):
     """As the fp32 instruction: an infinity times a nonzero weight is an infinity (also where a part of the weight
     is zero), a NaN stays in the outputs that read it, values next to the largest finite one do not overflow."""
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     pad = r // 2
     x = rnd(1, n, cin, h, w)
     wt = rnd(2, cout, cin, r, r) * np.float32(np.sqrt(2.0 / (cin * r * r)))
@@ -149,7 +166,7 @@ TINY = [(-116, 90), (-124, 100), (-140, 110), (90, -116), (100, -130), (-50, -60
 @pytest.mark.parametrize("scales", TINY)
 @pytest.mark.parametrize("case", [CASES[i] for i in (0, 1, 4, 5, 6, 8, 9)])
 def test_split_conv_tiny_operands(case, scales):
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     n, pad = min(n, 12), r // 2
     x = torch.ldexp(torch.from_numpy(rnd(1, n, cin, h, w)).double(), torch.tensor(scales[0])).float()
     wt = torch.ldexp(torch.from_numpy(rnd(2, cout, cin, r, r)).double() * (2.0 / (cin * r * r)) ** 0.5, torch.tensor(scales[1])).float()
