@@ -3,8 +3,8 @@
 //   dw[co][j] = sum_m dy[m][co] * X[m][j],   m = (img,p,q),  j = (r,t,ci), ci fastest,
 //   X[m][j] = x[img, p*stride+r-pad, q*stride+t-pad, ci]  (zero in the padding)
 //
-// fp32 storage runs in conv_wgrad_x3.hip where its channel counts allow and the reduction is long enough; here are
-// the kernel for bf16 storage and one for the rest (the 3-channel stem, short reductions, odd channel counts).  In the
+// fp32 storage runs in conv_wgrad_x3.hip where its channel counts allow and the layer is large enough; here are
+// the kernel for bf16 storage and one for the rest (small layers, the 3-channel stem, odd channel counts).  In the
 // latter both operands are read along their contiguous channel axis and staged in LDS as [m][channel]; the fp32 MFMA
 // (v_mfma_f32_32x32x2_f32) takes k = m.  A workgroup of 4 waves owns a 64 x 64 tile of dw; the m range is cut into
 // `splits` equal parts; each part writes its own partial tile and the parts are added in a fixed order, so the result is
@@ -68,15 +68,22 @@ __device__ __forceinline__ int gather_pixel(const WgradGeom& g, int m, int kr, i
   return (img * g.h + iy) * g.wd + ix;
 }
 
-// L_FAST: cin % 64 == 0 (a tile's columns lie inside one tap), cout % 4 == 0, byte offsets below 2^32.
-enum { L_GENERIC = 0, L_FAST = 1 };
+// L_FAST, L_DIRECT: cin % 64 == 0 (a tile's columns lie inside one tap), cout % 4 == 0, byte
+// offsets below 2^32.  L_DIRECT (fp32 storage only: bf16 operands are widened on their way
+// into LDS, which needs the registers) moves the chunks from global memory straight into LDS
+// (buffer_load_dwordx4 ... lds: a wave fills four 256-byte rows), rows beyond the range,
+// padded taps and columns beyond cout as offsets outside the buffer descriptor, which read as
+// zero.  Rows are unpadded; odd rows hold their two 128-byte halves swapped (the lane fetches
+// the half that belongs into its slot), so that the two rows one MFMA operand is read from
+// lie on different banks.  Two LDS stages, as in the forward kernel's direct loader.
+enum { L_GENERIC = 0, L_FAST = 1, L_DIRECT = 2 };
 
 template <int LOADER, class T>
 __global__ __launch_bounds__(256) void wgrad_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles,
                                                      int splits, int chunks_per_split, float* out,
                                                      size_t split_stride, int main_grid) {
-  constexpr bool FAST = LOADER == L_FAST;
-  constexpr int PITCH = LDT;
+  constexpr bool FAST = LOADER == L_FAST, DIRECT = LOADER == L_DIRECT;
+  constexpr int PITCH = DIRECT ? 64 : LDT;
   __shared__ __attribute__((aligned(256))) float As[2 * BKM * PITCH];
   __shared__ __attribute__((aligned(256))) float Bs[2 * BKM * PITCH];
 
@@ -182,7 +189,142 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradGeom g, int Mrows, int 
     }
   };
 
-  if constexpr (FAST) {
+  if constexpr (DIRECT) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(!DIRECT || sizeof(T) == 4, "the direct loader copies raw fp32 rows");
+    // lane -> LDS slot: row tid/16 (+16 on the second pass), 16-byte column tid%16; the slot of
+    // an odd row holds the column of the other half
+    const int row = tid >> 4;
+    const int col4 = (tid & 15) ^ ((row & 1) << 3);
+    const int tap = j0 / g.cin, ci0 = j0 - tap * g.cin;
+    const int kr = tap / g.s, kt = tap - kr * g.s;
+    const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0;
+    const bool a_col_ok = co0 + col4 * 4 < g.cout;
+    constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
+    uint32_t a_lane[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a_lane[i] = (uint32_t)(row + 16 * i) * (uint32_t)(g.cout * 4) + (uint32_t)(co0 + col4 * 4) * 4;
+    const uint32_t b_lane = (uint32_t)(ci0 + col4 * 4) * 4;
+    int r_org[2] = {0, 0}, r_p[2] = {0, 0}, r_q[2] = {0, 0};
+    const float inv_q = 1.0f / (float)g.q, inv_p = 1.0f / (float)g.p;
+    if (!plain) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int m = chunk_lo * BKM + row + 16 * i;
+        const int pq = g.p * g.q;
+        const int img = m / pq, rem = m - img * pq;
+        r_p[i] = rem / g.q;
+        r_q[i] = rem - r_p[i] * g.q;
+        r_org[i] = img * g.h * g.wd;
+      }
+    }
+    __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void*>(g.dy), 0, (int)(uint32_t)((size_t)Mrows * g.cout * 4), 0x00020000);
+    __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void*>(g.x), 0, (int)(uint32_t)((size_t)g.n_img * g.h * g.wd * g.cin * 4), 0x00020000);
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    const uint32_t lds_a = (uint32_t)(size_t)As + uwave * 1024, lds_b = (uint32_t)(size_t)Bs + uwave * 1024;
+    // loads of chunk kc (relative to chunk_lo) into stage buf; chunks are issued in order, so the
+    // gathered position advances by BKM rows per call without any division
+    auto issue = [&](int kc, int buf) {
+      const int mbase = (chunk_lo + kc) * BKM;
+      const int soff_a = (int)((uint32_t)mbase * (uint32_t)(g.cout * 4));   // below 2^32 (launcher)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int m = mbase + row + 16 * i;
+        const bool mok = m < Mrows;
+        const uint32_t va = (mok && a_col_ok) ? a_lane[i] : OUTSIDE;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(lds_a + buf * (BKM * 256) + i * (16 * 256)), 16, va,
+                                                 soff_a, 0, 0);
+        int pix = m;
+        if (!plain) {
+          const int iy = r_p[i] * g.stride + kr - g.pad, ix = r_q[i] * g.stride + kt - g.pad;
+          pix = ((unsigned)iy < (unsigned)g.h && (unsigned)ix < (unsigned)g.wd) ? r_org[i] + iy * g.wd + ix : -1;
+          // 32 positions on, without a loop that runs differently in every lane: the number of
+          // rows and of images passed are small quotients, exact in float with the half added
+          const int xq = r_q[i] + BKM;
+          const int wq = (int)(((float)xq + 0.5f) * inv_q);
+          r_q[i] = xq - wq * g.q;
+          const int xp = r_p[i] + wq;
+          const int wp = (int)(((float)xp + 0.5f) * inv_p);
+          r_p[i] = xp - wp * g.p;
+          r_org[i] += wp * (g.h * g.wd);
+        }
+        const uint32_t vb = (mok && pix >= 0) ? (uint32_t)pix * (uint32_t)(g.cin * 4) + b_lane : OUTSIDE;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(size_t)(lds_b + buf * (BKM * 256) + i * (16 * 256)), 16, vb,
+                                                 0, 0, 0);
+      }
+    };
+    // operand of MFMA step kk: lanes 0-31 row kk (even), lanes 32-63 row kk+1 (odd: halves swapped)
+    const int half = lane >> 5;
+    const float* a_rd = As + half * 64 + ((wm0 + (lane & 31)) ^ (half << 5));
+    const float* b_rd = Bs + half * 64 + ((wn0 + (lane & 31)) ^ (half << 5));
+    // Groups of four MFMAs (eight rows of the chunk): the operands of group g + 1 are read between the MFMAs
+    // of group g, and the last group's MFMAs are held back (pa, pb) until the next chunk's barrier has been
+    // passed and its first reads are on their way.  Same order of additions.
+    constexpr int NG = BKM / 8;
+    float pa[4] = {0.f, 0.f, 0.f, 0.f}, pb[4] = {0.f, 0.f, 0.f, 0.f};
+    auto mm4 = [&](const float (&a)[4], const float (&b)[4], int half) {
+      if (half != 1) {
+        acc = mfma32x32x2(a[0], b[0], acc);
+        acc = mfma32x32x2(a[1], b[1], acc);
+      }
+      if (half != 0) {
+        acc = mfma32x32x2(a[2], b[2], acc);
+        acc = mfma32x32x2(a[3], b[3], acc);
+      }
+    };
+    auto compute_direct = [&](int buf, bool prev) {
+      const float* as = a_rd + buf * (BKM * 64);
+      const float* bs = b_rd + buf * (BKM * 64);
+      float af[NG][4], bf[NG][4];
+      auto rd = [&](int g) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          af[g][u] = as[(g * 8 + u * 2) * 64];
+          bf[g][u] = bs[(g * 8 + u * 2) * 64];
+        }
+      };
+      rd(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (prev) mm4(pa, pb, 2);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 0; g + 1 < NG; ++g) {
+        mm4(af[g], bf[g], 0);
+        __builtin_amdgcn_sched_barrier(0);
+        rd(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mm4(af[g], bf[g], 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { pa[u] = af[NG - 1][u]; pb[u] = bf[NG - 1][u]; }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (n_chunks > 0) {
+      issue(0, 0);
+      int kc = 0;
+      for (; kc + 2 <= n_chunks; kc += 2) {     // whole pairs of chunks: stage 0, then stage 1
+        __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wave's part of chunk kc is in LDS
+        __syncthreads();                        // everybody's is, and chunk kc-1 has been read by all
+        issue(kc + 1, 1);
+        compute_direct(0, kc > 0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (kc + 2 < n_chunks) issue(kc + 2, 0);
+        compute_direct(1, true);
+      }
+      if (kc < n_chunks) {                      // an odd number of chunks: the last one sits in stage 0
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        compute_direct(0, kc > 0);
+      }
+      mm4(pa, pb, 2);
+    }
+#endif
+  } else if constexpr (FAST) {
     // 16 float4 per 64-wide row, 16 rows per pass, 2 passes per operand and chunk
     const int col4 = tid & 15, row = tid >> 4;
     const int tap = j0 / g.cin, ci0 = j0 - tap * g.cin;
@@ -590,13 +732,6 @@ struct WgradCfg {
 // bf16 storage on the bf16 matrix cores: channel counts the 128 x 128 tile of wgrad_bf16_kernel takes
 inline bool bf16_mfma_shape(int dtype, int cin, int cout) { return dtype == DT_BF16 && cin % 8 == 0 && cout % 8 == 0; }
 
-// fp32 storage: channel counts whose groups of four lie inside one filter tap, and more than ten steps of 16 positions
-// (the fully connected layer at minibatch 41, three steps: 10.5 us there, 7.7 here, where 512 small workgroups share
-// the chip and there are no sums to exchange)
-inline bool x3_shape(int dtype, long rows, int cin, int cout) {
-  return dtype == DT_F32 && cin % 4 == 0 && cout % 4 == 0 && rows > 160;
-}
-
 WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   WgradCfg c;
   const long J = (long)r * s * cin;
@@ -620,7 +755,7 @@ WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   c.tiles_j = (int)((J + BN - 1) / BN);
   const long tiles = (long)c.tiles_co * c.tiles_j;
   const long chunks = (Mrows + BKM - 1) / BKM;
-  // What is left here is small (at most 160 positions) or has channels the matrix-core kernels don't take.  One round of
+  // What is left here is small or has channels the matrix-core kernels don't take.  One round of
   // workgroups, at least 8 chunks of 32 rows each: three per CU, or two where whole groups of 64 channels meet few positions
   // (512 / 768 / 1024 / 1280 workgroups on the 3x3 layers at minibatch 41: 86 / 96 / 99 / 88 TFLOP/s, and beside a data
   // gradient two per CU leave that the larger share).
@@ -635,6 +770,29 @@ WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   return c;
 }
 
+// fp32 storage: whether the kernel on the bf16 matrix cores takes a shape.  Channel counts whose groups of four lie inside one
+// filter tap, and more than ten steps of 16 positions (the fully connected layer at minibatch 41, three steps: 10.5 us there, 7.7
+// here, where 512 small workgroups share the chip and there are no sums to exchange).  Where the direct kernel takes the shape
+// too, the one with the smaller predicted time: small layers are the fp32 instruction's (256->64 at 56x56, 1 image 11.8 us
+// against 13.0; 512->512 3x3 at 7x7, 2 images 12.4 against 14.5; from 400 million products on, almost none).  The constants are
+// fitted to 440 measured shapes (the layers of the ResNets at minibatches 1 to 64 and random ones): median errors of
+// 4-5 %, the choice within 0.3 % of the better one on average, 15 % at most.
+inline bool x3_shape(int dtype, long rows, int cin, int cout, int r, int s) {
+  if (dtype != DT_F32 || cin % 4 != 0 || cout % 4 != 0 || rows <= 160) return false;
+  if (cin % 64 != 0) return true;              // the other kernel is the per-element one
+  const double mb = (double)cout * r * s * cin * 4e-6;
+  auto rounds = [](long workgroups) { return (double)((workgroups + 255) / 256); };
+  auto sums = [&](int splits, double base, double per_mb) { return splits > 1 ? base + per_mb * 2 * splits * mb : 0.0; };   // written and read once
+  const WgradCfg c = choose(rows, cin, cout, r, s, dtype);
+  const double busy = rounds((long)c.tiles_co * c.tiles_j * c.splits) * (0.27 + 0.594 * c.chunks_per_split);
+  const double direct = 3.9 + (busy > 3.9 ? busy : 3.9) + sums(c.splits, 2.4, 0.22);
+  const WgradX3Cfg x = wgrad_x3_choose(rows, cin, cout, r, s);
+  const int groups = 8 / (x.wt * x.wt), steps = (x.steps_per_split + groups - 1) / groups;
+  const double x3 = 6.2 + rounds((long)x.tiles_co * x.tiles_j * x.splits) * (x.wt == 2 ? 2.47 + 1.22 * steps : 2.0 * steps - 0.86) +
+                    sums(x.splits, 2.9, 0.27);
+  return x3 < direct;
+}
+
 }  // namespace
 
 size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, int s, int dtype) {
@@ -645,7 +803,7 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
   }
   const long rows = (long)n_img * p * q;
   int splits = choose(rows, cin, cout, r, s, dtype).splits;
-  if (x3_shape(dtype, rows, cin, cout)) {
+  if (x3_shape(dtype, rows, cin, cout, r, s)) {
     // never less than the other kernel's parts: it runs where the operands leave the 32-bit ranges, and a size that grows
     // with the minibatch the way it does keeps plans under a budget as they were
     const int sx = wgrad_x3_choose(rows, cin, cout, r, s).splits;
@@ -677,12 +835,13 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
     return hipErrorInvalidValue;
   if (g.dtype != DT_F32 && g.dtype != DT_BF16) return hipErrorInvalidValue;
   const WgradCfg c = choose(Mrows, g.cin, g.cout, g.r, g.s, g.dtype);
-  // fp32 storage on the bf16 matrix cores: both operands inside 32-bit buffer ranges (the last bytes stay free for
+  // fp32 storage, the kernels with 16-byte loads: both operands inside 32-bit buffer ranges (the last bytes stay free for
   // the offset that stands for "outside") and 16-byte aligned; p, q <= 4096: the range over which the loader's float
   // quotients are exact
-  const bool x3 = x3_shape(g.dtype, Mrows, g.cin, g.cout) && g.p <= 4096 && g.q <= 4096 && Mrows * g.cout * 4 <= 0xFFFFFF00L &&
-                  (long)g.n_img * g.h * g.wd * g.cin * 4 <= 0xFFFFFF00L &&
-                  (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
+  const bool in_range = g.dtype == DT_F32 && g.p <= 4096 && g.q <= 4096 && Mrows * g.cout * 4 <= 0xFFFFFF00L &&
+                        (long)g.n_img * g.h * g.wd * g.cin * 4 <= 0xFFFFFF00L &&
+                        (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
+  const bool x3 = in_range && x3_shape(g.dtype, Mrows, g.cin, g.cout, g.r, g.s);
   const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s) : WgradX3Cfg{};
   const bool small = !x3 && conv_wgrad_smallc_takes(g);
   const int splits = x3 ? cx.splits : small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s, g.dtype) : c.splits;
@@ -692,6 +851,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   const long es = (long)dt_size(g.dtype);
   const bool fast = (g.cout % 4 == 0) && (g.cin % 64 == 0) && Mrows * g.cout * es < (1L << 32) &&
                     (long)g.n_img * g.h * g.wd * g.cin * es < (1L << 32);
+  const bool direct = fast && in_range;        // fp32 storage
   float* out = splits > 1 ? g.workspace : g.dw;
   const size_t count = (size_t)g.cout * J;
   const int main_grid = (int)((work + 7) / 8 * 8);
@@ -713,9 +873,9 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
     return hipErrorInvalidValue;   // (the split count, and with it the workspace, was sized for this kernel)
   if (probe) {
-    probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
+    probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : direct ? V_WGRAD_DIRECT : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
     probe->kernel = small ? "smallc" : mfma16 ? (gather == G_PLAIN ? "wgrad_bf16 plain" : gather == G_NEAR ? "wgrad_bf16 near" : "wgrad_bf16 far")
-                    : x3 ? (cx.wt == 2 ? "wgrad_x3 128x128" : "wgrad_x3 64x64") : fast ? "wgrad fast 64x64" : "wgrad generic 64x64";
+                    : x3 ? (cx.wt == 2 ? "wgrad_x3 128x128" : "wgrad_x3 64x64") : direct ? "wgrad direct 64x64" : fast ? "wgrad fast 64x64" : "wgrad generic 64x64";
     if (probe->dry) return hipSuccess;
   }
   if (probe && probe->before) (void)hipEventRecord(probe->before, st);
@@ -726,6 +886,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
     e = conv_wgrad_smallc(g, splits, out, count, st);
   } else if (g.dtype == DT_F32) {
     if (x3) e = conv_wgrad_x3(g, cx, (int)Mrows, (int)J, out, count, st);
+    else if (direct) ACC_WGRAD_LAUNCH(L_DIRECT, float);
     else if (fast) ACC_WGRAD_LAUNCH(L_FAST, float);
     else ACC_WGRAD_LAUNCH(L_GENERIC, float);
   } else if (mfma16) {

@@ -46,7 +46,9 @@ def test_bf16_weight_gradient_gathers():
 
 
 def test_fp32_layers_reach_the_kernels_their_parity_tests_name():
-    from test_gpu_x3 import CASES
+    from test_gpu_x3 import CASES, WGRAD_CASES
+    for n, h, w, cin, cout, r, stride, name in WGRAD_CASES:
+        assert kernel("wgrad", n, h, w, cin, cout, r, stride, r // 2, F32) == name, (n, h, w, cin, cout)
     for n, h, w, cin, cout, r, stride, fwd, dgrad in CASES:
         shape = (n, h, w, cin, cout, r, stride, r // 2, F32)
         assert (kernel("fwd", *shape), kernel("dgrad", *shape)) == (fwd, dgrad), shape
@@ -70,3 +72,15 @@ def test_fp32_forward(shape, name):
 def test_fp32_strided_data_gradients_reach_the_kernels_their_parity_tests_name():
     from test_gpu_strided_dgrad import CASES, KERNELS
     assert [kernel("dgrad", *c, F32) for c in CASES] == KERNELS
+
+
+# fp32 weight gradients: small layers stay with the fp32 instruction where its kernel takes the shape
+@pytest.mark.parametrize("shape,name", [
+    ((1, 56, 56, 256, 64, 1, 1, 0, F32), "wgrad direct 64x64"),
+    ((2, 7, 7, 512, 512, 3, 1, 1, F32), "wgrad direct 64x64"),
+    ((41, 14, 14, 256, 256, 3, 1, 1, F32), "wgrad_x3 128x128"),
+    ((41, 1, 1, 2048, 1000, 1, 1, 0, F32), "wgrad direct 64x64"),          # 41 positions
+    ((1, 5000, 3, 64, 64, 3, 1, 1, F32), "wgrad fast 64x64"),              # rows beyond the float quotients
+])
+def test_fp32_weight_gradient(shape, name):
+    assert kernel("wgrad", *shape) == name

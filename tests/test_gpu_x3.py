@@ -102,20 +102,28 @@ def test_split_conv_keeps_infinities_nan_and_the_largest_values(case):
     assert (np.abs(got[ok] - ref[ok]) / scale).max() <= 1e-4
 
 
-WGRAD_CASES = [  # n, h, w, cin, cout, r, stride
-    (9, 13, 11, 132, 260, 1, 1),      # ragged tiles of 128 x 128
-    (7, 14, 14, 36, 44, 3, 1),        # channels that fill no block, taps that change inside one
-    (2, 9, 9, 64, 64, 1, 1),          # 162 positions: the fewest this kernel takes
-    (5, 21, 3, 32, 40, 3, 1),         # rows of three positions: several wraps inside a thread's four
-    (11, 2, 20, 32, 32, 3, 1),        # images of two rows
-    (6, 31, 29, 48, 20, 3, 2),        # strided gather
-    (4, 28, 28, 64, 256, 1, 2),       # strided 1x1
-    (23, 14, 14, 256, 256, 3, 1),     # several parts, a ragged last step
+WX64, WX128, WDIRECT = "wgrad_x3 64x64", "wgrad_x3 128x128", "wgrad direct 64x64"
+WGRAD_CASES = [  # n, h, w, cin, cout, r, stride, kernel
+    (9, 13, 11, 132, 260, 1, 1, WX64),       # ragged tiles
+    (7, 14, 14, 36, 44, 3, 1, WX64),         # channels that fill no block, taps that change inside one
+    (2, 9, 9, 60, 64, 1, 1, WX64),           # 162 positions: the fewest this kernel takes
+    (5, 21, 3, 32, 40, 3, 1, WX64),          # rows of three positions: several wraps inside a thread's four
+    (11, 2, 20, 32, 32, 3, 1, WX64),         # images of two rows
+    (6, 31, 29, 48, 20, 3, 2, WX64),         # strided gather
+    (60, 28, 28, 68, 260, 1, 2, WX64),       # strided 1x1
+    (23, 14, 14, 256, 256, 3, 1, WX128),     # several parts, a ragged last step
+    (64, 28, 27, 260, 268, 1, 1, WX128),     # ragged 128 x 128 tiles
+    (30, 27, 29, 132, 260, 3, 2, WX128),     # the same, strided, channels that fill no block
+    # small layers that stay with the fp32 instruction
+    (2, 9, 9, 64, 64, 1, 1, WDIRECT),
+    (9, 21, 3, 64, 44, 3, 1, WDIRECT),       # rows of three positions
+    (3, 28, 27, 64, 252, 1, 2, WDIRECT),     # strided
+    (2, 31, 29, 128, 68, 3, 2, WDIRECT),
 ]
 
 
 def wgrad(case, x, dy):
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     ws = torch.empty(max(B().op_conv_workspace(n, h, w, cin, cout, r, stride, r // 2), 256), dtype=torch.uint8, device="cuda")
     dw = torch.full((cout, r, r, cin), float("nan"), device="cuda")
     B().op_conv_wgrad(dev(nhwc(x)), dev(nhwc(dy)), dw, stride, r // 2, ws)
@@ -125,7 +133,7 @@ def wgrad(case, x, dy):
 
 @pytest.mark.parametrize("case", WGRAD_CASES)
 def test_split_wgrad(case):
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     x = rnd(1, n, cin, h, w)
     dy = rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2))
     ref = O.conv_wgrad(x, dy, (cout, cin, r, r), stride, r // 2).astype(np.float64)
@@ -136,7 +144,7 @@ def test_split_wgrad(case):
 
 @pytest.mark.parametrize("case", [WGRAD_CASES[i] for i in (0, 1, 7)])
 def test_split_wgrad_keeps_infinities_nan_and_the_largest_values(case):
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     x = rnd(1, n, cin, h, w)
     dy = rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2))
     dy[0, 5] = 0.25                                   # exact in one bf16
@@ -181,7 +189,7 @@ def test_split_conv_tiny_operands(case, scales):
 @pytest.mark.parametrize("scales", TINY)
 @pytest.mark.parametrize("case", [WGRAD_CASES[i] for i in (0, 1, 7)])
 def test_split_wgrad_tiny_operands(case, scales):
-    n, h, w, cin, cout, r, stride = case
+    n, h, w, cin, cout, r, stride = case[:7]
     x = np.ldexp(rnd(1, n, cin, h, w).astype(np.float64), scales[0]).astype(np.float32)
     dy = np.ldexp(rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2)).astype(np.float64), scales[1]).astype(np.float32)
     cols = torch.nn.functional.unfold(torch.from_numpy(x).double(), r, padding=r // 2, stride=stride)
