@@ -545,7 +545,7 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   if ((int)blockIdx.x >= main_grid) {
     static_assert(D::LDS >= kWideScratch, "side jobs");
     const int id = (int)blockIdx.x - main_grid, sums = (int)wide_reduce_blocks(g.side.count);
-    if (id < sums) reduce_wide(g.side, id, lds);
+    if (id < sums) reduce_wide(g.side, id);
     else flip_wide(g.flip, id - sums, lds);
     return;
   }

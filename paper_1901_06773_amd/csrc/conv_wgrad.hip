@@ -14,6 +14,7 @@
 
 #include "kernels.h"
 #include "dtype.h"
+#include "parts_sum.h"
 #include "wgrad_side.h"
 
 namespace acc {
@@ -692,36 +693,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mro
 #endif
 }
 
-// dw[i] = part[0][i] + part[1][i] + ... in that order
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, float* dw, size_t count,
-                                                             int splits) {
-  const size_t i4 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i4 >= count) return;
-  if (i4 + 4 <= count && (count & 3) == 0) {
-    float4 s = *reinterpret_cast<const float4*>(part + i4);
-    // eight parts fetched at a time, added in their order: with hundreds of parts (the stem's
-    // weight gradient) one load waiting for the sum before it made this a chain of latencies
-    int k = 1;
-    for (; k + 8 <= splits; k += 8) {
-      float4 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(part + (size_t)(k + u) * count + i4);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
-    }
-    for (; k < splits; ++k) {
-      const float4 v = *reinterpret_cast<const float4*>(part + (size_t)k * count + i4);
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-    }
-    *reinterpret_cast<float4*>(dw + i4) = s;
-  } else {
-    for (size_t i = i4; i < count && i < i4 + 4; ++i) {
-      float s = part[i];
-      for (int k = 1; k < splits; ++k) s += part[(size_t)k * count + i];
-      dw[i] = s;
-    }
-  }
-}
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(ReduceJob job) { add_parts4(job, ((size_t)blockIdx.x * 256 + threadIdx.x) * 4); }
 
 struct WgradCfg {
   int tiles_co, tiles_j, splits, chunks_per_split;
@@ -818,7 +790,7 @@ hipError_t reduce_parts(const ReduceJob& job, hipStream_t st) {
   if (job.count == 0) return hipSuccess;
   if (!job.part || !job.dw || job.splits < 1) return hipErrorInvalidValue;
   const unsigned blocks = (unsigned)((job.count + 1023) / 1024);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, st, job.part, job.dw, job.count, job.splits);
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, st, job);
   return hipGetLastError();
 }
 

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   if ((int)blockIdx.x >= main_grid) {
     static_assert(D::LDS >= kWideScratch, "side jobs");
     const int id = (int)blockIdx.x - main_grid, sums = (int)wide_reduce_blocks(g.side.count);
-    if (id < sums) reduce_wide(g.side, id, lds);
+    if (id < sums) reduce_wide(g.side, id);
     else flip_wide(FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, id - sums, lds);
     return;
   }

@@ -6,12 +6,13 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
+#include "parts_sum.h"
 
 namespace acc {
 
 // elements of a weight gradient per workgroup: small gradients come in many parts, and their workgroups take fewer
-// elements and share out the parts (64->256 1x1, 16384 elements in 128 parts: the launch that carries them 56 us with
-// 8192 elements per workgroup, 38 with 512)
+// elements, one per thread (64->256 1x1, 16384 elements in 128 parts: the launch that carries them 56 us with
+// 8192 elements per workgroup, 41 with 512)
 __host__ __device__ inline int wide_reduce_piece(size_t count) { return count >= (size_t)8192 * 32 ? 8192 : 512; }
 constexpr int kWideFlip = 16;          // 32 x 32 tiles of a filter per workgroup
 constexpr int kWideScratch = kWideFlip * 32 * 33 * 4;
@@ -23,45 +24,13 @@ __host__ __device__ inline long wide_reduce_blocks(size_t count) {
 }
 inline long wide_flip_blocks(int cout, int cin, int r, int s) { return (flip_tiles(cout, cin, r, s) + kWideFlip - 1) / kWideFlip; }
 
-// dw[i] = sum of part[k][i], in a fixed order; piece `id` of the job.  scratch: 512 float4 of LDS
-__device__ __forceinline__ void reduce_wide(const ReduceJob& j, int id, void* scratch) {
+// piece `id` of the job
+__device__ __forceinline__ void reduce_wide(const ReduceJob& j, int id) {
   constexpr int U = 4;
   const int tid = threadIdx.x;
   if (wide_reduce_piece(j.count) == 512) {
-    // four groups of 128 threads add a quarter of the parts each, then the quarters are added in order
-    const int grp = tid >> 7, k0 = j.splits * grp / 4, k1 = j.splits * (grp + 1) / 4;
-    const size_t i4 = (size_t)id * 512 + (size_t)(tid & 127) * 4;
-    float sum[4] = {0.f, 0.f, 0.f, 0.f};
-    if ((j.count & 3) == 0) {
-      const bool ok = i4 < j.count;
-      const float* p = j.part + (ok ? i4 : 0);
-      int k = k0;
-      for (; k + 8 <= k1; k += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(p + (size_t)(k + u) * j.count);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { sum[0] += v[u].x; sum[1] += v[u].y; sum[2] += v[u].z; sum[3] += v[u].w; }
-      }
-      for (; k < k1; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(p + (size_t)k * j.count);
-        sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
-      }
-    } else {
-      for (int e = 0; e < 4; ++e)
-        if (i4 + e < j.count)
-          for (int k = k0; k < k1; ++k) sum[e] += j.part[(size_t)k * j.count + i4 + e];
-    }
-    float4* sh = static_cast<float4*>(scratch);
-    sh[tid] = make_float4(sum[0], sum[1], sum[2], sum[3]);
-    __syncthreads();
-    if (grp) return;
-    for (int q = 1; q < 4; ++q) {
-      const float4 v = sh[q * 128 + tid];
-      sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
-    }
-    for (int e = 0; e < 4; ++e)
-      if (i4 + e < j.count) j.dw[i4 + e] = sum[e];
+    const size_t i = (size_t)id * 512 + tid;
+    if (i < j.count) j.dw[i] = sum_parts1(j.part + i, j.count, j.splits);
     return;
   }
   const size_t base = (size_t)id * 8192 + (size_t)tid * 4;
@@ -99,12 +68,7 @@ __device__ __forceinline__ void reduce_wide(const ReduceJob& j, int id, void* sc
       if (ok[u]) *reinterpret_cast<float4*>(j.dw + at[u]) = sum[u];
     return;
   }
-  for (int u = 0; u < U; ++u)
-    for (size_t i = base + (size_t)u * 2048; i < j.count && i < base + (size_t)u * 2048 + 4; ++i) {
-      float s = j.part[i];
-      for (int k = 1; k < j.splits; ++k) s += j.part[(size_t)k * j.count + i];
-      j.dw[i] = s;
-    }
+  for (int u = 0; u < U; ++u) add_parts4(j, base + (size_t)u * 2048);
 }
 
 // sixteen 32 x 32 (co, ci) tiles of a flipped, transposed fp32 filter; scratch: kWideScratch bytes of LDS

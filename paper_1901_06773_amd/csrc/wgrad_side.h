@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
+#include "parts_sum.h"
 
 namespace acc {
 
@@ -16,32 +17,7 @@ __device__ __forceinline__ void wgrad_side_jobs(const WgradGeom& g, int id, floa
   const ReduceJob& rj = g.side;
   const int reduce_blocks = (int)((rj.count + 1023) / 1024);
   if (id < reduce_blocks) {
-    const size_t i4 = ((size_t)id * 256 + threadIdx.x) * 4;
-    if (i4 >= rj.count) return;
-    if (i4 + 4 <= rj.count && (rj.count & 3) == 0) {
-      float4 sum = *reinterpret_cast<const float4*>(rj.part + i4);
-      // eight parts fetched at a time, added in their order: with hundreds of parts (few tiles, many
-      // cuts of the minibatch range) one load waiting for the sum before it is a chain of latencies
-      int k = 1;
-      for (; k + 8 <= rj.splits; k += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(rj.part + (size_t)(k + u) * rj.count + i4);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { sum.x += v[u].x; sum.y += v[u].y; sum.z += v[u].z; sum.w += v[u].w; }
-      }
-      for (; k < rj.splits; ++k) {
-        const float4 v = *reinterpret_cast<const float4*>(rj.part + (size_t)k * rj.count + i4);
-        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-      }
-      *reinterpret_cast<float4*>(rj.dw + i4) = sum;
-    } else {
-      for (size_t i = i4; i < rj.count && i < i4 + 4; ++i) {
-        float sum = rj.part[i];
-        for (int k = 1; k < rj.splits; ++k) sum += rj.part[(size_t)k * rj.count + i];
-        rj.dw[i] = sum;
-      }
-    }
+    add_parts4(rj, ((size_t)id * 256 + threadIdx.x) * 4);
     return;
   }
   id -= reduce_blocks;

@@ -930,3 +930,47 @@ def test_observed_timeline_obeys_the_plan_and_tracks_the_prediction(case):
         curves = V.throughput_curves(ctx, net)
         assert curves["conv_fwd_3x3"][0]["tflops"] > 20 and curves["bn_fwd"][0]["gbs"] > 500
     ctx.close()
+
+
+def test_weight_gradient_has_the_same_bits_from_an_iteration_and_from_a_call():
+    """The parts of a split weight gradient are added in one order, whether a launch of its own does it or extra workgroups of
+    another launch (here: those of the second layer's weight gradient, for the third layer's)."""
+    import synth as S
+    from paper_1901_06773_amd import binding as b
+    c, hw, k, classes = 68, 28, 8, 8
+    net = S.NetSpec("three_convs", c, hw, hw, classes)
+    x = -1
+    for _ in range(3):
+        x = net.add(S.Layer(S.CONV, in0=x, cin=c, cout=c, r=3, s=3, stride=1, pad=1))
+    x = net.add(S.Layer(S.GAP, in0=x, cin=c, cout=c))
+    x = net.add(S.Layer(S.FC, in0=x, cin=c, cout=classes))
+    net.add(S.Layer(S.SOFTMAX_CE, in0=x, cin=classes, cout=1))
+    assert b.op_conv_kernel("wgrad", k, hw, hw, c, c, 3, 1, 1) == "wgrad_x3 64x64"
+    params = S.init_params(net)
+    images, labels = S.make_batch(net, k, 0)
+    ctx = b.Context(net.as_array(), (c, hw, hw), pool_bytes=256 << 20)
+    ctx.set_weights(params)
+    ctx.plan_swaps(k, 256 << 20, b.PLAN_NONE)
+    ctx.train_step(torch.from_numpy(images).cuda(), labels, 0.0)
+    grads = ctx.get_grads()
+    ctx.close()
+
+    w = [torch.from_numpy(params[i].reshape(c, c, 3, 3).transpose(0, 2, 3, 1).copy()).cuda() for i in range(3)]
+    wf = torch.from_numpy(params[4][: classes * c].reshape(classes, 1, 1, c).copy()).cuda()
+    x0 = torch.from_numpy(images.transpose(0, 2, 3, 1).copy()).cuda()
+    y = [torch.empty_like(x0) for _ in range(3)]
+    dy = torch.empty_like(x0)
+    ws = torch.empty(b.op_conv_workspace(k, hw, hw, c, c, 3, 1, 1), dtype=torch.uint8, device="cuda")
+    for i in range(3):
+        b.op_conv_fwd(y[i - 1] if i else x0, w[i], y[i], 1, 1)
+    f, z = torch.empty(k, 1, 1, c, device="cuda"), torch.empty(k, 1, 1, classes, device="cuda")
+    b.op_gap_fwd(y[2], f.view(k, c))
+    b.op_conv_fwd(f, wf, z, 1, 0)
+    rows, loss, dz, df = torch.empty(k, device="cuda"), torch.empty(1, device="cuda"), torch.empty(k, classes, device="cuda"), torch.empty_like(f)
+    b.op_softmax_ce(z.view(k, classes), torch.from_numpy(labels).cuda(), rows, loss, dz)
+    b.op_conv_dgrad(dz.view(k, 1, 1, classes), wf, df, 1, 0, ws)
+    b.op_gap_bwd(df.view(k, c), dy)
+    dw = torch.empty(c, 3, 3, c, device="cuda")
+    b.op_conv_wgrad(y[1], dy, dw, 1, 1, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(dw.cpu().numpy().transpose(0, 3, 1, 2).ravel(), grads[2])
