@@ -352,7 +352,9 @@ int acc_get_step_times_ms(acc_ctx* ctx, double* ms, int n);
  * `dtype` says (ACC_F32, or ACC_BF16 = the upper half of an fp32, round to nearest even);
  * dw (O-H-W-I), gamma, beta, mean, istd, dgamma, dbeta are always fp32.  Arithmetic is fp32
  * (bf16 products accumulate in fp32).  stream is a hipStream_t.  workspace may be NULL when
- * workspace_bytes is 0; query the need with acc_op_conv_workspace().  accumulate != 0 adds
+ * workspace_bytes is 0; acc_op_conv_workspace() is enough for every call of the shape, and what is
+ * fastest for acc_op_conv_wgrad (which also works with fewer parts of the sum, and refuses less
+ * than the fewest; an iteration of acc_train_step() uses the fewest).  accumulate != 0 adds
  * into dx instead of overwriting.  Every pointer must be 16-byte aligned (the kernels move
  * 16 bytes at a time); a misaligned one is ACC_EINVAL, like any other bad argument, and
  * nothing is launched. */

@@ -742,14 +742,16 @@ WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   return c;
 }
 
-// fp32 storage: whether the kernel on the bf16 matrix cores takes a shape.  Channel counts whose groups of four lie inside one
+constexpr int kMaxParts = 1 << 20;       // as many as are fastest
+
+// fp32 storage: whether the kernel on the bf16 matrix cores takes a shape, with max_splits parts at most.  Channel counts whose groups of four lie inside one
 // filter tap, and more than ten steps of 16 positions (the fully connected layer at minibatch 41, three steps: 10.5 us there, 7.7
 // here, where 512 small workgroups share the chip and there are no sums to exchange).  Where the direct kernel takes the shape
 // too, the one with the smaller predicted time: small layers are the fp32 instruction's (256->64 at 56x56, 1 image 11.8 us
 // against 13.0; 512->512 3x3 at 7x7, 2 images 12.4 against 14.5; from 400 million products on, almost none).  The constants are
 // fitted to 440 measured shapes (the layers of the ResNets at minibatches 1 to 64 and random ones): median errors of
 // 4-5 %, the choice within 0.3 % of the better one on average, 15 % at most.
-inline bool x3_shape(int dtype, long rows, int cin, int cout, int r, int s) {
+inline bool x3_shape(int dtype, long rows, int cin, int cout, int r, int s, int max_splits) {
   if (dtype != DT_F32 || cin % 4 != 0 || cout % 4 != 0 || rows <= 160) return false;
   if (cin % 64 != 0) return true;              // the other kernel is the per-element one
   const double mb = (double)cout * r * s * cin * 4e-6;
@@ -758,7 +760,7 @@ inline bool x3_shape(int dtype, long rows, int cin, int cout, int r, int s) {
   const WgradCfg c = choose(rows, cin, cout, r, s, dtype);
   const double busy = rounds((long)c.tiles_co * c.tiles_j * c.splits) * (0.27 + 0.594 * c.chunks_per_split);
   const double direct = 3.9 + (busy > 3.9 ? busy : 3.9) + sums(c.splits, 2.4, 0.22);
-  const WgradX3Cfg x = wgrad_x3_choose(rows, cin, cout, r, s);
+  const WgradX3Cfg x = wgrad_x3_choose(rows, cin, cout, r, s, max_splits);
   const int groups = 8 / (x.wt * x.wt), steps = (x.steps_per_split + groups - 1) / groups;
   const double x3 = 6.2 + rounds((long)x.tiles_co * x.tiles_j * x.splits) * (x.wt == 2 ? 2.47 + 1.22 * steps : 2.0 * steps - 0.86) +
                     sums(x.splits, 2.9, 0.27);
@@ -767,6 +769,11 @@ inline bool x3_shape(int dtype, long rows, int cin, int cout, int r, int s) {
 
 }  // namespace
 
+size_t wgrad_workspace_least(int n_img, int p, int q, int cin, int cout, int r, int s, int dtype) {
+  const int splits = choose((long)n_img * p * q, cin, cout, r, s, dtype).splits;
+  return splits <= 1 ? 0 : (size_t)splits * cout * r * s * cin * sizeof(float);
+}
+
 size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, int s, int dtype) {
   if (dtype < 0) {   // whichever storage type needs more
     const size_t a = wgrad_workspace_bytes(n_img, p, q, cin, cout, r, s, DT_F32);
@@ -774,16 +781,12 @@ size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, 
     return a > b ? a : b;
   }
   const long rows = (long)n_img * p * q;
-  int splits = choose(rows, cin, cout, r, s, dtype).splits;
-  if (x3_shape(dtype, rows, cin, cout, r, s)) {
-    // never less than the other kernel's parts: it runs where the operands leave the 32-bit ranges, and a size that grows
-    // with the minibatch the way it does keeps plans under a budget as they were
-    const int sx = wgrad_x3_choose(rows, cin, cout, r, s).splits;
-    if (sx > splits) splits = sx;
-  }
-  if (const int sc = wgrad_smallc_splits(rows, cin, cout, r, s, dtype); sc > splits) splits = sc;   // (either kernel may run)
-  if (splits <= 1) return 0;
-  return (size_t)splits * cout * r * s * cin * sizeof(float);
+  const size_t least = wgrad_workspace_least(n_img, p, q, cin, cout, r, s, dtype);
+  if (!x3_shape(dtype, rows, cin, cout, r, s, kMaxParts)) return least;
+  // (never less: the other kernels run where the operands leave the 32-bit ranges)
+  const int splits = wgrad_x3_choose(rows, cin, cout, r, s, kMaxParts).splits;
+  const size_t bytes = splits <= 1 ? 0 : (size_t)splits * cout * r * s * cin * sizeof(float);
+  return bytes > least ? bytes : least;
 }
 
 hipError_t reduce_parts(const ReduceJob& job, hipStream_t st) {
@@ -813,11 +816,15 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   const bool in_range = g.dtype == DT_F32 && g.p <= 4096 && g.q <= 4096 && Mrows * g.cout * 4 <= 0xFFFFFF00L &&
                         (long)g.n_img * g.h * g.wd * g.cin * 4 <= 0xFFFFFF00L &&
                         (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0;
-  const bool x3 = in_range && x3_shape(g.dtype, Mrows, g.cin, g.cout, g.r, g.s);
-  const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s) : WgradX3Cfg{};
+  // as many parts as are fastest where the workspace holds them, else no more than the other kernels take
+  const bool roomy = g.workspace_bytes >= wgrad_workspace_bytes(g.n_img, g.p, g.q, g.cin, g.cout, g.r, g.s, g.dtype);
+  const int max_splits = roomy ? kMaxParts : c.splits;
+  const bool x3 = in_range && x3_shape(g.dtype, Mrows, g.cin, g.cout, g.r, g.s, max_splits);
+  const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s, max_splits) : WgradX3Cfg{};
   const bool small = !x3 && conv_wgrad_smallc_takes(g);
-  const int splits = x3 ? cx.splits : small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s, g.dtype) : c.splits;
-  if (splits > 1 && !g.workspace) return hipErrorInvalidValue;
+  const int few = small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s, g.dtype) : 0;
+  const int splits = x3 ? cx.splits : small ? (few < c.splits ? few : c.splits) : c.splits;
+  if (splits > 1 && (!g.workspace || g.workspace_bytes < (size_t)splits * g.cout * J * sizeof(float))) return hipErrorInvalidValue;
   const long work = (long)c.tiles_co * c.tiles_j * c.splits;
   if (work > (1L << 30)) return hipErrorInvalidValue;
   const long es = (long)dt_size(g.dtype);

@@ -350,13 +350,12 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
 
 }  // namespace
 
-// How a weight gradient is cut, a function of the shape only (never of addresses or of the swap plan): the tile and
-// the number of parts with the smallest predicted time,
+// How a weight gradient is cut, never a function of addresses or of the swap plan: the tile and the number of parts, up
+// to max_splits, with the smallest predicted time,
 //   rounds of 256 workgroups x (fixed + per step of a group) + 3 us for the reduction + 1 byte / 4 TB/s for every part
 // written and read, with 7.0 + 1.05 us (128 x 128 tile) and 4.5 + 1.75 us (64 x 64, eight groups) as measured.  At least
-// 16 steps per part, as the kernels before (more parts of small layers gain little alone and made the scratch memory jump from one
-// minibatch to the next, so that plans no longer fitted under budgets they had fitted under); at most 32 MiB together.
-WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s) {
+// 16 steps per part (more parts of small layers gain little); at most 32 MiB together.
+WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s, int max_splits) {
   const long J = (long)r * s * cin, steps = (Mrows + 15) / 16;
   WgradX3Cfg best{};
   double best_us = 0;
@@ -365,7 +364,7 @@ WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s) {
     const int tco = (cout + 64 * wt - 1) / (64 * wt);
     const long tj = (J + 64 * wt - 1) / (64 * wt), tiles = tco * tj;
     const double part_us = (double)cout * J * 4 * 2 / 4.0e6;       // a part is written and read once
-    for (long want = 1; want <= 256; ++want) {
+    for (long want = 1; want <= 256 && want <= max_splits; ++want) {
       const long per = (steps + want - 1) / want, splits = (steps + per - 1) / per;
       if (splits != want) continue;
       if (splits > 1 && (per < 16 || splits * cout * J * 4 > (32L << 20))) break;

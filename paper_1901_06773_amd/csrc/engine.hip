@@ -753,7 +753,7 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       WgradGeom wg{};
       wg.x = ptr(s.x); wg.dy = ptr(s.dy); wg.dw = dw; wg.dtype = dt;
       wg.n_img = k; wg.h = 1; wg.wd = 1; wg.cin = l->cin; wg.p = 1; wg.q = 1; wg.cout = l->cout;
-      wg.r = 1; wg.s = 1; wg.stride = 1; wg.pad = 0; wg.workspace = ptr(s.ws2);
+      wg.r = 1; wg.s = 1; wg.stride = 1; wg.pad = 0; wg.workspace = ptr(s.ws2); wg.workspace_bytes = c->plan.tbytes[s.ws2];
       // the transposed filter for the data gradient is written by extra workgroups of the
       // weight-gradient launch; the parts of the weight gradient are added up by extra
       // workgroups of the data-gradient launch
@@ -803,6 +803,7 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       wg.n_img = k; wg.h = h; wg.wd = wd; wg.cin = l->cin; wg.p = ho; wg.q = wo; wg.cout = l->cout;
       wg.r = l->r; wg.s = l->s; wg.stride = l->stride; wg.pad = l->pad;
       wg.workspace = ptr(s.ws2);
+      wg.workspace_bytes = c->plan.tbytes[s.ws2];
       if (s.dx < 0) return wgrad(wg, conv_flops, nullptr);   // first layer: no data gradient
       const bool split = l->stride > 1 && (l->r > 1 || l->s > 1 || l->pad > 0);
       // The weight gradient reads x and dy and writes only its own partial sums and dw, so it

@@ -145,7 +145,8 @@ struct WgradGeom {
   int n_img, h, wd, cin;
   int p, q, cout;
   int r, s, stride, pad;
-  float* workspace;         // split-K partials, wgrad_workspace_bytes() bytes (may be null if 0)
+  float* workspace;         // split-K partials, workspace_bytes of them: at least wgrad_workspace_least() (may be null if 0)
+  size_t workspace_bytes;
   // Optional side job: extra workgroups appended to the launch write the flipped and
   // transposed filter wt[ci][r'][t'][co] = w[co][R-1-r'][S-1-t'][ci] of this layer (the data
   // gradient that follows needs it).  Both null: no side job.
@@ -154,8 +155,12 @@ struct WgradGeom {
   // Optional side job: extra workgroups add up the parts of an earlier weight gradient.
   ReduceJob side;
 };
-// dtype: DT_F32 / DT_BF16 (the two storage types cut the minibatch range differently), or -1 = the
-// larger of the two
+// Scratch for the parts of a weight gradient.  dtype: DT_F32 / DT_BF16 (the two storage types cut the minibatch range
+// differently), or -1 = the larger of the two.  _bytes: as many parts as are fastest for the call alone; _least: the fewest the
+// call works with.  An iteration's plan counts with the fewest: its scratch lies in the budget, and beside the data gradients, on a
+// stream of its own, more parts gain nothing (ResNet-50, 32 images, 9560 us with, 9532 without).  How a shape is cut,
+// and with it the bits of the result, depends on the shape and on which of the two sizes is there.
+size_t wgrad_workspace_least(int n_img, int p, int q, int cin, int cout, int r, int s, int dtype);
 size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, int s, int dtype);
 // If `deferred` is given and the gradient is split over the minibatch, the reduction of the
 // parts is not launched but described there (the caller appends it to a later launch or
@@ -167,7 +172,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe = n
 struct WgradX3Cfg {
   int wt, tiles_co, tiles_j, splits, steps_per_split;
 };
-WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s);
+WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s, int max_splits);
 hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st);
 // The kernel for a handful of input channels (conv_smallc.hip): parts it cuts the reduction into (0: the shape is not
 // its; a function of what wgrad_workspace_bytes() knows), whether it takes a launch, and the launch.

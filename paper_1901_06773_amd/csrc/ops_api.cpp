@@ -104,12 +104,12 @@ int conv_wgrad_op(const void* x, const void* dy, float* dw, int n, int h, int wd
   if (!x || !dy || !dw || !dtype_ok(dtype) || !conv_ok(n, h, wd, cin, cout, r, s, stride, pad)) return ACC_EINVAL;
   if (!al16({x, dy, dw, workspace})) return ACC_EINVAL;
   const int ho = out_dim(h, r, stride, pad), wo = out_dim(wd, s, stride, pad);
-  const size_t need = wgrad_workspace_bytes(n, ho, wo, cin, cout, r, s, dtype);
+  const size_t need = wgrad_workspace_least(n, ho, wo, cin, cout, r, s, dtype);
   if (need && (!workspace || workspace_bytes < need)) return ACC_EINVAL;
   WgradGeom g{};
   g.x = x; g.dy = dy; g.dw = dw; g.dtype = dtype;
   g.n_img = n; g.h = h; g.wd = wd; g.cin = cin; g.p = ho; g.q = wo; g.cout = cout;
-  g.r = r; g.s = s; g.stride = stride; g.pad = pad; g.workspace = (float*)workspace;
+  g.r = r; g.s = s; g.stride = stride; g.pad = pad; g.workspace = (float*)workspace; g.workspace_bytes = workspace ? workspace_bytes : 0;
   return status(conv_wgrad(g, st, probe));
 }
 }  // namespace

@@ -203,7 +203,7 @@ hipError_t conv_igemm(const ConvGeom& g_, hipStream_t st, LaunchProbe* probe) {
   stub_count_launch("conv_igemm", st);
   return hipSuccess;
 }
-size_t wgrad_workspace_bytes(int n_img, int p, int q, int cin, int cout, int r, int s, int) {
+size_t wgrad_workspace_least(int n_img, int p, int q, int cin, int cout, int r, int s, int) {
   const long rows = (long)n_img * p * q;
   const long splits = rows >= 2048 ? 8 : rows >= 256 ? 2 : 1;     // any step function of the minibatch will do here
   return splits > 1 ? (size_t)splits * cout * r * s * cin * sizeof(float) : 0;
@@ -212,8 +212,8 @@ hipError_t conv_wgrad(const WgradGeom& g_, hipStream_t st, LaunchProbe* probe, R
   dev(g_.x, "conv_wgrad: x"); dev(g_.dy, "conv_wgrad: dy"); dev(g_.dw, "conv_wgrad: dw"); dev(g_.workspace, "conv_wgrad: workspace");
   dev(g_.flip_w, "conv_wgrad: flip source"); dev(g_.flip_wt, "conv_wgrad: flip target");
   dev(g_.side.part, "conv_wgrad: reduce parts"); dev(g_.side.dw, "conv_wgrad: reduce target");
-  const size_t need = wgrad_workspace_bytes(g_.n_img, g_.p, g_.q, g_.cin, g_.cout, g_.r, g_.s, g_.dtype);
-  if (need && (!g_.workspace || !in_pool(g_.workspace, need))) { ++g.pointers_outside_pool; complain("conv_wgrad: workspace runs past the pool"); }
+  const size_t need = wgrad_workspace_least(g_.n_img, g_.p, g_.q, g_.cin, g_.cout, g_.r, g_.s, g_.dtype);
+  if (need && (!g_.workspace || g_.workspace_bytes < need || !in_pool(g_.workspace, g_.workspace_bytes))) { ++g.pointers_outside_pool; complain("conv_wgrad: workspace runs past the pool"); }
   if (deferred) *deferred = ReduceJob{nullptr, nullptr, 0, 0};
   if (need) {
     const ReduceJob job{g_.workspace, g_.dw, (size_t)g_.cout * g_.r * g_.s * g_.cin, (int)(need / ((size_t)g_.cout * g_.r * g_.s * g_.cin * 4))};

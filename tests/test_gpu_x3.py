@@ -196,3 +196,20 @@ def test_split_wgrad_tiny_operands(case, scales):
     ref = sum(d @ c.t() for d, c in zip(torch.from_numpy(dy).double().reshape(n, cout, -1), cols)).reshape(cout, cin, r, r).numpy()
     got = wgrad(case, x, dy)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("case,parts", [(WGRAD_CASES[7], 3), ((64, 14, 14, 132, 260, 1, 1, WX128), 49)])
+def test_split_wgrad_in_the_least_workspace(case, parts):
+    """More parts are taken where the workspace holds them; the fewest (those of the fp32 kernel's launch, one round of workgroups) are
+    enough, and less is refused."""
+    n, h, w, cin, cout, r, stride = case[:7]
+    x, dy = rnd(1, n, cin, h, w), rnd(3, n, cout, O.out_dim(h, r, stride, r // 2), O.out_dim(w, r, stride, r // 2))
+    ref = O.conv_wgrad(x, dy, (cout, cin, r, r), stride, r // 2).astype(np.float64)
+    least = parts * cout * cin * r * r * 4
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    dw = torch.full((cout, r, r, cin), float("nan"), device="cuda")
+    B().op_conv_wgrad(dev(nhwc(x)), dev(nhwc(dy)), dw, stride, r // 2, ws)
+    torch.cuda.synchronize()
+    assert np.linalg.norm(dw.cpu().numpy().transpose(0, 3, 1, 2) - ref) <= 2e-6 * np.linalg.norm(ref)
+    with pytest.raises(B().AccError):
+        B().op_conv_wgrad(dev(nhwc(x)), dev(nhwc(dy)), dw, stride, r // 2, ws[: least - 16])

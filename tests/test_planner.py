@@ -617,3 +617,13 @@ def test_simulated_timeline_is_consistent_with_the_plan(budget_gib):
     with pytest.raises(b.AccError) as e:
         ctx.timeline(observed=True)
     assert e.value.status == b.ACC_ESTATE
+
+
+@pytest.mark.parametrize("net,k,budget", [("resnet18", 64, 1445818624), ("resnet34", 192, 6111207424), ("resnet50", 64, 5415594240),
+                                          ("resnet152", 48, 8791748352), ("vgg16", 32, 3736492800)])
+def test_scratch_memory_does_not_take_budget(net, k, budget):
+    """The least budgets under which these networks train without swapping (fp32): what the weight gradients' scratch takes in a plan
+    is part of the budget, however many parts a call alone would rather use."""
+    n = getattr(S, net)()
+    ctx = B().Context(n.as_array(), (n.in_c, n.in_h, n.in_w))
+    assert ctx.plan_swaps(k, budget, B().PLAN_NONE)["n_swapped"] == 0
