@@ -335,8 +335,8 @@ typedef struct {
 int acc_get_kernel_profile(acc_ctx* ctx, acc_kernel_profile* out, int max_entries);
 /* One entry per convolution-kernel launch of the last train_step run at level 2 or 3, in issue
  * order: the step and layer record it belongs to, its role (0 forward product, 1 data gradient,
- * 2 weight gradient; FC layers use the same kernels), which kernel instance ran (index of
- * acc_get_kernel_profile's names in V_* order), milliseconds between the events around the
+ * 2 weight gradient; FC layers use the same kernels), which kernel instance ran (a number
+ * of its own per kernel, the V_* of csrc/kernels.h; it stays with the kernel), milliseconds between the events around the
  * launch and its algorithmic flops.  Returns the number of launches (which may exceed
  * max_entries: then only the first max_entries were written). */
 typedef struct {

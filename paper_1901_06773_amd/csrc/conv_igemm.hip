@@ -669,12 +669,11 @@ hipError_t launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* 
 }  // namespace
 
 const char* conv_variant_name(int v) {
-  static const char* names[V_COUNT] = {"igemm_kernel<fast>", "igemm_kernel<generic>", "wgrad_kernel<fast>",
+  static const char* names[V_COUNT] = {"?", "igemm_kernel<generic>", "wgrad_kernel<fast>",
                                        "wgrad_kernel<generic>", "igemm_kernel<direct>", "wgrad_kernel<direct>",
-                                       "wgrad_bf16_kernel", "igemm_bf16_kernel", "igemm_x3_kernel",
-                                       "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel",
-                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel",
-                                       "igemm_kernel<direct, two groups>"};
+                                       "wgrad_bf16_kernel", "igemm_bf16_kernel", "igemm_kernel<direct, two groups>",
+                                       "igemm_x3_kernel", "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel",
+                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel"};
   return (v >= 0 && v < V_COUNT) ? names[v] : "?";
 }
 

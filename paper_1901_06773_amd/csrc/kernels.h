@@ -132,8 +132,9 @@ hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, Lau
 // A handful of input channels (conv_smallc.hip): as above.
 bool conv_smallc_takes(const ConvGeom& g, long M);
 hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe);
-enum { V_IGEMM_FAST = 0, V_IGEMM_GENERIC, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16,
-       V_IGEMM_BF16, V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD, V_IGEMM_DIRECT_2G, V_COUNT };
+// Callers see these numbers (acc_get_launch_profile): one keeps its kernel, new ones go to the end.  0 was a kernel that is gone.
+enum { V_IGEMM_GENERIC = 1, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16, V_IGEMM_BF16, V_IGEMM_DIRECT_2G,
+       V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD, V_COUNT };
 const char* conv_variant_name(int v);
 
 // dw[co][(r,t,ci)] = sum_{img,p,q} dy[img,p,q,co] * x[img, p*stride+r-pad, q*stride+t-pad, ci]

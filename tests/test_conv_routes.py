@@ -84,3 +84,17 @@ def test_fp32_strided_data_gradients_reach_the_kernels_their_parity_tests_name()
 ])
 def test_fp32_weight_gradient(shape, name):
     assert kernel("wgrad", *shape) == name
+
+
+# the numbers a launch profile reports: one keeps its kernel
+@pytest.mark.parametrize("number,name", [
+    (1, "igemm_kernel<generic>"), (2, "wgrad_kernel<fast>"), (3, "wgrad_kernel<generic>"), (4, "igemm_kernel<direct>"),
+    (5, "wgrad_kernel<direct>"), (6, "wgrad_bf16_kernel"), (7, "igemm_bf16_kernel"), (8, "igemm_kernel<direct, two groups>"),
+    (0, "?"), (15, "?"), (-1, "?"),
+])
+def test_numbers_of_the_kernels(number, name):
+    import ctypes
+    from paper_1901_06773_amd import binding as b
+    f = b._lib._ZN3acc17conv_variant_nameEi
+    f.restype, f.argtypes = ctypes.c_char_p, [ctypes.c_int]
+    assert f(number).decode() == name
