@@ -893,39 +893,42 @@ void launch_short(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* 
 //   one workgroup per compute unit:  base + first + first_step * steps + (tiles - 1) * (next + next_step * steps) + memory,
 //   several (r <= per_cu resident):  base + (compute^2 + memory^2)^(1/2),  compute = the sum over rounds of
 //                                    max(first + first_step * steps, r * (next + next_step * steps)),
-// taps more per tile for filters larger than 1x1, and memory = per_mb * MB + per_mb_far * (MB beyond 200) of both operands
-// and the result, each once.  The constants are fitted to 481 measured launches (the layers of the ResNets at minibatches
-// 1 to 128 and random ones, every kernel on each; profiles/conv_f32_kernels_by_shape.txt): median errors of 1-4 %, the
-// choice is within 0.4 % of the best on average, 18 % at most.  The fp32 instruction's kernel is kept for the launches where it is
-// still the faster one, small ones above all (256->64 1x1 at 56x56, 4 images 7.6 against 8.9 us; 64->256, 128 images, 514 MB 165
-// against 176); it wins ties within 5 %.  A function of the shape and the alignment only, never of the swap plan (pool
-// offsets are multiples of 256).
+// taps more per tile for filters larger than 1x1, and memory = per_mb_read * MB of both operands + per_mb_written * MB of the
+// result, each once.  The constants are fitted to 500 measured launches (the layers of the ResNets at minibatches 1 to 128 and
+// random ones, every kernel on each; profiles/conv_f32_kernels_by_shape.txt), six sets of tensors in turn, so that large operands
+// come from memory and not from the caches, as in a program that touches other tensors between two calls: median errors of 1-4 %,
+// the choice is within 0.5 % of the best on average, 12 % at most (on the same tensors again and again: 0.7 %, 19 %).  The fp32
+// instruction's kernel is kept for the launches where it is still the faster one, small ones above all (256->64 1x1 at 56x56, 4
+// images 7.6 against 8.9 us) and those that write much more than they compute (64->256, 32 images 46.5 against 48.7, 128 images 165
+// against 176); it wins ties within 3 %.  A function of the shape and the alignment only, never of the swap plan (pool offsets
+// are multiples of 256).
 struct Kind {
   int bm, bn, ks, kc, per_cu;
-  double base, first, first_step, next, next_step, taps, per_mb, per_mb_far;
+  double base, first, first_step, next, next_step, taps, per_mb_read, per_mb_written;
 };
 enum { X3_128 = 0, X3_64, X3_WINDOW, X3_DEEP_2x1, X3_DEEP_2x2, X3_DEEP_1x1, X3_KINDS, F32_ONE = X3_KINDS, F32_TWO, KINDS };
 constexpr Kind kKinds[KINDS] = {
-    {128, 128, 1, 16, 2, 3.36, 3.81, 0.744, 2.87, 0.596, 0.68, 0.130, 0.139},   // igemm_x3_kernel<2, 2>
-    {64, 64, 1, 16, 5, 4.19, 0.04, 0.369, 0.475, 0.220, 0.35, 0.028, 0.316},    // igemm_x3_kernel<1, 1>
-    {128, 64, 4, 16, 1, 2.96, 4.17, 0.959, 4.47, 1.154, 0.52, 0.133, 0},        // igemm_x3_deep_kernel<2, 1, window>
-    {128, 64, 4, 16, 1, 5.35, 0.69, 1.156, 3.34, 1.662, 1.93, 0.092, 0.076},    // igemm_x3_deep_kernel<2, 1>
-    {128, 128, 2, 16, 1, 5.92, 1.61, 0.844, 4.67, 1.203, 1.34, 0.063, 0.034},   // igemm_x3_deep_kernel<2, 2>
-    {64, 64, 8, 16, 1, 4.30, 1.37, 1.411, 3.33, 1.820, 1.85, 0.063, 0.089},     // igemm_x3_deep_kernel<1, 1>
-    {64, 64, 1, 32, 4, 2.65, 4.49, 0.034, 0.521, 0.506, 0.11, 0.047, 0.104},    // igemm_kernel<direct>, fp32
-    {64, 64, 2, 32, 1, 3.04, 0.21, 1.002, 0.21, 1.002, 1.50, 0.029, 0},         // igemm_kernel<direct, two groups>: one tile at most
+    {128, 128, 1, 16, 2, 3.79, 3.34, 0.744, 1.78, 0.644, 0.78, 0.139, 0.324},    // igemm_x3_kernel<2, 2>
+    {64, 64, 1, 16, 5, 4.19, 0.154, 0.374, 0.093, 0.241, 0.046, 0.107, 0.335},   // igemm_x3_kernel<1, 1>
+    {128, 64, 4, 16, 1, 2.49, 3.90, 0.973, 3.39, 1.166, 0.47, 0.013, 0.414},     // igemm_x3_deep_kernel<2, 1, window>
+    {128, 64, 4, 16, 1, 5.47, 0.83, 1.137, 3.38, 1.683, 2.02, 0.148, 0.119},     // igemm_x3_deep_kernel<2, 1>
+    {128, 128, 2, 16, 1, 5.65, 1.72, 0.843, 3.56, 1.297, 0.76, 0.076, 0.160},    // igemm_x3_deep_kernel<2, 2>
+    {64, 64, 8, 16, 1, 4.19, 1.53, 1.449, 3.10, 1.861, 1.55, 0.118, 0.150},      // igemm_x3_deep_kernel<1, 1>
+    {64, 64, 1, 32, 4, 2.72, 4.73, 0.017, 0.597, 0.496, 0.08, 0.134, 0.134},     // igemm_kernel<direct>, fp32
+    {64, 64, 2, 32, 1, 3.19, 0.134, 0.995, 0.134, 0.995, 1.09, 0, 0.234},        // igemm_kernel<direct, two groups>: one tile at most
 };
-double predicted_us(const Kind& k, long M, long N, long K, bool taps, double mb) {
+double predicted_us(const Kind& k, const ConvGeom& g, long M, long K) {
+  const long N = g.n_out;
   const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
   const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
-  const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = taps ? k.taps * most : 0;
-  const double memory = k.per_mb * mb + k.per_mb_far * (mb > 200 ? mb - 200 : 0);
+  const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = g.r * g.s > 1 ? k.taps * most : 0;
+  const double read = 4e-6 * ((double)g.n_img * g.h * g.wd * g.c + (double)N * K), written = 4e-6 * (double)M * N;
+  const double memory = k.per_mb_read * read + k.per_mb_written * written;
   if (k.per_cu == 1) return k.base + first + (most - 1) * next + more + memory;
   auto round = [&](long r) { return r == 0 ? 0.0 : first > r * next ? first : r * next; };
   const double compute = (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu) + more;
   return k.base + std::sqrt(compute * compute + memory * memory);
 }
-double megabytes(const ConvGeom& g, long M, long K) { return 4e-6 * ((double)g.n_img * g.h * g.wd * g.c + (double)M * g.n_out + (double)g.n_out * K); }
 
 // the launches that read every tap from one window of consecutive pixels, if it fits
 bool window_takes(const ConvGeom& g) {
@@ -936,24 +939,23 @@ bool window_takes(const ConvGeom& g) {
 
 // the fastest of the kernels in this file, and its prediction
 int best_x3(const ConvGeom& g, long M, long K, double* us) {
-  const double mb = megabytes(g, M, K);
   const bool window = window_takes(g);
   int best = -1;
   for (int v = 0; v < X3_KINDS; ++v) {
     if (v == X3_WINDOW && !window) continue;
-    const double t = predicted_us(kKinds[v], M, g.n_out, K, g.r * g.s > 1, mb);
+    const double t = predicted_us(kKinds[v], g, M, K);
     if (best < 0 || t < *us) { best = v; *us = t; }
   }
   return best;
 }
 double fp32_us(const ConvGeom& g, long M, long K) {
-  return predicted_us(kKinds[conv_igemm_two_groups(g, M, K) ? F32_TWO : F32_ONE], M, g.n_out, K, g.r * g.s > 1, megabytes(g, M, K));
+  return predicted_us(kKinds[conv_igemm_two_groups(g, M, K) ? F32_TWO : F32_ONE], g, M, K);
 }
 
 // The same for the parts of a strided data gradient in one launch of a short kernel: the longest tile alone, or the compute
 // units' share of all tiles and part of a last one.  These constants and those of conv_igemm_x3_parts_takes() are fitted to
 // 45 shapes (2 to 256 images, 32 to 1024 channels, 3x3 and 5x5, stride 2), the sub-filters' launch included: median errors of
-// 3 to 5 %, and on average the choice is within 0.2 % of the best of the three ways, 7 % at most.
+// 3 to 5 %, and on 73 shapes the choice is within 0.2 % of the best of the three ways on average, 5 % at most.
 double predicted_parts_us(bool wide, const ConvGeom* parts, int n) {
   const Kind& k = kKinds[wide ? X3_128 : X3_64];
   double work = 0, longest = 0, last = 0;
@@ -1030,7 +1032,7 @@ hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, Launch
 bool conv_igemm_x3_slower(const ConvGeom& g, long M, long K) {
   double us = 0;
   best_x3(g, M, K, &us);
-  return fp32_us(g, M, K) < us * 1.05;
+  return fp32_us(g, M, K) < us * 1.03;
 }
 
 // The parts go into one launch where that is predicted to take less than the parts one after the other: 128 channels of 56x56, 32

@@ -61,7 +61,9 @@ def test_fp32_layers_reach_the_kernels_their_parity_tests_name():
     ((2, 8, 8, 224, 64, 1, 1, 0, F32), "igemm direct 64x64"),              # seven chunks of K: too short for two groups
     ((128, 56, 56, 64, 256, 1, 1, 0, F32), "igemm direct 64x64"),          # 411 MB of result, K of 64
     ((41, 14, 14, 256, 256, 3, 1, 1, F32), "igemm_x3_deep window 128x64"),
-    ((32, 56, 56, 64, 256, 1, 1, 0, F32), "igemm_x3 64x64"),
+    ((32, 56, 56, 64, 256, 1, 1, 0, F32), "igemm direct 64x64"),           # writes four times what it reads
+    ((41, 56, 56, 64, 256, 1, 1, 0, F32), "igemm direct 64x64"),
+    ((41, 28, 28, 128, 512, 1, 1, 0, F32), "igemm_x3 128x128"),
     ((2, 9, 7, 288, 40, 1, 1, 0, F32), "igemm direct 64x64, two groups"),
     ((41, 14, 14, 100, 256, 3, 1, 1, F32), "igemm generic 64x64"),         # channels not in 16s, r > 1
 ])
