@@ -1,7 +1,8 @@
 // Adding up the parts of a weight gradient: dw[i] = part[0][i] + part[1][i] + ..., in that order wherever it is done (a launch of
 // its own, or extra workgroups of another one), so that a gradient has the same bits on every way it is computed.
 // Several parts are fetched at a time: with hundreds of them (few tiles, many cuts of the minibatch range) one load
-// waiting for the sum before it is a chain of latencies.
+// waiting for the sum before it is a chain of latencies.  The parts that fill no batch are fetched together too, with bounds that the
+// whole batches do without.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -13,7 +14,15 @@ namespace acc {
 __device__ __forceinline__ float sum_parts1(const float* p, size_t count, int splits) {
   constexpr int U = 32;
   float sum = p[0];
-  for (int k = 1; k < splits; k += U) {
+  int k = 1;
+  for (; k + U <= splits; k += U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = p[(size_t)(k + u) * count];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum += v[u];
+  }
+  if (k < splits) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = p[k + u < splits ? (size_t)(k + u) * count : 0];   // beyond the last part: read, not added
@@ -30,7 +39,15 @@ __device__ __forceinline__ void add_parts4(const ReduceJob& j, size_t i4) {
     constexpr int U = 8;
     const float* p = j.part + i4;
     float4 sum = *reinterpret_cast<const float4*>(p);
-    for (int k = 1; k < j.splits; k += U) {
+    int k = 1;
+    for (; k + U <= j.splits; k += U) {
+      float4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(p + (size_t)(k + u) * j.count);
+#pragma unroll
+      for (int u = 0; u < U; ++u) { sum.x += v[u].x; sum.y += v[u].y; sum.z += v[u].z; sum.w += v[u].w; }
+    }
+    if (k < j.splits) {
       float4 v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(p + (k + u < j.splits ? (size_t)(k + u) * j.count : 0));
