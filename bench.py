@@ -61,7 +61,7 @@ def parse():
 # by what the same counters read for sgd_kernel
 # (profiles/resnet152_k41_hbm_traffic_pmc.txt).  A figure of that profile, not of this run: counters
 # need the profiler.  Known for the profiled workload and kernel only.
-PROFILED_TRAFFIC_BYTES = {("resnet152", 41, 8.0, "wgrad_x3_kernel"): 81.5e6, ("resnet152", 41, 8.0, "igemm_x3_kernel"): 90.0e6}
+PROFILED_TRAFFIC_BYTES = {("resnet152", 41, 8.0, "wgrad_x3_kernel"): 80.1e6, ("resnet152", 41, 8.0, "igemm_x3_kernel"): 79.0e6}
 
 
 def log(*a):
