@@ -12,9 +12,9 @@
 // Bound: the matrix cores sustain 2.0-2.08 PFLOP/s in bf16 (their clock falls under load), a sixth of that, 333
 // TFLOP/s, in these products; the rest is LDS traffic, splitting (13 vector instructions per two values) and the
 // fixed cost of a tile.  Measured against the fp32-instruction kernel this replaces (154 TFLOP/s ceiling), forward,
-// minibatch 41: 256->256 3x3 at 14x14 75.2 -> 49.5 us, 128->128 3x3 at 28x28 74.7 -> 51.0, 512->512 3x3 at 7x7
-// 77.4 -> 65.6, 256->1024 1x1 at 14x14 38.6 -> 29.0, 1024->256 35.6 -> 30.0, 64->256 at 56x56 (minibatch 32) 38.8
-// -> 33; error against float64 5.9e-7 -> 3.5e-7 on the first of them, smaller on all.
+// minibatch 41: 256->256 3x3 at 14x14 75.2 -> 50.2 us, 128->128 3x3 at 28x28 74.7 -> 51.0, 512->512 3x3 at 7x7
+// 77.4 -> 65.6, 256->1024 1x1 at 14x14 38.6 -> 29.0, 1024->256 35.6 -> 30.0;
+// error against float64 5.9e-7 -> 3.5e-7 on the first of them, smaller on all.
 #include <cmath>
 
 #include "kernels.h"
