@@ -1,6 +1,6 @@
 // Implicit-GEMM convolution, the kernel for what the others do not take: fp32 storage with channel counts that
-// are no multiple of 16 (the 3-channel stem, tiny layers; v_mfma_f32_32x32x2_f32), and bf16 storage below the
-// sizes of the 128 x 128 kernel (v_mfma_f32_32x32x16_bf16).  Used for the forward pass and, with a flipped /
+// are no multiple of 16 (the 3-channel stem, tiny layers; v_mfma_f32_32x32x2_f32), and bf16 storage with widths that do
+// not come in 8s (v_mfma_f32_32x32x16_bf16).  Used for the forward pass and, with a flipped /
 // transposed filter or a scattering epilogue, for the data gradient.
 //
 //   out[m][n] (+)= sum_k A[m][k] * W[n][k],   m = (img,p,q), k = (r,t,c), c fastest
@@ -726,7 +726,7 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
     return hipErrorInvalidValue;
   if (g.dtype != DT_F32 && g.dtype != DT_BF16) return hipErrorInvalidValue;
   if ((g.bias || g.relu) && (g.accumulate || g.stats || g.bnb.sums)) return hipErrorInvalidValue;
-  if (conv_igemm_bf16_takes(g, M, K))      // bf16 storage, large layers: 128 x 128 tiles
+  if (conv_igemm_bf16_takes(g, M, K))      // bf16 storage, widths in 8s
     return conv_igemm_bf16(g, (int)M, (int)K, st, probe);
   if (conv_smallc_takes(g, M)) return conv_smallc_fwd(g, st, probe);
   // The direct loader addresses both operands through buffer descriptors: 32-bit ranges, the last bytes kept free for the
@@ -737,7 +737,7 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
                       (margin_px + (long)g.n_img * g.h * g.wd) * g.c * es <= 0xFFFFFF00L &&
                       (long)g.n_out * K * es <= 0xFFFFFF00L &&
                       (reinterpret_cast<uintptr_t>(g.in) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.w) & 15) == 0;
-  if (g.dtype == DT_BF16)      // below the 128 x 128 kernel's sizes
+  if (g.dtype == DT_BF16)      // widths that conv_igemm_bf16.hip does not take
     return direct ? launch<L_DIRECT, bf16_t>(g, (int)M, (int)K, st, probe) : launch<L_GENERIC, bf16_t>(g, (int)M, (int)K, st, probe);
   // fp32 storage, whole 16-channel steps: products on the bf16 matrix cores, but for small launches
   if (conv_igemm_x3_takes(g, M, K) && !(direct && conv_igemm_x3_slower(g, M, K))) return conv_igemm_x3(g, (int)M, (int)K, st, probe);

@@ -1,19 +1,29 @@
 // Implicit-GEMM convolution for bf16 storage on the bf16 matrix cores of gfx950
-// (v_mfma_f32_32x32x16_bf16), forward pass and data gradient of the layers that carry the work.
+// (v_mfma_f32_32x32x16_bf16), forward pass and data gradient.
 //
-//   out[m][n] (+)= sum_k A[m][k] * W[n][k],   m = (img,p,q), k = (r,t,c), c fastest
+//   out[m][n] (+)= sum_k A[m][k] * W[n][k],   m = (img,p,q), k = (r,t,c)
 //
-// Same scheme as the 64 x 64 kernel of conv_igemm.hip (K-chunks of 128 bytes of a GEMM row go
-// from global memory straight into LDS, rows unpadded with their 16-byte columns XORed by the
-// row number, zero fill by offsets outside the buffer descriptor, two LDS stages), with a tile
-// of 128 x 128 per workgroup and 64 x 64 per wave (2 x 2 MFMA blocks).  One bf16 MFMA does in 32
-// cycles what sixteen fp32 ones do in 1024, so the 64 x 64 kernel, which reads 8 KB of LDS per
-// wave and chunk for 4 MFMAs, is bound by LDS bandwidth at a fraction of the matrix peak; here a
-// wave reads 16 KB for 16 MFMAs: every byte read from LDS feeds twice the arithmetic, every byte
-// fetched from memory likewise.  64 KB of LDS per workgroup, two workgroups per CU.
+// K-chunks of a GEMM row go from global memory straight into LDS (buffer_load ... lds), rows unpadded with their 16-byte
+// columns permuted by the row number, zero fill by offsets outside the buffer descriptor.  LDS has 64 banks here: sixteen
+// consecutive rows read at one column lie on different ones (with a permutation of eight rows every read took eight cycles
+// instead of four).
+//
+// What bounds it.  The matrix cores sustain about 2.0 PFLOP/s; a wave that multiplies 64 x 64 from fragments in LDS asks for
+// as many bytes of LDS, and a 128 x 128 tile for twice as many bytes of L2, as a 256 x 256 tile of eight waves of 128 x 64 does.
+// Large layers therefore run tiles of 256 x 256, and what remains is the start and the end of a tile (one workgroup
+// per compute unit: nobody computes while it stores) and the number of rounds.  Rows of a chunk are 128 bytes wherever LDS allows:
+// with 64-byte rows L2 answers twice as many requests (256->256 3x3 at 14x14, 512 images, 256 x 256 tile: 1.33e7 against 0.67e7, 136
+// against 126 us).  The taps of 64 channels run before the next 64 channels: rows are found in L2 again (134 -> 126 us).
+// Few tiles: the values of K are dealt out to groups of waves, down to eight waves that share one 32 x 32 tile.
+// Measured against one 128 x 128 kernel and a 64 x 64 one for the rest (us, six sets of tensors in turn): 256->256 3x3 at 14x14,
+// 512 images 142.6 -> 126.2; 512->512 3x3 at 7x7, 512 images 131.9 -> 111.6; 2048->512 1x1 at 7x7, 512 images 77.6 -> 59.7;
+// 256->1024 1x1 at 14x14, 512 images 109.2 -> 93.6; 512->512 3x3 at 7x7, 4 images 36.9 -> 14.2, 32 images 37.5 -> 22.8; channels that come
+// in 8s (a per-element loader before): 72->72 3x3 at 28x28, 128 images 169 -> 29, 200->200 731 -> 110.
+#include <cmath>
+
 #include "kernels.h"
 #include "dtype.h"
-#include "igemm_side.h"
+#include "side_wide.h"
 
 namespace acc {
 namespace {
@@ -21,11 +31,6 @@ namespace {
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-constexpr int TM = 128, TN = 128;        // tile of a workgroup
-constexpr int CHUNK = 128;               // bytes of a GEMM row per K-chunk: 64 bf16
-constexpr int BKE = CHUNK / 2;           // elements of K per chunk
-constexpr int STAGE = TM * CHUNK;        // bytes of one operand's stage: 16 KB
 
 __device__ __forceinline__ v16f mfma_bf16(const v4u& a, const v4u& b, v16f c) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -65,53 +70,78 @@ __device__ __forceinline__ size_t out_row_offset(const ConvGeom& g, int m) {
   return ((size_t)(img * g.out_h + g.out_y0 + p * g.out_stride) * g.out_w + g.out_x0 + q * g.out_stride) * g.n_out;
 }
 
-// ACT: the epilogue adds a bias and applies a ReLU (never together with accumulation)
-template <bool ACT>
-__global__ __launch_bounds__(256) void igemm_bf16_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles,
-                                                          int main_grid) {
-  __shared__ __attribute__((aligned(1024))) char As[2 * STAGE];
-  __shared__ __attribute__((aligned(1024))) char Bs[2 * STAGE];
+// A workgroup of KS groups of WM x WN waves owns a tile of 32*MB*WM rows and 32*NB*WN columns, a wave MB x NB blocks of
+// 32 x 32.  BK values of K per chunk, NS LDS stages per group.
+template <int WM_, int WN_, int KS_, int MB_, int NB_, int BK_, int NS_, int WPE_> struct Cfg {
+  static constexpr int WM = WM_, WN = WN_, KS = KS_, MB = MB_, NB = NB_, BK = BK_, NS = NS_, WPE = WPE_;
+  static constexpr int GT = 64 * WM * WN, THREADS = GT * KS;         // threads of a group, of the workgroup
+  static constexpr int BM = 32 * MB * WM, BN = 32 * NB * WN;
+  static constexpr int ROWB = BK * 2, CPR = BK / 8;                  // bytes and 16-byte columns of a staged row
+  static constexpr int RPP = GT / CPR, AI = BM / RPP, BI = BN / RPP; // rows one load instruction of a group fills; instructions
+  static constexpr int A_BYTES = BM * ROWB, STAGE = (BM + BN) * ROWB;
+  static constexpr int MAIN = KS * NS * STAGE;
+  static constexpr int EPF = NB * 128 + 16;                          // bytes per row staged in fp32 by one wave (KS == 1)
+  static constexpr int PITCH = BN + 4;                               // floats per row staged by a group (KS > 1)
+  static constexpr int OUT = KS == 1 ? WM * WN * 32 * EPF : KS * BM * PITCH * 4;
+  static constexpr int LDS0 = MAIN > OUT ? MAIN : OUT, LDS = LDS0 > wide_scratch<bf16_t>(THREADS) ? LDS0 : wide_scratch<bf16_t>(THREADS);
+};
+
+template <int N> __device__ __forceinline__ void wait_loads() {      // at most N loads of the wave still on their way
+#if defined(__HIP_DEVICE_COMPILE__)
+  static_assert(N < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);  // and every LDS access done
+#endif
+}
+
+template <class C, bool ACT, bool RAGGED>
+__global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles,
+                                                                         int main_grid) {
+  __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
   if ((int)blockIdx.x >= main_grid) {
-    igemm_side_jobs<bf16_t>(g, (int)blockIdx.x - main_grid, As);
+    wide_side_jobs<bf16_t, C::THREADS>(g.side, g.flip, (int)blockIdx.x - main_grid, lds);
     return;
   }
 #if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int MB = C::MB, NB = C::NB, AI = C::AI, BI = C::BI, CPR = C::CPR, ROWB = C::ROWB, NS = C::NS, KS = C::KS;
   // XCD-aware tile order: each XCD gets a contiguous range of tiles (neighbours share operand rows in its L2)
   const int per_xcd = main_grid >> 3;
   const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (tile >= n_tiles) return;
   const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
-  const int m0 = tile_m * TM, n0 = tile_n * TN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+  const int m0 = tile_m * C::BM, n0 = tile_n * C::BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / C::GT);
+  const int gt = KS == 1 ? tid : tid & (C::GT - 1);
+  const int uwave = __builtin_amdgcn_readfirstlane(gt >> 6);
+  const int wm0 = (uwave / C::WN) * 32 * MB, wn0 = (uwave % C::WN) * 32 * NB;
 
-  v16f acc[2][2];
+  v16f acc[MB][NB];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < MB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-  const int n_chunks = K / BKE;                       // the launcher admits whole chunks only
-  constexpr int CPR = CHUNK / 16;                     // 16-byte columns per row: 8
-  constexpr int RPI = 4096 / CHUNK;                   // rows one load instruction of the 4 waves fills: 32
-  constexpr int AI = TM / RPI, BI = TN / RPI;         // 4 and 4
-  const int lrow = tid / CPR;                         // row of the lane's LDS slot within the first RPI rows
-  const int lcol = (tid & (CPR - 1)) ^ (lrow & (CPR - 1));   // 16-byte column that belongs into that slot
+  // ---- loads: global memory straight into LDS, 16 bytes per lane, rows unpadded with their 16-byte columns permuted
+  // by the row number (the lane fetches the column that belongs into its slot)
+  const int n_chunks = (K + C::BK - 1) / C::BK;
+  auto swz = [](int row) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
+  const int lrow = gt / CPR, lcol = (gt & (CPR - 1)) ^ swz(lrow);
+  static_assert(C::RPP % 16 == 0, "the permutation repeats every sixteen rows");
   const int margin = g.pad * g.wd + g.pad + g.pad_dx; // pixels; the descriptor starts that far before the tensor
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;           // beyond any descriptor range: reads as zero
   uint32_t a_voff[AI], a_mask[AI], b_voff[BI];
   const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 && g.pad_dx == 0 && g.p == g.h && g.q == g.wd;
 #pragma unroll
   for (int i = 0; i < AI; ++i) {
+    const int m = m0 + lrow + C::RPP * i;
     if (plain) {      // 1x1, stride 1, no padding: GEMM row m is pixel m
-      const int m = m0 + lrow + RPI * i;
       a_voff[i] = (uint32_t)(m < M ? m : 0) * (uint32_t)(g.c * 2) + lcol * 16;
       a_mask[i] = m < M ? 1u : 0u;
       continue;
     }
-    const RowPos rp = decode_row(g, m0 + lrow + RPI * i, M);
+    const RowPos rp = decode_row(g, m, M);
     a_voff[i] = (uint32_t)(rp.pix + rp.iy0 * g.wd + rp.ix0 + margin) * (uint32_t)(g.c * 2) + lcol * 16;
     uint32_t mask = 0;
     for (int kr = 0; kr < g.r; ++kr)
@@ -123,7 +153,7 @@ __global__ __launch_bounds__(256) void igemm_bf16_kernel(ConvGeom g, int M, int 
   }
 #pragma unroll
   for (int i = 0; i < BI; ++i) {
-    const int n = n0 + lrow + RPI * i;
+    const int n = n0 + lrow + C::RPP * i;
     b_voff[i] = (uint32_t)(n < g.n_out ? n : 0) * (uint32_t)(K * 2) + lcol * 16;   // beyond n_out: filter 0, never stored
   }
   const size_t margin_bytes = (size_t)margin * g.c * 2;
@@ -133,135 +163,237 @@ __global__ __launch_bounds__(256) void igemm_bf16_kernel(ConvGeom g, int M, int 
   __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(g.w), 0, (int)(uint32_t)((size_t)g.n_out * K * 2), 0x00020000);
   typedef __attribute__((address_space(3))) void* lds_ptr;
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
-  const uint32_t lds_a = (uint32_t)(size_t)As + uwave * 1024, lds_b = (uint32_t)(size_t)Bs + uwave * 1024;
-  int kr = 0, kt = 0, c0 = 0;     // tap and channel offset of the chunk whose loads are issued next (uniform)
-  auto issue = [&](int kc, int buf) {
-    const int tap = kr * g.s + kt;
-    const int soff_a = ((kr * g.wd + kt) * g.c + c0) * 2;
-    const int soff_b = kc * CHUNK;
+  char* const lds_g = lds + grp * (NS * C::STAGE);
+  const uint32_t lds_w = (uint32_t)(size_t)lds_g + uwave * 1024;
+  // the group's chunks, and where the next one to be loaded lies.  Whole chunks inside one tap (not RAGGED): the same for
+  // all lanes; else every lane follows the 16-byte column it loads
+  const int first = KS == 1 ? 0 : (int)((long)n_chunks * grp / KS);
+  const int mine = KS == 1 ? n_chunks : (int)((long)n_chunks * (grp + 1) / KS) - first;
+  const int rounds = KS == 1 ? n_chunks : (n_chunks + KS - 1) / KS;
+  const int cols = g.c >> 3;                          // 16-byte columns of a pixel
+  int tap, kt, col = 0, soff_b, toff;                 // toff: bytes from the row's first pixel
+  const int taps = g.r * g.s;
+  if constexpr (RAGGED) {
+    const int u = first * CPR + lcol;
+    tap = u / cols;
+    col = u - tap * cols;
+    soff_b = first * ROWB;
+  } else {                                            // the taps of 64 channels, then those of the next: rows stay in L2 between taps
+    const int c0 = first / taps;
+    tap = first - c0 * taps;
+    soff_b = tap * g.c * 2 + c0 * ROWB;
+    col = c0 * CPR;
+  }
+  {
+    const int kr = tap / g.s;
+    kt = tap - kr * g.s;
+    toff = ((kr * g.wd + kt) * cols + col - (RAGGED ? lcol : 0)) * 16;
+  }
+  int left = (K >> 3) - first * CPR - lcol;           // RAGGED: columns of K from the lane's on
+  const int row_jump = (g.wd - g.s) * g.c * 2;
+  const int back_a = g.r * g.wd * g.c * 2 - ROWB, back_b = K * 2 - ROWB;
+  auto issue = [&](int stage) {
+    const uint32_t at = lds_w + stage * C::STAGE;
+    const bool k_ok = !RAGGED || left > 0;
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
-      const uint32_t voff = ((a_mask[i] >> tap) & 1u) ? a_voff[i] : OUTSIDE;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(lds_a + buf * STAGE + i * 4096), 16, voff, soff_a, 0, 0);
+      const bool ok = ((a_mask[i] >> (tap & 31)) & 1u) != 0 && k_ok;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(at + i * (C::GT * 16)), 16,
+                                               ok ? a_voff[i] + (RAGGED ? (uint32_t)toff : 0u) : OUTSIDE, RAGGED ? 0 : toff, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < BI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(size_t)(lds_b + buf * STAGE + i * 4096), 16, b_voff[i], soff_b, 0, 0);
-    c0 += BKE;
-    if (c0 == g.c) {
-      c0 = 0;
-      if (++kt == g.s) { kt = 0; ++kr; }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(size_t)(at + C::A_BYTES + i * (C::GT * 16)), 16, k_ok ? b_voff[i] : OUTSIDE,
+                                               soff_b, 0, 0);
+    if constexpr (RAGGED) {
+      soff_b += ROWB;
+      left -= CPR;
+      col += CPR;
+      const bool wrap = col >= cols;                  // (cols >= CPR: once at most)
+      col -= wrap ? cols : 0;
+      tap += wrap ? 1 : 0;
+      kt += wrap ? 1 : 0;
+      const bool down = kt == g.s;
+      kt = down ? 0 : kt;
+      toff += ROWB + (down ? row_jump : 0);           // the next tap of a filter row is the next pixel
+    } else {
+      soff_b += g.c * 2;
+      toff += g.c * 2;
+      if (++kt == g.s) { kt = 0; toff += row_jump; }
+      if (++tap == taps) { tap = 0; toff -= back_a; soff_b -= back_b; }
     }
   };
-  // fragment of a row: 16-byte column c16 sits in slot c16 ^ (row % 8); the lane's rows differ by
-  // multiples of 32, so the XOR term is the same for both of its blocks
+  // ---- fragments: 16-byte column c16 of a row sits in slot c16 ^ swz(row); the lane's blocks lie multiples of 32 rows apart
+  constexpr int NG = C::BK / 16;
   const int ra = wm0 + (lane & 31), rb = wn0 + (lane & 31);
-  const int xa = ra & (CPR - 1), xb = rb & (CPR - 1);
-  // One chunk = four groups of 16 values of K, four MFMAs each.  The reads of group g+1 are issued among the MFMAs of group
-  // g, and the last group's MFMAs are held back until the next chunk's barrier has been passed, its first reads
-  // and the loads of the chunk after are on their way: the matrix cores have work queued while the wave waits.
-  // (256 -> 256 3x3 on 14x14, 512 images: 877 -> 903 TFLOP/s against one group's reads, then its MFMAs; 128 on 28x28: 691 -> 723.)
-  struct Frags { v4u a[2], b[2]; } F[2];
-  auto rd = [&](Frags& f, int buf, int g8) {
-    const char* as = As + buf * STAGE + ra * CHUNK;
-    const char* bs = Bs + buf * STAGE + rb * CHUNK;
+  const int xa = swz(ra), xb = swz(rb);
+  struct Frags { v4u a[MB], b[NB]; } F[2];
+  auto rd = [&](Frags& f, const char* st, int g8) {
     const int c16 = g8 * 2 + (lane >> 5);
+    const char* as = st + ra * ROWB + ((c16 ^ xa) << 4);
+    const char* bs = st + C::A_BYTES + rb * ROWB + ((c16 ^ xb) << 4);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      f.a[i] = *reinterpret_cast<const v4u*>(as + i * 32 * CHUNK + ((c16 ^ xa) << 4));
-      f.b[i] = *reinterpret_cast<const v4u*>(bs + i * 32 * CHUNK + ((c16 ^ xb) << 4));
-    }
+    for (int i = 0; i < MB; ++i) f.a[i] = *reinterpret_cast<const v4u*>(as + i * 32 * ROWB);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) f.b[j] = *reinterpret_cast<const v4u*>(bs + j * 32 * ROWB);
   };
   auto mm = [&](const Frags& f) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(f.b[j], f.a[i], acc[i][j]);   // transposed block, see the epilogue
+      for (int j = 0; j < NB; ++j) acc[i][j] = mfma_bf16(f.b[j], f.a[i], acc[i][j]);   // transposed block, see the epilogue
   };
-  auto chunk = [&](int buf, bool prev, int next_kc) {
+  // One chunk = BK/16 groups of 16 values of K.  The reads of group g+1 are issued among the MFMAs of group g, and the last
+  // group's MFMAs are held back until the next chunk's barrier has been passed, its first reads and the loads of a later
+  // chunk are on their way: the matrix cores have work queued while the wave waits.
+  auto chunk = [&](int stage, bool prev, bool more, int to) {
+    const char* st = lds_g + stage * C::STAGE;
     __builtin_amdgcn_sched_barrier(0);
-    rd(F[0], buf, 0);
+    rd(F[0], st, 0);
     __builtin_amdgcn_sched_barrier(0);
+    if (more) issue(to);
     if (prev) mm(F[1]);
     __builtin_amdgcn_sched_barrier(0);
-    if (next_kc >= 0) issue(next_kc, buf ^ 1);
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g8 = 0; g8 < 3; ++g8) {
-      rd(F[(g8 + 1) & 1], buf, g8 + 1);
+    for (int g8 = 0; g8 + 1 < NG; ++g8) {
+      rd(F[(g8 + 1) & 1], st, g8 + 1);
       mm(F[g8 & 1]);
+      constexpr int RD = MB + NB, MF = MB * NB;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < RD; ++u) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, MF / RD > 0 ? MF / RD : 1, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    static_assert(NG % 2 == 0, "the held-back group is F[1]");
   };
-  // The barrier that opens chunk kc says two things: every wave's part of chunk kc has landed
-  // in LDS (each wave waits for its own loads first), and every wave is done with chunk kc-1,
-  // whose stage the loads of chunk kc+1 may now overwrite (its held-back fragments are in registers).
-  issue(0, 0);
-  int kc = 0;
-  for (; kc + 2 <= n_chunks; kc += 2) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wave's loads are in LDS
-    __syncthreads();
-    chunk(0, kc > 0, kc + 1);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    chunk(1, true, kc + 2 < n_chunks ? kc + 2 : -1);
+  // What opens chunk j: this wave's loads of chunk j have landed (those of later chunks may be on their way), and, where a
+  // group has several waves, a barrier: everybody's have, and everybody is done with chunk j-1, whose stage the next loads overwrite.
+  constexpr int L = AI + BI;
+  auto open = [&](int j) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int later = mine - 1 - j;                   // chunks behind this one that can have been issued: NS - 2 at most
+    if (NS > 3 && later >= 2) wait_loads<(NS > 3 ? 2 * L : 0)>();
+    else if (NS > 2 && later >= 1) wait_loads<(NS > 2 ? L : 0)>();
+    else wait_loads<0>();
+    if constexpr (C::GT > 64) __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(NS >= 2 && NS <= 4, "open() knows up to two later chunks");
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (s < mine) issue(s);
+  int stage = 0, to = NS - 1;
+  for (int j = 0; j < rounds; ++j) {
+    open(j);
+    if (KS == 1 || j < mine) chunk(stage, j > 0, j + NS - 1 < mine, to);
+    stage = stage + 1 == NS ? 0 : stage + 1;
+    to = to + 1 == NS ? 0 : to + 1;
   }
-  if (kc < n_chunks) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    chunk(0, kc > 0, -1);
-  }
-  mm(F[1]);
+  if (KS == 1 || mine > 0) mm(F[1]);
 
   // Epilogue.  The blocks were accumulated transposed (filter fragment first): register v of a
   // lane holds output channel 8*(v/4) + 4*(lane/32) + v%4 of GEMM row lane%32 of its block, i.e.
-  // four consecutive channels of one row per group of four registers.  They are staged in LDS,
-  // one region per wave, and the wave reads whole rows back: eight channels per lane, 128
-  // contiguous bytes of a row per eight lanes, one 16-byte store each.  Plain results are rounded
-  // to bf16 before staging (8-byte LDS writes, one pass over the wave's 64 rows); results that
-  // get a bias and a ReLU, or are added to what the tensor holds, are staged in fp32 (two passes
-  // of 32 rows) so that they are rounded once, after the addition.
-  __syncthreads();                                   // every wave is done reading the last chunk
-  char* stg = (wave < 2 ? As : Bs) + (wave & 1) * STAGE;        // 16 KB per wave
+  // four consecutive channels of one row per group of four registers.  They are staged in LDS and read back as whole rows:
+  // eight channels per lane, one 16-byte store each.
+  wait_loads<0>();
+  __builtin_amdgcn_s_barrier();                      // every wave is done reading the last chunk
+  asm volatile("" ::: "memory");
   const bool dense = g.out_stride == 1 && g.out_h == g.p && g.out_w == g.q;
-  const int c8 = lane & 7;                           // the lane's piece of a row: channels 8*c8 .. 8*c8+7
-  const int n = n0 + wn0 + 8 * c8;
-  const bool n_ok = n < g.n_out;                     // (n_out is a multiple of 8: a piece is stored whole or not at all)
   typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
   typedef float v2f __attribute__((ext_vector_type(2)));
   auto pack2 = [](float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));   // round to nearest even
   };
+  auto place = [&](int m, int n) { return static_cast<bf16_t*>(g.out) + (dense ? (size_t)m * g.n_out : out_row_offset(g, m)) + n; };
+  // eight fp32 results: bias and ReLU, or the old values, then one rounding
+  auto finish = [&](float (&f)[8], bf16_t* o, const float (&bias8)[8]) {
+    if constexpr (ACT) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        f[e] += bias8[e];
+        if (g.relu) f[e] = fmaxf(f[e], 0.f);
+      }
+    } else if (g.accumulate) {
+      const v4u old = *reinterpret_cast<const v4u*>(o);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        f[2 * w] += __uint_as_float(old[w] << 16);
+        f[2 * w + 1] += __uint_as_float(old[w] & 0xffff0000u);
+      }
+    }
+    v4u res;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) res[w] = pack2(f[2 * w], f[2 * w + 1]);
+    *reinterpret_cast<v4u*>(o) = res;
+  };
+  if constexpr (KS > 1) {
+    // the groups' sums side by side in fp32; every thread adds up pieces of eight channels, the groups in their order
+    float* red = reinterpret_cast<float*>(lds) + grp * (C::BM * C::PITCH);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const v16f& c = acc[i][j];
+          *reinterpret_cast<float4*>(red + (wm0 + 32 * i + (lane & 31)) * C::PITCH + wn0 + 32 * j + 8 * q4 + 4 * (lane >> 5)) =
+              make_float4(c[4 * q4], c[4 * q4 + 1], c[4 * q4 + 2], c[4 * q4 + 3]);
+        }
+    __syncthreads();
+    constexpr int PPR = C::BN / 8;                   // pieces of a row
+#pragma unroll
+    for (int pc = tid; pc < C::BM * PPR; pc += C::THREADS) {
+      const int row = pc / PPR, c8 = pc - row * PPR, m = m0 + row, n = n0 + 8 * c8;
+      if (m >= M || n >= g.n_out) continue;          // (n_out is a multiple of 8: a piece is stored whole or not at all)
+      const float* p = reinterpret_cast<const float*>(lds) + row * C::PITCH + 8 * c8;
+      float f[8] = {0, 0, 0, 0, 0, 0, 0, 0}, bias8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int u = 0; u < KS; ++u) {
+        const float4 lo = *reinterpret_cast<const float4*>(p + u * (C::BM * C::PITCH)), hi = *reinterpret_cast<const float4*>(p + u * (C::BM * C::PITCH) + 4);
+        f[0] += lo.x; f[1] += lo.y; f[2] += lo.z; f[3] += lo.w;
+        f[4] += hi.x; f[5] += hi.y; f[6] += hi.z; f[7] += hi.w;
+      }
+      if constexpr (ACT) {
+        if (g.bias) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) bias8[e] = g.bias[n + e];
+        }
+      }
+      finish(f, place(m, n), bias8);
+    }
+    return;
+  }
+  // One region per wave, 32 rows at a time.  Plain results are rounded to bf16 before staging; results that
+  // get a bias and a ReLU, or are added to what the tensor holds, are staged in fp32, so that they are rounded once, after
+  // the addition.
+  char* stg = lds + uwave * (32 * C::EPF);
+  constexpr int PPR = NB * 4, RPI = 64 / PPR, IT = 32 / RPI;      // pieces of a row, rows per instruction, instructions
+  const int c8 = lane % PPR, prow = lane / PPR;
+  const int n = n0 + wn0 + 8 * c8;
+  const bool n_ok = n < g.n_out;                     // (n_out is a multiple of 8: a piece is stored whole or not at all)
   if (!ACT && !g.accumulate) {
-    constexpr int EP = 144;                          // bytes per staged row: 128 + 16 (rows on different banks)
+    constexpr int EP = NB * 64 + 16;                 // bytes per staged row (rows on different banks)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
           const v16f& c = acc[i][j];
           uint2 pk;
           pk.x = pack2(c[4 * q4], c[4 * q4 + 1]);
           pk.y = pack2(c[4 * q4 + 2], c[4 * q4 + 3]);
-          const int row = 32 * i + (lane & 31), col = 32 * j + 8 * q4 + 4 * (lane >> 5);
-          *reinterpret_cast<uint2*>(stg + row * EP + col * 2) = pk;
+          *reinterpret_cast<uint2*>(stg + (lane & 31) * EP + (32 * j + 8 * q4 + 4 * (lane >> 5)) * 2) = pk;
         }
-    if (!n_ok) return;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int row = (lane >> 3) + 8 * it;
-      const int m = m0 + wm0 + row;
-      if (m >= M) continue;
-      const v4u piece = *reinterpret_cast<const v4u*>(stg + row * EP + c8 * 16);
-      bf16_t* o = static_cast<bf16_t*>(g.out) + (dense ? (size_t)m * g.n_out : out_row_offset(g, m)) + n;
-      *reinterpret_cast<v4u*>(o) = piece;
+      for (int it = 0; it < IT; ++it) {
+        const int row = prow + RPI * it, m = m0 + wm0 + 32 * i + row;
+        if (m >= M || !n_ok) continue;
+        *reinterpret_cast<v4u*>(place(m, n)) = *reinterpret_cast<const v4u*>(stg + row * EP + c8 * 16);
+      }
     }
     return;
   }
@@ -272,94 +404,141 @@ __global__ __launch_bounds__(256) void igemm_bf16_kernel(ConvGeom g, int M, int 
       for (int e = 0; e < 8; ++e) bias8[e] = g.bias[n + e];
     }
   }
-  constexpr int EPF = 272;                           // bytes per staged fp32 row: 256 + 16
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < MB; ++i) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const v16f& c = acc[i][j];
-        const int row = lane & 31, col = 32 * j + 8 * q4 + 4 * (lane >> 5);
-        *reinterpret_cast<float4*>(stg + row * EPF + col * 4) = make_float4(c[4 * q4], c[4 * q4 + 1], c[4 * q4 + 2], c[4 * q4 + 3]);
+        *reinterpret_cast<float4*>(stg + (lane & 31) * C::EPF + (32 * j + 8 * q4 + 4 * (lane >> 5)) * 4) =
+            make_float4(c[4 * q4], c[4 * q4 + 1], c[4 * q4 + 2], c[4 * q4 + 3]);
       }
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int row = (lane >> 3) + 8 * it;
-      const int m = m0 + wm0 + 32 * i + row;
+    for (int it = 0; it < IT; ++it) {
+      const int row = prow + RPI * it, m = m0 + wm0 + 32 * i + row;
       if (m >= M || !n_ok) continue;
-      const float4 lo = *reinterpret_cast<const float4*>(stg + row * EPF + c8 * 32);
-      const float4 hi = *reinterpret_cast<const float4*>(stg + row * EPF + c8 * 32 + 16);
+      const float4 lo = *reinterpret_cast<const float4*>(stg + row * C::EPF + c8 * 32);
+      const float4 hi = *reinterpret_cast<const float4*>(stg + row * C::EPF + c8 * 32 + 16);
       float f[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-      bf16_t* o = static_cast<bf16_t*>(g.out) + (dense ? (size_t)m * g.n_out : out_row_offset(g, m)) + n;
-      if constexpr (ACT) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          f[e] += bias8[e];
-          if (g.relu) f[e] = fmaxf(f[e], 0.f);
-        }
-      } else {
-        const v4u old = *reinterpret_cast<const v4u*>(o);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          f[2 * w] += __uint_as_float(old[w] << 16);
-          f[2 * w + 1] += __uint_as_float(old[w] & 0xffff0000u);
-        }
-      }
-      v4u res;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) res[w] = pack2(f[2 * w], f[2 * w + 1]);
-      *reinterpret_cast<v4u*>(o) = res;
+      finish(f, place(m, n), bias8);
     }
   }
 #else
-  (void)Bs; (void)&mfma_bf16; (void)&decode_row; (void)&out_row_offset;
+  (void)&mfma_bf16; (void)&decode_row; (void)&out_row_offset;
 #endif
+}
+
+template <class C>
+void launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
+  const int tm = (M + C::BM - 1) / C::BM, tn = (g.n_out + C::BN - 1) / C::BN, tiles = tm * tn, main_grid = (tiles + 7) / 8 * 8;
+  const dim3 grid((unsigned)(main_grid + wide_side_blocks(g.side, g.flip, C::THREADS)));
+  const bool ragged = g.c % C::BK != 0, act = g.bias || g.relu;
+  if (probe->before) (void)hipEventRecord(probe->before, st);
+#define ACC_BF16(A, R) hipLaunchKernelGGL((igemm_bf16_kernel<C, A, R>), grid, dim3(C::THREADS), 0, st, g, M, K, tn, tiles, main_grid)
+  if (act) { if (ragged) ACC_BF16(true, true); else ACC_BF16(true, false); }
+  else { if (ragged) ACC_BF16(false, true); else ACC_BF16(false, false); }
+#undef ACC_BF16
+  if (probe->after) (void)hipEventRecord(probe->after, st);
+}
+
+typedef Cfg<2, 4, 1, 4, 2, 64, 2, 2> T256x256;
+typedef Cfg<2, 4, 1, 2, 2, 64, 3, 2> T128x256;
+typedef Cfg<2, 2, 1, 4, 2, 32, 3, 2> T256x128;
+typedef Cfg<2, 2, 1, 2, 2, 64, 2, 2> T128x128;
+typedef Cfg<2, 2, 1, 2, 1, 64, 2, 2> T128x64;
+typedef Cfg<2, 2, 1, 1, 1, 64, 2, 2> T64x64;
+typedef Cfg<2, 2, 1, 1, 1, 64, 4, 2> T64x64s4;         // four LDS stages: long reductions of few tiles
+typedef Cfg<2, 1, 4, 1, 2, 64, 2, 2> T64x64k4;         // four groups of two waves
+typedef Cfg<1, 1, 4, 2, 2, 32, 2, 1> T64x64k4n;        // four groups of one wave, chunks of 32 values
+typedef Cfg<1, 1, 8, 1, 1, 32, 4, 2> T32x32k8;         // eight groups of one wave
+
+// Which kernel: the one with the smallest predicted time, in microseconds.  With steps = chunks of K per group of waves, and tiles
+// counted on the compute unit with the most,
+//   base + (compute^2 + memory^2)^(1/2),
+//   compute = one workgroup per compute unit: first + first_step * steps + (tiles - 1) * (next + next_step * steps),
+//             several (r <= per_cu resident): the sum over rounds of max(first + first_step * steps, r * (next + next_step * steps)),
+// taps more per tile for filters larger than 1x1, memory = per_mb_read * MB of both operands + per_mb_written * MB of the result,
+// each once.  The constants are fitted to 420 launches (the layers of the ResNets at minibatches 1 to 512 and random ones with
+// widths in 8s, every kernel on each, replayed from a graph, six sets of tensors in turn, so that large operands come from memory):
+// median errors of 3 to 6 %, the choice is within 0.8 % of the best on average, 26 % at most.  Without the 32 x 32 kernel the
+// average is 6 %, without the 256 x 256 one 1.8 %.  A function of the shape and the alignment only.
+struct Kind {
+  const char* name;
+  int bm, bn, ks, kc, per_cu;
+  double base, first, first_step, next, next_step, taps, per_mb_read, per_mb_written;
+};
+enum { K256x256 = 0, K128x256, K256x128, K128x128, K128x64, K64x64, K64x64S4, K64x64K4, K64x64K4N, K32x32K8, KINDS };
+constexpr Kind kKinds[KINDS] = {
+    {"igemm_bf16 256x256", 256, 256, 1, 64, 1, 4.714, 0.0, 1.277, 1.809, 1.818, 2.416, 0.203, 0.223},
+    {"igemm_bf16 128x256", 128, 256, 1, 64, 1, 3.027, 0.868, 0.730, 1.668, 0.954, 1.056, 0.189, 0.266},
+    {"igemm_bf16 256x128", 256, 128, 1, 32, 2, 3.643, 0.662, 0.481, 0.621, 0.478, 1.509, 0.179, 0.267},
+    {"igemm_bf16 128x128", 128, 128, 1, 64, 2, 2.311, 1.132, 0.623, 0.613, 0.487, 1.003, 0.169, 0.287},
+    {"igemm_bf16 128x64", 128, 64, 1, 64, 3, 1.983, 0.954, 0.555, 0.914, 0.298, 0.569, 0.166, 0.171},
+    {"igemm_bf16 64x64", 64, 64, 1, 64, 4, 2.097, 0.506, 0.484, 0.561, 0.176, 0.118, 0.161, 0.157},
+    {"igemm_bf16 64x64, four stages", 64, 64, 1, 64, 2, 1.646, 1.345, 0.310, 0.850, 0.196, 0.472, 0.094, 0.332},
+    {"igemm_bf16 64x64, four pairs", 64, 64, 4, 64, 1, 3.394, 0.0, 1.033, 2.060, 0.957, 1.338, 0.208, 0.249},
+    {"igemm_bf16 64x64, four waves", 64, 64, 4, 32, 2, 2.286, 1.275, 0.586, 0.914, 0.503, 0.035, 0.136, 0.431},
+    {"igemm_bf16 32x32, eight waves", 32, 32, 8, 32, 1, 0.0, 3.255, 0.543, 1.221, 0.487, 0.520, 0.271, 2.084},
+};
+double predicted_us(const Kind& k, const ConvGeom& g, long M, long K) {
+  const long N = g.n_out;
+  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
+  const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
+  const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = g.r * g.s > 1 ? k.taps * most : 0;
+  const double read = 2e-6 * ((double)g.n_img * g.h * g.wd * g.c + (double)N * K), written = 2e-6 * (double)M * N;
+  const double memory = k.per_mb_read * read + k.per_mb_written * written;
+  auto round = [&](long r) { return r == 0 ? 0.0 : first > r * next ? first : r * next; };
+  const double compute = more + (k.per_cu == 1 ? first + (most - 1) * next : (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu));
+  return k.base + std::sqrt(compute * compute + memory * memory);
+}
+int best_kind(const ConvGeom& g, long M, long K) {
+  int best = -1;
+  double us = 0;
+  for (int v = 0; v < KINDS; ++v) {
+    if (g.c < kKinds[v].kc) continue;                    // a chunk spans two taps at most
+    const double t = predicted_us(kKinds[v], g, M, K);
+    if (best < 0 || t < us) { best = v; us = t; }
+  }
+  return best;
 }
 
 }  // namespace
 
 bool conv_igemm_bf16_takes(const ConvGeom& g, long M, long K) {
   if (g.dtype != DT_BF16) return false;
-  // whole 64-channel chunks inside one tap, at most 32 taps, both operands within 32-bit byte ranges
-  // (the last bytes stay free for the offset that stands for "outside"), 16-byte aligned tensors;
-  // at least 128 output channels and enough rows that 128 x 128 tiles fill the chip; no fused
+  // channels that come in 8s, at least a chunk of 32 of them, at most 32 taps, both operands within 32-bit byte ranges
+  // (the last bytes stay free for the offset that stands for "outside"), 16-byte aligned tensors and rows of the result; no fused
   // batch-norm sums (those belong to fp32 storage)
   const long margin_px = (long)g.pad * g.wd + g.pad + g.pad_dx;
-  if (g.c % BKE != 0 || g.r * g.s > 32 || g.n_out < TN || g.n_out % 8 != 0 || g.stats || g.bnb.sums) return false;
+  if (g.c % 8 != 0 || g.c < 32 || g.r * g.s > 32 || g.n_out % 8 != 0 || g.stats || g.bnb.sums) return false;
   if ((margin_px + (long)g.n_img * g.h * g.wd) * g.c * 2 > 0xFFFFFF00L || (long)g.n_out * K * 2 > 0xFFFFFF00L) return false;
   if ((reinterpret_cast<uintptr_t>(g.in) & 15) || (reinterpret_cast<uintptr_t>(g.w) & 15) ||
       (reinterpret_cast<uintptr_t>(g.out) & 15)) return false;
-  const long tiles = ((M + TM - 1) / TM) * ((g.n_out + TN - 1) / TN);
-  return tiles >= 256;
+  return ((M + 31) / 32) * ((g.n_out + 31) / 32) <= (1L << 30);
 }
 
 hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
-  const int tm = (M + TM - 1) / TM, tn = (g.n_out + TN - 1) / TN;
-  const long tiles = (long)tm * tn;
-  if (tiles <= 0 || tiles > (1L << 30) || K % BKE != 0) return hipErrorInvalidValue;
-  const int main_grid = (int)((tiles + 7) / 8 * 8);
-  long side_blocks = 0;
-  if (g.side.count) {
-    if (!g.side.part || !g.side.dw || g.side.splits < 1) return hipErrorInvalidValue;
-    side_blocks = (long)((g.side.count + 1023) / 1024);
-  }
+  if (g.side.count && (!g.side.part || !g.side.dw || g.side.splits < 1)) return hipErrorInvalidValue;
   if ((g.bias || g.relu) && g.accumulate) return hipErrorInvalidValue;
-  if (g.flip.wt) {
-    if (!g.flip.w || g.flip.cout <= 0 || g.flip.cin <= 0 || g.flip.r <= 0 || g.flip.s <= 0) return hipErrorInvalidValue;
-    side_blocks += (long)((g.flip.cin + 31) / 32) * ((g.flip.cout + 31) / 32) * g.flip.r * g.flip.s;
-  }
-  if (main_grid + side_blocks > (1L << 30)) return hipErrorInvalidValue;
+  if (g.flip.wt && (!g.flip.w || g.flip.cout <= 0 || g.flip.cin <= 0 || g.flip.r <= 0 || g.flip.s <= 0)) return hipErrorInvalidValue;
+  if (wide_side_blocks(g.side, g.flip, 256) > (1L << 30) - 8) return hipErrorInvalidValue;
+  const int kind = best_kind(g, M, K);
   probe->variant = V_IGEMM_BF16;
-  probe->kernel = "igemm_bf16 128x128";
+  probe->kernel = kKinds[kind].name;
   if (probe->dry) return hipSuccess;
-  if (probe->before) (void)hipEventRecord(probe->before, st);
-  const dim3 grid((unsigned)(main_grid + side_blocks));
-  if (g.bias || g.relu)
-    hipLaunchKernelGGL(igemm_bf16_kernel<true>, grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
-  else
-    hipLaunchKernelGGL(igemm_bf16_kernel<false>, grid, dim3(256), 0, st, g, M, K, tn, (int)tiles, main_grid);
-  if (probe->after) (void)hipEventRecord(probe->after, st);
+  switch (kind) {
+    case K256x256: launch<T256x256>(g, M, K, st, probe); break;
+    case K128x256: launch<T128x256>(g, M, K, st, probe); break;
+    case K256x128: launch<T256x128>(g, M, K, st, probe); break;
+    case K128x128: launch<T128x128>(g, M, K, st, probe); break;
+    case K128x64: launch<T128x64>(g, M, K, st, probe); break;
+    case K64x64: launch<T64x64>(g, M, K, st, probe); break;
+    case K64x64S4: launch<T64x64s4>(g, M, K, st, probe); break;
+    case K64x64K4: launch<T64x64k4>(g, M, K, st, probe); break;
+    case K64x64K4N: launch<T64x64k4n>(g, M, K, st, probe); break;
+    default: launch<T32x32k8>(g, M, K, st, probe); break;
+  }
   return hipGetLastError();
 }
 

@@ -543,10 +543,8 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   [[maybe_unused]] constexpr int KS = D::KS, GT = D::GT;
   __shared__ __attribute__((aligned(1024))) char lds[D::LDS];
   if ((int)blockIdx.x >= main_grid) {
-    static_assert(D::LDS >= kWideScratch, "side jobs");
-    const int id = (int)blockIdx.x - main_grid, sums = (int)wide_reduce_blocks(g.side.count);
-    if (id < sums) reduce_wide(g.side, id);
-    else flip_wide(g.flip, id - sums, lds);
+    static_assert(D::LDS >= wide_scratch<float>(512), "side jobs");
+    wide_side_jobs<float, 512>(g.side, g.flip, (int)blockIdx.x - main_grid, lds);
     return;
   }
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -859,7 +857,7 @@ void launch_deep(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* p
   probe->kernel = WINDOW ? "igemm_x3_deep window 128x64" : WM * WN == 4 ? "igemm_x3_deep 128x128" : WM * WN == 2 ? "igemm_x3_deep 128x64"
                                                                                                               : "igemm_x3_deep 64x64";
   if (probe->dry) return;
-  const long side_blocks = wide_reduce_blocks(g.side.count) + (g.flip.wt ? wide_flip_blocks(g.flip.cout, g.flip.cin, g.flip.r, g.flip.s) : 0);
+  const long side_blocks = wide_side_blocks(g.side, g.flip, 512);
   using D = Deep<WM, WN, WINDOW>;
   const int tm = (M + D::BM - 1) / D::BM, tn = (g.n_out + D::BN - 1) / D::BN;
   const int tiles = tm * tn, main_grid = (tiles + 7) / 8 * 8;

@@ -74,10 +74,8 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   [[maybe_unused]] constexpr int KS = D::KS, GT = D::GT;
   __shared__ __attribute__((aligned(1024))) char lds[D::LDS];
   if ((int)blockIdx.x >= main_grid) {
-    static_assert(D::LDS >= kWideScratch, "side jobs");
-    const int id = (int)blockIdx.x - main_grid, sums = (int)wide_reduce_blocks(g.side.count);
-    if (id < sums) reduce_wide(g.side, id);
-    else flip_wide(FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, id - sums, lds);
+    static_assert(D::LDS >= wide_scratch<float>(512), "side jobs");
+    wide_side_jobs<float, 512>(g.side, FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, (int)blockIdx.x - main_grid, lds);
     return;
   }
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -381,7 +379,7 @@ WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s, int max_
 }
 
 hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st) {
-  const long side_blocks = wide_reduce_blocks(g.side.count) + (g.flip_wt ? wide_flip_blocks(g.cout, g.cin, g.r, g.s) : 0);
+  const long side_blocks = wide_side_blocks(g.side, FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, 512);
   const int tiles = c.tiles_co * c.tiles_j, main_grid = (int)(((long)tiles * c.splits + 7) / 8 * 8);
   const dim3 grid((unsigned)(main_grid + side_blocks));
   const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0;

@@ -112,7 +112,7 @@ struct LaunchProbe {
   bool dry = false;
 };
 hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe = nullptr);
-// The 128 x 128 kernel for bf16 storage (conv_igemm_bf16.hip): whether it takes this launch (a
+// The kernels for bf16 storage (conv_igemm_bf16.hip): whether they take this launch (a
 // function of the shape and the alignment only), and the launch itself; conv_igemm() routes to it.
 bool conv_igemm_bf16_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);

@@ -1,5 +1,5 @@
-// Side jobs of the launches whose workgroups have 512 threads and most of a compute unit's LDS: one such workgroup
-// runs per compute unit, so each takes a large piece with all its loads in flight (as 256-thread pieces, one 32 x 32
+// Side jobs of the launches whose workgroups have 256 or 512 threads and most of a compute unit's LDS: one or two such
+// workgroups run per compute unit, so each takes a large piece with all its loads in flight (as 256-thread pieces, one 32 x 32
 // tile or 1024 elements each, the 2304 tiles of a 512->512 3x3 filter took nine rounds of the chip: the 1x1 512->2048
 // data gradient that carries them 51.9 us against 31.4 for the same product without).
 #pragma once
@@ -12,35 +12,39 @@ namespace acc {
 
 // elements of a weight gradient per workgroup: small gradients come in many parts, and their workgroups take fewer
 // elements, one per thread (64->256 1x1, 16384 elements in 128 parts: the launch that carries them 56 us with
-// 8192 elements per workgroup, 41 with 512)
-__host__ __device__ inline int wide_reduce_piece(size_t count) { return count >= (size_t)8192 * 32 ? 8192 : 512; }
-constexpr int kWideFlip = 16;          // 32 x 32 tiles of a filter per workgroup
-constexpr int kWideScratch = kWideFlip * 32 * 33 * 4;
+// 8192 elements per workgroup of 512 threads, 41 with 512)
+__host__ __device__ constexpr int wide_reduce_piece(size_t count, int threads) { return count >= (size_t)8192 * 32 ? threads * 16 : threads; }
+__host__ __device__ constexpr int wide_flip(int threads) { return threads / 32; }          // 32 x 32 tiles of a filter per workgroup
+template <class T> constexpr int wide_scratch(int threads) { return wide_flip(threads) * 32 * 33 * (int)sizeof(T); }
 
 inline long flip_tiles(int cout, int cin, int r, int s) { return (long)((cin + 31) / 32) * ((cout + 31) / 32) * r * s; }
-__host__ __device__ inline long wide_reduce_blocks(size_t count) {
-  const size_t piece = wide_reduce_piece(count);
+__host__ __device__ inline long wide_reduce_blocks(size_t count, int threads) {
+  const size_t piece = wide_reduce_piece(count, threads);
   return (long)((count + piece - 1) / piece);
 }
-inline long wide_flip_blocks(int cout, int cin, int r, int s) { return (flip_tiles(cout, cin, r, s) + kWideFlip - 1) / kWideFlip; }
+// workgroups of both jobs
+inline long wide_side_blocks(const ReduceJob& j, const FlipJob& f, int threads) {
+  return wide_reduce_blocks(j.count, threads) + (f.wt ? (flip_tiles(f.cout, f.cin, f.r, f.s) + wide_flip(threads) - 1) / wide_flip(threads) : 0);
+}
 
 // piece `id` of the job
+template <int THREADS>
 __device__ __forceinline__ void reduce_wide(const ReduceJob& j, int id) {
   constexpr int U = 4;
   const int tid = threadIdx.x;
-  if (wide_reduce_piece(j.count) == 512) {
-    const size_t i = (size_t)id * 512 + tid;
+  if (wide_reduce_piece(j.count, THREADS) == THREADS) {
+    const size_t i = (size_t)id * THREADS + tid;
     if (i < j.count) j.dw[i] = sum_parts1(j.part + i, j.count, j.splits);
     return;
   }
-  const size_t base = (size_t)id * 8192 + (size_t)tid * 4;
+  const size_t base = (size_t)id * (THREADS * 16) + (size_t)tid * 4;
   if ((j.count & 3) == 0) {
     size_t at[U];
     bool ok[U];
     float4 sum[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const size_t i = base + (size_t)u * 2048;
+      const size_t i = base + (size_t)u * (THREADS * 4);
       ok[u] = i < j.count;
       at[u] = ok[u] ? i : 0;
       sum[u] = *reinterpret_cast<const float4*>(j.part + at[u]);
@@ -68,20 +72,22 @@ __device__ __forceinline__ void reduce_wide(const ReduceJob& j, int id) {
       if (ok[u]) *reinterpret_cast<float4*>(j.dw + at[u]) = sum[u];
     return;
   }
-  for (int u = 0; u < U; ++u) add_parts4(j, base + (size_t)u * 2048);
+  for (int u = 0; u < U; ++u) add_parts4(j, base + (size_t)u * (THREADS * 4));
 }
 
-// sixteen 32 x 32 (co, ci) tiles of a flipped, transposed fp32 filter; scratch: kWideScratch bytes of LDS
+// THREADS / 32 tiles of 32 x 32 (co, ci) of a flipped, transposed filter; scratch: wide_scratch<T>(THREADS) bytes of LDS
+template <class T, int THREADS>
 __device__ __forceinline__ void flip_wide(const FlipJob& f, int id, void* scratch) {
+  constexpr int SETS = THREADS / 256, FLIP = wide_flip(THREADS);     // 256 threads per tile, eight tiles each
   const int tid = threadIdx.x, tx = tid & 31, ty = (tid >> 5) & 7, hi = tid >> 8;
   const int bx = (f.cin + 31) / 32, by = (f.cout + 31) / 32, tiles = bx * by * f.r * f.s;
-  float (*lds)[32][33] = reinterpret_cast<float (*)[32][33]>(scratch);
-  const float* w = static_cast<const float*>(f.w);
-  float* wt = static_cast<float*>(f.wt);
-  float v[kWideFlip / 2][4];
+  T (*lds)[32][33] = reinterpret_cast<T (*)[32][33]>(scratch);
+  const T* w = static_cast<const T*>(f.w);
+  T* wt = static_cast<T*>(f.wt);
+  T v[8][4];
 #pragma unroll
-  for (int u = 0; u < kWideFlip / 2; ++u) {
-    const int t = id * kWideFlip + 2 * u + hi, tap = t / (bx * by), rem = t - tap * (bx * by);
+  for (int u = 0; u < 8; ++u) {
+    const int t = id * FLIP + SETS * u + hi, tap = t / (bx * by), rem = t - tap * (bx * by);
     const int co0 = (rem / bx) * 32, ci0 = (rem - (rem / bx) * bx) * 32;
     const int src = (f.r - 1 - tap / f.s) * f.s + (f.s - 1 - tap % f.s);
 #pragma unroll
@@ -92,20 +98,28 @@ __device__ __forceinline__ void flip_wide(const FlipJob& f, int id, void* scratc
     }
   }
 #pragma unroll
-  for (int u = 0; u < kWideFlip / 2; ++u)
+  for (int u = 0; u < 8; ++u)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) lds[2 * u + hi][ty + 8 * i][tx] = v[u][i];
+    for (int i = 0; i < 4; ++i) lds[SETS * u + hi][ty + 8 * i][tx] = v[u][i];
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < kWideFlip / 2; ++u) {
-    const int t = id * kWideFlip + 2 * u + hi, tap = t / (bx * by), rem = t - tap * (bx * by);
+  for (int u = 0; u < 8; ++u) {
+    const int t = id * FLIP + SETS * u + hi, tap = t / (bx * by), rem = t - tap * (bx * by);
     const int co0 = (rem / bx) * 32, ci0 = (rem - (rem / bx) * bx) * 32;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int ci = ci0 + ty + 8 * i, co = co0 + tx;
-      if (t < tiles && ci < f.cin && co < f.cout) wt[((size_t)ci * f.r * f.s + tap) * f.cout + co] = lds[2 * u + hi][tx][ty + 8 * i];
+      if (t < tiles && ci < f.cin && co < f.cout) wt[((size_t)ci * f.r * f.s + tap) * f.cout + co] = lds[SETS * u + hi][tx][ty + 8 * i];
     }
   }
+}
+
+// workgroup `id` of those that do a launch's side jobs; every thread of it is here
+template <class T, int THREADS>
+__device__ __forceinline__ void wide_side_jobs(const ReduceJob& j, const FlipJob& f, int id, void* scratch) {
+  const int sums = (int)wide_reduce_blocks(j.count, THREADS);
+  if (id < sums) reduce_wide<THREADS>(j, id);
+  else flip_wide<T, THREADS>(f, id - sums, scratch);
 }
 
 }  // namespace acc
