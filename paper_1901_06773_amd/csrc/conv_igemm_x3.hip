@@ -92,8 +92,8 @@ __device__ __forceinline__ x3_v16f plain_block(const ConvGeom& g, int mr, int nr
 }
 
 // Swizzled byte offset of 16-byte column `col` (0 or 1) of row `row` inside one plane: rows are 32 bytes (16 bf16),
-// and eight consecutive rows read at one column lie on different banks.
-[[maybe_unused]] __device__ __forceinline__ int plane_at(int row, int col) { return row * 32 + ((col ^ ((row >> 2) & 1)) << 4); }
+// and sixteen consecutive rows read at one column lie on different ones of the 64 banks.
+[[maybe_unused]] __device__ __forceinline__ int plane_at(int row, int col) { return row * 32 + ((col ^ ((row >> 3) & 1)) << 4); }
 
 // What follows the products: a wave's MB x NB blocks, rows from mw and columns from nw on, are summed for a
 // batch norm, masked, added to, biased and stored as the launch asks.
@@ -345,7 +345,7 @@ __device__ __forceinline__ void short_tile(const ConvGeom& g, int M, int K, int 
     advance();
   };
   const int st_at = plane_at(lrow, lk4 >> 1) + (lk4 & 1) * 8;   // rows RPP further on keep the swizzle
-  static_assert(RPP % 8 == 0, "swizzle period");
+  static_assert(RPP % 16 == 0, "swizzle period");
   auto put = [&](const x3_v4u& x, char* at, int plane) {
     uint32_t h0, m0_, l0, h1, m1_, l1;
     x3_split(__uint_as_float(x[0]), __uint_as_float(x[1]), h0, m0_, l0);
@@ -659,7 +659,7 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
     *reinterpret_cast<x3_v2u*>(at + 2 * plane) = x3_v2u{l0, l1};
   };
   char* const lds_g = lds + 2 * D::WBUF + grp * (D::NST * D::STAGE);
-  static_assert(RPP % 8 == 0, "swizzle period");
+  static_assert(RPP % 16 == 0, "swizzle period");
   const int st_at = plane_at(gt >> 2, (gt & 3) >> 1) + (gt & 1) * 8;
   auto store = [&](const Regs& R, int buf) {
     char* as = lds_g + (buf & (D::NST - 1)) * D::STAGE + st_at;

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   };
   // ---- split and store: channel e of the thread goes to row 16*e + c4, its four values of m side by side
   char* const lds_g = lds + grp * (D::NST * D::STAGE);
-  const int st_at = (BPW == 1 ? gw * D::BLOCK : 0) + c4 * 32 + (((m4 >> 1) ^ ((c4 >> 2) & 1)) << 4) + (m4 & 1) * 8;
+  const int st_at = (BPW == 1 ? gw * D::BLOCK : 0) + c4 * 32 + (((m4 >> 1) ^ ((c4 >> 3) & 1)) << 4) + (m4 & 1) * 8;
   auto store = [&](const Regs& R, int buf) {
     char* at = lds_g + (buf & (D::NST - 1)) * D::STAGE + st_at;
 #pragma unroll
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   };
   // ---- fragments and products
   struct Frags { x3_v4u a[3][2], b[3][2]; } F0, F1;
-  const int f_at = (lane & 31) * 32 + ((half ^ ((lane >> 2) & 1)) << 4);
+  const int f_at = (lane & 31) * 32 + ((half ^ ((lane >> 3) & 1)) << 4);
   const int fa_at = (wm0 >> 6) * D::BLOCK + f_at, fb_at = (WT + (wn0 >> 6)) * D::BLOCK + f_at;
   auto read = [&](Frags& F, int buf) {
     const char* st = lds_g + (buf & (D::NST - 1)) * D::STAGE;
