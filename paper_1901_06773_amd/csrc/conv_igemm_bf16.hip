@@ -178,6 +178,11 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
     tap = u / cols;
     col = u - tap * cols;
     soff_b = first * ROWB;
+  } else if constexpr (KS > 1) {                      // a group's own part of K, in the order of memory
+    const int u = first * CPR;
+    tap = u / cols;
+    col = u - tap * cols;
+    soff_b = first * ROWB;
   } else {                                            // the taps of 64 channels, then those of the next: rows stay in L2 between taps
     const int c0 = first / taps;
     tap = first - c0 * taps;
@@ -216,6 +221,14 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
       const bool down = kt == g.s;
       kt = down ? 0 : kt;
       toff += ROWB + (down ? row_jump : 0);           // the next tap of a filter row is the next pixel
+    } else if constexpr (KS > 1) {
+      soff_b += ROWB;
+      toff += ROWB;                                   // the next tap of a filter row is the next pixel
+      if ((col += CPR) == cols) {
+        col = 0;
+        ++tap;
+        if (++kt == g.s) { kt = 0; toff += row_jump; }
+      }
     } else {
       soff_b += g.c * 2;
       toff += g.c * 2;
@@ -349,13 +362,22 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
       const int row = pc / PPR, c8 = pc - row * PPR, m = m0 + row, n = n0 + 8 * c8;
       if (m >= M || n >= g.n_out) continue;          // (n_out is a multiple of 8: a piece is stored whole or not at all)
       const float* p = reinterpret_cast<const float*>(lds) + row * C::PITCH + 8 * c8;
-      float f[8] = {0, 0, 0, 0, 0, 0, 0, 0}, bias8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      float f[8], bias8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      float part[KS][8];
 #pragma unroll
       for (int u = 0; u < KS; ++u) {
         const float4 lo = *reinterpret_cast<const float4*>(p + u * (C::BM * C::PITCH)), hi = *reinterpret_cast<const float4*>(p + u * (C::BM * C::PITCH) + 4);
-        f[0] += lo.x; f[1] += lo.y; f[2] += lo.z; f[3] += lo.w;
-        f[4] += hi.x; f[5] += hi.y; f[6] += hi.z; f[7] += hi.w;
+        part[u][0] = lo.x; part[u][1] = lo.y; part[u][2] = lo.z; part[u][3] = lo.w;
+        part[u][4] = hi.x; part[u][5] = hi.y; part[u][6] = hi.z; part[u][7] = hi.w;
       }
+#pragma unroll
+      for (int d = KS / 2; d > 0; d /= 2)              // in pairs: the fewest roundings
+#pragma unroll
+        for (int u = 0; u < d; ++u)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) part[u][e] += part[u + d][e];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = part[0][e];
       if constexpr (ACT) {
         if (g.bias) {
 #pragma unroll
