@@ -673,7 +673,7 @@ const char* conv_variant_name(int v) {
                                        "wgrad_kernel<generic>", "igemm_kernel<direct>", "wgrad_kernel<direct>",
                                        "wgrad_bf16_kernel", "igemm_bf16_kernel", "igemm_kernel<direct, two groups>",
                                        "igemm_x3_kernel", "igemm_x3_deep_kernel<window>", "igemm_x3_deep_kernel",
-                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel"};
+                                       "wgrad_x3_kernel", "smallc_fwd_kernel", "smallc_wgrad_kernel", "?", "igemm_rows_kernel"};
   return (v >= 0 && v < V_COUNT) ? names[v] : "?";
 }
 
@@ -711,7 +711,7 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
   LaunchProbe local;
   if (!probe) probe = &local;
   if (g.split) return conv_igemm_split(g, st, probe);
-  if (!g.in || !g.w || !g.out) return hipErrorInvalidValue;
+  if (!g.in || (!g.w && !g.w_kn) || !g.out) return hipErrorInvalidValue;
   if (g.n_img <= 0 || g.h <= 0 || g.wd <= 0 || g.c <= 0 || g.p <= 0 || g.q <= 0 || g.n_out <= 0 ||
       g.r <= 0 || g.s <= 0 || g.stride <= 0 || g.pad < 0 || g.pad + g.pad_dx < 0 || g.out_stride <= 0 ||
       g.out_y0 < 0 || g.out_x0 < 0)
@@ -726,6 +726,8 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
     return hipErrorInvalidValue;
   if (g.dtype != DT_F32 && g.dtype != DT_BF16) return hipErrorInvalidValue;
   if ((g.bias || g.relu) && (g.accumulate || g.stats || g.bnb.sums)) return hipErrorInvalidValue;
+  if (conv_igemm_rows_takes(g, M, K)) return conv_igemm_rows(g, (int)M, (int)K, st, probe);
+  if (!g.w) return hipErrorInvalidValue;
   if (conv_igemm_bf16_takes(g, M, K))      // bf16 storage, widths in 8s
     return conv_igemm_bf16(g, (int)M, (int)K, st, probe);
   if (conv_smallc_takes(g, M)) return conv_smallc_fwd(g, st, probe);

@@ -1033,6 +1033,12 @@ bool conv_igemm_x3_slower(const ConvGeom& g, long M, long K) {
   return fp32_us(g, M, K) < us * 1.02 + 0.3;
 }
 
+double conv_igemm_x3_us(const ConvGeom& g, long M, long K) {
+  double us = 0;
+  best_x3(g, M, K, &us);
+  return g.c % 32 == 0 ? std::fmin(us, fp32_us(g, M, K)) : us;
+}
+
 // The parts go into one launch where that is predicted to take less than the parts one after the other: 128 channels of 56x56, 32
 // images 93 -> 71 us, 512 of 14x14, 256 images 396 -> 350; not 1024 channels of 14x14, 64 images (366 us apart, 391 together) and
 // 256 of 28x28 with 5x5 filters, 64 images (261, 276), which the deep kernels do better.

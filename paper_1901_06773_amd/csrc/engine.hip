@@ -737,6 +737,11 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       cg.in = ptr(s.x); cg.w = wk; cg.out = ptr(s.y); cg.dtype = dt;
       cg.n_img = k; cg.h = 1; cg.wd = 1; cg.c = l->cin; cg.p = 1; cg.q = 1; cg.n_out = l->cout;
       cg.r = 1; cg.s = 1; cg.stride = 1; cg.pad = 0; cg.out_h = 1; cg.out_w = 1; cg.out_stride = 1;
+      if (dt == ACC_F32) {   // bias (+ ReLU) in the same launch; bf16 results are rounded before the addition
+        cg.bias = w + (size_t)l->cout * l->cin;
+        cg.relu = s.relu ? 1 : 0;
+        return igemm(cg, conv_flops);
+      }
       hipError_t e = igemm(cg, conv_flops);
       if (e != hipSuccess) return e;
       return bias_add(ptr(s.y), w + (size_t)l->cout * l->cin, k, l->cout, dt, st, s.relu ? 1 : 0);
@@ -765,7 +770,7 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       if (e != hipSuccess) return e;
       ConvGeom cg{};
       cg.side = job;
-      cg.in = ptr(s.dy); cg.w = ptr(s.ws); cg.out = ptr(s.dx); cg.dtype = dt;
+      cg.in = ptr(s.dy); cg.w = ptr(s.ws); cg.w_kn = wk; cg.out = ptr(s.dx); cg.dtype = dt;
       cg.n_img = k; cg.h = 1; cg.wd = 1; cg.c = l->cout; cg.p = 1; cg.q = 1; cg.n_out = l->cin;
       cg.r = 1; cg.s = 1; cg.stride = 1; cg.pad = 0; cg.out_h = 1; cg.out_w = 1; cg.out_stride = 1;
       cg.accumulate = s.dx_accumulate;

@@ -90,6 +90,9 @@ struct ConvGeom {
   // the sub-filter of every part to w + its wt_offset (w is then a workspace) and runs the parts; p .. pad_dx, the
   // output's stride and first pixel come from them.
   const DgradSplit* split;
+  // Optional (1x1 filters): the same filter as w[k][n], the layout a data gradient finds it in.  conv_igemm_rows_takes() says
+  // whether the launch reads it, and w is then not read; it may be null if so.
+  const void* w_kn;
 };
 // Largest number of row slabs a batch-norm statistics pass adds up.
 constexpr int kBnMaxSlabs = 1024;
@@ -121,20 +124,26 @@ bool conv_igemm_x3_takes(const ConvGeom& g, long M, long K);
 hipError_t conv_igemm_x3(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
 // Whether the direct kernel with the fp32 instruction is predicted to be the faster one for a launch that both take.
 bool conv_igemm_x3_slower(const ConvGeom& g, long M, long K);
+// The faster of the two, predicted (microseconds).
+double conv_igemm_x3_us(const ConvGeom& g, long M, long K);
 // The direct fp32 kernel runs two groups of waves per tile: at most one tile per compute unit and at least eight chunks of 32
 // values of K (a function of the shape only).
 inline bool conv_igemm_two_groups(const ConvGeom& g, long M, long K) {
   return !(g.bias || g.relu) && ((M + 63) / 64) * ((g.n_out + 63) / 64) <= 256 && K >= 256;
 }
+// Few rows and a long reduction (conv_rows.hip): as above; with g.w_kn set, whether the launch reads that.
+bool conv_igemm_rows_takes(const ConvGeom& g, long M, long K);
+hipError_t conv_igemm_rows(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe);
 // The parts of a strided data gradient in one launch, where that is the faster way (a function of the shapes only).
 bool conv_igemm_x3_parts_takes(const ConvGeom* parts, int n);
 hipError_t conv_igemm_x3_parts(const ConvGeom* parts, int n, hipStream_t st, LaunchProbe* probe);
 // A handful of input channels (conv_smallc.hip): as above.
 bool conv_smallc_takes(const ConvGeom& g, long M);
 hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe);
-// Callers see these numbers (acc_get_launch_profile): one keeps its kernel, new ones go to the end.  0 was a kernel that is gone.
+// Callers see these numbers (acc_get_launch_profile): one keeps its kernel, new ones go to the end.  0 was a kernel that is gone, 15 is none.
 enum { V_IGEMM_GENERIC = 1, V_WGRAD_FAST, V_WGRAD_GENERIC, V_IGEMM_DIRECT, V_WGRAD_DIRECT, V_WGRAD_BF16, V_IGEMM_BF16, V_IGEMM_DIRECT_2G,
-       V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD, V_COUNT };
+       V_IGEMM_X3, V_IGEMM_X3_WINDOW, V_IGEMM_X3_DEEP, V_WGRAD_X3, V_SMALLC_FWD, V_SMALLC_WGRAD,
+       V_IGEMM_ROWS = 16, V_COUNT };
 const char* conv_variant_name(int v);
 
 // dw[co][(r,t,ci)] = sum_{img,p,q} dy[img,p,q,co] * x[img, p*stride+r-pad, q*stride+t-pad, ci]

@@ -80,7 +80,6 @@ int conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, in
   const size_t filt = al256((size_t)cout * cin * r * s * sizeof(float));
   if (!workspace || workspace_bytes < filt) return ACC_EINVAL;
   void* wt = workspace;
-  if (!dry && (e = filter_flip_transpose(w, wt, cout, cin, r, s, dtype, st)) != hipSuccess) return status(e);
   ConvGeom g{};
   g.in = dy; g.w = wt; g.out = dx; g.dtype = dtype;
   g.n_img = n; g.h = ho; g.wd = wo; g.c = cout; g.n_out = cin;
@@ -95,6 +94,11 @@ int conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, in
       if (bytes % 4) return ACC_EINVAL;
       if (!dry && (e = fill_zero((float*)dx, bytes / 4, st)) != hipSuccess) return status(e);
     }
+  }
+  g.w_kn = r == 1 ? w : nullptr;
+  if (!conv_igemm_rows_takes(g, (long)n * g.p * g.q, cout)) {     // that kernel reads the filter as it lies
+    g.w_kn = nullptr;
+    if (!dry && (e = filter_flip_transpose(w, wt, cout, cin, r, s, dtype, st)) != hipSuccess) return status(e);
   }
   return status(conv_igemm(g, st, probe));
 }
