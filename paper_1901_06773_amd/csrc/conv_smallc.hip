@@ -198,6 +198,205 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_fwd_kernel(ConvGeom g, S
 #endif
 }
 
+// The same with the rows in LDS as their parts: a value is split once per group of rows and not in each of the filter places that read it
+// (twelve of them for 7x7/2), which kept the vector units as busy as the matrix cores.  A fragment is then four words per part
+// (five, shifted by half a word, where positions lie an odd number of values apart).  The next group's values are asked for
+// before this one's products.  LDS holds two thirds of the rows that words would take; images too wide for one pair of them stay with the kernel above.
+// 3->64 7x7/2 at 224x224: fp32, 32 images 77 -> 60 us (128: 263 -> 213); bf16, 128 images 142 -> 101; 448x448, fp32, 8 images
+// 101 -> 64; 3x3 of 32 images at 224x224, bf16 87 -> 56. Results leave through a descriptor of their row, an address each and no test.
+// In fp32 a second set of fragments, read ahead, does not fit beside the next group's values (spills: 80 us).
+// A barrier for what lies in LDS: stores of results stay on their way.
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);                  // LDS accesses done, any number of vector memory accesses on their way
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#endif
+}
+template <class T> constexpr int kPairs = Parts<T>::N == 3 ? 7936 : 10752;       // pairs of values in LDS per part
+template <class T, bool ACT, bool ODD>
+__global__ __launch_bounds__(SC_THREADS, 1) void smallc_fwd_parts_kernel(ConvGeom g, SmallGeom sg, int groups_per_img, int n_groups) {
+  [[maybe_unused]] constexpr int NP = Parts<T>::N, PAIRS = kPairs<T>, U = (PAIRS + SC_THREADS - 1) / SC_THREADS;
+  __shared__ __attribute__((aligned(16))) uint32_t rows[NP * PAIRS + 4];
+  __shared__ __attribute__((aligned(16))) x3_v4u wf[NP * (SC_KPAD / 8) * 64];
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+  const int n0 = blockIdx.y * 64, jl = sg.s * sg.c, g8 = (jl + 7) >> 3, K = sg.r * jl, n_g8 = sg.r * g8, steps = (n_g8 + 1) >> 1;
+  const T* const x = static_cast<const T*>(g.in);
+  const int len = sg.wd * sg.c, lead = sg.pad * sg.c;
+  float nv[2 * U];                                     // the thread's pairs of the next group
+  auto ask = [&](int grp) {
+    const int img = grp / groups_per_img, p0 = (grp - img * groups_per_img) * sg.rows;
+    const int n_rows = min(sg.rows, sg.p - p0), in_rows = (n_rows - 1) * sg.stride + sg.r, total = in_rows * sg.row_words, iy0 = p0 * sg.stride - sg.pad;
+    int t = tid;
+    asm volatile("" : "+v"(t));                        // places are worked out again for every group: kept, they take 32 registers
+    // one image; what lies outside reads as zero
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x) + (size_t)img * sg.h * len, 0, sg.h * len * (int)sizeof(T), 0x00020000);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = 2 * (t + u * SC_THREADS), row = (int)__umulhi((uint32_t)i, sg.row_inv), at = i - row * sg.row_words - lead, iy = iy0 + row;
+      const bool in = (i < total) & ((unsigned)iy < (unsigned)sg.h);   // (row_words is even: a pair lies in one row)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int off = in & ((unsigned)(at + e) < (unsigned)len) ? (iy * len + at + e) * (int)sizeof(T) : (int)0x7ffffff0;
+        if constexpr (NP == 3) nv[2 * u + e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+        else nv[2 * u + e] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0));   // the bf16 itself
+      }
+    }
+  };
+  auto put = [&]() {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = tid + u * SC_THREADS;
+      if (i >= PAIRS) continue;
+      if constexpr (NP == 3) {
+        uint32_t h, m, l;
+        x3_split(nv[2 * u], nv[2 * u + 1], h, m, l);
+        rows[i] = h; rows[PAIRS + i] = m; rows[2 * PAIRS + i] = l;
+      } else {
+        rows[i] = __float_as_uint(nv[2 * u]) | __float_as_uint(nv[2 * u + 1]) << 16;
+      }
+    }
+  };
+  if ((int)blockIdx.x < n_groups) ask(blockIdx.x);
+  // filter -> parts
+  for (int i = tid; i < steps * 2 * 64; i += SC_THREADS) {
+    const int n = i & 63, grp = i >> 6, kr = grp / g8, j = (grp - kr * g8) * 8;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool ok = n0 + n < g.n_out && kr < sg.r && j + e < jl;
+      const float t = Elem<T>::load(static_cast<const T*>(g.w) + (ok ? (size_t)(n0 + n) * K + kr * jl + j + e : 0));
+      v[e] = ok ? t : 0.f;
+    }
+    x3_v4u f[NP];
+    to_parts<NP>(v, f);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) wf[(p * (SC_KPAD / 8) + grp) * 64 + n] = f[p];
+  }
+  const int qb = (sg.q + 31) >> 5, sc = sg.stride * sg.c;
+  for (int grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
+    const int img = grp / groups_per_img, p0 = (grp - img * groups_per_img) * sg.rows;
+    const int n_rows = min(sg.rows, sg.p - p0), pairs = (n_rows + 1) >> 1;
+    lds_barrier();                                     // the rows of the group before are no longer read
+    put();
+    lds_barrier();
+    if (grp + (int)gridDim.x < n_groups) ask(grp + gridDim.x);
+    for (int unit = wave; unit < pairs * qb; unit += SC_WAVES) {
+      const int pr = (unit / qb) * 2, q0 = (unit % qb) * 32;
+      x3_v16f acc[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      // the lane's position; one that does not exist reads the last one's values and is not stored
+      const int q = min(q0 + (lane & 31), sg.q - 1);
+      const int base0 = pr * sg.stride * sg.row_words + q * sc, base1 = min(pr + 1, n_rows - 1) * sg.stride * sg.row_words + q * sc;
+      const uint32_t odd = ODD ? (uint32_t)(q * sc & 1) * 16u : 0u;     // bits
+      struct Frags { x3_v4u a[2][NP], b[2][NP]; };
+      int kr = half / g8, part = half - kr * g8;        // the lane's group of eight
+      auto read = [&](Frags& f, int s) {
+        const int at = min(kr, sg.r - 1) * sg.row_words + part * 8;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            const uint32_t* w = rows + p * PAIRS + (((i == 0 ? base0 : base1) + at) >> 1);
+            if constexpr (ODD) {
+              const uint32_t t[5] = {w[0], w[1], w[2], w[3], w[4]};
+#pragma unroll
+              for (int e = 0; e < 4; ++e) f.a[i][p][e] = __builtin_amdgcn_alignbit(t[e + 1], t[e], odd);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) f.a[i][p][e] = w[e];
+            }
+          }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) f.b[j][p] = wf[(p * (SC_KPAD / 8) + 2 * s + half) * 64 + 32 * j + (lane & 31)];
+        part += 2;
+        while (part >= g8) { part -= g8; ++kr; }
+      };
+      auto multiply = [&](const Frags& f) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) product<NP>(f.a[i], f.b[j], acc[i][j]);
+      };
+      if constexpr (NP == 3) {
+#pragma unroll 1
+        for (int s = 0; s < steps; ++s) {
+          Frags f;
+          read(f, s);
+          multiply(f);
+        }
+      } else {
+      Frags f0, f1;
+      read(f0, 0);
+#pragma unroll 1
+      for (int s = 0; s < steps; s += 2) {
+        if (s + 1 < steps) read(f1, s + 1);
+        __builtin_amdgcn_sched_barrier(0);             // (a third set of fragments does not fit)
+        multiply(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 >= steps) break;
+        if (s + 2 < steps) read(f0, s + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (pr + i >= n_rows) continue;
+        // one row of results; positions and channels that do not exist are stored outside of it, which drops them
+        const size_t row0 = ((size_t)img * sg.p + p0 + pr + i) * sg.q;
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(static_cast<T*>(g.out) + row0 * g.n_out, 0, sg.q * g.n_out * (int)sizeof(T), 0x00020000);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int n = n0 + 32 * j + (lane & 31);
+          if (any_nonfinite(acc[i][j])) {
+            // in fp32, from memory (a value beside the window times a padded zero weight, or a part of a value, may have
+            // made the block what it is)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int k = 0; k < K; k += 2) {
+              const int kk = min(k + half, K - 1), fr = kk / jl, fj = kk - fr * jl;
+              const int iy = (p0 + pr + i) * sg.stride - sg.pad + fr, at = q * sc - lead + fj;
+              const bool in = k + half < K && (unsigned)iy < (unsigned)sg.h && (unsigned)at < (unsigned)len;
+              float av = in ? Elem<T>::load(x + ((size_t)img * sg.h + iy) * len + at) : 0.f;
+              float bv = k + half < K && n < g.n_out ? Elem<T>::load(static_cast<const T*>(g.w) + (size_t)n * K + kk) : 0.f;
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+            }
+          } else if constexpr (NP == 3) {
+            acc[i][j] *= kX3Unscale;
+          }
+          const float bias_n = ACT && g.bias ? g.bias[min(n, g.n_out - 1)] : 0.f;
+          const int at = n < g.n_out ? ((q0 + 4 * half) * g.n_out + n) * (int)sizeof(T) : (int)0x7f000000;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            float val = acc[i][j][v];
+            if constexpr (ACT) {
+              val += bias_n;
+              if (g.relu) val = fmaxf(val, 0.f);
+            }
+            const int off = at + (8 * (v >> 2) + (v & 3)) * g.n_out * (int)sizeof(T);
+            if constexpr (NP == 3) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), ro, off, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)x3_pack(val, val), ro, off, 0, 0);
+          }
+        }
+      }
+    }
+  }
+#else
+  (void)rows; (void)wf;
+#endif
+}
+
 // ---- weight gradient: dw[co][j] = sum_m dy[m][co] * X[m][j], j = (kr, kt, ci) <= 160 columns, 64 output channels per
 // workgroup column.  A step is 16 positions of one output row: dy comes straight from memory (eight positions per lane), X
 // from the rows in LDS, every lane at its own columns' places.  The waves take every eighth step of a group of rows and keep
@@ -353,8 +552,15 @@ bool conv_smallc_takes(const ConvGeom& g, long M) {
 }
 
 hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
-  const SmallGeom sg = small_geom(g.h, g.wd, g.c, g.p, g.q, g.r, g.s, g.stride, g.pad);
-  const int per_img = (g.p + sg.rows - 1) / sg.rows;
+  SmallGeom sg = small_geom(g.h, g.wd, g.c, g.p, g.q, g.r, g.s, g.stride, g.pad);
+  // rows held as parts: as many as fit, in pairs; one pair at least
+  const long room = g.dtype == DT_F32 ? 2 * kPairs<float> : 2 * kPairs<bf16_t>;
+  auto values = [&](int rows) { return (long)((rows - 1) * sg.stride + sg.r) * sg.row_words; };
+  int rows = sg.rows;
+  while (rows > 2 && values(rows) > room) rows = (rows - 1) & ~1;
+  const bool parts = rows > 0 && values(rows) <= room && (long)sg.h * sg.wd * sg.c < (1L << 28) && (long)(sg.q + 32) * g.n_out < (1L << 28);
+  if (parts) sg.rows = rows;
+  const int per_img = sg.rows < 1 ? 0 : (g.p + sg.rows - 1) / sg.rows;
   const long groups = (long)per_img * g.n_img;
   if (sg.rows < 1 || groups > (1L << 30)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(groups < 256 ? groups : 256), (g.n_out + 63) / 64);
@@ -362,8 +568,11 @@ hipError_t conv_smallc_fwd(const ConvGeom& g, hipStream_t st, LaunchProbe* probe
   probe->kernel = "smallc";
   if (probe->dry) return hipSuccess;
   if (probe->before) (void)hipEventRecord(probe->before, st);
-  const bool act = g.bias || g.relu;
-#define ACC_SC(T, A) hipLaunchKernelGGL((smallc_fwd_kernel<T, A>), grid, dim3(SC_THREADS), 0, st, g, sg, per_img, (int)groups)
+  const bool act = g.bias || g.relu, odd = (sg.stride * sg.c & 1) != 0;
+#define ACC_SC(T, A) do { \
+    if (!parts) hipLaunchKernelGGL((smallc_fwd_kernel<T, A>), grid, dim3(SC_THREADS), 0, st, g, sg, per_img, (int)groups); \
+    else if (odd) hipLaunchKernelGGL((smallc_fwd_parts_kernel<T, A, true>), grid, dim3(SC_THREADS), 0, st, g, sg, per_img, (int)groups); \
+    else hipLaunchKernelGGL((smallc_fwd_parts_kernel<T, A, false>), grid, dim3(SC_THREADS), 0, st, g, sg, per_img, (int)groups); } while (0)
   if (g.dtype == DT_F32) { if (act) ACC_SC(float, true); else ACC_SC(float, false); }
   else { if (act) ACC_SC(bf16_t, true); else ACC_SC(bf16_t, false); }
 #undef ACC_SC
