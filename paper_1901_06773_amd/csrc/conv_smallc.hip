@@ -397,13 +397,38 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_fwd_parts_kernel(ConvGeo
 #endif
 }
 
+// Input rows as stage_rows() places them, from global memory straight into LDS: 64 consecutive words per instruction; bf16 values arrive as the
+// low halves of their words.  What lies outside the image reads as zero.  The caller waits for the loads.
+template <class T>
+__device__ __forceinline__ void stage_rows_direct(const T* __restrict__ x, const SmallGeom& sg, int img, int p0, int n_rows, float* lds, int wave, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  const int in_rows = (n_rows - 1) * sg.stride + sg.r, len = sg.wd * sg.c, lead = sg.pad * sg.c;
+  const int total = in_rows * sg.row_words, iy0 = p0 * sg.stride - sg.pad;
+  const int lo = min(max(iy0, 0), sg.h), hi = max(min(iy0 + in_rows, sg.h), lo);             // rows of the image among them
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x) + ((size_t)img * sg.h + lo) * len, 0, (hi - lo) * len * (int)sizeof(T), 0x00020000);
+  const uint32_t to = (uint32_t)(size_t)lds;
+#pragma unroll 4
+  for (int i0 = wave * 64; i0 < total; i0 += SC_THREADS) {
+    const int i = i0 + lane, row = (int)__umulhi((uint32_t)i, sg.row_inv), at = i - row * sg.row_words - lead, iy = iy0 + row;
+    const bool ok = (i < total) & ((unsigned)at < (unsigned)len) & ((unsigned)iy < (unsigned)sg.h);
+    const int off = ok ? ((iy - lo) * len + at) * (int)sizeof(T) : (int)0x7ffffff0;
+    if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(size_t)(to + i0 * 4), 4, off, 0, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(size_t)(to + i0 * 4), 2, off, 0, 0, 0);
+  }
+#endif
+}
+static_assert(SC_ROW_WORDS % 64 == 0, "an instruction writes 64 words");
+
 // ---- weight gradient: dw[co][j] = sum_m dy[m][co] * X[m][j], j = (kr, kt, ci) <= 160 columns, 64 output channels per
 // workgroup column.  A step is 16 positions of one output row: dy comes straight from memory (eight positions per lane), X
 // from the rows in LDS, every lane at its own columns' places.  The waves take every eighth step of a group of rows and keep
 // the whole 64 x 160 block (2 x 5 blocks of 32 x 32); the workgroup adds them up at the end and writes one part.
-// Bound by trips to memory that nothing hides (the sums take 160 registers, so few loads can be on their way): the rows of a group
-// staged many words at a time instead of a row's, and the first dy values asked for before them, 124 -> 106 us (3->64 7x7/2
-// at 224x224, fp32, 32 images) and 278 -> 247 us (bf16, 128 images); sixteen words at a time spill and take 159 and 338.
+// Bound by vector instructions beside the matrix cores, and by trips to memory (the sums take 160 registers, so few loads can be on their
+// way): the rows go into LDS without passing through registers, all of a group's words at once, and the dy values of the next step
+// are asked for a step ahead, through a descriptor that gives zeros outside (a test on the value waits for it where it is asked for).
+// With the sum of the parts, 3->64 7x7/2 at 224x224, fp32, 32 images 110 -> 76 us (rows alone 102); bf16, 128 images 254 -> 114
+// (rows alone 227); 3x3, bf16, 32 images 231 -> 97.
 template <class T>
 __global__ __launch_bounds__(SC_THREADS, 1) void smallc_wgrad_kernel(WgradGeom g, SmallGeom sg, int rows_total, int rows_per_split,
                                                                       float* out, size_t split_stride) {
@@ -427,33 +452,44 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_wgrad_kernel(WgradGeom g
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][b][v] = 0.f;
   const int spr = (sg.q + 15) >> 4;                    // steps per output row
+  auto fragment = [](const float (&v)[8], x3_v4u (&f)[NP]) {
+    if constexpr (NP == 3) {
+      to_parts<NP>(v, f);
+    } else {                                           // a bf16 in the low half of each word
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[0][e] = __float_as_uint(v[2 * e]) | __float_as_uint(v[2 * e + 1]) << 16;
+    }
+  };
   const T* dy = static_cast<const T*>(g.dy);
   const bool c_ok[2] = {co0 + (lane & 31) < g.cout, co0 + 32 + (lane & 31) < g.cout};
   for (int r0 = lo; r0 < hi;) {
     const int img = r0 / sg.p, p0 = r0 - img * sg.p, n_rows = min(min(sg.rows, sg.p - p0), hi - r0);
+    // positions and channels that do not exist read as zero (without a test on the value, which would wait for it here)
+    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(dy) + (size_t)r0 * sg.q * g.cout, 0,
+                                                                        n_rows * sg.q * g.cout * (int)sizeof(T), 0x00020000);
     auto load = [&](int s, float (&v)[2][8]) {
       const int row = s / spr, q = (s - row * spr) * 16 + half * 8;
-      const T* src = dy + ((size_t)(r0 + row) * sg.q + q) * g.cout + co0 + (lane & 31);
+      const int at = ((row * sg.q + q) * g.cout + co0 + (lane & 31)) * (int)sizeof(T);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const bool ok = c_ok[i] & (q + e < sg.q);
-          const T* a = ok ? src + (size_t)e * g.cout + 32 * i : dy;
-          const float t = Elem<T>::load(a);
-          v[i][e] = ok ? t : 0.f;
+          const int off = c_ok[i] & (q + e < sg.q) ? at + (e * g.cout + 32 * i) * (int)sizeof(T) : (int)0x7ffffff0;
+          if constexpr (NP == 3) v[i][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, off, 0, 0));
+          else v[i][e] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rd, off, 0, 0));   // the bf16 itself
         }
     };
     const int n_steps = n_rows * spr;
     float nv[2][8];
     if (wave < n_steps) load(wave, nv);                // on its way while the rows are staged
     __syncthreads();
-    stage_rows<NP == 1 ? 8 : 4>(static_cast<const T*>(g.x), sg, img, p0, n_rows, rows);   // (the sums hold 160 registers)
+    stage_rows_direct(static_cast<const T*>(g.x), sg, img, p0, n_rows, rows, wave, lane);
+    __builtin_amdgcn_s_waitcnt(0x0070);                // this wave's loads have landed, in LDS too
     __syncthreads();
     for (int s = wave; s < n_steps; s += SC_WAVES) {
       x3_v4u a[2][NP];
-      to_parts<NP>(nv[0], a[0]);
-      to_parts<NP>(nv[1], a[1]);
+      fragment(nv[0], a[0]);
+      fragment(nv[1], a[1]);
       if (s + SC_WAVES < n_steps) load(s + SC_WAVES, nv);
       const int row = s / spr, q = (s - row * spr) * 16 + half * 8;
       const float* base = rows + row * sg.stride * sg.row_words;
@@ -466,7 +502,7 @@ __global__ __launch_bounds__(SC_THREADS, 1) void smallc_wgrad_kernel(WgradGeom g
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = base[col[b] + at[e]];
         x3_v4u f[NP];
-        to_parts<NP>(v, f);
+        fragment(v, f);
         product<NP>(a[0], f, acc[0][b]);
         product<NP>(a[1], f, acc[1][b]);
       }
@@ -592,7 +628,9 @@ int wgrad_smallc_splits(long Mrows, int cin, int cout, int r, int s, int dtype) 
 
 bool conv_wgrad_smallc_takes(const WgradGeom& g) {
   const long M = (long)g.n_img * g.p * g.q;
-  if (!wgrad_smallc_splits(M, g.cin, g.cout, g.r, g.s, g.dtype) || g.side.count || g.flip_wt || (g.cout + 63) / 64 > 65535) return false;
+  if (!wgrad_smallc_splits(M, g.cin, g.cout, g.r, g.s, g.dtype) || g.side.count || g.flip_wt || (g.cout + 63) / 64 > 65535 ||
+      (g.q + 32L) * g.cout >= (1L << 25))
+    return false;
   if ((g.q - 1) * (long)g.stride + g.s > g.wd + 2L * g.pad || (g.p - 1) * (long)g.stride + g.r > g.h + 2L * g.pad) return false;
   return small_geom(g.h, g.wd, g.cin, g.p, g.q, g.r, g.s, g.stride, g.pad).rows > 0;
 }
