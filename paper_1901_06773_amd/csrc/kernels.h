@@ -231,7 +231,10 @@ hipError_t relu_mask(void* dy, const void* y, size_t count, int dtype, hipStream
 hipError_t relu_bias_backward(void* dy, const void* y, float* db, long rows, int c, void* workspace, int dtype,
                               hipStream_t st);
 hipError_t column_sum(const void* dy, float* db, long rows, int c, int dtype, hipStream_t st);
-// loss_rows: n floats of scratch; loss: one float
+// loss_rows: n floats of scratch; loss: one float.  Loss (loss_rows may be null: not wanted) and gradient (dz may be null) in one launch,
+// or one of them.
+hipError_t softmax_ce(const void* z, const int32_t* labels, float* loss_rows, float* loss, void* dz, int n, int classes, int dtype,
+                      hipStream_t st);
 hipError_t softmax_ce_forward(const void* z, const int32_t* labels, float* loss_rows, float* loss,
                               int n, int classes, int dtype, hipStream_t st);
 hipError_t softmax_ce_backward(const void* z, const int32_t* labels, void* dz, int n, int classes,

@@ -474,61 +474,77 @@ __global__ __launch_bounds__(THREADS) void column_sum_kernel(const T* __restrict
   const int ch = blockIdx.x * THREADS + threadIdx.x;
   if (ch >= c) return;
   float sum = 0.f;
-  for (long r = 0; r < rows; ++r) sum += Elem<T>::load(dy + (size_t)r * c + ch);
+  long r = 0;
+  for (; r + 16 <= rows; r += 16) {     // sixteen rows on their way at once
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = Elem<T>::load(dy + (size_t)(r + u) * c + ch);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) sum += v[u];
+  }
+  for (; r < rows; ++r) sum += Elem<T>::load(dy + (size_t)r * c + ch);
   db[ch] = sum;
 }
 
-// Fixed-order block reductions (tree over a power-of-two block, same order every run).
-__device__ __forceinline__ float block_max(float v, float* sh) {
-  sh[threadIdx.x] = v;
+// Fixed-order block reductions: a butterfly in every wave, then the waves in order.
+template <class F>
+__device__ __forceinline__ float block_reduce(float v, float* sh, F op) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = THREADS / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const float r = sh[0];
-  __syncthreads();
-  return r;
-}
-__device__ __forceinline__ float block_sum(float v, float* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = THREADS / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  const float r = sh[0];
+  float r = sh[0];
+#pragma unroll
+  for (int w = 1; w < THREADS / 64; ++w) r = op(r, sh[w]);
   __syncthreads();
   return r;
 }
 
 // one workgroup per sample: loss_rows[i] = logsumexp(z_i) - z_i[label]; optionally
-// dz = (softmax - onehot) / n
-template <class T>
+// dz = (softmax - onehot) / n.  V > 0: at most V * THREADS classes, a thread keeps its logits.
+// Bound by the launch and trips through LDS: 41 rows of 1000 classes, loss and gradient 13 us in three launches, 9 in two.
+template <class T, int V>
 __global__ __launch_bounds__(THREADS) void softmax_ce_kernel(const T* __restrict__ z,
                                                              const int32_t* __restrict__ labels,
                                                              float* __restrict__ loss_rows,
                                                              T* __restrict__ dz, int n, int classes) {
-  __shared__ float sh[THREADS];
+  __shared__ float sh[THREADS / 64];
   const int i = blockIdx.x;
   const T* zi = z + (size_t)i * classes;
-  float mx = -INFINITY;
-  for (int j = threadIdx.x; j < classes; j += THREADS) mx = fmaxf(mx, Elem<T>::load(zi + j));
-  mx = block_max(mx, sh);
-  float se = 0.f;
-  for (int j = threadIdx.x; j < classes; j += THREADS) se += expf(Elem<T>::load(zi + j) - mx);
-  se = block_sum(se, sh);
-  // everything relative to the row maximum: z - mx is exact for the logits near the maximum (the only ones
-  // that matter), so neither the loss nor a probability close to one loses digits to the size of the logits
-  const float lg = logf(se);
   const int lab = labels[i];
   // a label outside [0, classes) reads nothing: the row's loss is NaN and its gradient has no one-hot term
   const bool lab_ok = (unsigned)lab < (unsigned)classes;
-  if (loss_rows && threadIdx.x == 0) loss_rows[i] = lab_ok ? lg - (Elem<T>::load(zi + lab) - mx) : NAN;
+  float z_lab = Elem<T>::load(zi + (lab_ok ? lab : 0));
+  asm volatile("" : "+v"(z_lab));      // read here: dz may be z, and another thread's gradient lies there later
+  float v[V > 0 ? V : 1];
+  auto each = [&](auto&& use) {
+    if constexpr (V > 0) {
+#pragma unroll
+      for (int u = 0; u < V; ++u)
+        if ((int)threadIdx.x + u * THREADS < classes) use((int)threadIdx.x + u * THREADS, v[u]);
+    } else {
+      for (int j = threadIdx.x; j < classes; j += THREADS) use(j, Elem<T>::load(zi + j));
+    }
+  };
+  if constexpr (V > 0) {
+#pragma unroll
+    for (int u = 0; u < V; ++u) v[u] = Elem<T>::load(zi + min((int)threadIdx.x + u * THREADS, classes - 1));
+  }
+  float mx = -INFINITY;
+  each([&](int, float t) { mx = fmaxf(mx, t); });
+  mx = block_reduce(mx, sh, [](float a, float b) { return fmaxf(a, b); });
+  float se = 0.f;
+  each([&](int, float t) { se += expf(t - mx); });
+  se = block_reduce(se, sh, [](float a, float b) { return a + b; });
+  // everything relative to the row maximum: z - mx is exact for the logits near the maximum (the only ones
+  // that matter), so neither the loss nor a probability close to one loses digits to the size of the logits
+  const float lg = logf(se);
+  if (loss_rows && threadIdx.x == 0) loss_rows[i] = lab_ok ? lg - (z_lab - mx) : NAN;
   if (dz) {
     const float inv_n = 1.f / (float)n;
-    for (int j = threadIdx.x; j < classes; j += THREADS)
-      Elem<T>::store(dz + (size_t)i * classes + j, (expf((Elem<T>::load(zi + j) - mx) - lg) - (j == lab ? 1.f : 0.f)) * inv_n);
+    each([&](int j, float t) {
+      Elem<T>::store(dz + (size_t)i * classes + j, (expf((t - mx) - lg) - (j == lab ? 1.f : 0.f)) * inv_n);
+    });
   }
 }
 
@@ -536,7 +552,15 @@ __global__ __launch_bounds__(THREADS) void softmax_ce_kernel(const T* __restrict
 __global__ void loss_mean_kernel(const float* __restrict__ loss_rows, float* __restrict__ loss, int n) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     double s = 0.0;
-    for (int i = 0; i < n; ++i) s += (double)loss_rows[i];
+    int i = 0;
+    for (; i + 16 <= n; i += 16) {      // sixteen on their way at once
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = loss_rows[i + u];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += (double)v[u];
+    }
+    for (; i < n; ++i) s += (double)loss_rows[i];
     *loss = (float)(s / n);
   }
 }
@@ -764,21 +788,28 @@ hipError_t column_sum(const void* dy, float* db, long rows, int c, int dtype, hi
   return hipGetLastError();
 }
 
+hipError_t softmax_ce(const void* z, const int32_t* labels, float* loss_rows, float* loss, void* dz, int n, int classes, int dtype,
+                      hipStream_t st) {
+  if (!z || !labels || n <= 0 || classes <= 0 || (loss_rows && !loss)) return hipErrorInvalidValue;
+#define ACC_SOFTMAX(V) \
+  ACC_DISPATCH(dtype, hipLaunchKernelGGL((softmax_ce_kernel<T, V>), dim3(n), dim3(THREADS), 0, st, (const T*)z, labels, loss_rows, (T*)dz, n, classes))
+  if (classes <= 4 * THREADS) ACC_SOFTMAX(4);
+  else ACC_SOFTMAX(0);
+#undef ACC_SOFTMAX
+  if (loss_rows) hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(64), 0, st, loss_rows, loss, n);
+  return hipGetLastError();
+}
+
 hipError_t softmax_ce_forward(const void* z, const int32_t* labels, float* loss_rows, float* loss,
                               int n, int classes, int dtype, hipStream_t st) {
-  if (!z || !labels || !loss_rows || !loss || n <= 0 || classes <= 0) return hipErrorInvalidValue;
-  ACC_DISPATCH(dtype, hipLaunchKernelGGL(softmax_ce_kernel<T>, dim3(n), dim3(THREADS), 0, st, (const T*)z, labels,
-                                         loss_rows, (T*)nullptr, n, classes));
-  hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(64), 0, st, loss_rows, loss, n);
-  return hipGetLastError();
+  if (!loss_rows) return hipErrorInvalidValue;
+  return softmax_ce(z, labels, loss_rows, loss, nullptr, n, classes, dtype, st);
 }
 
 hipError_t softmax_ce_backward(const void* z, const int32_t* labels, void* dz, int n, int classes, int dtype,
                                hipStream_t st) {
-  if (!z || !labels || !dz || n <= 0 || classes <= 0) return hipErrorInvalidValue;
-  ACC_DISPATCH(dtype, hipLaunchKernelGGL(softmax_ce_kernel<T>, dim3(n), dim3(THREADS), 0, st, (const T*)z, labels,
-                                         (float*)nullptr, (T*)dz, n, classes));
-  return hipGetLastError();
+  if (!dz) return hipErrorInvalidValue;
+  return softmax_ce(z, labels, nullptr, nullptr, dz, n, classes, dtype, st);
 }
 
 hipError_t sgd_update(float* w, const float* g, float lr, size_t count, void* w_bf16, hipStream_t st) {

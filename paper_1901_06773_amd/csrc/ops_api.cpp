@@ -195,8 +195,5 @@ extern "C" int acc_op_softmax_ce(const void* z, const int32_t* labels, float* lo
                                  int classes, int dtype, void* stream) {
   if (!z || !labels || !dtype_ok(dtype) || n <= 0 || classes <= 0 || (!loss_rows && !dz) || (loss_rows && !loss))
     return ACC_EINVAL;
-  hipError_t e = hipSuccess;
-  if (loss_rows) e = softmax_ce_forward(z, labels, loss_rows, loss, n, classes, dtype, (hipStream_t)stream);
-  if (e == hipSuccess && dz) e = softmax_ce_backward(z, labels, dz, n, classes, dtype, (hipStream_t)stream);
-  return status(e);
+  return status(softmax_ce(z, labels, loss_rows, loss, dz, n, classes, dtype, (hipStream_t)stream));
 }
