@@ -112,6 +112,41 @@ __global__ __launch_bounds__(THREADS) void maxpool_fwd_kernel(const T* __restric
   }
 }
 
+// The same for 3x3 windows, V channels (16 bytes) per thread: the nine loads go out together, places that do not exist read the window's centre
+// column or row instead and are not compared; indices in 32 bits.  Bound by HBM.  3x3/2 of 64 channels at 112x112: fp32, 32 images 31.6 -> 27.8 us
+// (129 MB), 2 images 7.0 -> 4.2; bf16, 128 images 91.5 -> 50.1.
+template <class T, int V>
+__global__ __launch_bounds__(THREADS) void maxpool3_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, int total, int h, int wd, int c,
+                                                               int stride, int pad, int ho, int wo) {
+  const int cg = c / V;
+  for (int i = blockIdx.x * THREADS + threadIdx.x; i < total; i += gridDim.x * THREADS) {
+    const uint32_t pix = (uint32_t)i / (uint32_t)cg, g = i - pix * cg, row = pix / (uint32_t)wo, q = pix - row * wo;
+    const uint32_t img = row / (uint32_t)ho, p = row - img * ho;
+    const int iy = (int)p * stride - pad, ix = (int)q * stride - pad;
+    const T* xi = x + (size_t)img * h * wd * c + (size_t)g * V;
+    union Raw { uint4 u; T t[16 / sizeof(T)]; } v[9];
+    bool ok[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const int yy = iy + k / 3, xx = ix + k % 3;
+      ok[k] = ((unsigned)yy < (unsigned)h) & ((unsigned)xx < (unsigned)wd);
+      v[k].u = *reinterpret_cast<const uint4*>(xi + ((size_t)min(max(yy, 0), h - 1) * wd + min(max(xx, 0), wd - 1)) * c);
+    }
+    Raw best = v[0];
+    bool have = false;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const bool more = ok[k] & (!have | (Elem<T>::load(&v[k].t[j]) > Elem<T>::load(&best.t[j])));
+        best.t[j] = more ? v[k].t[j] : best.t[j];
+      }
+      have |= ok[k];
+    }
+    *reinterpret_cast<uint4*>(y + (size_t)i * V) = best.u;
+  }
+}
+
 // Gather form of the max-pool gradient: one thread per input position and group of V
 // channels (V = 4 as float4 when c % 4 == 0, else 1); for every window that covers the
 // position, find the window's first maximum again and take the window's dy where this
@@ -671,6 +706,18 @@ hipError_t maxpool_forward(const void* x, void* y, int n, int h, int wd, int c, 
   const int ho = (h + 2 * pad - r) / stride + 1, wo = (wd + 2 * pad - s) / stride + 1;
   if (ho <= 0 || wo <= 0) return hipErrorInvalidValue;
   const size_t total = (size_t)n * ho * wo * (c / 4);
+  const int v = dtype == DT_BF16 ? 8 : 4;
+  const size_t wide = total * 4 / v;
+  if (r == 3 && s == 3 && c % v == 0 && wide <= (size_t)1 << 30 && !((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15)) {
+    const unsigned blocks = grid_for(wide, 256 * 64);
+    if (dtype == DT_F32)
+      hipLaunchKernelGGL((maxpool3_fwd_kernel<float, 4>), dim3(blocks), dim3(THREADS), 0, st, (const float*)x, (float*)y, (int)wide, h, wd, c, stride, pad, ho, wo);
+    else if (dtype == DT_BF16)
+      hipLaunchKernelGGL((maxpool3_fwd_kernel<bf16_t, 8>), dim3(blocks), dim3(THREADS), 0, st, (const bf16_t*)x, (bf16_t*)y, (int)wide, h, wd, c, stride, pad, ho, wo);
+    else
+      return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   ACC_DISPATCH(dtype, hipLaunchKernelGGL(maxpool_fwd_kernel<T>, dim3(grid_for(total)), dim3(THREADS), 0, st,
                                          (const T*)x, (T*)y, n, h, wd, c, r, s, stride, pad, ho, wo));
   return hipGetLastError();
