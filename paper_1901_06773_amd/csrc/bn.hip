@@ -16,8 +16,7 @@ namespace acc {
 namespace {
 
 constexpr int MAX_SLABS = kBnMaxSlabs;   // row slabs of the reduction grid (upper bound)
-constexpr int ROWS_PER_THREAD = 4;  // rows a thread of the reduction sums at least (else fewer slabs)
-constexpr int THREADS = 256;
+constexpr int THREADS = kBnThreads;
 // The finishing kernels: a workgroup adds up FIN_CH channels, FIN_LANES slabs at a time.  The slabs come from memory in
 // 64-byte pieces (doubles), every load of a thread in flight at once, so the launch lasts little longer than one trip
 // (up to 1024 slabs of 64 to 512 channels, in a step: 9.4 -> 5.9 us against one wave per channel, which used 32 bytes of a line).
@@ -46,30 +45,6 @@ template <> struct ElemV<bf16_t, 8> {
     *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
   }
 };
-
-// How the threads of a workgroup cover the channels: tpr threads of V channels each across a row, rpi rows per trip;
-// col_slices workgroups (grid.y) where a row is wider than one covers.
-struct ReduceShape {
-  int tpr, rpi, col_slices;
-};
-
-__host__ __device__ inline ReduceShape reduce_shape(int groups, bool even, long rows) {   // groups of V channels
-  ReduceShape s;
-  s.col_slices = (groups + 63) / 64;
-  // even: slices of like width (65 groups as 33 + 32; bf16 520 channels, 41 images of 28x28 backward 53 -> 47 us), else as
-  // wide as can be (65 as 64 + 1; fp32 516 channels 107 us against 110)
-  s.tpr = even ? (groups + s.col_slices - 1) / s.col_slices : groups < 64 ? groups : 64;
-  // small tensors: two slices at least, so that half as many slabs fill the chip (every workgroup of the slice kernels reads its channels
-  // of all of them again).  fp32, forward / backward: 256 channels, 20 images of 28x28 18.0 -> 14.4 / 26.2 -> 24.1 us, 41 of 14x14
-  // 11.9 -> 11.1 / 16.2 -> 16.3, 128 channels, 5 of 56x56 11.7 -> 10.8 / 16.1 -> 16.1.  Below 32 groups a slice's rows get too short to gain
-  if (!even && rows <= 16384 && s.col_slices == 1 && groups >= 32) {
-    s.col_slices = 2;
-    s.tpr = (groups + 1) / 2;
-  }
-  // tpr need not divide 256: the leftover threads idle
-  s.rpi = THREADS / s.tpr;
-  return s;
-}
 
 // A tensor, how a workgroup covers its channels, and the rows of one workgroup (0: trips in turn).
 struct Span {
@@ -388,13 +363,6 @@ constexpr int SL_WGS = 256;                 // workgroups of a launch, about: on
                                             // slice's partials, and in the step the kernel shares the chip with a weight
                                             // gradient (ResNet-152 at minibatch 41, images/s at 192 / 256 / 320 / 384 /
                                             // 512 / 768 / 1024: 1215 / 1233 / 1216 / 1218 / 1223 / 1219 / 1218)
-constexpr int kSliceMaxSlabs = 512;         // beyond: the separate finishing launch
-constexpr long kSliceMaxRows = 16384;       // ... and, with 2-byte storage, larger tensors: a slice's row segment is 64 bytes
-                                            // there (ResNet-152 bf16 at minibatch 512: 3320 with, 3909 images/s without the
-                                            // slice kernels; fp32 at minibatch 128: 1326 with, 1310 without)
-template <class T> __host__ __device__ constexpr bool slice_takes(long rows, int slabs) {
-  return slabs <= kSliceMaxSlabs && (sizeof(T) == 4 || rows <= kSliceMaxRows);
-}
 constexpr int kSlicePhasesMax = 16;
 
 struct SliceScratch {
@@ -608,24 +576,6 @@ inline dim3 slice_grid(long rows, int c, long* rows_per_wg) {
   return dim3((unsigned)((rows + per - 1) / per), (unsigned)slices);
 }
 
-// slab count: a function of the shape only; at least ROWS_PER_THREAD rows per thread and
-// slab, about 1024 workgroups over all column slices (the partials the finishing kernel has
-// to read grow with slabs * c)
-template <class T>
-inline int slab_count(long rows, const ReduceShape& rs) {
-  long s = (rows + (long)rs.rpi * ROWS_PER_THREAD - 1) / ((long)rs.rpi * ROWS_PER_THREAD);
-  const long cap = MAX_SLABS / rs.col_slices > 0 ? MAX_SLABS / rs.col_slices : 1;
-  if (s > cap) s = cap;
-  // few enough for the slice kernels: then as few as one batch of their partial loads
-  // (128 slabs of doubles), as long as that leaves a workgroup per compute unit
-  if (slice_takes<T>(rows, (int)s)) {
-    const long one_batch = 128 > 256 / rs.col_slices ? 128 : 256 / rs.col_slices;
-    if (s > one_batch) s = one_batch;
-  }
-  if (s < 1) s = 1;
-  return (int)s;
-}
-
 // about 16 workgroups per compute unit at most, and threads for a whole number of rows
 inline Flat apply_flat(long rows, int c, int v, unsigned* blocks) {
   Flat f{(size_t)rows * (c / v), 0, c, c / v};
@@ -673,18 +623,18 @@ hipError_t bn_forward_v(const T* x, const float* gamma, const float* beta, const
   double* part = static_cast<double*>(workspace);
   float* coef = reinterpret_cast<float*>(part + (size_t)2 * MAX_SLABS * c);
   if (ready.part) {   // the producer of x left the sums
-    if (slice_takes<T>(rows, ready.slabs))
+    if (slice_takes((int)sizeof(T), rows, ready.slabs))
       bn_forward_slices(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, ready.part, ready.slabs, ready.stride, st);
     else
       bn_forward_finish<T, V>(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, ready.part, ready.slabs, ready.stride,
                               coef, st);
     return hipGetLastError();
   }
-  const ReduceShape rs = reduce_shape(c / V, V == 8, rows);
-  const int slabs = slab_count<T>(rows, rs);
+  const SumShape rs = bn_sum_shape(rows, c, V, (int)sizeof(T), /*backward=*/false, /*stores=*/false);
+  const int slabs = rs.slabs;
   hipLaunchKernelGGL((bn_reduce_kernel<0, T, V, false>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, (const T*)nullptr,
                      (const T*)nullptr, nullptr, nullptr, part, (T*)nullptr, Span{rows, c, rs.tpr, rs.rpi, V == 8 ? 0 : (rows + slabs - 1) / slabs});
-  if (slice_takes<T>(rows, slabs))
+  if (slice_takes((int)sizeof(T), rows, rs.slabs))
     bn_forward_slices(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, (const double*)part, slabs, MAX_SLABS, st);
   else
     bn_forward_finish<T, V>(x, gamma, beta, res, y, mean, istd, rows, c, relu, eps, (const double*)part, slabs, MAX_SLABS, coef, st);
@@ -719,19 +669,19 @@ hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma
   double* part = static_cast<double*>(workspace);
   float* coef = reinterpret_cast<float*>(part + (size_t)2 * MAX_SLABS * c);
   if (ready.part) {   // the data gradient left the sums
-    if (slice_takes<T>(rows, ready.slabs))
+    if (slice_takes((int)sizeof(T), rows, ready.slabs))
       bn_backward_slices(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, ready.part, ready.slabs, ready.stride, st);
     else
       bn_backward_finish<T, V>(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, ready.part, ready.slabs,
                                ready.stride, coef, st);
     return hipGetLastError();
   }
-  const ReduceShape rs = reduce_shape(c / V, V == 8, rows);
-  const int slabs = slab_count<T>(rows, rs);
   // Where the masked gradient is wanted anyway, this pass stores it and the next one reads it in the place of dy and y: a
   // tensor less (fp32 256 channels, 295750 rows 489 -> 416 us, 1024 channels, 6936 rows 52 -> 45; bf16 512 channels, 200704 rows 324 -> 272).
   // Below a million elements the store costs as much (8.2 -> 8.5 us for 128 rows of 1024).
   const bool g_early = y && g_out && rows * c >= (1L << 20);
+  const SumShape rs = bn_sum_shape(rows, c, V, (int)sizeof(T), /*backward=*/true, g_early);
+  const int slabs = rs.slabs;
   if (g_early)
     hipLaunchKernelGGL((bn_reduce_kernel<1, T, V, true>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, dy, y, mean,
                        istd, part, g_out, Span{rows, c, rs.tpr, rs.rpi, 0});
@@ -739,7 +689,7 @@ hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma
     hipLaunchKernelGGL((bn_reduce_kernel<1, T, V, false>), dim3(slabs, rs.col_slices), dim3(THREADS), 0, st, x, dy, y, mean,
                        istd, part, (T*)nullptr, Span{rows, c, rs.tpr, rs.rpi, (rows + slabs - 1) / slabs});
   if (g_early) { dy = g_out; y = nullptr; g_out = nullptr; }
-  if (slice_takes<T>(rows, slabs))
+  if (slice_takes((int)sizeof(T), rows, rs.slabs))
     bn_backward_slices(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, (const double*)part, slabs, MAX_SLABS, st);
   else
     bn_backward_finish<T, V>(x, dy, y, gamma, mean, istd, dx, dgamma, dbeta, g_out, rows, c, (const double*)part, slabs,

@@ -1,0 +1,70 @@
+// Host-side arithmetic of batch norm's sums: how the workgroups of the pass that sums cover a rows x c tensor
+// (no device code here).
+#pragma once
+
+namespace acc {
+
+constexpr int kBnThreads = 256;              // threads of a workgroup
+constexpr int kBnMaxSlabs = 1024;            // largest number of row slabs that a statistics pass adds up
+constexpr int kBnRowsPerThread = 4;          // rows a thread of the reduction sums at least (else fewer slabs)
+constexpr int kSliceMaxSlabs = 512;          // finish and apply in one launch up to here; beyond, the separate finishing launch
+constexpr long kSliceMaxRows = 16384;        // ... and, with 2-byte storage, larger tensors: a slice's row segment is 64 bytes
+                                             // there (ResNet-152 bf16 at minibatch 512: 3320 with, 3909 images/s without the
+                                             // slice kernels; fp32 at minibatch 128: 1326 with, 1310 without)
+constexpr bool slice_takes(int elem_size, long rows, long slabs) {
+  return slabs <= kSliceMaxSlabs && (elem_size == 4 || rows <= kSliceMaxRows);
+}
+
+// tpr threads of v channels each across a row, rpi rows per trip; col_slices workgroups (grid.y) where a row is wider than one
+// covers; slabs of rows (grid.x).
+struct SumShape {
+  int tpr, rpi, col_slices, slabs;
+};
+
+// as many slabs as give every thread kBnRowsPerThread rows
+inline long slabs_wanted(long rows, int rpi) { return (rows + (long)rpi * kBnRowsPerThread - 1) / ((long)rpi * kBnRowsPerThread); }
+
+// elem_size: bytes of a stored value; v: channels per thread; stores: the pass stores the masked gradient as it sums.
+// A function of the shape only.
+inline SumShape bn_sum_shape(long rows, int c, int v, int elem_size, bool backward, bool stores) {
+  const int groups = c / v;
+  SumShape s;
+  s.col_slices = (groups + 63) / 64;
+  // eight channels per thread: slices of like width (65 groups as 33 + 32; bf16 520 channels, 41 images of 28x28 backward 53 -> 47 us), else
+  // as wide as can be (65 as 64 + 1; fp32 516 channels 107 us against 110)
+  const bool even = v == 8;
+  s.tpr = even ? (groups + s.col_slices - 1) / s.col_slices : groups < 64 ? groups : 64;
+  // Small tensors: two slices, where they halve the slabs (every workgroup of the slice kernels reads its channels of all of them again).
+  // They do between 129 slabs of one slice, below which the sums only get shorter rows, and 512, from where one slice goes to the
+  // finishing launch.  One slice -> two, fp32, forward / backward (us): 128 channels, 2000 rows 6.3 -> 6.9 / 7.8 -> 9.1 (not taken), 8036 rows
+  // 9.3 -> 8.3 / 12.0 -> 11.0, 16384 rows 11.3 -> 10.6 / 16.6 -> 16.1; 256 channels, 4096 rows 9.7 -> 8.4 / 12.5 -> 11.1; bf16, four channels
+  // per thread, 200 channels, 8036 rows 13.2 -> 12.0 / 15.8 -> 14.9, 12544 rows (628 slabs) 13.9 -> 15.3 / 16.2 -> 20.3 (not taken).
+  // Beyond 512 slabs fp32 still gains forward (132 to 256 channels, 10000 to 16384 rows: 1.02 to 1.36 times as fast) and backward where rows
+  // come in whole 128-byte lines (160 channels, 13000 rows 17.6 -> 15.9, 192, 16000 rows 22.6 -> 20.7, 256, 12544 rows 24.2 -> 22.1; 252 channels,
+  // 14500 rows 0.82 times as fast, 200 0.83), but for the pass that stores the masked gradient as it sums at 256 channels only (12544 rows
+  // 26.7 -> 25.6; 192 channels, 16384 rows 0.94 times as fast, 224 0.93 to 1.03).
+  // Below 32 groups a slice's rows get too short to gain.
+  const long one = slabs_wanted(rows, kBnThreads / s.tpr);
+  const bool finish_too = elem_size == 4 && (!backward || c % (stores ? 256 : 32) == 0);
+  if (!even && rows <= kSliceMaxRows && s.col_slices == 1 && groups >= 32 && one > 128 && (one <= kSliceMaxSlabs || finish_too)) {
+    s.col_slices = 2;
+    s.tpr = (groups + 1) / 2;
+  }
+  // tpr need not divide kBnThreads: the leftover threads idle
+  s.rpi = kBnThreads / s.tpr;
+  // at least kBnRowsPerThread rows per thread and slab, about 1024 workgroups over all column slices (the partials the finishing
+  // kernel has to read grow with slabs * c)
+  long n = slabs_wanted(rows, s.rpi);
+  const long cap = kBnMaxSlabs / s.col_slices > 0 ? kBnMaxSlabs / s.col_slices : 1;
+  if (n > cap) n = cap;
+  // few enough for the slice kernels: then as few as one batch of their partial loads
+  // (128 slabs of doubles), as long as that leaves a workgroup per compute unit
+  if (slice_takes(elem_size, rows, n)) {
+    const long one_batch = 128 > 256 / s.col_slices ? 128 : 256 / s.col_slices;
+    if (n > one_batch) n = one_batch;
+  }
+  s.slabs = n < 1 ? 1 : (int)n;
+  return s;
+}
+
+}  // namespace acc

@@ -10,6 +10,7 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "bn_shape.h"
 #include "dgrad_split.h"
 
 namespace acc {
@@ -94,8 +95,6 @@ struct ConvGeom {
   // whether the launch reads it, and w is then not read; it may be null if so.
   const void* w_kn;
 };
-// Largest number of row slabs a batch-norm statistics pass adds up.
-constexpr int kBnMaxSlabs = 1024;
 // Number of 32-row blocks conv_igemm writes sums for (2 per 64-row tile).
 inline long conv_stat_slabs(long rows) { return ((rows + 63) / 64) * 2; }
 // Partial sums a convolution launch has left for a batch norm: float part[2][stride][c], `slabs` of
