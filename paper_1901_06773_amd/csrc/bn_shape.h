@@ -30,9 +30,10 @@ inline SumShape bn_sum_shape(long rows, int c, int v, int elem_size, bool backwa
   const int groups = c / v;
   SumShape s;
   s.col_slices = (groups + 63) / 64;
-  // eight channels per thread: slices of like width (65 groups as 33 + 32; bf16 520 channels, 41 images of 28x28 backward 53 -> 47 us), else
-  // as wide as can be (65 as 64 + 1; fp32 516 channels 107 us against 110)
-  const bool even = v == 8;
+  // Eight channels per thread, or two slices that store gradients: slices of like width (65 groups as 33 + 32; bf16 520 channels, 41 images of
+  // 28x28 backward 53 -> 47 us; fp32 storing the masked gradient, 25088 rows of 264 channels 63.5 -> 47.9, of 320 61.0 -> 51.3, of 384
+  // 65.6 -> 58.9), else as wide as can be (65 as 64 + 1; fp32 516 channels 107 us against 110; storing, 25088 rows of 1028 180 against 191)
+  const bool even = v == 8 || (stores && s.col_slices == 2);
   s.tpr = even ? (groups + s.col_slices - 1) / s.col_slices : groups < 64 ? groups : 64;
   // Small tensors: two slices, where they halve the slabs (every workgroup of the slice kernels reads its channels of all of them again).
   // They do between 129 slabs of one slice, below which the sums only get shorter rows, and 512, from where one slice goes to the
@@ -46,7 +47,7 @@ inline SumShape bn_sum_shape(long rows, int c, int v, int elem_size, bool backwa
   // Below 32 groups a slice's rows get too short to gain.
   const long one = slabs_wanted(rows, kBnThreads / s.tpr);
   const bool finish_too = elem_size == 4 && (!backward || c % (stores ? 256 : 32) == 0);
-  if (!even && rows <= kSliceMaxRows && s.col_slices == 1 && groups >= 32 && one > 128 && (one <= kSliceMaxSlabs || finish_too)) {
+  if (v == 4 && rows <= kSliceMaxRows && s.col_slices == 1 && groups >= 32 && one > 128 && (one <= kSliceMaxSlabs || finish_too)) {
     s.col_slices = 2;
     s.tpr = (groups + 1) / 2;
   }

@@ -48,6 +48,13 @@ def test_slices_of_channels(shapes, rows, c, es, back, slices):
     assert shapes([(rows, c, 4, es, back > 0, back == 2)])[0][2] == slices
 
 
+# the pass that stores as it sums: no slice of a few threads beside one of 64
+@pytest.mark.parametrize("rows,c,es,tpr", [(12544, 260, 4, 33), (25088, 264, 4, 33), (25088, 320, 4, 40), (12544, 384, 4, 48), (25088, 512, 4, 64), (16384, 300, 2, 38)])
+def test_slices_of_like_width_where_gradients_are_stored(shapes, rows, c, es, tpr):
+    assert shapes([(rows, c, 4, es, 1, 1)])[0][0] == tpr
+    assert shapes([(rows, c, 4, es, 1, 0)])[0][0] == 64
+
+
 def test_everything_is_covered(shapes):
     cases = [(rows, c, v, es, back > 0, back == 2) for rows in (1, 3, 49, 513, 2048, 4097, 9999, 16384, 16385, 200704, 1 << 31)
              for c in (4, 8, 64, 124, 128, 132, 200, 252, 256, 260, 264, 320, 512, 516, 2048, 65536) for v, es in ((4, 4), (4, 2), (8, 2))
