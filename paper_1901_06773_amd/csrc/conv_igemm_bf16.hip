@@ -484,7 +484,9 @@ typedef Cfg<1, 1, 8, 1, 1, 32, 4, 2> T32x32k8;         // eight groups of one wa
 // each once.  The constants are fitted to 420 launches (the layers of the ResNets at minibatches 1 to 512 and random ones with
 // widths in 8s, every kernel on each, replayed from a graph, six sets of tensors in turn, so that large operands come from memory):
 // median errors of 3 to 6 %, the choice is within 0.8 % of the best on average, 26 % at most.  Without the 32 x 32 kernel the
-// average is 6 %, without the 256 x 256 one 1.8 %.  A function of the shape and the alignment only.
+// average is 6 %, without the 256 x 256 one 1.8 %.  Strided filters (137 more launches) within 1.1 % on average, 16 % at most; with
+// the whole input counted for each of them 2 % and 33 %: 42x39 128->256 1x1/2, 125 images 16.9 -> 12.1 us, 56x56 128->128 3x3/2,
+// 128 images 59.7 -> 53.7.  A function of the shape and the alignment only.
 struct Kind {
   const char* name;
   int bm, bn, ks, kc, per_cu;
@@ -508,7 +510,10 @@ double predicted_us(const Kind& k, const ConvGeom& g, long M, long K) {
   const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
   const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
   const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = g.r * g.s > 1 ? k.taps * most : 0;
-  const double read = 2e-6 * ((double)g.n_img * g.h * g.wd * g.c + (double)N * K), written = 2e-6 * (double)M * N;
+  // pixels that are read: all of the input, or, by strided filters smaller than their stride, those under a tap; chunks of 32 values (half
+  // lines of memory) find nothing again that a tap of a strided filter has read before
+  const double taps = (double)M * g.r * g.s, in = (double)g.n_img * g.h * g.wd, pixels = g.stride > 1 && (taps < in || k.kc == 32) ? taps : in;
+  const double read = 2e-6 * (pixels * g.c + (double)N * K), written = 2e-6 * (double)M * N;
   const double memory = k.per_mb_read * read + k.per_mb_written * written;
   auto round = [&](long r) { return r == 0 ? 0.0 : first > r * next ? first : r * next; };
   const double compute = more + (k.per_cu == 1 ? first + (most - 1) * next : (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu));

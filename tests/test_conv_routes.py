@@ -100,3 +100,15 @@ def test_numbers_of_the_kernels(number, name):
     f = b._lib._ZN3acc17conv_variant_nameEi
     f.restype, f.argtypes = ctypes.c_char_p, [ctypes.c_int]
     assert f(number).decode() == name
+
+
+# bf16, strided filters: what is read is counted, not what the input holds
+@pytest.mark.parametrize("shape,name", [
+    ((125, 42, 39, 128, 256, 1, 2, 0, BF16), "igemm_bf16 256x256"),
+    ((86, 26, 26, 512, 176, 1, 2, 0, BF16), "igemm_bf16 64x64"),
+    ((41, 56, 56, 256, 512, 1, 2, 0, BF16), "igemm_bf16 256x256"),
+    ((128, 56, 56, 128, 128, 3, 2, 1, BF16), "igemm_bf16 128x128"),
+    ((32, 28, 28, 128, 128, 3, 2, 1, BF16), "igemm_bf16 64x64, four stages"),
+])
+def test_bf16_strided_filters(shape, name):
+    assert kernel("fwd", *shape) == name
