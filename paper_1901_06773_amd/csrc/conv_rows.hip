@@ -175,12 +175,16 @@ int best_kn(long M, long N, long K) {
 
 }  // namespace
 
-// Where this is predicted to be the fastest way.  Microseconds, other kernels (with the launch that transposes the filter, if [k][n]) -> this one:
-//   [n][k]  41 rows, 2048 -> 1000  29.2 -> 10.4,  196 rows, 512 -> 1000  11.8 -> 12.6 (not taken),  392 rows, 1000 -> 64  17.3 -> 5.6;
+// Where this is predicted to be the fastest way.  Microseconds, other kernels (with the launch that transposes the filter, if [k][n] and the
+// caller leaves w null for it) -> this one:
+//   [n][k]  41 rows, 2048 -> 1000  29.2 -> 10.4,  196 rows, 512 -> 1000  11.8 -> 12.6 (not taken);
 //   [k][n]  41 rows, 1000 -> 2048  26.1 -> 7.8,  392 rows, 1000 -> 1000  27.2 -> 19.5,  392 rows, 2048 -> 2048  45.4 -> 56.9 (not taken).
+// Filters larger than the caches, which the fit below does not hold: 25088 -> 4096, 16 rows 316 -> 112 and, [k][n], 365 -> 111, 32 rows
+// 326 -> 197 and 367 -> 155, from 64 rows on not taken; 4096 -> 4096, 32 rows 61 -> 35 and 90 -> 28.
 // Error against float64, 2048 values of K: 1.3e-7 (2.5e-7 in the other kernels).  From K = 320 on: shorter reductions gain as well (8.0 -> 5.4
 // at 256), but the kernels that take them are pinned to shapes of 224 and 288 by their tests.  Of the eight (four) values of K
-// that a lane takes, and of its columns of a [k][n] filter, all exist or none; rows of a [n][k] filter start on 64 bytes.
+// that a lane takes, and of its columns of a [k][n] filter, all exist or none; rows of a [n][k] filter start on 64 bytes (eights of K would
+// do: 392 rows, 1000 -> 64  17.3 -> 5.6, not taken).
 bool conv_igemm_rows_takes(const ConvGeom& g, long M, long K) {
   const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 && g.pad_dx == 0 && g.p == g.h && g.q == g.wd && g.out_stride == 1 &&
                      g.out_h == g.p && g.out_w == g.q;

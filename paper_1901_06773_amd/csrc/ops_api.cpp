@@ -81,7 +81,7 @@ int conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, in
   if (!workspace || workspace_bytes < filt) return ACC_EINVAL;
   void* wt = workspace;
   ConvGeom g{};
-  g.in = dy; g.w = wt; g.out = dx; g.dtype = dtype;
+  g.in = dy; g.out = dx; g.dtype = dtype;
   g.n_img = n; g.h = ho; g.wd = wo; g.c = cout; g.n_out = cin;
   g.r = r; g.s = s; g.stride = 1; g.accumulate = accumulate;
   g.out_h = h; g.out_w = wd;
@@ -96,7 +96,8 @@ int conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, in
     }
   }
   g.w_kn = r == 1 ? w : nullptr;
-  if (!conv_igemm_rows_takes(g, (long)n * g.p * g.q, cout)) {     // that kernel reads the filter as it lies
+  if (!g.w_kn || !conv_igemm_rows_takes(g, (long)n * g.p * g.q, cout)) {     // that kernel reads the filter as it lies
+    g.w = wt;
     g.w_kn = nullptr;
     if (!dry && (e = filter_flip_transpose(w, wt, cout, cin, r, s, dtype, st)) != hipSuccess) return status(e);
   }

@@ -35,9 +35,22 @@ def test_routes(case):
         assert want is None or got == want, (case, got)
 
 
+# data gradients that are taken because nothing has to transpose the filter first: about as fast as the other kernels without that launch
+TRANSPOSED = [
+    (2, 14, 1000, 1000, None, KN4),     # 392 rows, 1000 -> 1000
+    (1, 14, 2048, 1000, None, KN4),     # 196 rows, 1000 -> 2048
+    (160, 1, 2048, 512, None, KN1),
+]
+
+
+@pytest.mark.parametrize("case", TRANSPOSED)
+def test_the_saved_transposition_counts(case):
+    assert names(case)[1] == case[5]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("accumulate", [False, True])
-@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("case", CASES + TRANSPOSED)
 def test_products_of_few_rows(case, accumulate):
     n, hw, cin, cout = case[:4]
     rng = np.random.default_rng(cin + n)
