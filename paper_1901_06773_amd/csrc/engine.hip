@@ -759,21 +759,20 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       wg.x = ptr(s.x); wg.dy = ptr(s.dy); wg.dw = dw; wg.dtype = dt;
       wg.n_img = k; wg.h = 1; wg.wd = 1; wg.cin = l->cin; wg.p = 1; wg.q = 1; wg.cout = l->cout;
       wg.r = 1; wg.s = 1; wg.stride = 1; wg.pad = 0; wg.workspace = ptr(s.ws2); wg.workspace_bytes = c->plan.tbytes[s.ws2];
-      // the transposed filter for the data gradient is written by extra workgroups of the
-      // weight-gradient launch; the parts of the weight gradient are added up by extra
-      // workgroups of the data-gradient launch
-      wg.flip_w = wk; wg.flip_wt = ptr(s.ws);
-      ReduceJob job;
-      hipError_t e = wgrad(wg, conv_flops, &job);
-      if (e != hipSuccess) return e;
-      e = column_sum(ptr(s.dy), dw + (size_t)l->cout * l->cin, k, l->cout, dt, st);
-      if (e != hipSuccess) return e;
       ConvGeom cg{};
-      cg.side = job;
       cg.in = ptr(s.dy); cg.w = ptr(s.ws); cg.w_kn = wk; cg.out = ptr(s.dx); cg.dtype = dt;
       cg.n_img = k; cg.h = 1; cg.wd = 1; cg.c = l->cout; cg.p = 1; cg.q = 1; cg.n_out = l->cin;
       cg.r = 1; cg.s = 1; cg.stride = 1; cg.pad = 0; cg.out_h = 1; cg.out_w = 1; cg.out_stride = 1;
       cg.accumulate = s.dx_accumulate;
+      // the data gradient reads the filter as it lies, or transposed by extra workgroups of the weight-gradient launch (there is no
+      // launch to spare here, so s.ws is named when asking); the parts of the weight gradient are added up by extra
+      // workgroups of the data-gradient launch
+      if (conv_igemm_rows_takes(cg, k, l->cout)) cg.w = nullptr;
+      else { wg.flip_w = wk; wg.flip_wt = ptr(s.ws); }
+      hipError_t e = wgrad(wg, conv_flops, &cg.side);
+      if (e != hipSuccess) return e;
+      e = column_sum(ptr(s.dy), dw + (size_t)l->cout * l->cin, k, l->cout, dt, st);
+      if (e != hipSuccess) return e;
       return igemm(cg, conv_flops);
     }
     case K_GAP_B:

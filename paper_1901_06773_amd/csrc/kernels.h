@@ -92,7 +92,8 @@ struct ConvGeom {
   // output's stride and first pixel come from them.
   const DgradSplit* split;
   // Optional (1x1 filters): the same filter as w[k][n], the layout a data gradient finds it in.  conv_igemm_rows_takes() says
-  // whether the launch reads it, and w is then not read; it may be null if so.
+  // whether the launch reads it, and w is then not read and may be null.  A caller that asks with w null would need a launch of
+  // its own to write it, and the answer counts that.
   const void* w_kn;
 };
 // Number of 32-row blocks conv_igemm writes sums for (2 per 64-row tile).

@@ -125,6 +125,12 @@ int main(int argc, char** argv) {
       steps(2, "swapping step with graph mode on");
       if (stub_counters().graph_launches != g0) rc = 1;  // plans that swap never use the graph
     }
+  } else if (scenario == "small_large") {
+    // fully connected layers on either side of the line where the data gradient reads the filter as it lies
+    for (int k : {16, 96}) {
+      if (acc_plan_swaps(c, k, budget, ACC_PLAN_DYNAMIC, &s) != ACC_OK) { rc = fail("plan", c); break; }
+      steps(2, "step");
+    }
   } else if (scenario == "selftest") {
     // the stand-in must see planted mistakes: a wait on an event nobody recorded, a wait on last
     // iteration's record, a timing read on an untimed event, a copy that leaves the pool
@@ -157,12 +163,12 @@ int main(int argc, char** argv) {
          g.events_created, g.events_destroyed, stub_live_events(), g.max_live_events, g.records, g.stream_waits, g.host_waits,
          g.elapsed_reads, g.copies, g.copy_bytes / (double)GiB, g.launches);
   printf("violations: dead_event_uses %ld waits_on_unrecorded %ld waits_on_stale %ld elapsed_on_untimed %ld copies_out_of_range %ld "
-         "pointers_outside_pool %ld null_streams %ld sync_in_capture %ld leaked_events %ld (waits on own stream: %ld)\n",
+         "pointers_outside_pool %ld null_streams %ld sync_in_capture %ld filters_for_nobody %ld filters_missing %ld leaked_events %ld (waits on own stream: %ld)\n",
          g.dead_event_uses, g.waits_on_unrecorded, g.waits_on_stale, g.elapsed_on_untimed, g.copies_out_of_range,
-         g.pointers_outside_pool, g.null_streams, g.sync_in_capture, stub_live_events(), g.waits_on_own_stream);
+         g.pointers_outside_pool, g.null_streams, g.sync_in_capture, g.filters_for_nobody, g.filters_missing, stub_live_events(), g.waits_on_own_stream);
   if (g.first_complaint[0]) printf("first complaint: %s\n", g.first_complaint);
   const long bad = g.dead_event_uses + g.waits_on_unrecorded + g.waits_on_stale + g.elapsed_on_untimed + g.copies_out_of_range +
-                   g.pointers_outside_pool + g.null_streams + g.sync_in_capture + stub_live_events();
+                   g.pointers_outside_pool + g.null_streams + g.sync_in_capture + g.filters_for_nobody + g.filters_missing + stub_live_events();
   for (int i = 0; i < 4; ++i) stub_free_stream(st[i]);
   if (rc) return rc;
   printf(bad ? "RESULT: violations\n" : "RESULT: clean\n");

@@ -190,8 +190,16 @@ bool conv_igemm_bf16_takes(const ConvGeom&, long, long) { return false; }
 hipError_t conv_igemm_bf16(const ConvGeom&, int, int, hipStream_t, const LaunchProbe*) { return hipErrorInvalidValue; }
 const char* conv_variant_name(int v) { return v == V_WGRAD_DIRECT ? "wgrad_kernel<stub>" : "igemm_kernel<stub>"; }
 
+bool conv_igemm_rows_takes(const ConvGeom& g_, long M, long K) {      // a line somewhere between the layers and minibatches run here
+  return g_.dtype == DT_F32 && g_.r * g_.s == 1 && g_.h * g_.wd == 1 && M <= 64 && K <= 1000;
+}
+static const void* g_transposed = nullptr;      // the filter that a weight gradient's launch has written last, until it is read
 hipError_t conv_igemm(const ConvGeom& g_, hipStream_t st, LaunchProbe* probe) {
-  dev(g_.in, "conv_igemm: input"); dev(g_.w, "conv_igemm: filter"); dev(g_.out, "conv_igemm: output");
+  dev(g_.in, "conv_igemm: input"); dev(g_.w, "conv_igemm: filter"); dev(g_.w_kn, "conv_igemm: filter [k][n]"); dev(g_.out, "conv_igemm: output");
+  const void* reads = g_.w_kn && conv_igemm_rows_takes(g_, (long)g_.n_img * g_.p * g_.q, (long)g_.r * g_.s * g_.c) ? g_.w_kn : g_.w;
+  if (!reads && !g_.split) { ++g.filters_missing; complain("conv_igemm: no filter"); }
+  if (g_transposed && reads != g_transposed) { ++g.filters_for_nobody; complain("conv_igemm: does not read the filter that was transposed for it"); }
+  g_transposed = nullptr;
   dev(g_.side.part, "conv_igemm: reduce parts"); dev(g_.side.dw, "conv_igemm: reduce target");
   dev(g_.flip.w, "conv_igemm: flip source"); dev(g_.flip.wt, "conv_igemm: flip target");
   dev(g_.stats, "conv_igemm: stats"); dev(g_.bnb.sums, "conv_igemm: bn backward sums");
@@ -214,6 +222,7 @@ hipError_t conv_wgrad(const WgradGeom& g_, hipStream_t st, LaunchProbe* probe, R
   dev(g_.side.part, "conv_wgrad: reduce parts"); dev(g_.side.dw, "conv_wgrad: reduce target");
   const size_t need = wgrad_workspace_least(g_.n_img, g_.p, g_.q, g_.cin, g_.cout, g_.r, g_.s, g_.dtype);
   if (need && (!g_.workspace || g_.workspace_bytes < need || !in_pool(g_.workspace, g_.workspace_bytes))) { ++g.pointers_outside_pool; complain("conv_wgrad: workspace runs past the pool"); }
+  g_transposed = g_.flip_wt;
   if (deferred) *deferred = ReduceJob{nullptr, nullptr, 0, 0};
   if (need) {
     const ReduceJob job{g_.workspace, g_.dw, (size_t)g_.cout * g_.r * g_.s * g_.cin, (int)(need / ((size_t)g_.cout * g_.r * g_.s * g_.cin * 4))};

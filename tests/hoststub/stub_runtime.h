@@ -10,6 +10,7 @@ struct StubCounters {
   // what must stay zero
   long dead_event_uses = 0, waits_on_unrecorded = 0, waits_on_stale = 0, elapsed_on_untimed = 0;
   long copies_out_of_range = 0, pointers_outside_pool = 0, null_streams = 0, sync_in_capture = 0;
+  long filters_for_nobody = 0, filters_missing = 0;   // transposed ones that the next data gradient does not read; reads of one that is not written
   long waits_on_own_stream = 0;   // reported, not an error
   char first_complaint[160] = {0};
 };

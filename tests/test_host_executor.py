@@ -87,3 +87,11 @@ def test_planner_chosen_swaps_are_clean_on_the_host(binaries, net):
     built, out = binaries
     rc, log = run(built["limit"], spec_file(out, getattr(S, net)()), "dynamic")
     assert rc == 0 and "RESULT: clean" in log and "ERROR" not in log, log[-3000:]
+
+
+@pytest.mark.parametrize("net", ["resnet34", "vgg16"])
+def test_filters_are_transposed_for_data_gradients_that_read_them(binaries, net):
+    built, out = binaries
+    rc, log = run(built["limit"], spec_file(out, getattr(S, net)()), "small_large")
+    assert rc == 0 and "RESULT: clean" in log and "ERROR" not in log, log[-3000:]
+    assert "filters_for_nobody 0 filters_missing 0" in log
