@@ -449,8 +449,13 @@ class Context:
 # ---- single operations on torch device tensors (NHWC activations, O-H-W-I filters)
 def _stream_ptr(torch):
     """Handle of the current stream of the current device, without the Stream object that current_stream() makes of it: that object
-    was 2.8 of the 7.5 us that a call of one small layer kept the host busy."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    was 2.8 of the 7.5 us that a call of one small layer kept the host busy.  The short way is private to torch: a version without
+    it takes the public one."""
+    try:
+        device, stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
+    return stream(device())
 
 
 def op_conv_workspace(n, h, w, cin, cout, r, stride, pad) -> int:
