@@ -1,6 +1,7 @@
 """GPU parity of the bf16 convolutions at the sizes where their kernels can go wrong: ragged row and column tiles, widths
 that end inside a chunk of K or span two taps with it, reductions that deal unevenly to the groups of waves or leave
-some without a chunk, strided gathers and scattered results, accumulation.
+some without a chunk, strided gathers and scattered results, accumulation (the tilings that these data gradients do not reach:
+test_gpu_igemm_bf16_taps.py, which names them for both directions).
 
 Tolerance: the operands are bf16 on both sides and their products exact in fp32; the result is rounded once to bf16 (eight
 significant bits: 2^-8 of a value at most, 2^-8 / sqrt(3) = 2.3e-3 in the l2 norm if every value were the worst one of its

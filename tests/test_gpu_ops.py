@@ -404,24 +404,24 @@ def test_conv_full_size_sampled(case):
 
 # ------------------------------------------------------------------ bf16 storage
 BF16_CASES = [
-    (2, 14, 14, 64, 96, 3, 1, 1),      # fast path (channels a multiple of 64), N tail
+    (2, 14, 14, 64, 96, 3, 1, 1),      # whole chunks of channels, 32 x 32 tiles
     (3, 9, 9, 128, 256, 1, 1, 0),
     (2, 16, 16, 64, 128, 1, 2, 0),     # strided 1x1
     (5, 28, 28, 64, 64, 3, 1, 1),      # several tiles
-    (2, 16, 16, 32, 16, 3, 1, 1),      # 32 channels: per-element path in bf16
-    (2, 12, 10, 20, 24, 3, 1, 1),      # ragged channels
+    (2, 16, 16, 32, 16, 3, 1, 1),      # one chunk of 32 channels per tap; a data gradient over 16: the per-element loader
+    (2, 12, 10, 20, 24, 3, 1, 1),      # ragged channels: the per-element loader
     (2, 23, 23, 8, 16, 7, 2, 3),       # stem-like
-    # input channels a multiple of 128: the weight gradient runs on the bf16 matrix cores (128 x 128 tiles)
+    # weight gradients in several tiles of 128 x 128
     (4, 14, 14, 256, 128, 3, 1, 1),    # filter taps and padding; 784 rows = 12 chunks of 64 and a ragged one
     (6, 14, 14, 128, 200, 3, 1, 1),    # output channels end inside the second row of tiles
     (8, 28, 28, 128, 128, 3, 2, 1),    # strided 3x3
     (9, 7, 7, 512, 512, 1, 2, 0),      # strided 1x1
     (41, 14, 14, 256, 256, 3, 1, 1),   # benchmark-sized layer: the minibatch range is cut into parts
-    # at least 256 tiles of 128 x 128: forward and data gradient run in the 128 x 128 bf16 kernel
-    (16, 56, 56, 64, 128, 1, 1, 0),    # one chunk of K, 392 row tiles
-    (44, 28, 28, 128, 128, 3, 1, 1),   # taps and padding; 34496 rows: the last row tile is half full
+    # large layers: forward and data gradient in tiles of 128 x 64 and 128 x 128 (256 x 256 and the rest: test_gpu_igemm_bf16_taps.py)
+    (16, 56, 56, 64, 128, 1, 1, 0),    # one chunk of K, 392 row tiles of 128
+    (44, 28, 28, 128, 128, 3, 1, 1),   # taps and padding; 34496 rows: the last row tile of 128 is half full
     (44, 56, 56, 128, 128, 1, 2, 0),   # strided gather forward, scattering data gradient
-    (44, 28, 28, 128, 200, 1, 1, 0),   # output channels end inside the second column of tiles
+    (44, 28, 28, 128, 200, 1, 1, 0),   # output channels end inside the second column of 128 x 128 tiles
 ]
 
 

@@ -80,3 +80,21 @@ def test_infinities_and_nan_stay_in_their_rows_and_columns():
     ref[1, 70] = np.nan
     ref[3] = np.nan
     np.testing.assert_array_equal(y.cpu().numpy().reshape(5, 72), ref)
+
+
+# (rows, columns of the result, kernel): a filter that is read as it lies, one, two and four columns per lane
+@pytest.mark.parametrize("n,cin,cout,name", [(5, 72, 2044, KN1), (41, 2048, 1000, KN2), (95, 2048, 2048, KN4)])
+@pytest.mark.gpu
+def test_infinities_and_nan_through_a_filter_read_as_it_lies(n, cin, cout, name):
+    assert B().op_conv_kernel("dgrad", n, 1, 1, cin, cout, 1, 1, 0, 0) == name
+    dy, w = np.ones((n, 1, 1, cout), np.float32), np.full((cout, 1, 1, cin), 0.5, np.float32)
+    dy[1, 0, 0, cout - 1], dy[3, 0, 0, 7], w[300, 0, 0, cin - 3] = np.inf, np.nan, -np.inf
+    ws = torch.empty(B().op_conv_workspace(n, 1, 1, cin, cout, 1, 1, 0), dtype=torch.uint8, device="cuda")
+    dx = torch.empty((n, 1, 1, cin), device="cuda")
+    B().op_conv_dgrad(dev(dy), dev(w), dx, 1, 0, ws)
+    ref = np.full((n, cin), cout / 2.0)
+    ref[:, cin - 3] = -np.inf
+    ref[1] = np.inf
+    ref[1, cin - 3] = np.nan
+    ref[3] = np.nan
+    np.testing.assert_array_equal(dx.cpu().numpy().reshape(n, cin), ref)
