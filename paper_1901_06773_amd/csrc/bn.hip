@@ -678,8 +678,8 @@ hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma
   }
   // Where the masked gradient is wanted anyway, this pass stores it and the next one reads it in the place of dy and y: a
   // tensor less (fp32 256 channels, 295750 rows 489 -> 416 us, 1024 channels, 6936 rows 52 -> 45; bf16 512 channels, 200704 rows 324 -> 272).
-  // Below a million elements the store costs as much (8.2 -> 8.5 us for 128 rows of 1024).
-  const bool g_early = y && g_out && rows * c >= (1L << 20);
+  // Below a million elements the store costs as much (8.2 -> 8.5 us for 128 rows of 1024).  Not over x, which the next pass reads.
+  const bool g_early = y && g_out && g_out != x && rows * c >= (1L << 20);
   const SumShape rs = bn_sum_shape(rows, c, V, (int)sizeof(T), /*backward=*/true, g_early);
   const int slabs = rs.slabs;
   if (g_early)

@@ -32,3 +32,25 @@ def test_bn_bwd_masked_gradient(rows, c, dtype, in_place):
     assert (db.double() - ref_db).abs().max() <= rows * 2.0 ** -22 and (dg.double() - ref_dg).abs().max() <= rows * 2.0 ** -22
     eps = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -21
     assert ((dx.double().view(rows, c) - ref).abs() <= ref.abs() * eps + 20 * 2.0 ** -21).all()
+
+
+@pytest.mark.parametrize("over", ["x", "y"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_bn_bwd_masked_gradient_over_an_input(over, dtype):
+    """The masked gradient may lie over a tensor that the call has read: the same bits as in a place of its own."""
+    from paper_1901_06773_amd import binding as b
+    rows, c = 8200, 256
+    g = torch.Generator().manual_seed(3)
+    x, dy, y = (torch.randn(1, 1, rows, c, generator=g).to(dtype).cuda() for _ in range(3))
+    gamma = (torch.rand(c, generator=g) + 0.5).cuda()
+    mean, istd = x.double().reshape(rows, c).mean(0).float(), (x.double().reshape(rows, c).var(0, unbiased=False) + 1e-5).rsqrt().float()
+    ws = torch.empty(b.op_bn_workspace(c), dtype=torch.uint8, device="cuda")
+    want_g = torch.where(y > 0, dy, torch.zeros_like(dy))
+    gd, xh = want_g.double().view(rows, c), (x.double().view(rows, c) - mean.double()) * istd.double()
+    ref = gamma.double() * istd.double() * (gd - gd.mean(0) - xh * (gd * xh).mean(0))
+    dx, dg, db = torch.empty_like(x), torch.empty(c, device="cuda"), torch.empty(c, device="cuda")
+    b.op_bn_bwd(x, dy, y, gamma, mean, istd, dx, dg, db, x if over == "x" else y, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(x if over == "x" else y, want_g)
+    eps = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -21
+    assert ((dx.double().view(rows, c) - ref).abs() <= ref.abs() * eps + 20 * 2.0 ** -21).all()
