@@ -665,7 +665,7 @@ void bn_backward_slices(const T* x, const T* dy, const T* y, const float* gamma,
 template <class T, int V>
 hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma, const float* mean,
                          const float* istd, T* dx, float* dgamma, float* dbeta, T* g_out, long rows, int c,
-                         void* workspace, hipStream_t st, const BnSums& ready) {
+                         void* workspace, hipStream_t st, const BnSums& ready, bool in_iteration) {
   double* part = static_cast<double*>(workspace);
   float* coef = reinterpret_cast<float*>(part + (size_t)2 * MAX_SLABS * c);
   if (ready.part) {   // the data gradient left the sums
@@ -676,10 +676,8 @@ hipError_t bn_backward_v(const T* x, const T* dy, const T* y, const float* gamma
                                ready.stride, coef, st);
     return hipGetLastError();
   }
-  // Where the masked gradient is wanted anyway, this pass stores it and the next one reads it in the place of dy and y: a
-  // tensor less (fp32 256 channels, 295750 rows 489 -> 416 us, 1024 channels, 6936 rows 52 -> 45; bf16 512 channels, 200704 rows 324 -> 272).
-  // Below a million elements the store costs as much (8.2 -> 8.5 us for 128 rows of 1024).  Not over x, which the next pass reads.
-  const bool g_early = y && g_out && g_out != x && rows * c >= (1L << 20);
+  // (not over x, which the next pass reads)
+  const bool g_early = y && g_out && g_out != x && bn_stores_early(rows, c, (int)sizeof(T), in_iteration);
   const SumShape rs = bn_sum_shape(rows, c, V, (int)sizeof(T), /*backward=*/true, g_early);
   const int slabs = rs.slabs;
   if (g_early)
@@ -726,7 +724,7 @@ hipError_t bn_forward(const void* x, const float* gamma, const float* beta, cons
 
 hipError_t bn_backward(const void* x, const void* dy, const void* y, const float* gamma, const float* mean,
                        const float* istd, void* dx, float* dgamma, float* dbeta, void* g_out, long rows, int c,
-                       void* workspace, int dtype, hipStream_t st, const BnSums* ready_sums) {
+                       void* workspace, int dtype, hipStream_t st, const BnSums* ready_sums, bool in_iteration) {
   if (!x || !dy || !gamma || !mean || !istd || !dx || !dgamma || !dbeta || !workspace)
     return hipErrorInvalidValue;
   if (rows <= 0 || c <= 0 || (c & 3)) return hipErrorInvalidValue;
@@ -735,13 +733,13 @@ hipError_t bn_backward(const void* x, const void* dy, const void* y, const float
     return hipErrorInvalidValue;
   if (dtype == DT_F32)
     return bn_backward_v<float, 4>((const float*)x, (const float*)dy, (const float*)y, gamma, mean, istd, (float*)dx, dgamma,
-                         dbeta, (float*)g_out, rows, c, workspace, st, ready);
+                         dbeta, (float*)g_out, rows, c, workspace, st, ready, in_iteration);
   if (dtype == DT_BF16 && wide_bf16(rows, c))
     return bn_backward_v<bf16_t, 8>((const bf16_t*)x, (const bf16_t*)dy, (const bf16_t*)y, gamma, mean, istd, (bf16_t*)dx,
-                                    dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready);
+                                    dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready, in_iteration);
   if (dtype == DT_BF16)
     return bn_backward_v<bf16_t, 4>((const bf16_t*)x, (const bf16_t*)dy, (const bf16_t*)y, gamma, mean, istd, (bf16_t*)dx,
-                         dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready);
+                         dgamma, dbeta, (bf16_t*)g_out, rows, c, workspace, st, ready, in_iteration);
   return hipErrorInvalidValue;
 }
 

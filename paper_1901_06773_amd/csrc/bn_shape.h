@@ -68,4 +68,14 @@ inline SumShape bn_sum_shape(long rows, int c, int v, int elem_size, bool backwa
   return s;
 }
 
+// Whether the pass that sums stores the masked gradient that is wanted anyway, and the next one reads it in the place of dy and y: a tensor
+// less (fp32 256 channels, 295750 rows 489 -> 416 us, 1024 channels, 6936 rows 52 -> 45; bf16 512 channels, 200704 rows 324 -> 272).
+// Below a million elements the store costs as much (8.2 -> 8.5 us for 128 rows of 1024).  In an iteration, where a weight gradient runs beside
+// and the caches hold smaller tensors, fp32 from 20 million on: ResNet-152, 41 images 30.0 ms from one million on, 29.6 from 12, 29.4 from 20
+// or never; 128 images 78.6, 78.2, 78.3, 78.7; ResNet-101, 32 images 16.97, 16.83, 16.78, 16.83.  (bf16, ResNet-50, 128 images 13.0 ms from
+// one million on, 13.3 never.)  A function of the shape only: with or without the other stream an iteration gives the same bits.
+inline bool bn_stores_early(long rows, int c, int elem_size, bool in_iteration) {
+  return rows * c >= (in_iteration && elem_size == 4 ? 20L << 20 : 1L << 20);
+}
+
 }  // namespace acc

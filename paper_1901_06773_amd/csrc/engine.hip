@@ -790,7 +790,8 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
                            (long)k * T(s.x).h * T(s.x).w, l->cin, ptr(s.ws), dt, st, &ready);
       }
       return bn_backward(ptr(s.x), ptr(s.dy), ptr(s.y), w, stat, stat + l->cin, ptr(s.dx), dw, dw + l->cin,
-                         s.g_inplace ? ptr(s.dy) : nullptr, (long)k * T(s.x).h * T(s.x).w, l->cin, ptr(s.ws), dt, st);
+                         s.g_inplace ? ptr(s.dy) : nullptr, (long)k * T(s.x).h * T(s.x).w, l->cin, ptr(s.ws), dt, st, nullptr,
+                         /*in_iteration=*/true);
     }
     case K_CONV_B: {
       const int h = T(s.x).h, wd = T(s.x).w, ho = T(s.dy).h, wo = T(s.dy).w;

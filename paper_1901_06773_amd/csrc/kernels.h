@@ -207,11 +207,12 @@ hipError_t bn_forward(const void* x, const float* gamma, const float* beta, cons
                       void* y, float* mean, float* istd, long rows, int c, int relu, float eps,
                       void* workspace, int dtype, hipStream_t st, const BnSums* ready_sums = nullptr);
 // ready_sums (may be null): the sums of g and g * xhat are already there (a data-gradient launch
-// wrote them, ConvGeom::bnb, and masked dy); they are not computed again, and y must be null.
+// wrote them, ConvGeom::bnb, and masked dy); they are not computed again, and y must be null.  in_iteration: the launch is one of a
+// whole step, beside a weight gradient (bn_shape.h).
 hipError_t bn_backward(const void* x, const void* dy, const void* y, const float* gamma,
                        const float* mean, const float* istd, void* dx, float* dgamma, float* dbeta,
                        void* g_out, long rows, int c, void* workspace, int dtype, hipStream_t st,
-                       const BnSums* ready_sums = nullptr);
+                       const BnSums* ready_sums = nullptr, bool in_iteration = false);
 
 hipError_t maxpool_forward(const void* x, void* y, int n, int h, int wd, int c, int r, int s,
                            int stride, int pad, int dtype, hipStream_t st);

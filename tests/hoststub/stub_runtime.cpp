@@ -256,7 +256,7 @@ hipError_t bn_forward(const void* x, const float* gamma, const float* beta, cons
 }
 hipError_t bn_backward(const void* x, const void* dy, const void* y, const float* gamma, const float* mean, const float* istd,
                        void* dx, float* dgamma, float* dbeta, void* g_out, long rows, int c, void* workspace, int dtype,
-                       hipStream_t st, const BnSums* ready) {
+                       hipStream_t st, const BnSums* ready, bool) {
   dev(x, "bn_backward: x"); dev(dy, "bn_backward: dy"); dev(y, "bn_backward: y"); dev(gamma, "bn_backward: gamma");
   dev(mean, "bn_backward: mean"); dev(istd, "bn_backward: istd"); dev(dx, "bn_backward: dx"); dev(dgamma, "bn_backward: dgamma");
   dev(dbeta, "bn_backward: dbeta"); dev(g_out, "bn_backward: g_out"); dev(workspace, "bn_backward: workspace");

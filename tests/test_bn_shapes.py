@@ -13,7 +13,7 @@ int main() {
   long rows; int c, v, es, back, stores;
   while (std::scanf("%ld %d %d %d %d %d", &rows, &c, &v, &es, &back, &stores) == 6) {
     const acc::SumShape s = acc::bn_sum_shape(rows, c, v, es, back, stores);
-    std::printf("%d %d %d %d\\n", s.tpr, s.rpi, s.col_slices, s.slabs);
+    std::printf("%d %d %d %d %d %d\\n", s.tpr, s.rpi, s.col_slices, s.slabs, acc::bn_stores_early(rows, c, es, false), acc::bn_stores_early(rows, c, es, true));
   }
 }
 """
@@ -55,11 +55,20 @@ def test_slices_of_like_width_where_gradients_are_stored(shapes, rows, c, es, tp
     assert shapes([(rows, c, 4, es, 1, 0)])[0][0] == 64
 
 
+# alone / in an iteration
+@pytest.mark.parametrize("rows,c,es,alone,step", [
+    (8036, 1024, 4, True, False), (32144, 512, 4, True, False), (128576, 256, 4, True, True), (25088, 1024, 4, True, True),
+    (8036, 1024, 2, True, True), (1023, 1024, 4, False, False), (1023, 1024, 2, False, False),
+])
+def test_where_the_sums_store_the_masked_gradient(shapes, rows, c, es, alone, step):
+    assert shapes([(rows, c, 4, es, 1, 1)])[0][4:] == (alone, step)
+
+
 def test_everything_is_covered(shapes):
     cases = [(rows, c, v, es, back > 0, back == 2) for rows in (1, 3, 49, 513, 2048, 4097, 9999, 16384, 16385, 200704, 1 << 31)
              for c in (4, 8, 64, 124, 128, 132, 200, 252, 256, 260, 264, 320, 512, 516, 2048, 65536) for v, es in ((4, 4), (4, 2), (8, 2))
              for back in (0, 1, 2) if c % v == 0]
-    for (rows, c, v, es, back, stores), (tpr, rpi, cols, slabs) in zip(cases, shapes(cases)):
+    for (rows, c, v, es, back, stores), (tpr, rpi, cols, slabs, _, _) in zip(cases, shapes(cases)):
         assert 1 <= tpr <= 64 and tpr * rpi <= 256 and rpi >= 1
         assert cols * tpr * v >= c > (cols - 1) * tpr * v              # no slice without channels
         assert 1 <= slabs <= 1024 and slabs * cols <= max(1024, cols)
