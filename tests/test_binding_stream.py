@@ -1,6 +1,9 @@
 """The stream that single-operation calls use: the current one of the current device, by whichever way the installed torch offers."""
 import types
 
+import pytest
+import torch  # noqa: F401  (before the library: both are to use the HIP runtime that torch brings)
+
 from paper_1901_06773_amd import binding as B
 
 
@@ -16,8 +19,6 @@ def test_the_short_way_asks_for_the_current_device():
 
 
 def test_errors_of_the_runtime_are_not_swallowed():
-    import pytest
-
     def broken():
         raise RuntimeError("no device")
     c = types.SimpleNamespace(_cuda_getDevice=broken, _cuda_getCurrentRawStream=lambda d: 0)
