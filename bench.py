@@ -1,6 +1,6 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path: ResNet-152 fp32 training steps under an 8 GiB device-memory
-budget on one MI355X (benchmark configs[3]), synthetic ImageNet-shaped data.
+budget on one MI355X, synthetic ImageNet-shaped data.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--k auto|N] [--budget-gib 8]
 
@@ -36,7 +36,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--k", default="auto", help="headline minibatch, or 'auto' = best of the sweep")
-    ap.add_argument("--sweep", default="32,64,128,256", help="minibatch sizes of the sweep (configs[3])")
+    ap.add_argument("--sweep", default="32,64,128,256", help="minibatch sizes of the sweep")
     ap.add_argument("--swap-points", default="64,128,4x",
                     help="minibatches at which the swap engine is measured in detail after the headline "
                          "('4x' = four times the largest minibatch that needs no swap; '' = none)")
@@ -44,7 +44,7 @@ def parse():
     ap.add_argument("--net", default="resnet152", choices=["vgg16", "resnet18", "resnet34", "resnet50", "resnet101", "resnet152"])
     ap.add_argument("--mode", default="dynamic", choices=["dynamic", "naive", "none"])
     ap.add_argument("--dtype", default="f32", choices=["f32", "bf16"],
-                    help="storage of activations / gradients / kernel-side weights (bf16: configs[4])")
+                    help="storage of activations / gradients / kernel-side weights")
     ap.add_argument("--serial", action="store_true",
                     help="weight gradients on the compute stream instead of their own (every kernel runs alone: "
                          "the setting in which single kernels are timed)")
@@ -181,7 +181,7 @@ def main():
         torch.cuda.synchronize()
         return (time.perf_counter() - t) / steps, loss
 
-    # ---- sweep (configs[3]): short runs, to find the throughput-optimal minibatch
+    # ---- sweep: short runs, to find the throughput-optimal minibatch
     sweep = []
     for k in trainable:
         try:

@@ -56,12 +56,12 @@ struct Span {
 // Sums over the rows of one slab, per channel, of up to two quantities.  Bound by memory: x (and dy, y) read once, V channels
 // = 16 bytes per thread and load, U rows in flight.  With the apply passes below, bf16 512 channels, 256 images of 28x28, residual:
 // forward 196 -> 153 us, backward 354 -> 313 (8-byte loads, coefficients fetched per element before); what is left of
-// the way to 134 / 223 us of traffic at 4.6 TB/s is the second read of x, dy and y, which the caches don't hold: in slices of
-// 1/2 or 1/4 of the channels, one after the other, the rows become too short (862 us both ways), and walking back from the
-// end in the second pass gives nothing.
-// The rows of a slab: consecutive ones, or, where a pass reads bf16 eight channels at a time or stores a tensor, trips of a few
-// rows dealt out to the slabs in turn, so that the launch as a whole walks through one contiguous window after the other (bf16 1024
-// channels, 81648 rows forward 96.4 -> 90.7 us; fp32 sums alone gain nothing, small ones lose 3 %).
+// the way to 134 / 223 us of traffic at 4.6 TB/s is the second read: of x, and of dy and y or, where the sums have stored it
+// (G; 313 -> 272 us), of the masked gradient, which the caches don't hold.  In slices of 1/2 or 1/4 of the channels, one after the other,
+// the rows become too short (862 us both ways), and walking back from the end in the second pass gives nothing.
+// The rows of a slab: consecutive ones, or, in a forward pass that reads bf16 eight channels at a time and in a backward pass that stores
+// the masked gradient, trips of a few rows dealt out to the slabs in turn, so that the launch as a whole walks through one contiguous window
+// after the other (bf16 1024 channels, 81648 rows forward 96.4 -> 90.7 us; fp32 sums alone gain nothing, small ones lose 3 %).
 // MODE 0: (x, x*x).   MODE 1: (g, g*xhat) with g = dy * [y > 0] (y optional).
 // G: MODE 1 with y, and g is stored (over dy if the caller says so).
 template <int MODE, class T, int V, bool G>

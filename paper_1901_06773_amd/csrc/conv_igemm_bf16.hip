@@ -483,10 +483,13 @@ typedef Cfg<1, 1, 8, 1, 1, 32, 4, 2> T32x32k8;         // eight groups of one wa
 // taps more per tile for filters larger than 1x1, memory = per_mb_read * MB of both operands + per_mb_written * MB of the result,
 // each once.  The constants are fitted to 420 launches (the layers of the ResNets at minibatches 1 to 512 and random ones with
 // widths in 8s, every kernel on each, replayed from a graph, six sets of tensors in turn, so that large operands come from memory):
-// median errors of 3 to 6 %, the choice is within 0.8 % of the best on average, 26 % at most.  Without the 32 x 32 kernel the
-// average is 6 %, without the 256 x 256 one 1.8 %.  Strided filters (137 more launches) within 1.1 % on average, 16 % at most; with
-// the whole input counted for each of them 2 % and 33 %: 42x39 128->256 1x1/2, 125 images 16.9 -> 12.1 us, 56x56 128->128 3x3/2,
-// 128 images 59.7 -> 53.7.  A function of the shape and the alignment only.
+// median errors of 3 to 6 %, the choice is within 0.8 % of the best on average, 26 % at most.  Strided filters (137 more launches)
+// within 1.1 % on average, 16 % at most; with the whole input counted for each of them 2 % and 33 %: 42x39 128->256 1x1/2,
+// 125 images 16.9 -> 12.1 us, 56x56 128->128 3x3/2, 128 images 59.7 -> 53.7.
+// What each is worth, over those and 138 more forward launches: without it the choice gets slower on average by, and is off the best by at
+// most, 256 x 256 0.7 % and 26 %, 128 x 256 0.2 and 19, 128 x 128 0.9 and 45, 128 x 64 0.5 and 23, 64 x 64 0.7 and 18, its four stages 1.6 and 28,
+// four pairs 0.3 and 20, four waves 0.1 and 34, 32 x 32 6 and 155; 256 x 128 is the only large one for fewer than 64 channels and
+// worth nothing from there on.  A function of the shape and the alignment only.
 struct Kind {
   const char* name;
   int bm, bn, ks, kc, per_cu;

@@ -112,8 +112,8 @@ __global__ __launch_bounds__(THREADS) void maxpool_fwd_kernel(const T* __restric
   }
 }
 
-// The same for 3x3 windows, V channels (16 bytes) per thread: the nine loads go out together, places that do not exist read the window's centre
-// column or row instead and are not compared; indices in 32 bits.  Bound by HBM.  3x3/2 of 64 channels at 112x112: fp32, 32 images 31.6 -> 27.8 us
+// The same for 3x3 windows, V channels (16 bytes) per thread: the nine loads go out together, places that do not exist read the nearest one
+// that does and are not compared; indices in 32 bits.  Bound by HBM.  3x3/2 of 64 channels at 112x112: fp32, 32 images 31.6 -> 27.8 us
 // (129 MB), 2 images 7.0 -> 4.2; bf16, 128 images 91.5 -> 50.1.
 template <class T, int V>
 __global__ __launch_bounds__(THREADS) void maxpool3_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, int total, int h, int wd, int c,

@@ -109,7 +109,7 @@ def _head(net: NetSpec, src: int, cin: int, classes: int) -> None:
 
 def bottleneck_unit(cin: int = 64, planes: int = 16, hw: int = 16, classes: int = 10) -> NetSpec:
     """One identity-shortcut bottleneck block followed by global average pooling,
-    a fully connected layer and softmax cross-entropy (BASELINE configs[0])."""
+    a fully connected layer and softmax cross-entropy."""
     net = NetSpec(f"bottleneck_{cin}_{planes}_{hw}", cin, hw, hw, classes)
     out = _bottleneck(net, -1, cin, planes, 1, project=False, variant="v1",
                       expansion=cin // planes)

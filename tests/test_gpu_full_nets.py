@@ -177,15 +177,15 @@ def full_net_case(name, k):
 
 
 def test_resnet50_minibatch_32_against_the_oracle():
-    """configs[1]."""
+    """ResNet-50 at minibatch 32."""
     full_net_case("resnet50", 32)
 
 
 def test_resnet101_minibatch_32_against_the_oracle():
-    """The network of configs[2] at the largest minibatch the oracle finishes within a minute."""
+    """ResNet-101 at the largest minibatch the oracle finishes within a minute."""
     full_net_case("resnet101", 32)
 
 
 def test_resnet152_minibatch_16_against_the_oracle():
-    """The benchmark's network (configs[3])."""
+    """The benchmark's network."""
     full_net_case("resnet152", 16)

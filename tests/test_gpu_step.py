@@ -64,7 +64,7 @@ def tall_chain():
 
 
 NETS = {
-    "config1_unit": (lambda: S.bottleneck_unit(), 2),                       # BASELINE configs[0]
+    "config1_unit": (lambda: S.bottleneck_unit(), 2),
     "mini_resnet_w8": (lambda: S.resnet((1, 2), in_hw=32, classes=10, width=8), 3),
     "mini_resnet_w32": (lambda: S.resnet((1, 1, 2, 1), in_hw=64, classes=100, width=32), 5),
     # 30 x 30 input: the stem leaves 15 x 15 for the max-pool (odd: ragged last windows and blocks)
@@ -412,7 +412,7 @@ def test_resnet152_at_the_benchmark_size_swapped_and_resident_agree_bit_for_bit(
     assert np.log(1000.0) < ref["losses"][0] < np.log(1000.0) + 3.0
 
 
-# ------------------------------------------------------------------ bf16 storage (configs[4]'s arithmetic)
+# ------------------------------------------------------------------ bf16 storage
 def l2_close(gpu, ref, what, tol):
     gpu = np.asarray(gpu, np.float64); ref = np.asarray(ref, np.float64)
     assert np.isfinite(gpu).all(), f"{what}: non-finite values"
@@ -520,8 +520,8 @@ def _output_shapes(net):
 @pytest.mark.parametrize("name", ["config1_unit", "mini_resnet_w8", "mini_resnet_w32", "wide_chain", "tall_chain", "resnet50"])
 def test_bf16_step_against_the_fp32_oracle(name):
     """Activations, their gradients and the weights the kernels read stored as bf16, fp32
-    accumulation, fp32 master weights and statistics, against the fp32 oracle (configs[4]'s
-    arithmetic; ResNet-50 at its full input size and minibatch 8 is the deep case).
+    accumulation, fp32 master weights and statistics, against the fp32 oracle
+    (ResNet-50 at its full input size and minibatch 8 is the deep case).
     End to end: the loss within 2e-2, every gradient finite.  Gradient tensors: compared in a
     second iteration that runs on the oracle's forward activations (rounded to bf16 on their
     way in, acc_inject_output), so that ReLU masks and max-pool winners are taken from the
@@ -623,13 +623,13 @@ def _budgeted_vs_resident(net, k, budget, expect_swaps, dtype=0, steps=2):
 
 
 def test_config_resnet50_uncapped_needs_no_swap():
-    """configs[1]: ResNet-50, minibatch 32, no memory cap: the planner must choose zero swaps."""
+    """ResNet-50, minibatch 32, no memory cap: the planner must choose zero swaps."""
     plan, out = _budgeted_vs_resident(S.resnet50(), 32, 64 * GiB, expect_swaps=False)
     assert plan["n_swapped"] == 0 and out["stats"]["bytes_out"] == 0
 
 
 def test_config_resnet101_under_12_gib():
-    """configs[2]: ResNet-101, minibatch 64, 12 GiB: planner-chosen swaps, same bits as the
+    """ResNet-101, minibatch 64, 12 GiB: planner-chosen swaps, same bits as the
     resident run."""
     net = S.resnet101()
     plan, out = _budgeted_vs_resident(net, 64, 12 * GiB, expect_swaps=_needs_swap(net, 64, 12 * GiB))
@@ -645,7 +645,7 @@ def _needs_swap(net, k, budget, dtype=0):
 
 
 def test_config_resnet152_under_8_gib_at_twice_the_resident_minibatch():
-    """configs[3]: ResNet-152 under 8 GiB at minibatch 64 (the resident maximum is 46)."""
+    """ResNet-152 under 8 GiB at minibatch 64 (the resident maximum is 46)."""
     plan, out = _budgeted_vs_resident(S.resnet152(), 64, 8 * GiB, expect_swaps=True)
     assert out["stats"]["bytes_out"] == plan["bytes_swapped"] > 2 * GiB
 
@@ -683,7 +683,7 @@ def test_vgg16_at_full_size_swapping_everything_keeps_the_bits():
 
 
 def test_config_resnet152_bf16_under_24_gib():
-    """configs[4]: ResNet-152 with bf16 storage, 24 GiB; at minibatch 320 (the resident maximum
+    """ResNet-152 with bf16 storage, 24 GiB; at minibatch 320 (the resident maximum
     is 291) so that the resident reference run stays small."""
     b = B()
     plan, out = _budgeted_vs_resident(S.resnet152(), 320, 24 * GiB, expect_swaps=True, dtype=b.BF16, steps=1)

@@ -13,7 +13,7 @@ import oracle as O
 import synth as S
 
 NETS = {
-    "config1_unit": lambda: S.bottleneck_unit(),                      # BASELINE configs[0]
+    "config1_unit": lambda: S.bottleneck_unit(),
     "mini_resnet_v1": lambda: S.resnet((1, 2), in_hw=20, classes=7, width=4),
     "mini_resnet_v15": lambda: S.resnet((2, 1), in_hw=18, classes=5, width=4, variant="v1.5"),
     "mini_resnet_basic": lambda: S.resnet((2, 1), in_hw=20, classes=6, width=4, block="basic"),

@@ -439,7 +439,7 @@ def test_no_swap_when_everything_fits_and_untrainable_below_the_layer_peak():
     b = B()
     net = S.resnet50()
     ctx = ctx_of(net)
-    s = ctx.plan_swaps(32, 64 * GiB, b.PLAN_DYNAMIC)          # BASELINE configs[1]: zero swaps
+    s = ctx.plan_swaps(32, 64 * GiB, b.PLAN_DYNAMIC)          # zero swaps
     assert s["n_swapped"] == 0 and s["bytes_swapped"] == 0 and s["t_stall"] < 1e-3
     lo = ctx.plan_swaps(32, 1 << 40, b.PLAN_NAIVE_ALL)["layer_peak_bytes"]
     with pytest.raises(b.AccError) as e:
