@@ -3,9 +3,9 @@
 //   dw[co][j] = sum_m dy[m][co] * X[m][j],   m = (img,p,q),  j = (r,t,ci), ci fastest,
 //   X[m][j] = x[img, p*stride+r-pad, q*stride+t-pad, ci]  (zero in the padding)
 //
-// fp32 storage runs in conv_wgrad_x3.hip where its channel counts allow and the layer is large enough; here are
-// the kernel for bf16 storage and one for the rest (small layers, the 3-channel stem, odd channel counts).  In the
-// latter both operands are read along their contiguous channel axis and staged in LDS as [m][channel]; the fp32 MFMA
+// fp32 storage runs in conv_wgrad_x3.hip where its channel counts allow and the layer is large enough, bf16 storage in
+// conv_wgrad_bf16.hip where its channels come in 8s; here is the kernel for the rest (small layers, the 3-channel stem, odd channel
+// counts).  Both operands are read along their contiguous channel axis and staged in LDS as [m][channel]; the fp32 MFMA
 // (v_mfma_f32_32x32x2_f32) takes k = m.  A workgroup of 4 waves owns a 64 x 64 tile of dw; the m range is cut into
 // `splits` equal parts; each part writes its own partial tile and the parts are added in a fixed order, so the result is
 // deterministic (no atomics).  Two chunks of 32 rows in LDS, two more in registers, every steady-state load unconditional
@@ -474,225 +474,6 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradGeom g, int Mrows, int 
 }
 
 
-// ---------------------------------------------------------------------------------------------
-// bf16 storage on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16).  The instruction wants eight
-// consecutive values of the reduction index per lane; here that index is the minibatch position
-// m, and memory is contiguous along channels.  So every thread loads an 8 x 8 block (eight rows
-// of m, sixteen bytes = eight channels each), transposes it in registers (32 byte permutes) and
-// writes eight 16-byte vectors "channel c, rows m..m+7" into LDS, where a fragment read is one
-// ds_read_b128 per lane again.  A workgroup of 4 waves owns a 128 x 128 tile of dw, each wave
-// 64 x 64 (2 x 2 MFMA blocks: 16 MFMAs per 16 fragment reads and chunk of 64 rows), two LDS
-// stages of 32 KB, the global loads of the next chunk in flight during the MFMAs of this one.
-// Waves 0-1 stage dy, waves 2-3 gather x.  LDS layout per stage and operand: [8 row groups][128
-// channels] of 16 bytes, a channel's position inside its group of eight XORed with
-// (group >> 1) & 7: the eight vectors a thread writes with one instruction land on different
-// banks, and so do the 32 consecutive channels a half-wave reads.
-// Needs cin % 8 == 0 (the eight channels a thread stages lie inside one filter tap; the tap is the
-// thread's own, a tile's 128 columns may span several) and cout % 8 == 0.
-constexpr int WB_BM = 128, WB_BN = 128, WB_BK = 64;
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ v16f mfma32x32x16bf(const v4u& a, const v4u& b, v16f c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-#else
-  return c;  // the host pass never runs this
-#endif
-}
-
-__device__ __forceinline__ int wb_slot(int kg, int ch) {   // 16-byte slot of (row group, channel) inside a stage
-  const int o = ch >> 3;
-  return kg * WB_BM + (o << 3) + ((ch & 7) ^ ((o >> 1) & 7));
-}
-
-//
-// How x is gathered: G_PLAIN, 1x1 filters without stride or padding, row m is pixel m; G_NEAR, output maps of at most 4096 rows
-// and columns, where positions move on by quotients in float (exact there, tried over the whole range) and 24-bit products;
-// G_FAR, larger maps, where a quotient rounds across a whole number (from 6.5 million columns on) or a product needs more bits:
-// integer division (256->256 3x3 at 14x14, 512 images: 170 us with the quotients, 181 so).
-enum { G_PLAIN = 0, G_NEAR, G_FAR };
-template <int GATHER>
-__global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles,
-                                                          int splits, int chunks_per_split, float* out,
-                                                          size_t split_stride, int main_grid) {
-  __shared__ __attribute__((aligned(1024))) v4u As[2 * 8 * WB_BM];
-  __shared__ __attribute__((aligned(1024))) v4u Bs[2 * 8 * WB_BN];
-  if ((int)blockIdx.x >= main_grid) {
-    wgrad_side_jobs<bf16_t>(g, (int)blockIdx.x - main_grid, reinterpret_cast<float*>(As));
-    return;
-  }
-#if defined(__HIP_DEVICE_COMPILE__)
-  const int per_xcd = main_grid >> 3;
-  const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (work >= tiles * splits) return;
-  const int split = work / tiles, tile = work - split * tiles;
-  const int tile_co = tile / tiles_j, tile_j = tile - tile_co * tiles_j;
-  const int co0 = tile_co * WB_BM, j0 = tile_j * WB_BN;
-  const int chunk_lo = split * chunks_per_split;
-  const int n_chunks_all = (Mrows + WB_BK - 1) / WB_BK;
-  const int n_chunks = min(chunk_lo + chunks_per_split, n_chunks_all) - chunk_lo;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
-
-  v16f acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
-  // ---- staging role of the thread: operand (uniform per wave), row group, group of eight channels
-  const bool role_b = tid >= 128;
-  const int u = tid & 127, oct = u & 15, kg = u >> 4;
-  const int jt = j0 + oct * 8;                 // first of the thread's eight columns of dw
-  const bool b_col_ok = jt < J;
-  const int tap = (b_col_ok ? jt : 0) / g.cin, ci0 = (b_col_ok ? jt : 0) - tap * g.cin;
-  const int kr = tap / g.s, kt = tap - kr * g.s;
-  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;   // beyond the descriptor's range: reads as zero
-  const bool a_col_ok = co0 + oct * 8 < g.cout;
-  const uint32_t a_lane = (uint32_t)(co0 + oct * 8) * 2u, b_lane = (uint32_t)ci0 * 2u;
-  // (the role is the same for a whole wave; said so explicitly, or the descriptor ends up in vector registers)
-  const uint64_t base = role_b ? reinterpret_cast<uint64_t>(g.x) : reinterpret_cast<uint64_t>(g.dy);
-  const int bytes = (int)(uint32_t)(role_b ? (size_t)g.n_img * g.h * g.wd * g.cin * 2 : (size_t)Mrows * g.cout * 2);
-  const uint32_t base_lo = __builtin_amdgcn_readfirstlane((uint32_t)base), base_hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)base_hi << 32 | base_lo), 0,
-                                                                __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-  // The eight rows of a thread, two register sets (one chunk is written to LDS while the loads of the next but one are on
-  // their way).  Offsets are moved on from chunk to chunk: adds and selects, dy as the input of a 1x1 convolution would be.
-  struct Regs { v4u r[8]; } R0, R1;
-  const int gh = role_b ? g.h : g.p, gwd = role_b ? g.wd : g.q, gs = role_b ? g.stride : 1;
-  const int gy = role_b ? kr - g.pad : 0, gx = role_b ? kt - g.pad : 0;
-  const uint32_t row_b = (uint32_t)(role_b ? g.cin : g.cout) * 2u;
-  const uint32_t wrap_q = (uint32_t)(gs * gwd - g.q * gs) * row_b, wrap_p = (uint32_t)((gh - g.p * gs) * gwd) * row_b;
-  const int m_lim = (role_b ? b_col_ok : a_col_ok) ? Mrows : 0;
-  int m_next = chunk_lo * WB_BK + kg * 8, p0, q0;
-  uint32_t off;
-  {
-    const int pq = g.p * g.q, img = m_next / pq, rem = m_next - img * pq;
-    p0 = rem / g.q;
-    q0 = rem - p0 * g.q;
-    off = (uint32_t)((img * gh + p0 * gs + gy) * gwd + q0 * gs + gx) * row_b + (role_b ? b_lane : a_lane);
-  }
-  const float inv_q = 1.0f / (float)g.q, inv_p = 1.0f / (float)g.p;
-  auto load = [&](Regs& R) {
-    uint32_t voff[8];
-    if constexpr (GATHER == G_PLAIN) {
-#pragma unroll
-      for (int r = 0; r < 8; ++r) voff[r] = m_next + r < m_lim ? off + r * row_b : OUTSIDE;
-      off += WB_BK * row_b;
-    } else {
-      int p = p0, q = q0;
-      uint32_t o = off;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const bool wq = q + 1 == g.q, wp = wq & (p + 1 == g.p);
-        const int iy = (GATHER == G_NEAR ? __mul24(p, gs) : p * gs) + gy, ix = (GATHER == G_NEAR ? __mul24(q, gs) : q * gs) + gx;
-        const bool in = ((unsigned)iy < (unsigned)gh) & ((unsigned)ix < (unsigned)gwd) & (m_next + r < m_lim);
-        voff[r] = in ? o : OUTSIDE;
-        o += gs * row_b + (wq ? wrap_q : 0u) + (wp ? wrap_p : 0u);
-        q = wq ? 0 : q + 1;
-        p = wp ? 0 : p + (wq ? 1 : 0);
-      }
-      // 64 rows on: small quotients, exact in float with the half added (p, q <= 4096)
-      const int xq = q0 + WB_BK, nq = GATHER == G_NEAR ? (int)(((float)xq + 0.5f) * inv_q) : xq / g.q;
-      q0 = xq - nq * g.q;
-      const int xp = p0 + nq, np = GATHER == G_NEAR ? (int)(((float)xp + 0.5f) * inv_p) : xp / g.p;
-      p0 = xp - np * g.p;
-      off += WB_BK * gs * row_b + (uint32_t)nq * wrap_q + (uint32_t)np * wrap_p;
-    }
-    m_next += WB_BK;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) R.r[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[r], 0, 0);
-  };
-  // 8 x 8 transpose of 16-bit values: vector c = channel c of the thread's eight, rows 0..7
-  v4u* stage_base = (role_b ? Bs : As);
-  const int slot0 = kg * WB_BM + (oct << 3);
-  const int sw = (oct >> 1) & 7;
-  auto transpose_store = [&](const Regs& R, int buf) {
-    v4u* dst = stage_base + buf * (8 * WB_BM) + slot0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
-      v4u v;
-      v.x = __builtin_amdgcn_perm(R.r[1][c >> 1], R.r[0][c >> 1], sel);
-      v.y = __builtin_amdgcn_perm(R.r[3][c >> 1], R.r[2][c >> 1], sel);
-      v.z = __builtin_amdgcn_perm(R.r[5][c >> 1], R.r[4][c >> 1], sel);
-      v.w = __builtin_amdgcn_perm(R.r[7][c >> 1], R.r[6][c >> 1], sel);
-      dst[c ^ sw] = v;
-    }
-  };
-  // fragment slots of the lane: rows of dw (channels of dy) wm0 + 32*bi + lane%32, columns
-  // (channels of x) wn0 + 32*bj + lane%32; row group 2*s + lane/32 in MFMA step s
-  int a_at[2], b_at[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    a_at[i] = wb_slot(lane >> 5, wm0 + 32 * i + (lane & 31));
-    b_at[i] = wb_slot(lane >> 5, wn0 + 32 * i + (lane & 31));
-  }
-  auto compute = [&](int buf) {
-    const v4u* as = As + buf * (8 * WB_BM);
-    const v4u* bs = Bs + buf * (8 * WB_BN);
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      v4u a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = as[a_at[i] + s4 * 2 * WB_BM];
-        b[i] = bs[b_at[i] + s4 * 2 * WB_BN];
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32x32x16bf(a[i], b[j], acc[i][j]);
-    }
-  };
-  if (n_chunks > 0) load(R0);
-  if (n_chunks > 1) load(R1);
-  if (n_chunks > 0) transpose_store(R0, 0);
-  __syncthreads();
-  int kc = 0;
-  for (; kc + 4 <= n_chunks; kc += 2) {      // steady state: every load and store unconditional
-    load(R0);
-    compute(0);
-    transpose_store(R1, 1);
-    __syncthreads();
-    load(R1);
-    compute(1);
-    transpose_store(R0, 0);
-    __syncthreads();
-  }
-  for (; kc < n_chunks; kc += 2) {
-    if (kc + 2 < n_chunks) load(R0);
-    compute(0);
-    if (kc + 1 < n_chunks) transpose_store(R1, 1);
-    __syncthreads();
-    if (kc + 1 >= n_chunks) break;
-    if (kc + 3 < n_chunks) load(R1);
-    compute(1);
-    if (kc + 2 < n_chunks) transpose_store(R0, 0);
-    __syncthreads();
-  }
-  float* dst = out + (size_t)split * split_stride;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int jcol = j0 + wn0 + 32 * j + (lane & 31);
-      if (jcol >= J) continue;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int co = co0 + wm0 + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (co < g.cout) dst[(size_t)co * J + jcol] = acc[i][j][v];
-      }
-    }
-#else
-  (void)Bs; (void)&mfma32x32x16bf; (void)&wb_slot;
-#endif
-}
-
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(ReduceJob job) { add_parts4(job, ((size_t)blockIdx.x * 256 + threadIdx.x) * 4); }
 
 // Few elements in many parts, one element per thread: a chain of trips to memory, 32 parts in flight instead of eight, in four times the waves.
@@ -709,19 +490,19 @@ struct WgradCfg {
 
 // The choices below depend on the shape only, never on addresses or on the swap plan.
 //
-// bf16 storage on the bf16 matrix cores: channel counts the 128 x 128 tile of wgrad_bf16_kernel takes
+// bf16 storage on the bf16 matrix cores: channel counts whose groups of eight lie inside one filter tap
 inline bool bf16_mfma_shape(int dtype, int cin, int cout) { return dtype == DT_BF16 && cin % 8 == 0 && cout % 8 == 0; }
 
 WgradCfg choose(long Mrows, int cin, int cout, int r, int s, int dtype) {
   WgradCfg c;
   const long J = (long)r * s * cin;
   if (bf16_mfma_shape(dtype, cin, cout)) {
-    // 128 x 128 tiles, chunks of 64 rows; two workgroups per CU (64 KB of LDS each): one round of 512,
-    // at least four chunks per part
-    c.tiles_co = (cout + WB_BM - 1) / WB_BM;
-    c.tiles_j = (int)((J + WB_BN - 1) / WB_BN);
+    // as many parts as wgrad_bf16_kernel may cut a shape into (it has tiles of its own): 512 workgroups of 128 x 128 and
+    // at least 256 rows per part.  Scratch memory, and with it a plan, is sized for them.
+    c.tiles_co = (cout + 128 - 1) / 128;
+    c.tiles_j = (int)((J + 128 - 1) / 128);
     const long tiles = (long)c.tiles_co * c.tiles_j;
-    const long chunks = (Mrows + WB_BK - 1) / WB_BK;
+    const long chunks = (Mrows + 64 - 1) / 64;
     long splits = 512 / tiles;
     const long max_splits = chunks / 4 > 0 ? chunks / 4 : 1;
     if (splits > max_splits) splits = max_splits;
@@ -835,7 +616,9 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   const WgradX3Cfg cx = x3 ? wgrad_x3_choose(Mrows, g.cin, g.cout, g.r, g.s, max_splits) : WgradX3Cfg{};
   const bool small = !x3 && conv_wgrad_smallc_takes(g);
   const int few = small ? wgrad_smallc_splits(Mrows, g.cin, g.cout, g.r, g.s, g.dtype) : 0;
-  const int splits = x3 ? cx.splits : small ? (few < c.splits ? few : c.splits) : c.splits;
+  const bool mfma16 = !small && bf16_mfma_shape(g.dtype, g.cin, g.cout);
+  const WgradBf16Cfg cb = mfma16 ? wgrad_bf16_choose(Mrows, (long)g.n_img * g.h * g.wd, g.cin, g.cout, g.r, g.s, c.splits) : WgradBf16Cfg{};
+  const int splits = x3 ? cx.splits : small ? (few < c.splits ? few : c.splits) : mfma16 ? cb.splits : c.splits;
   if (splits > 1 && (!g.workspace || g.workspace_bytes < (size_t)splits * g.cout * J * sizeof(float))) return hipErrorInvalidValue;
   const long work = (long)c.tiles_co * c.tiles_j * c.splits;
   if (work > (1L << 30)) return hipErrorInvalidValue;
@@ -856,16 +639,14 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   const dim3 grid((unsigned)(main_grid + reduce_blocks + flip_blocks));
   hipError_t e = hipSuccess;
   const int tiles = c.tiles_co * c.tiles_j;
-  const bool mfma16 = bf16_mfma_shape(g.dtype, g.cin, g.cout);
-  const int gather = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 ? G_PLAIN : g.p <= 4096 && g.q <= 4096 ? G_NEAR : G_FAR;
-  // bf16 matrix cores: the shapes choose() cut into 128 x 128 tiles; byte offsets inside 32-bit buffer
+  // bf16 matrix cores: byte offsets inside 32-bit buffer
   // ranges (the last bytes stay free for the offset that stands for "outside"), 16-byte aligned operands
   if (mfma16 && !(Mrows * g.cout * es <= 0xFFFFFF00L && (long)g.n_img * g.h * g.wd * g.cin * es <= 0xFFFFFF00L &&
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
-    return hipErrorInvalidValue;   // (the split count, and with it the workspace, was sized for this kernel)
-  if (probe) {
+    return hipErrorInvalidValue;   // (the parts, and with them the workspace, were sized for this kernel)
+  if (probe) {                             // (near and far, maps beyond 4096 rows or columns, are one kernel: names that callers know)
     probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : direct ? V_WGRAD_DIRECT : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
-    probe->kernel = small ? "smallc" : mfma16 ? (gather == G_PLAIN ? "wgrad_bf16 plain" : gather == G_NEAR ? "wgrad_bf16 near" : "wgrad_bf16 far")
+    probe->kernel = small ? "smallc" : mfma16 ? (g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 ? "wgrad_bf16 plain" : g.p <= 4096 && g.q <= 4096 ? "wgrad_bf16 near" : "wgrad_bf16 far")
                     : x3 ? (cx.wt == 2 ? "wgrad_x3 128x128" : "wgrad_x3 64x64") : direct ? "wgrad direct 64x64" : fast ? "wgrad fast 64x64" : "wgrad generic 64x64";
     if (probe->dry) return hipSuccess;
   }
@@ -881,12 +662,7 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
     else if (fast) ACC_WGRAD_LAUNCH(L_FAST, float);
     else ACC_WGRAD_LAUNCH(L_GENERIC, float);
   } else if (mfma16) {
-#define ACC_WBF16(G) hipLaunchKernelGGL(wgrad_bf16_kernel<G>, grid, dim3(256), 0, st, g, (int)Mrows, (int)J, c.tiles_j, tiles, \
-                                        c.splits, c.chunks_per_split, out, count, main_grid)
-    if (gather == G_PLAIN) ACC_WBF16(G_PLAIN);
-    else if (gather == G_NEAR) ACC_WBF16(G_NEAR);
-    else ACC_WBF16(G_FAR);
-#undef ACC_WBF16
+    e = conv_wgrad_bf16(g, cb, (int)Mrows, (int)J, out, count, st);
   } else {
     if (fast) ACC_WGRAD_LAUNCH(L_FAST, bf16_t); else ACC_WGRAD_LAUNCH(L_GENERIC, bf16_t);
   }
