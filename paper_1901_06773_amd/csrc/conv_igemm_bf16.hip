@@ -20,6 +20,7 @@
 // 256->1024 1x1 at 14x14, 512 images 109.2 -> 93.6; 512->512 3x3 at 7x7, 4 images 36.9 -> 14.2, 32 images 37.5 -> 22.8; channels that come
 // in 8s (a per-element loader before): 72->72 3x3 at 28x28, 128 images 169 -> 29, 200->200 731 -> 110.
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.h"
 #include "dtype.h"
@@ -76,6 +77,9 @@ template <int WM_, int WN_, int KS_, int MB_, int NB_, int BK_, int NS_, int WPE
   static constexpr int WM = WM_, WN = WN_, KS = KS_, MB = MB_, NB = NB_, BK = BK_, NS = NS_, WPE = WPE_;
   static constexpr int GT = 64 * WM * WN, THREADS = GT * KS;         // threads of a group, of the workgroup
   static constexpr int BM = 32 * MB * WM, BN = 32 * NB * WN;
+  // Loads among the matrix instructions of the tiles that have a compute unit to themselves and two stages: 256->256 3x3 at 14x14, 512
+  // images 130 -> 125 us; smaller tiles, where other workgroups fill the gap, gain nothing.
+  static constexpr bool SPREAD = KS == 1 && NS == 2 && THREADS == 512;
   static constexpr int ROWB = BK * 2, CPR = BK / 8;                  // bytes and 16-byte columns of a staged row
   static constexpr int RPP = GT / CPR, AI = BM / RPP, BI = BN / RPP; // rows one load instruction of a group fills; instructions
   static constexpr int A_BYTES = BM * ROWB, STAGE = (BM + BN) * ROWB;
@@ -93,22 +97,11 @@ template <int N> __device__ __forceinline__ void wait_loads() {      // at most 
 #endif
 }
 
+// One tile, its first row m0 and column n0; `lds`: C::LDS bytes.
 template <class C, bool ACT, bool RAGGED>
-__global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles,
-                                                                         int main_grid) {
-  __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
-  if ((int)blockIdx.x >= main_grid) {
-    wide_side_jobs<bf16_t, C::THREADS>(g.side, g.flip, (int)blockIdx.x - main_grid, lds);
-    return;
-  }
+__device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, int n0, char* lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int MB = C::MB, NB = C::NB, AI = C::AI, BI = C::BI, CPR = C::CPR, ROWB = C::ROWB, NS = C::NS, KS = C::KS;
-  // XCD-aware tile order: each XCD gets a contiguous range of tiles (neighbours share operand rows in its L2)
-  const int per_xcd = main_grid >> 3;
-  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (tile >= n_tiles) return;
-  const int tile_m = tile / n_tiles_n, tile_n = tile - tile_m * n_tiles_n;
-  const int m0 = tile_m * C::BM, n0 = tile_n * C::BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / C::GT);
   const int gt = KS == 1 ? tid : tid & (C::GT - 1);
@@ -197,19 +190,21 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
   int left = (K >> 3) - first * CPR - lcol;           // RAGGED: columns of K from the lane's on
   const int row_jump = (g.wd - g.s) * g.c * 2;
   const int back_a = g.r * g.wd * g.c * 2 - ROWB, back_b = K * 2 - ROWB;
-  auto issue = [&](int stage) {
-    const uint32_t at = lds_w + stage * C::STAGE;
+  constexpr int L = AI + BI, MF = MB * NB;
+  // load u of the next chunk (first those of A), which goes to the stage at `at`; advance() when all have been issued
+  auto load = [&](int u, uint32_t at) {
     const bool k_ok = !RAGGED || left > 0;
-#pragma unroll
-    for (int i = 0; i < AI; ++i) {
-      const bool ok = ((a_mask[i] >> (tap & 31)) & 1u) != 0 && k_ok;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(at + i * (C::GT * 16)), 16,
-                                               ok ? a_voff[i] + (RAGGED ? (uint32_t)toff : 0u) : OUTSIDE, RAGGED ? 0 : toff, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < BI; ++i)
+    if (u < AI) {
+      const bool ok = ((a_mask[u] >> (tap & 31)) & 1u) != 0 && k_ok;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(at + u * (C::GT * 16)), 16,
+                                               ok ? a_voff[u] + (RAGGED ? (uint32_t)toff : 0u) : OUTSIDE, RAGGED ? 0 : toff, 0, 0);
+    } else {
+      const int i = u - AI;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_b, (lds_ptr)(size_t)(at + C::A_BYTES + i * (C::GT * 16)), 16, k_ok ? b_voff[i] : OUTSIDE,
                                                soff_b, 0, 0);
+    }
+  };
+  auto advance = [&]() {
     if constexpr (RAGGED) {
       soff_b += ROWB;
       left -= CPR;
@@ -236,6 +231,11 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
       if (++tap == taps) { tap = 0; toff -= back_a; soff_b -= back_b; }
     }
   };
+  auto issue = [&](int stage) {
+#pragma unroll
+    for (int u = 0; u < L; ++u) load(u, lds_w + stage * C::STAGE);
+    advance();
+  };
   // ---- fragments: 16-byte column c16 of a row sits in slot c16 ^ swz(row); the lane's blocks lie multiples of 32 rows apart
   constexpr int NG = C::BK / 16;
   const int ra = wm0 + (lane & 31), rb = wn0 + (lane & 31);
@@ -252,26 +252,17 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
   };
   auto mm = [&](const Frags& f) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) acc[i][j] = mfma_bf16(f.b[j], f.a[i], acc[i][j]);   // transposed block, see the epilogue
+    for (int u = 0; u < MF; ++u) acc[u / NB][u % NB] = mfma_bf16(f.b[u % NB], f.a[u / NB], acc[u / NB][u % NB]);   // transposed block, see the epilogue
   };
   // One chunk = BK/16 groups of 16 values of K.  The reads of group g+1 are issued among the MFMAs of group g, and the last
-  // group's MFMAs are held back until the next chunk's barrier has been passed, its first reads and the loads of a later
-  // chunk are on their way: the matrix cores have work queued while the wave waits.
-  auto chunk = [&](int stage, bool prev, bool more, int to) {
-    const char* st = lds_g + stage * C::STAGE;
-    __builtin_amdgcn_sched_barrier(0);
-    rd(F[0], st, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (more) issue(to);
-    if (prev) mm(F[1]);
-    __builtin_amdgcn_sched_barrier(0);
+  // group's MFMAs are held back until the next chunk's barrier has been passed and its first reads are on their way; the loads of a later
+  // chunk are issued before or (SPREAD) among them: the matrix cores have work queued while the wave waits.
+  auto groups = [&](const char* st) {
 #pragma unroll
     for (int g8 = 0; g8 + 1 < NG; ++g8) {
       rd(F[(g8 + 1) & 1], st, g8 + 1);
       mm(F[g8 & 1]);
-      constexpr int RD = MB + NB, MF = MB * NB;
+      constexpr int RD = MB + NB;
 #pragma unroll
       for (int u = 0; u < RD; ++u) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
@@ -281,9 +272,34 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
     }
     static_assert(NG % 2 == 0, "the held-back group is F[1]");
   };
+  auto chunk = [&](int stage, bool prev, bool more, int to) {
+    const char* st = lds_g + stage * C::STAGE;
+    __builtin_amdgcn_sched_barrier(0);
+    rd(F[0], st, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) issue(to);
+    if (prev) mm(F[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    groups(st);
+  };
+  auto spread_chunk = [&](int stage, int to) {
+    const char* st = lds_g + stage * C::STAGE;
+    __builtin_amdgcn_sched_barrier(0);
+    rd(F[0], st, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < MF; ++u) {
+      acc[u / NB][u % NB] = mfma_bf16(F[1].b[u % NB], F[1].a[u / NB], acc[u / NB][u % NB]);
+#pragma unroll
+      for (int l = u * L / MF; l < (u + 1) * L / MF; ++l) load(l, lds_w + to * C::STAGE);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    advance();
+    __builtin_amdgcn_sched_barrier(0);
+    groups(st);
+  };
   // What opens chunk j: this wave's loads of chunk j have landed (those of later chunks may be on their way), and, where a
   // group has several waves, a barrier: everybody's have, and everybody is done with chunk j-1, whose stage the next loads overwrite.
-  constexpr int L = AI + BI;
   auto open = [&](int j) {
     __builtin_amdgcn_sched_barrier(0);
     const int later = mine - 1 - j;                   // chunks behind this one that can have been issued: NS - 2 at most
@@ -298,12 +314,27 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < mine) issue(s);
-  int stage = 0, to = NS - 1;
-  for (int j = 0; j < rounds; ++j) {
-    open(j);
-    if (KS == 1 || j < mine) chunk(stage, j > 0, j + NS - 1 < mine, to);
-    stage = stage + 1 == NS ? 0 : stage + 1;
-    to = to + 1 == NS ? 0 : to + 1;
+  if constexpr (C::SPREAD) {
+    static_assert(KS == 1 && NS == 2, "the last chunk is the one without loads");
+    open(0);
+    chunk(0, false, mine > 1, 1);
+    int j = 1;
+    for (; j + 1 < mine; ++j) {
+      open(j);
+      spread_chunk(j & 1, (j & 1) ^ 1);
+    }
+    if (j < mine) {
+      open(j);
+      chunk(j & 1, true, false, 0);
+    }
+  } else {
+    int stage = 0, to = NS - 1;
+    for (int j = 0; j < rounds; ++j) {
+      open(j);
+      if (KS == 1 || j < mine) chunk(stage, j > 0, j + NS - 1 < mine, to);
+      stage = stage + 1 == NS ? 0 : stage + 1;
+      to = to + 1 == NS ? 0 : to + 1;
+    }
   }
   if (KS == 1 || mine > 0) mm(F[1]);
 
@@ -451,6 +482,46 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
 #endif
 }
 
+template <class C, bool ACT, bool RAGGED>
+__global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles, int main_grid) {
+  __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
+  if ((int)blockIdx.x >= main_grid) {
+    wide_side_jobs<bf16_t, C::THREADS>(g.side, g.flip, (int)blockIdx.x - main_grid, lds);
+    return;
+  }
+  // XCD-aware tile order: each XCD gets a contiguous range of tiles (neighbours share operand rows in its L2)
+  const int per_xcd = main_grid >> 3;
+  const int at = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (at >= n_tiles) return;
+  const int tile_m = at / n_tiles_n, tile_n = at - tile_m * n_tiles_n;
+  tile<C, ACT, RAGGED>(g, M, K, tile_m * C::BM, tile_n * C::BN, lds);
+}
+
+// Two heights of tiles in one launch: n_tiles of C in main_grid workgroups, then the rows from `m` on in `tiles` of T (as wide) in `grid` more.
+struct Tail {
+  int m, tiles, grid;
+};
+template <class C, class T, bool ACT, bool RAGGED>
+__global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_tail_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles, int main_grid, Tail tail) {
+  __shared__ __attribute__((aligned(1024))) char lds[C::LDS > T::LDS ? C::LDS : T::LDS];
+  const int id = (int)blockIdx.x - main_grid;
+  if (id >= tail.grid) {
+    wide_side_jobs<bf16_t, C::THREADS>(g.side, g.flip, id - tail.grid, lds);
+    return;
+  }
+  if (id >= 0) {
+    const int at = (id & 7) * (tail.grid >> 3) + (id >> 3);
+    if (at >= tail.tiles) return;
+    const int tile_m = at / n_tiles_n, tile_n = at - tile_m * n_tiles_n;
+    tile<T, ACT, RAGGED>(g, M, K, tail.m + tile_m * T::BM, tile_n * T::BN, lds);
+    return;
+  }
+  const int at = (blockIdx.x & 7) * (main_grid >> 3) + (blockIdx.x >> 3);
+  if (at >= n_tiles) return;
+  const int tile_m = at / n_tiles_n, tile_n = at - tile_m * n_tiles_n;
+  tile<C, ACT, RAGGED>(g, M, K, tile_m * C::BM, tile_n * C::BN, lds);
+}
+
 template <class C>
 void launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
   const int tm = (M + C::BM - 1) / C::BM, tn = (g.n_out + C::BN - 1) / C::BN, tiles = tm * tn, main_grid = (tiles + 7) / 8 * 8;
@@ -464,8 +535,27 @@ void launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe)
   if (probe->after) (void)hipEventRecord(probe->after, st);
 }
 
+// the rows from tail_m (whole tiles of C) on in tiles of T
+template <class C, class T>
+void launch_tail(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe, int tail_m) {
+  static_assert(T::BN == C::BN && T::THREADS == C::THREADS && T::BK == C::BK, "one launch");
+  const int tn = (g.n_out + C::BN - 1) / C::BN, tiles = tail_m / C::BM * tn, main_grid = (tiles + 7) / 8 * 8;
+  const int tail_tiles = (M - tail_m + T::BM - 1) / T::BM * tn;
+  const Tail tail{tail_m, tail_tiles, (tail_tiles + 7) / 8 * 8};
+  const dim3 grid((unsigned)(main_grid + tail.grid + wide_side_blocks(g.side, g.flip, C::THREADS)));
+  const bool ragged = g.c % C::BK != 0, act = g.bias || g.relu;
+  if (probe->before) (void)hipEventRecord(probe->before, st);
+#define ACC_BF16(A, R) hipLaunchKernelGGL((igemm_bf16_tail_kernel<C, T, A, R>), grid, dim3(C::THREADS), 0, st, g, M, K, tn, tiles, main_grid, tail)
+  if (act) { if (ragged) ACC_BF16(true, true); else ACC_BF16(true, false); }
+  else { if (ragged) ACC_BF16(false, true); else ACC_BF16(false, false); }
+#undef ACC_BF16
+  if (probe->after) (void)hipEventRecord(probe->after, st);
+}
+
 typedef Cfg<2, 4, 1, 4, 2, 64, 2, 2> T256x256;
 typedef Cfg<2, 4, 1, 2, 2, 64, 3, 2> T128x256;
+typedef Cfg<2, 4, 1, 3, 2, 64, 2, 2> L192x256;         // the last rows behind tiles of 256 x 256
+typedef Cfg<2, 4, 1, 1, 2, 64, 2, 2> L64x256;
 typedef Cfg<2, 2, 1, 4, 2, 32, 3, 2> T256x128;
 typedef Cfg<2, 2, 1, 2, 2, 64, 2, 2> T128x128;
 typedef Cfg<2, 2, 1, 2, 1, 64, 2, 2> T128x64;
@@ -477,7 +567,7 @@ typedef Cfg<1, 1, 8, 1, 1, 32, 4, 2> T32x32k8;         // eight groups of one wa
 
 // Which kernel: the one with the smallest predicted time, in microseconds.  With steps = chunks of K per group of waves, and tiles
 // counted on the compute unit with the most,
-//   base + (compute^2 + memory^2)^(1/2),
+//   base + (compute^2 + memory^2)^(1/2),           (256 x 256: tiles = the rounds of heights())
 //   compute = one workgroup per compute unit: first + first_step * steps + (tiles - 1) * (next + next_step * steps),
 //             several (r <= per_cu resident): the sum over rounds of max(first + first_step * steps, r * (next + next_step * steps)),
 // taps more per tile for filters larger than 1x1, memory = per_mb_read * MB of both operands + per_mb_written * MB of the result,
@@ -508,18 +598,46 @@ constexpr Kind kKinds[KINDS] = {
     {"igemm_bf16 64x64, four waves", 64, 64, 4, 32, 2, 2.286, 1.275, 0.586, 0.914, 0.503, 0.035, 0.136, 0.431},
     {"igemm_bf16 32x32, eight waves", 32, 32, 8, 32, 1, 0.0, 3.255, 0.543, 1.221, 0.487, 0.520, 0.271, 2.084},
 };
-double predicted_us(const Kind& k, const ConvGeom& g, long M, long K) {
-  const long N = g.n_out;
-  const long tiles = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
-  const long most = (tiles + 255) / 256;                 // tiles of the busiest compute unit
-  const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = g.r * g.s > 1 ? k.taps * most : 0;
+// Tiles of 256 x 256 take a compute unit each, and in their last round most units may have none (392 tiles: 256 and 136).  The rows that don't
+// fill a round run behind the others as tiles of 192 or 64 rows in the same launch, where that makes the rounds fewer, a round of 192 rows
+// counted as 0.8 of one of 256, one of 64 as 0.4 (the half of the chip that runs a part round runs it faster).  us, 256 x 256
+// alone -> with lower tiles: 256->256 3x3 at 14x14, 512 images (256 + 182 x 192) 123 -> 114, at 28x28, 200 images (256 + 476 x 192) 185 -> 170;
+// 128->256 3x3 at 28x28, 256 images (256 + 704 x 192) 140 -> 127; 1024->512 1x1 at 28x28, 128 images (768 + 64 x 64) 131 -> 123;
+// layers that wait for memory gain nothing and keep one height.
+struct Heights {
+  int low, rows;                                         // height of the lower tiles (0: none), rows of the higher ones
+  double rounds;
+};
+Heights heights(long M, long N) {
+  const long tn = (N + 255) / 256, all = (M + 255) / 256 * tn, plain = (all + 255) / 256;
+  Heights best{0, 0, (double)plain};
+  for (long full = plain - 1; full >= 1 && full >= plain - 3; --full) {
+    const long rows = full * 256 / tn * 256, rest = M - rows;
+    if (rows <= 0 || rest <= 0) continue;
+    const long r192 = ((rest + 191) / 192 * tn + 255) / 256, r64 = ((rest + 63) / 64 * tn + 255) / 256;
+    if (r192 <= 3 && full + 0.8 * r192 < best.rounds - 0.05) best = Heights{192, (int)rows, full + 0.8 * r192};
+    if (r64 == 1 && full + 0.4 < best.rounds - 0.05) best = Heights{64, (int)rows, full + 0.4};
+  }
+  return best;
+}
+double memory_us(const Kind& k, const ConvGeom& g, long M, long K) {
   // pixels that are read: all of the input, or, by strided filters smaller than their stride, those under a tap; chunks of 32 values (half
   // lines of memory) find nothing again that a tap of a strided filter has read before
   const double taps = (double)M * g.r * g.s, in = (double)g.n_img * g.h * g.wd, pixels = g.stride > 1 && (taps < in || k.kc == 32) ? taps : in;
-  const double read = 2e-6 * (pixels * g.c + (double)N * K), written = 2e-6 * (double)M * N;
-  const double memory = k.per_mb_read * read + k.per_mb_written * written;
+  const double read = 2e-6 * (pixels * g.c + (double)g.n_out * K), written = 2e-6 * (double)M * g.n_out;
+  return k.per_mb_read * read + k.per_mb_written * written;
+}
+double compute_us(const Kind& k, const ConvGeom& g, long M, long K) {
+  const long tiles = ((M + k.bm - 1) / k.bm) * ((g.n_out + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
+  const long whole = (tiles + 255) / 256;                // tiles of the busiest compute unit
+  const double most = k.bm == 256 && k.bn == 256 ? heights(M, g.n_out).rounds : (double)whole;
+  const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = g.r * g.s > 1 ? k.taps * most : 0;
   auto round = [&](long r) { return r == 0 ? 0.0 : first > r * next ? first : r * next; };
-  const double compute = more + (k.per_cu == 1 ? first + (most - 1) * next : (most / k.per_cu) * round(k.per_cu) + round(most % k.per_cu));
+  return more + (k.per_cu == 1 ? first + (most - 1) * next : (whole / k.per_cu) * round(k.per_cu) + round(whole % k.per_cu));
+}
+bool bound_by_memory(const Kind& k, const ConvGeom& g, long M, long K) { return memory_us(k, g, M, K) > compute_us(k, g, M, K); }
+double predicted_us(const Kind& k, const ConvGeom& g, long M, long K) {
+  const double compute = compute_us(k, g, M, K), memory = memory_us(k, g, M, K);
   return k.base + std::sqrt(compute * compute + memory * memory);
 }
 int best_kind(const ConvGeom& g, long M, long K) {
@@ -556,9 +674,16 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, Laun
   const int kind = best_kind(g, M, K);
   probe->variant = V_IGEMM_BF16;
   probe->kernel = kKinds[kind].name;
+  Heights h{0, 0, 0};
+  if (kind == K256x256 && !bound_by_memory(kKinds[kind], g, M, K)) h = heights(M, g.n_out);
+  if (h.low) probe->kernel = h.low == 192 ? "igemm_bf16 256x256 and 192x256" : "igemm_bf16 256x256 and 64x256";
   if (probe->dry) return hipSuccess;
   switch (kind) {
-    case K256x256: launch<T256x256>(g, M, K, st, probe); break;
+    case K256x256:
+      if (h.low == 192) launch_tail<T256x256, L192x256>(g, M, K, st, probe, h.rows);
+      else if (h.low == 64) launch_tail<T256x256, L64x256>(g, M, K, st, probe, h.rows);
+      else launch<T256x256>(g, M, K, st, probe);
+      break;
     case K128x256: launch<T128x256>(g, M, K, st, probe); break;
     case K256x128: launch<T256x128>(g, M, K, st, probe); break;
     case K128x128: launch<T128x128>(g, M, K, st, probe); break;
