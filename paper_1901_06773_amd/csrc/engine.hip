@@ -136,6 +136,12 @@ struct acc_ctx {
 // stream: it waits on an event of older work first.  The windows are far deeper than any
 // dependency between the streams (the pool holds a few dozen maps at a time).
 constexpr int kStepWindow = 32, kWindows = 3, kCopyWindow = 64;
+// Iterations that swap up to this many bytes each way are bound by the host that issues them: a copy on a stream of its own costs it two
+// event records and two waits, 13 us with the copy, and hides a copy of a few microseconds.  Their copies go to the compute stream.  One
+// bottleneck block, all nine maps swapped, fp32 / bf16, us per iteration with the copies on their own streams -> in the compute stream:
+// 256 KB 439 -> 281 / 469 -> 340, 512 KB 457 -> 381 / 475 -> 431, 1 MB 467 -> 400 / 484 -> 450, 1.5 MB 480 -> 423 / 486 -> 471, 3 MB
+// 511 -> 479 / -, from 4 MB on copies beside the kernels are the faster way (541 against 547).
+constexpr size_t kOneStreamBytes = 5u << 18;
 // Event timing of steps and copies is refused for plans that swap more than this per
 // iteration: such runs (ResNet-152, minibatch 224 and 256, all maps swapped, 36-41 GiB each
 // way) ended in a crash of the process at its next HIP call, cause unknown; the same
@@ -983,6 +989,10 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
     c->drop_graph();
     (void)hipGetLastError();
   };
+  // Few small maps: the copies in the compute stream, in the order of the list (whose every wait is for something
+  // before it), without an event for each.
+  const bool one_stream = P.n_swapped > 0 && P.host_bytes <= kOneStreamBytes && !c->profiling && !c->calibrating;
+  const hipStream_t s_out = one_stream ? c->s_c : c->s_o, s_in = one_stream ? c->s_c : c->s_i;
   int n_compute = 0;
   double t_waited = 0.0;     // host time spent blocked on the flow-control windows (the GPU is behind, not the host)
   auto window_wait = [&](hipEvent_t e) {
@@ -992,9 +1002,9 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
     return r;
   };
   for (const Instr& in : P.instrs) {
-    if ((in.op == I_LOAD_INPUT || in.op == I_PREFETCH) && in.seq >= kCopyWindow)
+    if (!one_stream && (in.op == I_LOAD_INPUT || in.op == I_PREFETCH) && in.seq >= kCopyWindow)
       HIPCHK(c, window_wait(c->ev_h2d[in.seq - kCopyWindow]));
-    if (in.op == I_OFFLOAD && in.seq >= kCopyWindow)
+    if (!one_stream && in.op == I_OFFLOAD && in.seq >= kCopyWindow)
       HIPCHK(c, window_wait(c->ev_d2h[in.seq - kCopyWindow]));
     if (in.op == I_COMPUTE && n_compute % kStepWindow == 0 && n_compute / kStepWindow >= kWindows)
       HIPCHK(c, window_wait(c->ev_window[n_compute / kStepWindow - kWindows]));
@@ -1006,17 +1016,17 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
             hipError_t e = fill_pseudo_input(c, (float*)dst, (size_t)P.k * g.in_c * g.in_h * g.in_w);
             if (e != hipSuccess) return c->hipfail(e, "fill_pseudo_input");
           } else {
-            hipError_t e = fill_zero((float*)dst, (size_t)P.k, c->s_i);
+            hipError_t e = fill_zero((float*)dst, (size_t)P.k, s_in);
             if (e != hipSuccess) return c->hipfail(e, "fill_zero(labels)");
           }
         } else if (in.arg == g.t_stage) {
           const size_t bytes = (size_t)P.k * g.in_c * g.in_h * g.in_w * sizeof(float);
           HIPCHK(c, hipMemcpyAsync(dst, images, bytes,
-                                   images_loc == ACC_LOC_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, c->s_i));
+                                   images_loc == ACC_LOC_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s_in));
         } else {
-          HIPCHK(c, hipMemcpyAsync(dst, labels, (size_t)P.k * sizeof(int32_t), hipMemcpyHostToDevice, c->s_i));
+          HIPCHK(c, hipMemcpyAsync(dst, labels, (size_t)P.k * sizeof(int32_t), hipMemcpyHostToDevice, s_in));
         }
-        HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
+        if (!one_stream) HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
         break;
       }
       case I_COMPUTE: {
@@ -1049,8 +1059,8 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
           }
           break;
         }
-        if (in.wait_d2h >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_c, c->ev_d2h[in.wait_d2h], 0));
-        if (in.wait_h2d >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_c, c->ev_h2d[in.wait_h2d], 0));
+        if (!one_stream && in.wait_d2h >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_c, c->ev_d2h[in.wait_d2h], 0));
+        if (!one_stream && in.wait_h2d >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_c, c->ev_h2d[in.wait_h2d], 0));
         if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_a[in.arg], c->s_c));
         // weight gradients that went to their own stream and must be complete before this step
         // (their operands may be released after it; the update reads their results)
@@ -1081,33 +1091,33 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
             const hipError_t ep = fill_words(c->dyn + b.off, b.bytes, kReleased, c->s_c);
             if (ep != hipSuccess) return c->hipfail(ep, "poison fill");
           }
-        if (in.record) HIPCHK(c, hipEventRecord(c->ev_step[in.arg], c->s_c));
+        if (in.record && !one_stream) HIPCHK(c, hipEventRecord(c->ev_step[in.arg], c->s_c));
         if (++n_compute % kStepWindow == 0) HIPCHK(c, hipEventRecord(c->ev_window[n_compute / kStepWindow - 1], c->s_c));
         break;
       }
       case I_OFFLOAD: {
-        HIPCHK(c, hipStreamWaitEvent(c->s_o, c->ev_step[in.wait_step], 0));
+        if (!one_stream) HIPCHK(c, hipStreamWaitEvent(c->s_o, c->ev_step[in.wait_step], 0));
         if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_a[in.seq], c->s_o));
         HIPCHK(c, hipMemcpyAsync((char*)c->res.host + P.host_off[in.arg], c->dyn + P.off1[in.arg], P.tbytes[in.arg],
-                                 hipMemcpyDeviceToHost, c->s_o));
+                                 hipMemcpyDeviceToHost, s_out));
         if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_b[in.seq], c->s_o));
         if (poison) {
           const acc_ctx::Block& b = c->poison_after_d2h[in.seq];
-          const hipError_t ep = fill_words(c->dyn + b.off, b.bytes, kReleased, c->s_o);
+          const hipError_t ep = fill_words(c->dyn + b.off, b.bytes, kReleased, s_out);
           if (ep != hipSuccess) return c->hipfail(ep, "poison fill");
         }
-        HIPCHK(c, hipEventRecord(c->ev_d2h[in.seq], c->s_o));
+        if (!one_stream) HIPCHK(c, hipEventRecord(c->ev_d2h[in.seq], c->s_o));
         bytes_out += P.tbytes[in.arg];
         break;
       }
       case I_PREFETCH: {
-        if (in.wait_step >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_i, c->ev_step[in.wait_step], 0));
-        if (in.wait_d2h >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_i, c->ev_d2h[in.wait_d2h], 0));
+        if (!one_stream && in.wait_step >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_i, c->ev_step[in.wait_step], 0));
+        if (!one_stream && in.wait_d2h >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_i, c->ev_d2h[in.wait_d2h], 0));
         if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_a[P.n_d2h + in.seq], c->s_i));
         HIPCHK(c, hipMemcpyAsync(c->dyn + P.off2[in.arg], (char*)c->res.host + P.host_off[in.arg], P.tbytes[in.arg],
-                                 hipMemcpyHostToDevice, c->s_i));
+                                 hipMemcpyHostToDevice, s_in));
         if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_b[P.n_d2h + in.seq], c->s_i));
-        HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
+        if (!one_stream) HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
         c->cur_off[in.arg] = P.off2[in.arg];
         bytes_in += P.tbytes[in.arg];
         break;
@@ -1134,8 +1144,10 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
   HIPCHK(c, hipEventRecord(c->ev_end, c->s_c));
   const double t_issued = now_ms();
   HIPCHK(c, hipStreamSynchronize(c->s_c));
-  HIPCHK(c, hipStreamSynchronize(c->s_o));
-  HIPCHK(c, hipStreamSynchronize(c->s_i));
+  if (!one_stream) {
+    HIPCHK(c, hipStreamSynchronize(c->s_o));
+    HIPCHK(c, hipStreamSynchronize(c->s_i));
+  }
   if (c->s_w) HIPCHK(c, hipStreamSynchronize(c->s_w));
   const double t_done = now_ms();
   if (loss_out) *loss_out = *c->h_loss;
