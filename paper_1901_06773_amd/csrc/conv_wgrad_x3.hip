@@ -13,8 +13,10 @@
 // stored.  Pipeline as in conv_igemm_x3.hip: step j multiplied out of registers, j+1 read from LDS, j+2 split and
 // stored, later loads issued.
 //
-// Bound as there (333 TFLOP/s in these products); what is lost goes to the gather and the splitting (about 170 vector
-// instructions per wave and step beside 24 matrix instructions) and to the parts, which are written and read once.
+// Bound: the vector instructions (104 per wave and step for the splitting, a few for the offsets, beside 24 matrix instructions; with half the matrix
+// instructions left out 256->256 3x3 at 14x14, 41 images, takes 60 us instead of 68) and the parts, which are written and read
+// once.  Offsets worked out 64 at a time (TABLE below) instead of by every lane for its own rows: 183 -> 109 vector instructions per step, that
+// layer 67.2 -> 61.5 us, 512->512 3x3 at 7x7 83.0 -> 74.5, 128->128 3x3/2 at 55x55, 19 images 41.9 -> 39.4; 98 shapes 4 % on average.
 // Measured against the fp32-instruction kernel this replaces, minibatch 41, reduction of the parts included:
 // 256->256 3x3 at 14x14 115.7 -> 63.8 us, 128->128 3x3 at 28x28 96.1 -> 63.7, 512->512 3x3 at 7x7 117.8 -> 79.6, 256->1024
 // 1x1 at 14x14 44.4 -> 35.5, 64->256 at 56x56 (minibatch 32) 42.9 -> 39.3; error against float64 6.2e-7 -> 3.6e-7 on the
@@ -67,12 +69,19 @@ __device__ __forceinline__ x3_v16f plain_wgrad_block(const WgradGeom& g, int co,
   return acc;
 }
 
-template <int WT, bool PLAIN>
+// How a thread finds its rows of x.  PLAIN: 1x1 filters without stride or padding, row m is pixel m.  TABLE: the wave's 64 channels lie in
+// one filter tap; every fourth step its lanes work out the offsets of the next 64 positions, one each, and leave them in LDS, where a
+// thread finds those of its four rows with one read.  LANES: several taps, every lane follows its own rows (some 60
+// vector instructions per step and block).
+enum { PLAIN = 0, TABLE, LANES };
+
+template <int WT, int GATHER>
 __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows, int J, int tiles_j, int tiles, int splits,
                                                           int steps_per_split, float* out, size_t split_stride, int main_grid) {
   using D = WDeep<WT>;
   [[maybe_unused]] constexpr int KS = D::KS, GT = D::GT;
-  __shared__ __attribute__((aligned(1024))) char lds[D::LDS];
+  constexpr int TAB = GATHER == TABLE ? 8 * D::BPW * 256 : 0;       // 64 offsets per wave and block that it stages
+  __shared__ __attribute__((aligned(1024))) char lds[D::LDS + TAB];
   if ((int)blockIdx.x >= main_grid) {
     static_assert(D::LDS >= wide_scratch<float>(512), "side jobs");
     wide_side_jobs<float, 512>(g.side, FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, (int)blockIdx.x - main_grid, lds);
@@ -107,7 +116,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   uint32_t row_b[BPW], off[BPW];                         // bytes per position; offset of the thread's first row of the step loaded next
   // the gather: position (p, q) reads pixel (p*gs + gy, q*gs + gx) of a gh x gw image; what the offset gains where q, where p wraps
   int gh[BPW], gwd[BPW], gs[BPW], gy[BPW], gx[BPW];
-  uint32_t wrap_q[BPW], wrap_p[BPW];
+  uint32_t wrap_q[BPW], wrap_p[BPW], ch_of[BPW];
   int m_next = first * 16 + m4 * 4;                      // the thread's first row of the step that is loaded next
   int p0 = 0, q0 = 0;
   const float inv_q = 1.0f / (float)g.q, inv_p = 1.0f / (float)g.p;
@@ -136,6 +145,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
       row_b[b] = (uint32_t)g.cin * 4u;
       gh[b] = g.h; gwd[b] = g.wd; gs[b] = g.stride; gy[b] = kr - g.pad; gx[b] = tap - kr * g.s - g.pad;
     }
+    ch_of[b] = ch;
     // offsets modulo 2^32; one that is used lies inside the tensor
     off[b] = (uint32_t)((img0 * gh[b] + p0 * gs[b] + gy[b]) * gwd[b] + q0 * gs[b] + gx[b]) * row_b[b] + ch;
     wrap_q[b] = (uint32_t)(gs[b] * gwd[b] - g.q * gs[b]) * row_b[b];
@@ -146,12 +156,55 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base), hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
     rs[b] = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
   }
+  // TABLE: the lane's position of the 64 that are worked out next: its row, the input pixel (ty, tx) it reads and its offset without the channel;
+  // 64 positions on = whole images, rows and columns, with one wrap of each at most
+  constexpr int NTB = GATHER == TABLE ? BPW : 1;
+  uint32_t* const tab = reinterpret_cast<uint32_t*>(lds + D::LDS) + (tid >> 6) * (BPW * 64);
+  int tm = first * 16 + lane, turn = 0, tx[NTB], ty[NTB];
+  uint32_t toff[NTB], ch_off[NTB];
+  const int d_img = 64 / pq, d_p = (64 - d_img * pq) / g.q, d_q = 64 - d_img * pq - d_p * g.q;
+  if constexpr (GATHER == TABLE) {
+    const int img = tm / pq, rem = tm - img * pq, p = rem / g.q, q = rem - p * g.q;
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+      // (the same for the whole wave: one tap)
+      gy[b] = __builtin_amdgcn_readfirstlane(gy[b]);
+      gx[b] = __builtin_amdgcn_readfirstlane(gx[b]);
+      ty[b] = p * gs[b] + gy[b];
+      tx[b] = q * gs[b] + gx[b];
+      toff[b] = (uint32_t)((img * gh[b] + ty[b]) * gwd[b] + tx[b]) * row_b[b];
+      ch_off[b] = m_lim[b] ? ch_of[b] : OUTSIDE;
+    }
+  }
+  auto fill = [&]() {              // the offsets of the next 64 positions
+#pragma unroll
+    for (int b = 0; b < NTB; ++b) {
+      const bool in = ((unsigned)ty[b] < (unsigned)gh[b]) & ((unsigned)tx[b] < (unsigned)gwd[b]) & (tm < Mrows);
+      tab[b * 64 + lane] = in ? toff[b] : OUTSIDE;
+      tx[b] += d_q * gs[b];
+      const bool wx = tx[b] >= g.q * gs[b] + gx[b];
+      tx[b] -= wx ? g.q * gs[b] : 0;
+      ty[b] += d_p * gs[b] + (wx ? gs[b] : 0);
+      const bool wy = ty[b] >= g.p * gs[b] + gy[b];
+      ty[b] -= wy ? g.p * gs[b] : 0;
+      toff[b] += (uint32_t)((d_img * gh[b] + d_p * gs[b]) * gwd[b] + d_q * gs[b]) * row_b[b] + (wx ? wrap_q[b] : 0u) + (wy ? wrap_p[b] : 0u);
+    }
+    tm += 64;
+  };
   constexpr int NR = BPW == 2 ? 1 : 2;                   // register sets of loads in flight
   struct Regs { x3_v4u v[BPW][4]; } R0, R1_;
   Regs& R1 = NR == 2 ? R1_ : R0;
   auto load = [&](Regs& R) {
     uint32_t voff[BPW][4];
-    if constexpr (PLAIN) {
+    if constexpr (GATHER == TABLE) {
+#pragma unroll
+      for (int b = 0; b < BPW; ++b) {
+        const x3_v4u t = *reinterpret_cast<const x3_v4u*>(tab + b * 64 + turn * 16 + m4 * 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) voff[b][u] = __builtin_elementwise_add_sat(t[u], ch_off[b]);     // what is outside stays there
+      }
+      turn = (turn + 1) & 3;
+    } else if constexpr (GATHER == PLAIN) {
 #pragma unroll
       for (int b = 0; b < BPW; ++b) {
         uint32_t o = off[b];
@@ -194,6 +247,10 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
 #pragma unroll
       for (int u = 0; u < 4; ++u) R.v[b][u] = __builtin_amdgcn_raw_buffer_load_b128(rs[b], voff[b][u], 0, 0);
     m_next += 16;
+  };
+  auto prepare = [&]() {           // before load(): outside what is scheduled by hand
+    if constexpr (GATHER == TABLE)
+      if (turn == 0) fill();
   };
   // ---- split and store: channel e of the thread goes to row 16*e + c4, its four values of m side by side
   char* const lds_g = lds + grp * (D::NST * D::STAGE);
@@ -248,12 +305,13 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   // Step j: fragments F multiplied, fragments of j+1 read from stage (j+1)&1 into G, step j+2 (in R) stored into
   // stage j&1, whose last reader was step j-1's read of j; its registers are loaded with step j+2+NR.
   auto step = [&](const Frags& F, Frags& G, Regs& R, int par) {
+    prepare();
     __builtin_amdgcn_sched_barrier(0);
     read(G, par ^ 1);
     store(R, par);
     load(R);
     multiply(F);
-    constexpr int V = (104 * BPW + (PLAIN ? 12 : 60) * BPW + 23) / 24;
+    constexpr int V = (104 * BPW + (GATHER == PLAIN ? 12 : GATHER == TABLE ? 6 : 60) * BPW + 23) / 24;
 #pragma unroll
     for (int u = 0; u < 24; ++u) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -263,14 +321,15 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  if (mine > 0) load(R0);
-  if (NR == 2 && mine > 1) load(R1);
+  auto fetch = [&](Regs& R) { prepare(); load(R); };
+  if (mine > 0) fetch(R0);
+  if (NR == 2 && mine > 1) fetch(R1);
   if (mine > 0) store(R0, 0);
-  if (mine > NR) load(R0);
+  if (mine > NR) fetch(R0);
   sync();
   if (mine > 0) read(F0, 0);
   if (mine > 1) store(R1, 1);
-  if (mine > NR + 1) load(R1);
+  if (mine > NR + 1) fetch(R1);
   sync();
   int j = 0;
   for (; j + 4 + NR <= mine; j += 2) {   // steady state: every load and store unconditional
@@ -282,13 +341,13 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
   for (; j < rounds; j += 2) {
     if (j + 1 < mine) read(F1, 1);
     if (j + 2 < mine) store(R0, 0);
-    if (j + 2 + NR < mine) load(R0);
+    if (j + 2 + NR < mine) fetch(R0);
     if (j < mine) multiply(F0);
     sync();
     if (j + 1 >= rounds) break;
     if (j + 2 < mine) read(F0, 0);
     if (j + 3 < mine) store(R1, 1);
-    if (j + 3 + NR < mine) load(R1);
+    if (j + 3 + NR < mine) fetch(R1);
     if (j + 1 < mine) multiply(F1);
     sync();
   }
@@ -382,11 +441,11 @@ hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int
   const long side_blocks = wide_side_blocks(g.side, FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, 512);
   const int tiles = c.tiles_co * c.tiles_j, main_grid = (int)(((long)tiles * c.splits + 7) / 8 * 8);
   const dim3 grid((unsigned)(main_grid + side_blocks));
-  const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0;
+  const int gather = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 ? PLAIN : g.cin % 64 == 0 || g.r * g.s == 1 ? TABLE : LANES;
 #define ACC_WX3(W, P) hipLaunchKernelGGL((wgrad_x3_kernel<W, P>), grid, dim3(512), 0, st, g, Mrows, J, c.tiles_j, tiles, c.splits, \
                                          c.steps_per_split, out, count, main_grid)
-  if (c.wt == 2) { if (plain) ACC_WX3(2, true); else ACC_WX3(2, false); }
-  else { if (plain) ACC_WX3(1, true); else ACC_WX3(1, false); }
+  if (c.wt == 2) { if (gather == PLAIN) ACC_WX3(2, PLAIN); else if (gather == TABLE) ACC_WX3(2, TABLE); else ACC_WX3(2, LANES); }
+  else { if (gather == PLAIN) ACC_WX3(1, PLAIN); else if (gather == TABLE) ACC_WX3(1, TABLE); else ACC_WX3(1, LANES); }
 #undef ACC_WX3
   return hipGetLastError();
 }
