@@ -696,22 +696,31 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   struct Frags { x3_v4u a[3][2], b[3][2]; } F0, F1;
   const int fa_at = plane_at(wm0 + (lane & 31), half), fb_at = plane_at(wn0 + (lane & 31), half);
   int at[2] = {fa_at, fa_at + 32 * 32};
-  const char* wb = lds;
-  auto aim = [&]() {               // WINDOW: where the next step's rows lie
+  const int ks_r = KS / g.s, ks_t = KS - ks_r * g.s;
+  auto aim = [&]() {               // WINDOW: where the rows of the step lie that is read next
     if constexpr (WINDOW) {
-      const int shift = ckr * g.wd + ckt;
-      wb = lds + (cw & 1) * D::WBUF;
+      const int shift = ckr * g.wd + ckt, wb = (cw & 1) * D::WBUF;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        at[i] = plane_at((mask[i] >> ctap) & 1u ? wm0 + (lane & 31) + 32 * i + shift : D::WROWS, half);
-      ctap += KS; ckt += KS;
-      while (ckt >= g.s) { ckt -= g.s; ++ckr; }
-      if (ctap >= taps) { ctap -= taps; ++cw; ckr -= g.r; }
+      for (int i = 0; i < 2; ++i) {
+        at[i] = wb + plane_at((mask[i] >> ctap) & 1u ? wm0 + (lane & 31) + 32 * i + shift : D::WROWS, half);
+        asm volatile("" : "+v"(at[i]));      // worked out here, not where it is used
+      }
+      // KS taps on, without branches: all ones where there is no wrap
+      ckt += ks_t - g.s;
+      ckr += ks_r + 1;
+      const int same_row = ckt >> 31;
+      ckt += g.s & same_row;
+      ckr += same_row;
+      ctap += KS - taps;
+      const int same_window = ctap >> 31;
+      ctap += taps & same_window;
+      cw += 1 + same_window;
+      ckr -= g.r & ~same_window;
     }
   };
   auto read = [&](Frags& F, int buf) {
     const char* st = lds_g + (buf & (D::NST - 1)) * D::STAGE;
-    const char* as = WINDOW ? wb : st;
+    const char* as = WINDOW ? lds : st;
     const char* bs = st + 3 * D::AP + fb_at;
     constexpr int APL = WINDOW ? D::WPLANE : D::AP;
 #pragma unroll
@@ -743,19 +752,29 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   // Step j: fragments F multiplied, fragments of j+1 read from stage (j+1)&1 into G, step j+2 (in R) stored into
   // stage j&1, whose last reader was step j-1's read of j; its registers are loaded with step j+2+NR.
   auto step = [&](const Frags& F, Frags& G, Regs& R, int par) {
-    aim();
     __builtin_amdgcn_sched_barrier(0);
     read(G, par ^ 1);
+    x3_product<2, 0, 2, 2>(F.a, F.b, acc);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    aim();                         // for the next step, behind matrix instructions: nothing stands between the barrier and them
     store(R, par);
     load(R);
-    multiply(F);
-    constexpr int V = (26 * (AI + BI) + 23) / 24 + (AI + BI) / 6;
+    x3_product<0, 2, 2, 2>(F.a, F.b, acc);
+    x3_product<1, 1, 2, 2>(F.a, F.b, acc);
+    x3_product<1, 0, 2, 2>(F.a, F.b, acc);
+    x3_product<0, 1, 2, 2>(F.a, F.b, acc);
+    x3_product<0, 0, 2, 2>(F.a, F.b, acc);
+    constexpr int V = (26 * (AI + BI) + (WINDOW ? 20 : 6) + 19) / 20;
 #pragma unroll
-    for (int u = 0; u < 24; ++u) {
+    for (int u = 0; u < 20; ++u) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (u < 12) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
-      if (u >= 12) __builtin_amdgcn_sched_group_barrier(0x200, (3 * (AI + BI) + 23) / 24, 0);
+      if (u >= 8) __builtin_amdgcn_sched_group_barrier(0x200, (3 * (AI + BI) + 23) / 24, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -787,6 +806,7 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   window(-1);
   aim();
   if (mine > 0) read(F0, 0);
+  aim();
   if (mine > 1) store(R1, 1);
   if (mine > NR + 1) load(R1);
   sync();
@@ -801,16 +821,16 @@ __global__ __launch_bounds__(512, 1) void igemm_x3_deep_kernel(ConvGeom g, int M
   }
   for (; j < rounds; j += 2) {
     window(j);
-    aim();
     if (j + 1 < mine) read(F1, 1);
+    aim();
     if (j + 2 < mine) store(R0, 0);
     if (j + 2 + NR < mine) load(R0);
     if (j < mine) multiply(F0);
     sync();
     if (j + 1 >= rounds) break;
     window(j + 1);
-    aim();
     if (j + 2 < mine) read(F0, 0);
+    aim();
     if (j + 3 < mine) store(R1, 1);
     if (j + 3 + NR < mine) load(R1);
     if (j + 1 < mine) multiply(F1);
