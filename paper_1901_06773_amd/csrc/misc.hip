@@ -19,24 +19,29 @@ inline unsigned grid_for(size_t work, size_t cap = 256 * 32) {
 
 // wt[ci][r'][t'][co] = w[co][R-1-r'][S-1-t'][ci]; a 32x32 LDS tile transposes (co, ci)
 // so that both the read (ci fastest) and the write (co fastest) are coalesced.
+// Bound by the launch and one trip to memory each way: a thread's four values are asked for at once, those that do not exist as the first.
 template <class T>
 __global__ __launch_bounds__(256) void flip_transpose_kernel(const T* __restrict__ w,
                                                              T* __restrict__ wt, int cout, int cin,
                                                              int r, int s) {
   __shared__ T tile[32][33];
-  const int tap = blockIdx.z;                       // r'*s + t' of the output
-  const int kr = r - 1 - tap / s, kt = s - 1 - tap % s;
-  const int src_tap = kr * s + kt;
+  const int tap = blockIdx.z, taps = r * s;         // r'*s + t' of the output; flipped it is the last tap less that
+  const int src_tap = taps - 1 - tap;
   const int co0 = blockIdx.y * 32, ci0 = blockIdx.x * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-  for (int i = ty; i < 32; i += 8) {
-    const int co = co0 + i, ci = ci0 + tx;
-    tile[i][tx] = (co < cout && ci < cin) ? w[((size_t)co * r * s + src_tap) * cin + ci] : T(0);
+  T v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int co = co0 + ty + 8 * u, ci = ci0 + tx;
+    v[u] = w[co < cout && ci < cin ? ((size_t)co * taps + src_tap) * cin + ci : 0];
   }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) tile[ty + 8 * u][tx] = v[u];
   __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int ci = ci0 + i, co = co0 + tx;
-    if (ci < cin && co < cout) wt[((size_t)ci * r * s + tap) * cout + co] = tile[tx][i];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int ci = ci0 + ty + 8 * u, co = co0 + tx;
+    if (ci < cin && co < cout) wt[((size_t)ci * taps + tap) * cout + co] = tile[tx][ty + 8 * u];
   }
 }
 
@@ -58,23 +63,28 @@ __global__ __launch_bounds__(256) void gather_transpose_kernel(const T* __restri
     const int kr = src_tap / s, kt = src_tap - kr * s;
     int part = -1, jr = 0, jt = 0;                  // the class of the tap, and the tap's place in it
     for (int i = 0; i < gp.count; ++i) {
-      const int dr = kr - gp.r0[i], dt = kt - gp.t0[i];
-      if (dr >= 0 && dt >= 0 && dr % step == 0 && dt % step == 0 && dr / step < gp.nr[i] && dt / step < gp.ns[i]) {
-        part = i; jr = dr / step; jt = dt / step;
+      const int dr = kr - gp.r0[i], dt = kt - gp.t0[i], qr = dr / step, qt = dt / step;
+      if (dr >= 0 && dt >= 0 && qr * step == dr && qt * step == dt && qr < gp.nr[i] && qt < gp.ns[i]) {
+        part = i; jr = qr; jt = qt;
       }
     }
     if (part < 0) continue;                         // (the same for the whole workgroup)
     const int nr = gp.nr[part], ns = gp.ns[part], tap = (nr - 1 - jr) * ns + (ns - 1 - jt);
     T* wt = reinterpret_cast<T*>(out + gp.offset[part]);
     __syncthreads();
-    for (int i = ty; i < 32; i += 8) {
-      const int co = co0 + i, ci = ci0 + tx;
-      tile[i][tx] = (co < cout && ci < cin) ? w[((size_t)co * r * s + src_tap) * cin + ci] : T(0);
+    T v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int co = co0 + ty + 8 * u, ci = ci0 + tx;
+      v[u] = w[co < cout && ci < cin ? ((size_t)co * r * s + src_tap) * cin + ci : 0];
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) tile[ty + 8 * u][tx] = v[u];
     __syncthreads();
-    for (int i = ty; i < 32; i += 8) {
-      const int ci = ci0 + i, co = co0 + tx;
-      if (ci < cin && co < cout) wt[((size_t)ci * nr * ns + tap) * cout + co] = tile[tx][i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int ci = ci0 + ty + 8 * u, co = co0 + tx;
+      if (ci < cin && co < cout) wt[((size_t)ci * nr * ns + tap) * cout + co] = tile[tx][ty + 8 * u];
     }
   }
 }
