@@ -727,9 +727,9 @@ hipError_t conv_igemm(const ConvGeom& g, hipStream_t st, LaunchProbe* probe) {
   if (g.dtype != DT_F32 && g.dtype != DT_BF16) return hipErrorInvalidValue;
   if ((g.bias || g.relu) && (g.accumulate || g.stats || g.bnb.sums)) return hipErrorInvalidValue;
   if (conv_igemm_rows_takes(g, M, K)) return conv_igemm_rows(g, (int)M, (int)K, st, probe);
-  if (!g.w) return hipErrorInvalidValue;
   if (conv_igemm_bf16_takes(g, M, K))      // bf16 storage, widths in 8s
     return conv_igemm_bf16(g, (int)M, (int)K, st, probe);
+  if (!g.w) return hipErrorInvalidValue;
   if (conv_smallc_takes(g, M)) return conv_smallc_fwd(g, st, probe);
   // The direct loader addresses both operands through buffer descriptors: 32-bit ranges, the last bytes kept free for the
   // offset that stands for "outside"; 16-byte loads want aligned tensors.  The choice depends on the shape and the

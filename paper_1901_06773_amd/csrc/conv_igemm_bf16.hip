@@ -97,8 +97,20 @@ template <int N> __device__ __forceinline__ void wait_loads() {      // at most 
 #endif
 }
 
-// One tile, its first row m0 and column n0; `lds`: C::LDS bytes.
-template <class C, bool ACT, bool RAGGED>
+// 16 bytes per lane from memory to LDS, lane l's to at + 16 * l.  Written out, because before a transposing LDS read the compiler waits for
+// every such load it knows of, those of later chunks too; open() below counts them.  (One wait state between writing m0 and an LDS
+// load that reads it; nothing else in these kernels uses m0.)
+typedef unsigned srsrc __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_lds16(srsrc rs, uint32_t voff, uint32_t soff, uint32_t at) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");
+#endif
+}
+
+// One tile, its first row m0 and column n0; `lds`: C::LDS bytes.  KN (whole chunks): the filter is read as a data gradient finds it, g.w_kn[c][taps, the
+// last first][n]: rows of a chunk are its 64 c, of BN columns, and the LDS read transposes (ds_read_b64_tr_b16 hands every lane
+// of a group of sixteen the four rows of one of sixteen columns).  The same products in the same order.
+template <class C, bool ACT, bool RAGGED, bool KN = false>
 __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, int n0, char* lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int MB = C::MB, NB = C::NB, AI = C::AI, BI = C::BI, CPR = C::CPR, ROWB = C::ROWB, NS = C::NS, KS = C::KS;
@@ -144,10 +156,22 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
       }
     a_mask[i] = mask;
   }
+  const int taps = g.r * g.s;
+  const uint32_t row_n = (uint32_t)g.n_out * 2u;      // KN: bytes of one tap of one c
+  // KN: the lane's 16-byte column of BN and its rows a multiple of four apart; 64-byte pieces of a row are XORed with what the row says, so
+  // that the four rows that sixteen lanes read 32 bytes of each lie on different banks
+  constexpr int PB = C::BN * 2, CB = C::BN / 8, RB = C::GT / CB;
+  auto kn_xor = [](int row) { return PB == 64 ? 0 : PB == 128 ? (row >> 1) & 1 : row & 3; };
+  static_assert(!KN || (RB % 4 == 0 && BI * RB == C::BK), "whole rows, four at a time");
 #pragma unroll
   for (int i = 0; i < BI; ++i) {
-    const int n = n0 + lrow + C::RPP * i;
-    b_voff[i] = (uint32_t)(n < g.n_out ? n : 0) * (uint32_t)(K * 2) + lcol * 16;   // beyond n_out: filter 0, never stored
+    if constexpr (KN) {
+      const int row = gt / CB, n = n0 + 8 * ((gt % CB) ^ (kn_xor(row) << 2));
+      b_voff[i] = n < g.n_out ? (uint32_t)(row + RB * i) * ((uint32_t)taps * row_n) + (uint32_t)n * 2u : OUTSIDE;
+    } else {
+      const int n = n0 + lrow + C::RPP * i;
+      b_voff[i] = (uint32_t)(n < g.n_out ? n : 0) * (uint32_t)(K * 2) + lcol * 16;   // beyond n_out: filter 0, never stored
+    }
   }
   const size_t margin_bytes = (size_t)margin * g.c * 2;
   const size_t a_bytes = margin_bytes + (size_t)g.n_img * g.h * g.wd * g.c * 2;
@@ -155,6 +179,11 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
       const_cast<char*>(reinterpret_cast<const char*>(g.in)) - margin_bytes, 0, (int)(uint32_t)a_bytes, 0x00020000);
   __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(g.w), 0, (int)(uint32_t)((size_t)g.n_out * K * 2), 0x00020000);
+  auto descriptor = [](const void* p, size_t bytes) {
+    const uint64_t at = reinterpret_cast<uint64_t>(p);
+    return srsrc{(uint32_t)at, (uint32_t)(at >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
+  };
+  [[maybe_unused]] const srsrc kn_a = descriptor(static_cast<const char*>(g.in) - margin_bytes, a_bytes), kn_b = descriptor(g.w_kn, (size_t)g.n_out * K * 2);
   typedef __attribute__((address_space(3))) void* lds_ptr;
   char* const lds_g = lds + grp * (NS * C::STAGE);
   const uint32_t lds_w = (uint32_t)(size_t)lds_g + uwave * 1024;
@@ -165,7 +194,6 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
   const int rounds = KS == 1 ? n_chunks : (n_chunks + KS - 1) / KS;
   const int cols = g.c >> 3;                          // 16-byte columns of a pixel
   int tap, kt, col = 0, soff_b, toff;                 // toff: bytes from the row's first pixel
-  const int taps = g.r * g.s;
   if constexpr (RAGGED) {
     const int u = first * CPR + lcol;
     tap = u / cols;
@@ -187,6 +215,7 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
     kt = tap - kr * g.s;
     toff = ((kr * g.wd + kt) * cols + col - (RAGGED ? lcol : 0)) * 16;
   }
+  if constexpr (KN) soff_b = (col * 8 * taps + taps - 1 - tap) * (int)row_n;
   int left = (K >> 3) - first * CPR - lcol;           // RAGGED: columns of K from the lane's on
   const int row_jump = (g.wd - g.s) * g.c * 2;
   const int back_a = g.r * g.wd * g.c * 2 - ROWB, back_b = K * 2 - ROWB;
@@ -194,6 +223,11 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
   // load u of the next chunk (first those of A), which goes to the stage at `at`; advance() when all have been issued
   auto load = [&](int u, uint32_t at) {
     const bool k_ok = !RAGGED || left > 0;
+    if constexpr (KN) {
+      if (u < AI) load_lds16(kn_a, ((a_mask[u] >> (tap & 31)) & 1u) != 0 ? a_voff[u] : OUTSIDE, (uint32_t)toff, at + u * (C::GT * 16));
+      else load_lds16(kn_b, b_voff[u - AI], (uint32_t)soff_b, at + C::A_BYTES + (u - AI) * (C::GT * 16));
+      return;
+    }
     if (u < AI) {
       const bool ok = ((a_mask[u] >> (tap & 31)) & 1u) != 0 && k_ok;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr)(size_t)(at + u * (C::GT * 16)), 16,
@@ -217,18 +251,19 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
       kt = down ? 0 : kt;
       toff += ROWB + (down ? row_jump : 0);           // the next tap of a filter row is the next pixel
     } else if constexpr (KS > 1) {
-      soff_b += ROWB;
+      soff_b += KN ? C::BK * taps * (int)row_n : ROWB;
       toff += ROWB;                                   // the next tap of a filter row is the next pixel
       if ((col += CPR) == cols) {
         col = 0;
         ++tap;
+        if constexpr (KN) soff_b = (taps - 1 - tap) * (int)row_n;
         if (++kt == g.s) { kt = 0; toff += row_jump; }
       }
     } else {
-      soff_b += g.c * 2;
+      soff_b += KN ? -(int)row_n : g.c * 2;
       toff += g.c * 2;
       if (++kt == g.s) { kt = 0; toff += row_jump; }
-      if (++tap == taps) { tap = 0; toff -= back_a; soff_b -= back_b; }
+      if (++tap == taps) { tap = 0; toff -= back_a; soff_b += KN ? (C::BK + 1) * taps * (int)row_n : -back_b; }
     }
   };
   auto issue = [&](int stage) {
@@ -241,9 +276,32 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
   const int ra = wm0 + (lane & 31), rb = wn0 + (lane & 31);
   const int xa = swz(ra), xb = swz(rb);
   struct Frags { v4u a[MB], b[NB]; } F[2];
+  // KN: lane t of sixteen names four columns of row t/4 and receives rows 0..3 of column t; a fragment wants column lane%32 and eight rows: two reads
+  typedef short v4s __attribute__((ext_vector_type(4)));
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  typedef __attribute__((address_space(3))) v4s* tr_ptr;
+  const int frow = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  [[maybe_unused]] int kn_at[NB];
+  if constexpr (KN) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      kn_at[j] = C::A_BYTES + frow * PB + (((wn0 / 32 + j) ^ kn_xor(frow)) << 6) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+  }
   auto rd = [&](Frags& f, const char* st, int g8) {
     const int c16 = g8 * 2 + (lane >> 5);
     const char* as = st + ra * ROWB + ((c16 ^ xa) << 4);
+    if constexpr (KN) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) f.a[i] = *reinterpret_cast<const v4u*>(as + i * 32 * ROWB);
+      auto* const st3 = (__attribute__((address_space(3))) char*)const_cast<char*>(st);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const v2u lo = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(st3 + kn_at[j] + g8 * 16 * PB)));
+        const v2u hi = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(st3 + kn_at[j] + g8 * 16 * PB + 4 * PB)));
+        f.b[j] = v4u{lo.x, lo.y, hi.x, hi.y};
+      }
+      return;
+    }
     const char* bs = st + C::A_BYTES + rb * ROWB + ((c16 ^ xb) << 4);
 #pragma unroll
     for (int i = 0; i < MB; ++i) f.a[i] = *reinterpret_cast<const v4u*>(as + i * 32 * ROWB);
@@ -262,7 +320,7 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
     for (int g8 = 0; g8 + 1 < NG; ++g8) {
       rd(F[(g8 + 1) & 1], st, g8 + 1);
       mm(F[g8 & 1]);
-      constexpr int RD = MB + NB;
+      constexpr int RD = MB + (KN ? 2 : 1) * NB;
 #pragma unroll
       for (int u = 0; u < RD; ++u) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
@@ -478,11 +536,11 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
     }
   }
 #else
-  (void)&mfma_bf16; (void)&decode_row; (void)&out_row_offset;
+  (void)&mfma_bf16; (void)&decode_row; (void)&out_row_offset; (void)&load_lds16;
 #endif
 }
 
-template <class C, bool ACT, bool RAGGED>
+template <class C, bool ACT, bool RAGGED, bool KN>
 __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles, int main_grid) {
   __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
   if ((int)blockIdx.x >= main_grid) {
@@ -494,14 +552,14 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_kernel(ConvGeom
   const int at = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (at >= n_tiles) return;
   const int tile_m = at / n_tiles_n, tile_n = at - tile_m * n_tiles_n;
-  tile<C, ACT, RAGGED>(g, M, K, tile_m * C::BM, tile_n * C::BN, lds);
+  tile<C, ACT, RAGGED, KN>(g, M, K, tile_m * C::BM, tile_n * C::BN, lds);
 }
 
 // Two heights of tiles in one launch: n_tiles of C in main_grid workgroups, then the rows from `m` on in `tiles` of T (as wide) in `grid` more.
 struct Tail {
   int m, tiles, grid;
 };
-template <class C, class T, bool ACT, bool RAGGED>
+template <class C, class T, bool ACT, bool RAGGED, bool KN>
 __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_tail_kernel(ConvGeom g, int M, int K, int n_tiles_n, int n_tiles, int main_grid, Tail tail) {
   __shared__ __attribute__((aligned(1024))) char lds[C::LDS > T::LDS ? C::LDS : T::LDS];
   const int id = (int)blockIdx.x - main_grid;
@@ -513,14 +571,17 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void igemm_bf16_tail_kernel(Con
     const int at = (id & 7) * (tail.grid >> 3) + (id >> 3);
     if (at >= tail.tiles) return;
     const int tile_m = at / n_tiles_n, tile_n = at - tile_m * n_tiles_n;
-    tile<T, ACT, RAGGED>(g, M, K, tail.m + tile_m * T::BM, tile_n * T::BN, lds);
+    tile<T, ACT, RAGGED, KN>(g, M, K, tail.m + tile_m * T::BM, tile_n * T::BN, lds);
     return;
   }
   const int at = (blockIdx.x & 7) * (main_grid >> 3) + (blockIdx.x >> 3);
   if (at >= n_tiles) return;
   const int tile_m = at / n_tiles_n, tile_n = at - tile_m * n_tiles_n;
-  tile<C, ACT, RAGGED>(g, M, K, tile_m * C::BM, tile_n * C::BN, lds);
+  tile<C, ACT, RAGGED, KN>(g, M, K, tile_m * C::BM, tile_n * C::BN, lds);
 }
+
+// the launch was given the filter as a data gradient finds it, and only that
+inline bool reads_kn(const ConvGeom& g) { return g.w_kn && !g.w; }
 
 template <class C>
 void launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe) {
@@ -528,9 +589,10 @@ void launch(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* probe)
   const dim3 grid((unsigned)(main_grid + wide_side_blocks(g.side, g.flip, C::THREADS)));
   const bool ragged = g.c % C::BK != 0, act = g.bias || g.relu;
   if (probe->before) (void)hipEventRecord(probe->before, st);
-#define ACC_BF16(A, R) hipLaunchKernelGGL((igemm_bf16_kernel<C, A, R>), grid, dim3(C::THREADS), 0, st, g, M, K, tn, tiles, main_grid)
-  if (act) { if (ragged) ACC_BF16(true, true); else ACC_BF16(true, false); }
-  else { if (ragged) ACC_BF16(false, true); else ACC_BF16(false, false); }
+#define ACC_BF16(...) hipLaunchKernelGGL((igemm_bf16_kernel<C, __VA_ARGS__>), grid, dim3(C::THREADS), 0, st, g, M, K, tn, tiles, main_grid)
+  if (reads_kn(g)) ACC_BF16(false, false, true);
+  else if (act) { if (ragged) ACC_BF16(true, true, false); else ACC_BF16(true, false, false); }
+  else { if (ragged) ACC_BF16(false, true, false); else ACC_BF16(false, false, false); }
 #undef ACC_BF16
   if (probe->after) (void)hipEventRecord(probe->after, st);
 }
@@ -545,9 +607,10 @@ void launch_tail(const ConvGeom& g, int M, int K, hipStream_t st, LaunchProbe* p
   const dim3 grid((unsigned)(main_grid + tail.grid + wide_side_blocks(g.side, g.flip, C::THREADS)));
   const bool ragged = g.c % C::BK != 0, act = g.bias || g.relu;
   if (probe->before) (void)hipEventRecord(probe->before, st);
-#define ACC_BF16(A, R) hipLaunchKernelGGL((igemm_bf16_tail_kernel<C, T, A, R>), grid, dim3(C::THREADS), 0, st, g, M, K, tn, tiles, main_grid, tail)
-  if (act) { if (ragged) ACC_BF16(true, true); else ACC_BF16(true, false); }
-  else { if (ragged) ACC_BF16(false, true); else ACC_BF16(false, false); }
+#define ACC_BF16(...) hipLaunchKernelGGL((igemm_bf16_tail_kernel<C, T, __VA_ARGS__>), grid, dim3(C::THREADS), 0, st, g, M, K, tn, tiles, main_grid, tail)
+  if (reads_kn(g)) ACC_BF16(false, false, true);
+  else if (act) { if (ragged) ACC_BF16(true, true, false); else ACC_BF16(true, false, false); }
+  else { if (ragged) ACC_BF16(false, true, false); else ACC_BF16(false, false, false); }
 #undef ACC_BF16
   if (probe->after) (void)hipEventRecord(probe->after, st);
 }
@@ -663,6 +726,8 @@ bool conv_igemm_bf16_takes(const ConvGeom& g, long M, long K) {
   if ((margin_px + (long)g.n_img * g.h * g.wd) * g.c * 2 > 0xFFFFFF00L || (long)g.n_out * K * 2 > 0xFFFFFF00L) return false;
   if ((reinterpret_cast<uintptr_t>(g.in) & 15) || (reinterpret_cast<uintptr_t>(g.w) & 15) ||
       (reinterpret_cast<uintptr_t>(g.out) & 15)) return false;
+  // the filter as it lies: whole chunks of the kernel that will run, nothing fused behind, its offsets within 30 bits
+  if (reads_kn(g) && ((long)g.n_out * K * 2 >= (1L << 30) || (reinterpret_cast<uintptr_t>(g.w_kn) & 15) || g.bias || g.relu || g.c % kKinds[best_kind(g, M, K)].kc != 0)) return false;
   return ((M + 31) / 32) * ((g.n_out + 31) / 32) <= (1L << 30);
 }
 

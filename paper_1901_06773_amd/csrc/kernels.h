@@ -91,7 +91,8 @@ struct ConvGeom {
   // the sub-filter of every part to w + its wt_offset (w is then a workspace) and runs the parts; p .. pad_dx, the
   // output's stride and first pixel come from them.
   const DgradSplit* split;
-  // Optional (1x1 filters): the same filter as w[k][n], the layout a data gradient finds it in.  conv_igemm_rows_takes() says
+  // Optional (1x1 filters, and with bf16 storage all): the same filter as w[c][taps, the last first][n], the layout a data gradient finds it in: w[k][n] of
+  // 1x1.  bf16: read where w is null and conv_igemm_bf16_takes() says so; fp32:  conv_igemm_rows_takes() says
   // whether the launch reads it, and w is then not read and may be null.  A caller that asks with w null would need a launch of
   // its own to write it, and the answer counts that.
   const void* w_kn;

@@ -95,7 +95,9 @@ int conv_dgrad(const void* dy, const void* w, void* dx, int n, int h, int wd, in
       if (!dry && (e = fill_zero((float*)dx, bytes / 4, st)) != hipSuccess) return status(e);
     }
   }
-  g.w_kn = r == 1 ? w : nullptr;
+  g.w_kn = w;
+  if (dtype == DT_BF16 && conv_igemm_bf16_takes(g, (long)n * g.p * g.q, (long)r * s * cout)) return status(conv_igemm(g, st, probe));   // reads the filter as it lies
+  if (r != 1) g.w_kn = nullptr;
   if (!g.w_kn || !conv_igemm_rows_takes(g, (long)n * g.p * g.q, cout)) {     // that kernel reads the filter as it lies
     g.w = wt;
     g.w_kn = nullptr;
