@@ -690,17 +690,20 @@ double memory_us(const Kind& k, const ConvGeom& g, long M, long K) {
   const double read = 2e-6 * (pixels * g.c + (double)g.n_out * K), written = 2e-6 * (double)M * g.n_out;
   return k.per_mb_read * read + k.per_mb_written * written;
 }
-double compute_us(const Kind& k, const ConvGeom& g, long M, long K) {
+double compute_us(const Kind& k, const ConvGeom& g, long M, long K, bool lower) {
   const long tiles = ((M + k.bm - 1) / k.bm) * ((g.n_out + k.bn - 1) / k.bn), steps = ((K + k.kc - 1) / k.kc + k.ks - 1) / k.ks;
   const long whole = (tiles + 255) / 256;                // tiles of the busiest compute unit
-  const double most = k.bm == 256 && k.bn == 256 ? heights(M, g.n_out).rounds : (double)whole;
+  const double most = lower ? heights(M, g.n_out).rounds : (double)whole;
   const double first = k.first + k.first_step * steps, next = k.next + k.next_step * steps, more = g.r * g.s > 1 ? k.taps * most : 0;
   auto round = [&](long r) { return r == 0 ? 0.0 : first > r * next ? first : r * next; };
   return more + (k.per_cu == 1 ? first + (most - 1) * next : (whole / k.per_cu) * round(k.per_cu) + round(whole % k.per_cu));
 }
-bool bound_by_memory(const Kind& k, const ConvGeom& g, long M, long K) { return memory_us(k, g, M, K) > compute_us(k, g, M, K); }
+// whether a launch of 256 x 256 tiles may have lower ones: it does not wait for memory
+bool lower_tiles(const Kind& k, const ConvGeom& g, long M, long K) {
+  return k.bm == 256 && k.bn == 256 && memory_us(k, g, M, K) <= compute_us(k, g, M, K, false);
+}
 double predicted_us(const Kind& k, const ConvGeom& g, long M, long K) {
-  const double compute = compute_us(k, g, M, K), memory = memory_us(k, g, M, K);
+  const double compute = compute_us(k, g, M, K, lower_tiles(k, g, M, K)), memory = memory_us(k, g, M, K);
   return k.base + std::sqrt(compute * compute + memory * memory);
 }
 int best_kind(const ConvGeom& g, long M, long K) {
@@ -740,7 +743,7 @@ hipError_t conv_igemm_bf16(const ConvGeom& g, int M, int K, hipStream_t st, Laun
   probe->variant = V_IGEMM_BF16;
   probe->kernel = kKinds[kind].name;
   Heights h{0, 0, 0};
-  if (kind == K256x256 && !bound_by_memory(kKinds[kind], g, M, K)) h = heights(M, g.n_out);
+  if (kind == K256x256 && lower_tiles(kKinds[kind], g, M, K)) h = heights(M, g.n_out);
   if (h.low) probe->kernel = h.low == 192 ? "igemm_bf16 256x256 and 192x256" : "igemm_bf16 256x256 and 64x256";
   if (probe->dry) return hipSuccess;
   switch (kind) {
