@@ -664,6 +664,22 @@ hipError_t flush_pending_reduce(acc_ctx* c) {
   return hipStreamWaitEvent(c->s_c, c->ev_flush, 0);
 }
 
+// bf16 storage: whether the data gradient of a convolution step reads the filter as it lies (a function of the shapes); nobody flips it then.
+bool dgrad_reads_as_it_lies(const acc_ctx* c, const Step& s) {
+  const Graph& g = c->g;
+  if (g.dtype != ACC_BF16) return false;
+  const acc_layer& l = g.layers[s.layer];
+  const Tensor &x = g.tensors[s.x], &dy = g.tensors[s.dy];
+  if (l.stride > 1 && (l.r > 1 || l.s > 1 || l.pad > 0)) return false;      // in parts
+  ConvGeom cg{};
+  cg.dtype = g.dtype;
+  cg.w_kn = c->d_params16 + g.params[s.layer].offset;
+  cg.n_img = c->plan.k; cg.h = dy.h; cg.wd = dy.w; cg.c = l.cout; cg.n_out = l.cin;
+  cg.r = l.r; cg.s = l.s; cg.stride = 1;
+  cg.p = l.stride == 1 ? x.h : dy.h; cg.q = l.stride == 1 ? x.w : dy.w; cg.pad = l.stride == 1 ? l.r - 1 - l.pad : 0;
+  return conv_igemm_bf16_takes(cg, (long)cg.n_img * cg.p * cg.q, (long)l.r * l.s * l.cout);
+}
+
 hipError_t run_step(acc_ctx* c, int j, float lr) {
   const Graph& g = c->g;
   const Step& s = g.steps[j];
@@ -843,10 +859,11 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       }
       // the flipped, transposed filter: written by the previous conv backward step's launch,
       // unless this is the first one
-      if (s.flips_itself && (e = filter_flip_transpose(wk, ptr(s.ws), l->cout, l->cin, l->r, l->s, dt, st)) != hipSuccess)
+      const bool as_it_lies = dgrad_reads_as_it_lies(c, s);
+      if (s.flips_itself && !as_it_lies && (e = filter_flip_transpose(wk, ptr(s.ws), l->cout, l->cin, l->r, l->s, dt, st)) != hipSuccess)
         return e;
       ConvGeom cg{};
-      if (s.flip_for >= 0) {   // ... and the next one's rides on this step's launch
+      if (s.flip_for >= 0 && !dgrad_reads_as_it_lies(c, g.steps[s.flip_for])) {   // ... and the next one's rides on this step's launch
         const Step& nx = g.steps[s.flip_for];
         const acc_layer& nl = g.layers[nx.layer];
         const float* nw = c->d_params + g.params[nx.layer].offset;
@@ -854,7 +871,9 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
         cg.flip.wt = ptr(nx.ws);
         cg.flip.cout = nl.cout; cg.flip.cin = nl.cin; cg.flip.r = nl.r; cg.flip.s = nl.s;
       }
-      cg.in = ptr(s.dy); cg.w = ptr(s.ws); cg.out = ptr(s.dx); cg.dtype = dt;
+      cg.in = ptr(s.dy); cg.out = ptr(s.dx); cg.dtype = dt;
+      if (as_it_lies) cg.w_kn = wk;
+      else cg.w = ptr(s.ws);
       cg.n_img = k; cg.h = ho; cg.wd = wo; cg.c = l->cout; cg.n_out = l->cin;
       cg.r = l->r; cg.s = l->s; cg.stride = 1; cg.accumulate = s.dx_accumulate;
       cg.out_h = h; cg.out_w = wd;
