@@ -233,12 +233,125 @@ __global__ __launch_bounds__(THREADS) void maxpool_bwd_kernel(const T* __restric
 // Longer strips load less and leave fewer threads, each a longer chain of trips to memory.  Measured at strips of 1 / 2 / 4 / 8
 // (and the kernel before), 64 channels: fp32, 2 images of 112x112 (100 thousand blocks) 7.7 / 9.0 / 14.4 / 22.9 (11.5) us; 4 images
 // (200 thousand) 12.9 / 11.8 / 15.5 / 25.1 (18.8); 16 images (0.8 million) 37 / 31 / 28 / 31 (52); 32 images 66 / 54 / 49.5 /
-// 47.9 (103); bf16 at 32 images 62 / 49 / 45 / 50 (75).
+// 47.9 (103); bf16 at 32 images, by a scan, 62 / 49 / 45 / 50 (75).
 inline int maxpool_strip(size_t blocks, size_t elem_bytes) {
   if (blocks < 160 << 10) return 1;
   if (blocks < 512 << 10) return 2;
   return elem_bytes == 2 || blocks < 1280 << 10 ? 4 : 8;
 }
+// Three rows of five columns of x, four channels each, and in every 3x3 window over them the first position that holds the
+// maximum.  NaN as in a plain scan with ">": at the first position of a window (that lies in the map) it stays, elsewhere it
+// is passed over.
+template <class T> struct FirstMax;
+template <> struct FirstMax<float> {
+  float v[3][5][4];
+  bool row_ok[3], col_ok[5];
+  __device__ __forceinline__ void load(int i, const float* p, int c, const int (&col)[5], const bool (&cols)[5], bool ok) {
+    row_ok[i] = ok;
+#pragma unroll
+    for (int t = 0; t < 5; ++t) {
+      col_ok[t] = cols[t];
+      Elem<float>::load4(p + (size_t)col[t] * c, v[i][t]);
+    }
+  }
+  __device__ __forceinline__ void down() {
+    row_ok[0] = row_ok[2];
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[0][t][j] = v[2][t][j];
+  }
+  __device__ __forceinline__ void head(int, const bool (&)[5]) {}
+  static __device__ __forceinline__ int place(int at, int) { return at; }      // 3 * row + column
+  __device__ __forceinline__ void first(int (&at)[4], int t0) const {
+    float best[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) at[j] = -1;
+#pragma unroll
+    for (int kr = 0; kr < 3; ++kr)
+#pragma unroll
+      for (int kt = 0; kt < 3; ++kt) {
+        const bool ok = row_ok[kr] && col_ok[t0 + kt];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float x = v[kr][t0 + kt][j];
+          const bool more = ok & ((at[j] < 0) | (x > best[j]));
+          best[j] = more ? x : best[j];
+          at[j] = more ? 3 * kr + kt : at[j];
+        }
+      }
+  }
+};
+// bf16: an integer per value, its rank (16 bits that compare as the values do: both zeros are one, a NaN and what lies outside
+// the map rank below everything) above a number that falls from 15 to 1 along the three rows of five.  The largest integer of
+// a window is its first maximum, and a row can be left as the largest of its part of either window: eight registers in place
+// of twenty, and two instructions for a value of a row and its windows where the scan has five for each value of a window.
+// Registers decide here: with all fifteen integers kept and a scan for rows that hold a NaN (147 to 170 registers, three or two
+// waves instead of four) the kernel took 288 to 370 us.  64 channels of 112x112, scan and this, 2 / 8 / 32 / 128 images: 7.8 / 18.6 /
+// 45.8 / 168 and 7.4 / 15.8 / 38.5 / 153 us (the 514 MB of 128 images take 111 at the rate of a large copy); what is left
+// is the loads of overlapping columns and the wait for them.
+template <> struct FirstMax<bf16_t> {
+  typedef short Short2 __attribute__((ext_vector_type(2)));
+  typedef unsigned short UShort2 __attribute__((ext_vector_type(2)));
+  int key[3][2][4];
+  unsigned lead[3][2][2];                         // the first values of either part, as loaded
+  static __device__ __forceinline__ unsigned bits(Short2 v) { return __builtin_bit_cast(unsigned, v); }
+  __device__ __forceinline__ void load(int i, const bf16_t* p, int c, const int (&col)[5], const bool (&cols)[5], bool ok) {
+    uint2 q[5];
+#pragma unroll
+    for (int t = 0; t < 5; ++t) q[t] = *reinterpret_cast<const uint2*>(p + (size_t)col[t] * c);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      int v[5][2];
+#pragma unroll
+      for (int t = 0; t < 5; ++t) {
+        const unsigned w = k ? q[t].y : q[t].x;
+        const Short2 sign = __builtin_bit_cast(Short2, w) >> 15;
+        // negative values downwards from zero; 127 more, which takes a positive NaN round to the lowest
+        const Short2 r = __builtin_bit_cast(Short2, w ^ (bits(sign) & 0x7fff7fffu)) - sign + (short)0x7f;
+        const unsigned rank = ok && cols[t] ? bits(r) : 0x80008000u, code = 15 - (5 * i + t);
+        v[t][0] = (int)(rank << 16 | code);
+        v[t][1] = (int)((rank & 0xffff0000u) | code);
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        key[i][0][2 * k + j] = max(max(v[0][j], v[1][j]), v[2][j]);
+        key[i][1][2 * k + j] = max(max(v[2][j], v[3][j]), v[4][j]);
+      }
+      lead[i][0][k] = cols[0] ? (k ? q[0].y : q[0].x) : (k ? q[1].y : q[1].x);
+      lead[i][1][k] = k ? q[2].y : q[2].x;
+    }
+  }
+  __device__ __forceinline__ void down() {
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) key[0][w][j] = key[2][w][j] + 10;
+      lead[0][w][0] = lead[2][w][0];
+      lead[0][w][1] = lead[2][w][1];
+    }
+  }
+  // row i is the first one of its windows: a NaN at their first position stays
+  __device__ __forceinline__ void head(int i, const bool (&cols)[5]) {
+    UShort2 top = 0;
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) top = __builtin_elementwise_max(top, __builtin_bit_cast(UShort2, lead[i][w][k] & 0x7fff7fffu));
+    if (top.x <= 0x7f80 && top.y <= 0x7f80) return;
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if ((lead[i][w][j >> 1] >> 16 * (j & 1) & 0x7fffu) > 0x7f80u)
+          key[i][w][j] = 0x7fff0000 | (15 - (5 * i + (w ? 2 : cols[0] ? 0 : 1)));
+  }
+  static __device__ __forceinline__ int place(int at, int t0) { return 15 - (5 * (at / 3) + at % 3 + t0); }
+  __device__ __forceinline__ void first(int (&at)[4], int t0) const {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) at[j] = max(max(key[0][t0 >> 1][j], key[1][t0 >> 1][j]), key[2][t0 >> 1][j]) & 15;
+  }
+};
 template <class T>
 __global__ __launch_bounds__(THREADS) void maxpool3s2_bwd_kernel(const T* __restrict__ x,
                                                                  const T* __restrict__ dy, T* __restrict__ dx, int n,
@@ -263,58 +376,43 @@ __global__ __launch_bounds__(THREADS) void maxpool3s2_bwd_kernel(const T* __rest
       col_ok[t] = (unsigned)xx < (unsigned)wd;
       col[t] = col_ok[t] ? xx : 0;
     }
-    struct Row { float v[5][4]; bool ok; } r0, r1, r2;
-    auto load_row = [&](Row& r, int yy) {
-      r.ok = (unsigned)yy < (unsigned)h;
-      const T* p = xi + (size_t)(r.ok ? yy : 0) * wd * c;
-#pragma unroll
-      for (int t = 0; t < 5; ++t) Elem<T>::load4(p + (size_t)col[t] * c, r.v[t]);
+    FirstMax<T> rows;                            // three rows of x and the windows over them
+    struct Win { int at[4]; float d[4]; };       // which position holds the first maximum, gradient of the window
+    auto load_row = [&](int i, int yy) {
+      const bool ok = (unsigned)yy < (unsigned)h;
+      const T* p = xi + (size_t)(ok ? yy : 0) * wd * c;
+      rows.load(i, p, c, col, col_ok, ok);
     };
-    struct Win { int at[4]; float d[4]; };      // place of the first maximum (3 * row + column), gradient of the window
     auto window = [&](Win& w, int p, int q, int t0) {
       const bool exists = p < ho && q < wo;
-      float best[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w.at[j] = -1;
-#pragma unroll
-      for (int kr = 0; kr < 3; ++kr) {
-        const Row& r = kr == 0 ? r0 : kr == 1 ? r1 : r2;
-#pragma unroll
-        for (int kt = 0; kt < 3; ++kt) {
-          const bool ok = r.ok && col_ok[t0 + kt];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float v = r.v[t0 + kt][j];
-            const bool more = ok & ((w.at[j] < 0) | (v > best[j]));
-            best[j] = more ? v : best[j];
-            w.at[j] = more ? 3 * kr + kt : w.at[j];
-          }
-        }
-      }
+      rows.first(w.at, t0);
       Elem<T>::load4(dyi + (exists ? ((size_t)p * wo + q) * c : 0), w.d);
 #pragma unroll
       for (int j = 0; j < 4; ++j) w.at[j] = exists ? w.at[j] : -1;
     };
     Win u0, u1, l0, l1;                          // windows (a, b), (a, b+1) and (a+1, b), (a+1, b+1)
-    load_row(r0, 2 * a0 - 1);
-    load_row(r1, 2 * a0);
-    load_row(r2, 2 * a0 + 1);
+    load_row(0, 2 * a0 - 1);
+    load_row(1, 2 * a0);
+    load_row(2, 2 * a0 + 1);
+    if (a0 == 0) rows.head(1, col_ok);
+    else rows.head(0, col_ok);
     window(u0, a0, b, 0);
     window(u1, a0, b + 1, 2);
     for (int a = a0; a < a0 + strip && a < hb; ++a) {
-      r0 = r2;
-      load_row(r1, 2 * a + 2);
-      load_row(r2, 2 * a + 3);
+      rows.down();
+      load_row(1, 2 * a + 2);
+      load_row(2, 2 * a + 3);
+      rows.head(0, col_ok);
       window(l0, a + 1, b, 0);
       window(l1, a + 1, b + 1, 2);
       float o[2][2][4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        auto take = [&](float acc, const Win& w, int at) { return w.at[j] == at ? acc + w.d[j] : acc; };
-        o[0][0][j] = take(0.f, u0, 4);
-        o[0][1][j] = take(take(0.f, u0, 5), u1, 3);
-        o[1][0][j] = take(take(0.f, u0, 7), l0, 1);
-        o[1][1][j] = take(take(take(take(0.f, u0, 8), u1, 6), l0, 2), l1, 0);
+        auto take = [&](float acc, const Win& w, int at, int t0) { return w.at[j] == FirstMax<T>::place(at, t0) ? acc + w.d[j] : acc; };
+        o[0][0][j] = take(0.f, u0, 4, 0);
+        o[0][1][j] = take(take(0.f, u0, 5, 0), u1, 3, 2);
+        o[1][0][j] = take(take(0.f, u0, 7, 0), l0, 1, 0);
+        o[1][1][j] = take(take(take(take(0.f, u0, 8, 0), u1, 6, 2), l0, 2, 0), l1, 0, 2);
       }
 #pragma unroll
       for (int ry = 0; ry < 2; ++ry)
