@@ -644,9 +644,9 @@ hipError_t conv_wgrad(const WgradGeom& g, hipStream_t st, LaunchProbe* probe, Re
   if (mfma16 && !(Mrows * g.cout * es <= 0xFFFFFF00L && (long)g.n_img * g.h * g.wd * g.cin * es <= 0xFFFFFF00L &&
                   (reinterpret_cast<uintptr_t>(g.x) & 15) == 0 && (reinterpret_cast<uintptr_t>(g.dy) & 15) == 0))
     return hipErrorInvalidValue;   // (the parts, and with them the workspace, were sized for this kernel)
-  if (probe) {                             // (near and far, maps beyond 4096 rows or columns, are one kernel: names that callers know)
+  if (probe) {
     probe->variant = small ? V_SMALLC_WGRAD : mfma16 ? V_WGRAD_BF16 : x3 ? V_WGRAD_X3 : direct ? V_WGRAD_DIRECT : fast ? V_WGRAD_FAST : V_WGRAD_GENERIC;
-    probe->kernel = small ? "smallc" : mfma16 ? (g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0 ? "wgrad_bf16 plain" : g.p <= 4096 && g.q <= 4096 ? "wgrad_bf16 near" : "wgrad_bf16 far")
+    probe->kernel = small ? "smallc" : mfma16 ? wgrad_bf16_name(g, cb)
                     : x3 ? (cx.wt == 2 ? "wgrad_x3 128x128" : "wgrad_x3 64x64") : direct ? "wgrad direct 64x64" : fast ? "wgrad fast 64x64" : "wgrad generic 64x64";
     if (probe->dry) return hipSuccess;
   }

@@ -384,20 +384,24 @@ typedef WCfg<2, 1, 2, 2, 2, 32, 3, 2> W128x64;
 // (1.02 to 2.2).  Without 256 x 128 the choice of the best would be slower by up to 4 %, without 128 x 256 10, 64 x 64 72, 64 x 128 19,
 // 128 x 64 10; 128 x 128, 64 x 256 and 256 x 256, which the parts leave half of the chip, are worth 1 to 3 % of single shapes and aren't here.
 struct Kind {
-  const char* name;
+  const char *gathered, *plain;                        // what a probe is told: filters of any kind, 1x1 without stride or padding
   int bm, bn, ck, threads, per_cu;
   double base, first, first_step, next, next_step, taps, per_mb, sum_base, sum_mb, per_mb_result;
 };
 enum { K256x128 = 0, K128x256, K64x64, K64x128, K128x64, KINDS };
+#define ACC_WN(N) "wgrad_bf16 " N, "wgrad_bf16 " N " plain"
 #define ACC_WK(C) C::BM, C::BN, C::CK, C::THREADS
 constexpr Kind kKinds[KINDS] = {
-    {"256x128", ACC_WK(W256x128), 1, 0.000, 4.685, 0.753, 0.600, 0.600, 1.314, 0.118, 2.606, 0.114, 0.165},
-    {"128x256", ACC_WK(W128x256), 1, 0.000, 5.140, 0.564, 0.000, 0.891, 1.829, 0.129, 2.807, 0.124, 0.161},
-    {"64x64", ACC_WK(W64x64), 2, 2.207, 0.080, 0.850, 1.053, 0.286, 0.881, 0.172, 1.680, 0.212, 0.247},
-    {"64x128", ACC_WK(W64x128), 2, 2.249, 0.000, 0.557, 0.581, 0.234, 1.185, 0.150, 1.886, 0.181, 0.240},
-    {"128x64", ACC_WK(W128x64), 2, 3.234, 0.065, 0.269, 0.070, 0.264, 0.768, 0.150, 2.219, 0.178, 0.178},
+    {ACC_WN("256x128"), ACC_WK(W256x128), 1, 0.000, 4.685, 0.753, 0.600, 0.600, 1.314, 0.118, 2.606, 0.114, 0.165},
+    {ACC_WN("128x256"), ACC_WK(W128x256), 1, 0.000, 5.140, 0.564, 0.000, 0.891, 1.829, 0.129, 2.807, 0.124, 0.161},
+    {ACC_WN("64x64"), ACC_WK(W64x64), 2, 2.207, 0.080, 0.850, 1.053, 0.286, 0.881, 0.172, 1.680, 0.212, 0.247},
+    {ACC_WN("64x128"), ACC_WK(W64x128), 2, 2.249, 0.000, 0.557, 0.581, 0.234, 1.185, 0.150, 1.886, 0.181, 0.240},
+    {ACC_WN("128x64"), ACC_WK(W128x64), 2, 3.234, 0.065, 0.269, 0.070, 0.264, 0.768, 0.150, 2.219, 0.178, 0.178},
 };
 #undef ACC_WK
+#undef ACC_WN
+
+inline bool plain_filter(const WgradGeom& g) { return g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0; }
 
 WgradBf16Cfg cut(const Kind& k, long Mrows, int cout, long J, int max_splits) {
   WgradBf16Cfg c{};
@@ -441,13 +445,15 @@ WgradBf16Cfg wgrad_bf16_choose(long Mrows, long pixels, int cin, int cout, int r
   return best;
 }
 
+const char* wgrad_bf16_name(const WgradGeom& g, const WgradBf16Cfg& c) { return plain_filter(g) ? kKinds[c.kind].plain : kKinds[c.kind].gathered; }
+
 hipError_t conv_wgrad_bf16(const WgradGeom& g, const WgradBf16Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st) {
   const long work = (long)c.tiles_co * c.tiles_j * c.splits;
   const int threads = kKinds[c.kind].threads, tiles = c.tiles_co * c.tiles_j;
   const long side = wide_side_blocks(g.side, FlipJob{g.flip_w, g.flip_wt, g.cout, g.cin, g.r, g.s}, threads);
   const long main_grid = (work + 7) / 8 * 8;
   if (main_grid + side > (1L << 30)) return hipErrorInvalidValue;
-  const bool plain = g.r == 1 && g.s == 1 && g.stride == 1 && g.pad == 0;
+  const bool plain = plain_filter(g);
   const dim3 grid((unsigned)(main_grid + side));
 #define ACC_WB(C, G) hipLaunchKernelGGL((wgrad_bf16_kernel<C, G>), grid, dim3(C::THREADS), 0, st, g, Mrows, J, c.tiles_j, tiles, \
                                         c.splits, c.chunks_per_split, out, count, (int)main_grid)

@@ -186,11 +186,12 @@ struct WgradX3Cfg {
 WgradX3Cfg wgrad_x3_choose(long Mrows, int cin, int cout, int r, int s, int max_splits);
 hipError_t conv_wgrad_x3(const WgradGeom& g, const WgradX3Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st);
 // The kernel for bf16 storage (conv_wgrad_bf16.hip): how it cuts a shape (pixels: of the input), with max_splits
-// parts at most, and the launch.
+// parts at most, the name of the tiling, and the launch.
 struct WgradBf16Cfg {
   int kind, tiles_co, tiles_j, splits, chunks_per_split;
 };
 WgradBf16Cfg wgrad_bf16_choose(long Mrows, long pixels, int cin, int cout, int r, int s, int max_splits);
+const char* wgrad_bf16_name(const WgradGeom& g, const WgradBf16Cfg& c);
 hipError_t conv_wgrad_bf16(const WgradGeom& g, const WgradBf16Cfg& c, int Mrows, int J, float* out, size_t count, hipStream_t st);
 // The kernel for a handful of input channels (conv_smallc.hip): parts it cuts the reduction into (0: the shape is not
 // its; a function of what wgrad_workspace_bytes() knows), whether it takes a launch, and the launch.

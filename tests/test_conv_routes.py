@@ -37,12 +37,20 @@ def test_few_channels(shape, fwd, wgrad):
     assert (kernel("wgrad", *shape) == "smallc") == wgrad
 
 
-def test_bf16_weight_gradient_gathers():
-    assert kernel("wgrad", 512, 14, 14, 256, 256, 3, 1, 1, BF16) == "wgrad_bf16 near"
-    assert kernel("wgrad", 64, 14, 14, 256, 256, 1, 1, 0, BF16) == "wgrad_bf16 plain"
-    assert kernel("wgrad", 1, 4096, 4, 8, 8, 3, 1, 1, BF16) == "wgrad_bf16 near"
-    assert kernel("wgrad", 1, 4097, 4, 8, 8, 3, 1, 1, BF16) == "wgrad_bf16 far"
-    assert kernel("wgrad", 1, 4, 4097, 8, 8, 3, 1, 1, BF16) == "wgrad_bf16 far"
+# bf16 weight gradients: the tiling; 1x1 filters without a stride find a position's pixel without counting
+@pytest.mark.parametrize("shape,name", [
+    ((512, 14, 14, 256, 256, 3, 1, 1, BF16), "wgrad_bf16 256x128"),
+    ((512, 7, 7, 512, 512, 3, 1, 1, BF16), "wgrad_bf16 256x128"),
+    ((256, 28, 28, 512, 128, 1, 1, 0, BF16), "wgrad_bf16 128x256 plain"),
+    ((64, 14, 14, 256, 256, 1, 1, 0, BF16), "wgrad_bf16 64x64 plain"),
+    ((64, 14, 14, 256, 256, 1, 2, 0, BF16), "wgrad_bf16 64x64"),
+    ((1, 4096, 4, 8, 8, 3, 1, 1, BF16), "wgrad_bf16 64x64"),
+    ((1, 4097, 4, 8, 8, 3, 1, 1, BF16), "wgrad_bf16 64x64"),          # maps of any size
+    ((8, 56, 56, 3, 64, 3, 1, 1, BF16), "smallc"),
+    ((8, 56, 56, 12, 64, 3, 1, 1, BF16), "wgrad generic 64x64"),      # channels not in 8s
+])
+def test_bf16_weight_gradient(shape, name):
+    assert kernel("wgrad", *shape) == name
 
 
 def test_fp32_layers_reach_the_kernels_their_parity_tests_name():

@@ -1,4 +1,4 @@
-"""GPU parity of the bf16 weight gradient at the edges of its tilings: tiles that the channels fill whole, by a remainder or by eight channels,
+"""GPU parity of the bf16 weight gradient at the edges of its five tilings, on 1x1 filters and on others: tiles that the channels fill whole, by a remainder or by eight channels,
 columns of a tile that span filter taps, fewer positions than a chunk, one more and one fewer than whole chunks, maps smaller than a chunk (a
 row's position wraps over whole images), strides, paddings and filters of every kind, one part and many.
 
@@ -7,41 +7,71 @@ Normal values make that less than 1e-5 of the l2 norm for the sizes here; whole 
 import pytest
 import torch
 
-pytestmark = pytest.mark.gpu
-
-# n, h, w, cin, cout, r, stride, pad
+# n, h, w, cin, cout, r, stride, pad, tiling
 CASES = [
-    (20, 14, 14, 256, 256, 3, 1, 1),    # whole tiles
-    (9, 15, 13, 264, 136, 3, 1, 1),     # remainders of eight in both directions, columns that span taps
-    (64, 7, 7, 512, 512, 3, 1, 1),      # maps of 49 positions, chunks of 64 and 128
-    (31, 28, 28, 512, 128, 1, 1, 0),
-    (40, 28, 28, 128, 512, 1, 1, 0),
-    (16, 56, 56, 64, 64, 1, 1, 0),      # few elements in many parts
-    (16, 55, 56, 64, 64, 3, 1, 1),
-    (8, 56, 55, 64, 256, 1, 2, 0),      # strided, smaller than its stride
-    (5, 27, 29, 128, 128, 3, 2, 1),
-    (3, 30, 31, 40, 72, 3, 2, 1),
-    (1, 1, 1, 64, 64, 1, 1, 0),         # one position
-    (1, 3, 21, 64, 128, 1, 1, 0),       # 63, 64, 65, 127, 129 positions
-    (1, 8, 8, 128, 64, 1, 1, 0),
-    (1, 5, 13, 72, 64, 1, 1, 0),
-    (1, 1, 127, 64, 8, 3, 1, 1),
-    (1, 3, 43, 8, 200, 3, 1, 1),
-    (200, 1, 1, 2048, 1000, 1, 1, 0),   # a fully connected layer
-    (70, 1, 2, 24, 40, 3, 1, 1),        # maps of two positions
-    (50, 2, 3, 32, 32, 5, 3, 2),
-    (2, 33, 17, 16, 48, 5, 1, 2),
-    (3, 12, 12, 32, 136, 3, 4, 0),
-    (4, 16, 16, 136, 264, 2, 1, 1),     # even filters
-    (2, 9, 70, 384, 24, 2, 1, 0),
+    (20, 14, 14, 256, 256, 3, 1, 1, "64x64"),    # whole tiles
+    (9, 15, 13, 264, 136, 3, 1, 1, "64x64"),     # remainders of eight in both directions, columns that span taps
+    (64, 7, 7, 512, 512, 3, 1, 1, "128x256"),      # maps of 49 positions, chunks of 64 and 128
+    (31, 28, 28, 512, 128, 1, 1, 0, "64x64 plain"),
+    (40, 28, 28, 128, 512, 1, 1, 0, "64x64 plain"),
+    (16, 56, 56, 64, 64, 1, 1, 0, "64x64 plain"),      # few elements in many parts
+    (16, 55, 56, 64, 64, 3, 1, 1, "64x64"),
+    (8, 56, 55, 64, 256, 1, 2, 0, "64x64"),      # strided, smaller than its stride
+    (5, 27, 29, 128, 128, 3, 2, 1, "64x64"),
+    (3, 30, 31, 40, 72, 3, 2, 1, "64x64"),
+    (1, 1, 1, 64, 64, 1, 1, 0, "64x128 plain"),         # one position
+    (1, 3, 21, 64, 128, 1, 1, 0, "64x128 plain"),       # 63, 64, 65, 127, 129 positions
+    (1, 8, 8, 128, 64, 1, 1, 0, "64x128 plain"),
+    (1, 5, 13, 72, 64, 1, 1, 0, "64x128 plain"),
+    (1, 1, 127, 64, 8, 3, 1, 1, "64x64"),
+    (1, 3, 43, 8, 200, 3, 1, 1, "64x64"),
+    (200, 1, 1, 2048, 1000, 1, 1, 0, "128x64 plain"),   # a fully connected layer
+    (70, 1, 2, 24, 40, 3, 1, 1, "64x64"),        # maps of two positions
+    (50, 2, 3, 32, 32, 5, 3, 2, "64x128"),
+    (2, 33, 17, 16, 48, 5, 1, 2, "64x64"),
+    (3, 12, 12, 32, 136, 3, 4, 0, "64x128"),
+    (4, 16, 16, 136, 264, 2, 1, 1, "128x64"),     # even filters
+    (2, 9, 70, 384, 24, 2, 1, 0, "64x64"),
+    # the two large tilings, in several parts
+    (512, 14, 14, 256, 256, 3, 1, 1, "256x128"),   # whole tiles, fourteen parts of 112 whole chunks
+    (301, 13, 11, 200, 504, 3, 1, 1, "256x128"),   # both directions end inside a tile, the range inside a chunk
+    (301, 13, 11, 264, 136, 3, 1, 1, "256x128"),   # one tile, half of its channels there
+    (257, 7, 7, 512, 512, 3, 1, 1, "256x128"),     # an image is less than a chunk
+    (301, 13, 11, 512, 512, 3, 2, 1, "256x128"),
+    (256, 28, 28, 320, 392, 1, 2, 0, "256x128"),
+    (130, 28, 27, 200, 504, 1, 1, 0, "256x128 plain"),
+    (512, 14, 14, 264, 136, 1, 1, 0, "256x128 plain"),
+    (301, 13, 11, 136, 520, 3, 1, 1, "128x256"),
+    (257, 7, 7, 200, 504, 3, 1, 1, "128x256"),
+    (63, 28, 27, 448, 208, 2, 1, 0, "256x128"),
+    (256, 28, 28, 136, 520, 1, 2, 0, "128x256"),
+    (256, 28, 28, 512, 128, 1, 1, 0, "128x256 plain"),
+    (301, 13, 11, 136, 520, 1, 1, 0, "128x256 plain"),
+    (51, 33, 30, 456, 200, 1, 1, 0, "128x256 plain"),
+    # 64 x 128 and 128 x 64 in several parts
+    (75, 17, 15, 416, 160, 3, 2, 1, "64x128"),
+    (33, 39, 39, 352, 80, 1, 1, 0, "64x128 plain"),
+    (37, 21, 20, 104, 304, 3, 1, 1, "128x64"),
+    (33, 27, 26, 488, 424, 1, 1, 0, "128x64 plain"),
 ]
 
 
+@pytest.mark.parametrize("case", CASES)
+def test_tiling(case):
+    from paper_1901_06773_amd import binding as b
+    assert b.op_conv_kernel("wgrad", *case[:8], b.BF16) == "wgrad_bf16 " + case[8]
+
+
+def test_every_tiling_has_cases():
+    assert {c[8] for c in CASES} == {t + f for t in ("256x128", "128x256", "64x64", "64x128", "128x64") for f in ("", " plain")}
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("whole", [False, True])
 @pytest.mark.parametrize("case", CASES)
 def test_wgrad_bf16(case, whole):
     from paper_1901_06773_amd import binding as b
-    n, h, w, ci, co, r, st, pad = case
+    n, h, w, ci, co, r, st, pad = case[:8]
     ho, wo = (h + 2 * pad - r) // st + 1, (w + 2 * pad - r) // st + 1
     gen = torch.Generator(device="cuda").manual_seed(n * h + w + ci)
     def values(*shape):

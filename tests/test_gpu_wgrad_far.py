@@ -1,5 +1,6 @@
-"""bf16 weight gradient on maps of millions of rows or columns, beyond the range in which the kernel may move its positions on by
-float quotients and 24-bit products (up to 4096): every position counts, the ones at the ends of a row above all.
+"""bf16 weight gradient on maps of millions of rows or columns, and of a few rows or columns on either side of 4096: a thread counts the pixels of its
+rows on from chunk to chunk, by whole images, rows and columns with one wrap of each at most, and that has to hold for any map.  Every
+position counts, the ones at the ends of a row above all.
 
 The operands are whole numbers up to 2 at a few thousand positions, zero elsewhere, so every sum is a whole number below 2^24 and the
 result is exact in any order."""
