@@ -24,22 +24,11 @@
 
 #include "kernels.h"
 #include "dtype.h"
+#include "lds_load.h"
 #include "side_wide.h"
 
 namespace acc {
 namespace {
-
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ v16f mfma_bf16(const v4u& a, const v4u& b, v16f c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-#else
-  return c;  // the host pass never runs this
-#endif
-}
 
 struct RowPos {  // decoded GEMM row
   int pix;       // img * h * wd (pixel index of the image origin)
@@ -89,23 +78,6 @@ template <int WM_, int WN_, int KS_, int MB_, int NB_, int BK_, int NS_, int WPE
   static constexpr int OUT = KS == 1 ? WM * WN * 32 * EPF : KS * BM * PITCH * 4;
   static constexpr int LDS0 = MAIN > OUT ? MAIN : OUT, LDS = LDS0 > wide_scratch<bf16_t>(THREADS) ? LDS0 : wide_scratch<bf16_t>(THREADS);
 };
-
-template <int N> __device__ __forceinline__ void wait_loads() {      // at most N loads of the wave still on their way
-#if defined(__HIP_DEVICE_COMPILE__)
-  static_assert(N < 64, "vmcnt has six bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);  // and every LDS access done
-#endif
-}
-
-// 16 bytes per lane from memory to LDS, lane l's to at + 16 * l.  Written out, because before a transposing LDS read the compiler waits for
-// every such load it knows of, those of later chunks too; open() below counts them.  (One wait state between writing m0 and an LDS
-// load that reads it; nothing else in these kernels uses m0.)
-typedef unsigned srsrc __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void load_lds16(srsrc rs, uint32_t voff, uint32_t soff, uint32_t at) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");
-#endif
-}
 
 // One tile, its first row m0 and column n0; `lds`: C::LDS bytes.  KN (whole chunks): the filter is read as a data gradient finds it, g.w_kn[c][taps, the
 // last first][n]: rows of a chunk are its 64 c, of BN columns, and the LDS read transposes (ds_read_b64_tr_b16 hands every lane
@@ -158,15 +130,13 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
   }
   const int taps = g.r * g.s;
   const uint32_t row_n = (uint32_t)g.n_out * 2u;      // KN: bytes of one tap of one c
-  // KN: the lane's 16-byte column of BN and its rows a multiple of four apart; 64-byte pieces of a row are XORed with what the row says, so
-  // that the four rows that sixteen lanes read 32 bytes of each lie on different banks
+  // KN: the lane's 16-byte column of BN and its rows a multiple of four apart
   constexpr int PB = C::BN * 2, CB = C::BN / 8, RB = C::GT / CB;
-  auto kn_xor = [](int row) { return PB == 64 ? 0 : PB == 128 ? (row >> 1) & 1 : row & 3; };
   static_assert(!KN || (RB % 4 == 0 && BI * RB == C::BK), "whole rows, four at a time");
 #pragma unroll
   for (int i = 0; i < BI; ++i) {
     if constexpr (KN) {
-      const int row = gt / CB, n = n0 + 8 * ((gt % CB) ^ (kn_xor(row) << 2));
+      const int row = gt / CB, n = n0 + 8 * ((gt % CB) ^ (row_xor<PB>(row) << 2));
       b_voff[i] = n < g.n_out ? (uint32_t)(row + RB * i) * ((uint32_t)taps * row_n) + (uint32_t)n * 2u : OUTSIDE;
     } else {
       const int n = n0 + lrow + C::RPP * i;
@@ -179,10 +149,6 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
       const_cast<char*>(reinterpret_cast<const char*>(g.in)) - margin_bytes, 0, (int)(uint32_t)a_bytes, 0x00020000);
   __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(g.w), 0, (int)(uint32_t)((size_t)g.n_out * K * 2), 0x00020000);
-  auto descriptor = [](const void* p, size_t bytes) {
-    const uint64_t at = reinterpret_cast<uint64_t>(p);
-    return srsrc{(uint32_t)at, (uint32_t)(at >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
-  };
   [[maybe_unused]] const srsrc kn_a = descriptor(static_cast<const char*>(g.in) - margin_bytes, a_bytes), kn_b = descriptor(g.w_kn, (size_t)g.n_out * K * 2);
   typedef __attribute__((address_space(3))) void* lds_ptr;
   char* const lds_g = lds + grp * (NS * C::STAGE);
@@ -223,7 +189,7 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
   // load u of the next chunk (first those of A), which goes to the stage at `at`; advance() when all have been issued
   auto load = [&](int u, uint32_t at) {
     const bool k_ok = !RAGGED || left > 0;
-    if constexpr (KN) {
+    if constexpr (KN) {                               // (all loads of such an instance, or none, are load_lds16's)
       if (u < AI) load_lds16(kn_a, ((a_mask[u] >> (tap & 31)) & 1u) != 0 ? a_voff[u] : OUTSIDE, (uint32_t)toff, at + u * (C::GT * 16));
       else load_lds16(kn_b, b_voff[u - AI], (uint32_t)soff_b, at + C::A_BYTES + (u - AI) * (C::GT * 16));
       return;
@@ -285,7 +251,7 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
   if constexpr (KN) {
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-      kn_at[j] = C::A_BYTES + frow * PB + (((wn0 / 32 + j) ^ kn_xor(frow)) << 6) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+      kn_at[j] = C::A_BYTES + frow * PB + (((wn0 / 32 + j) ^ row_xor<PB>(frow)) << 6) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
   }
   auto rd = [&](Frags& f, const char* st, int g8) {
     const int c16 = g8 * 2 + (lane >> 5);

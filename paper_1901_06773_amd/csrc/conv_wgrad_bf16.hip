@@ -20,23 +20,13 @@
 
 #include "kernels.h"
 #include "dtype.h"
+#include "lds_load.h"
 #include "side_wide.h"
 
 namespace acc {
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef short v4s __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ v16f mfma_bf16(const v4u& a, const v4u& b, v16f c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-#else
-  return c;  // the host pass never runs this
-#endif
-}
 
 // A workgroup of KS groups of WM x WN waves owns a tile of 32*MB*WM output channels and 32*NB*WN columns of dw, a wave MB x NB
 // blocks of 32 x 32; of every chunk of CK = BK*KS positions each group multiplies its BK.  NS LDS stages.
@@ -56,27 +46,6 @@ template <int WM_, int WN_, int KS_, int MB_, int NB_, int BK_, int NS_, int WPE
   static_assert(BK % 32 == 0, "an even number of steps of 16 positions");
   static_assert(KS >= 2 && NS >= 2, "the epilogue adds the groups' sums");
 };
-
-template <int N> __device__ __forceinline__ void wait_loads() {      // at most N loads of the wave still on their way
-#if defined(__HIP_DEVICE_COMPILE__)
-  static_assert(N < 64, "vmcnt has six bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);  // and every LDS access done
-#endif
-}
-
-// 16 bytes per lane from memory to LDS, lane l's to at + 16 * l.  Written out, because before a transposing LDS read the compiler waits
-// for every such load it knows of, those of later chunks too.  There is no register to wait for: open() below counts them.
-// (One wait state between writing m0 and an LDS load that reads it; nothing else in these kernels uses m0.)
-typedef unsigned srsrc __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void load_lds16(srsrc rs, uint32_t voff, uint32_t at) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(at), "v"(voff), "s"(rs) : "memory");
-#endif
-}
-
-// Which 64-byte piece of a staged row a piece of memory goes to: XORed with this, so that the four rows that sixteen lanes read
-// 32 bytes of each lie on different banks.
-template <int PITCH> __device__ __forceinline__ int row_xor(int row) { return PITCH == 128 ? (row >> 1) & 1 : row & 3; }
 
 // PLAIN: 1x1 filters without stride or padding, row m is pixel m; else a thread follows the pixels of its rows.
 struct Yes { static constexpr bool value = true; };
@@ -151,10 +120,6 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void wgrad_bf16_kernel(WgradGeo
       b_off[i] = (uint32_t)((img * g.h + by[i]) * g.wd + bx[i]) * b_row + (uint32_t)ci0 * 2u;
     }
   }
-  auto descriptor = [](const void* p, size_t bytes) {
-    const uint64_t at = reinterpret_cast<uint64_t>(p);
-    return srsrc{(uint32_t)at, (uint32_t)(at >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
-  };
   const srsrc rs_a = descriptor(g.dy, (size_t)Mrows * g.cout * 2), rs_b = descriptor(g.x, (size_t)g.n_img * g.h * g.wd * g.cin * 2);
   const uint32_t lds0 = (uint32_t)(size_t)lds, lds_w = lds0 + wave * 1024;
   // load u of a chunk (first those of dy), which goes to the stage at `at`
