@@ -45,6 +45,7 @@ struct acc_ctx {
   bool wgrad_overlap = true;           // use s_w when there is one (off: everything on s_c)
   std::vector<hipEvent_t> ev_fork, ev_wdone;   // per conv backward step: its dy is ready / its wgrad is done
   std::vector<char> wgrad_in_flight;   // per step: its wgrad went to s_w in this iteration
+  std::vector<char> as_it_lies;        // per step, under the current plan: its data gradient reads the layer's own filter, not a flipped copy
   std::vector<int> bn_ready_slabs;     // per step: a BN forward step finds its sums in its workspace (slab count)
   ReduceJob pending_reduce{nullptr, nullptr, 0, 0};   // parts of the last conv weight gradient, not added up yet
   hipStream_t pending_stream = nullptr;               // ... and the stream that gradient ran on
@@ -398,6 +399,43 @@ extern "C" int acc_set_calibration(acc_ctx* c, const int* ks, int nk, const doub
 // ---------------------------------------------------------------------------- planning
 namespace {
 
+// strided filters other than 1x1 without padding: the data gradient runs in parts (dgrad_split())
+bool dgrad_in_parts(const acc_layer& l) { return l.stride > 1 && (l.r > 1 || l.s > 1 || l.pad > 0); }
+
+// The data gradient of a convolution step as a convolution of dy, without its tensors and its filter (and, in parts, without the parts).
+ConvGeom dgrad_geom(const Graph& g, const Step& s, int k) {
+  const acc_layer& l = g.layers[s.layer];
+  const Tensor &x = g.tensors[s.x], &dy = g.tensors[s.dy];
+  ConvGeom cg{};
+  cg.dtype = g.dtype;
+  cg.n_img = k; cg.h = dy.h; cg.wd = dy.w; cg.c = l.cout; cg.n_out = l.cin;
+  cg.r = l.r; cg.s = l.s; cg.stride = 1; cg.accumulate = s.dx_accumulate;
+  cg.out_h = x.h; cg.out_w = x.w;
+  if (dgrad_in_parts(l)) return cg;
+  if (l.stride == 1) {
+    cg.p = x.h; cg.q = x.w; cg.pad = l.r - 1 - l.pad; cg.out_stride = 1;
+  } else {  // 1x1, pad 0: dense product on the strided positions, zeros elsewhere
+    cg.p = dy.h; cg.q = dy.w; cg.pad = 0; cg.out_stride = l.stride;
+  }
+  return cg;
+}
+
+// bf16 storage: the steps whose data gradient reads the filter as it lies (a function of the shapes; the tensors of a plan are aligned).  Nobody
+// flips a copy for them.
+std::vector<char> reads_as_it_lies(const acc_ctx* c, int k) {
+  const Graph& g = c->g;
+  std::vector<char> as_it_lies(g.steps.size(), 0);
+  if (g.dtype != ACC_BF16) return as_it_lies;
+  for (size_t j = 0; j < g.steps.size(); ++j) {
+    const Step& s = g.steps[j];
+    if (s.kind != K_CONV_B || s.dx < 0 || dgrad_in_parts(g.layers[s.layer])) continue;
+    ConvGeom cg = dgrad_geom(g, s, k);
+    cg.w_kn = c->d_params16 + g.params[s.layer].offset;
+    as_it_lies[j] = conv_igemm_bf16_takes(cg, (long)cg.n_img * cg.p * cg.q, (long)cg.r * cg.s * cg.c);
+  }
+  return as_it_lies;
+}
+
 int install_plan(acc_ctx* c, Plan&& p, acc_plan_summary* out, double t0) {
   if (c->have_res) {
     if (p.budget > c->res.pool_bytes) return c->fail(ACC_EPOOL, "budget exceeds the pool");
@@ -421,6 +459,8 @@ int install_plan(acc_ctx* c, Plan&& p, acc_plan_summary* out, double t0) {
     for (auto& e : c->ev_window) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
   c->plan = std::move(p);
+  c->as_it_lies.assign(c->g.steps.size(), 0);
+  if (c->have_res) c->as_it_lies = reads_as_it_lies(c, c->plan.k);
   c->obs_start.clear(); c->obs_end.clear();   // observations belong to the plan they ran under
   c->stats = acc_stats{};
   {
@@ -664,22 +704,6 @@ hipError_t flush_pending_reduce(acc_ctx* c) {
   return hipStreamWaitEvent(c->s_c, c->ev_flush, 0);
 }
 
-// bf16 storage: whether the data gradient of a convolution step reads the filter as it lies (a function of the shapes); nobody flips it then.
-bool dgrad_reads_as_it_lies(const acc_ctx* c, const Step& s) {
-  const Graph& g = c->g;
-  if (g.dtype != ACC_BF16) return false;
-  const acc_layer& l = g.layers[s.layer];
-  const Tensor &x = g.tensors[s.x], &dy = g.tensors[s.dy];
-  if (l.stride > 1 && (l.r > 1 || l.s > 1 || l.pad > 0)) return false;      // in parts
-  ConvGeom cg{};
-  cg.dtype = g.dtype;
-  cg.w_kn = c->d_params16 + g.params[s.layer].offset;
-  cg.n_img = c->plan.k; cg.h = dy.h; cg.wd = dy.w; cg.c = l.cout; cg.n_out = l.cin;
-  cg.r = l.r; cg.s = l.s; cg.stride = 1;
-  cg.p = l.stride == 1 ? x.h : dy.h; cg.q = l.stride == 1 ? x.w : dy.w; cg.pad = l.stride == 1 ? l.r - 1 - l.pad : 0;
-  return conv_igemm_bf16_takes(cg, (long)cg.n_img * cg.p * cg.q, (long)l.r * l.s * l.cout);
-}
-
 hipError_t run_step(acc_ctx* c, int j, float lr) {
   const Graph& g = c->g;
   const Step& s = g.steps[j];
@@ -832,7 +856,7 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       wg.workspace = ptr(s.ws2);
       wg.workspace_bytes = c->plan.tbytes[s.ws2];
       if (s.dx < 0) return wgrad(wg, conv_flops, nullptr);   // first layer: no data gradient
-      const bool split = l->stride > 1 && (l->r > 1 || l->s > 1 || l->pad > 0);
+      const bool split = dgrad_in_parts(*l);
       // The weight gradient reads x and dy and writes only its own partial sums and dw, so it
       // may run beside the steps that follow: on the weight-gradient stream if there is one
       // (not while single kernels are being timed), joined kWgradLag conv steps later.
@@ -859,11 +883,11 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
       }
       // the flipped, transposed filter: written by the previous conv backward step's launch,
       // unless this is the first one
-      const bool as_it_lies = dgrad_reads_as_it_lies(c, s);
+      const bool as_it_lies = c->as_it_lies[j];
       if (s.flips_itself && !as_it_lies && (e = filter_flip_transpose(wk, ptr(s.ws), l->cout, l->cin, l->r, l->s, dt, st)) != hipSuccess)
         return e;
-      ConvGeom cg{};
-      if (s.flip_for >= 0 && !dgrad_reads_as_it_lies(c, g.steps[s.flip_for])) {   // ... and the next one's rides on this step's launch
+      ConvGeom cg = dgrad_geom(g, s, k);
+      if (s.flip_for >= 0 && !c->as_it_lies[s.flip_for]) {   // ... and the next one's rides on this step's launch
         const Step& nx = g.steps[s.flip_for];
         const acc_layer& nl = g.layers[nx.layer];
         const float* nw = c->d_params + g.params[nx.layer].offset;
@@ -871,12 +895,9 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
         cg.flip.wt = ptr(nx.ws);
         cg.flip.cout = nl.cout; cg.flip.cin = nl.cin; cg.flip.r = nl.r; cg.flip.s = nl.s;
       }
-      cg.in = ptr(s.dy); cg.out = ptr(s.dx); cg.dtype = dt;
+      cg.in = ptr(s.dy); cg.out = ptr(s.dx);
       if (as_it_lies) cg.w_kn = wk;
       else cg.w = ptr(s.ws);
-      cg.n_img = k; cg.h = ho; cg.wd = wo; cg.c = l->cout; cg.n_out = l->cin;
-      cg.r = l->r; cg.s = l->s; cg.stride = 1; cg.accumulate = s.dx_accumulate;
-      cg.out_h = h; cg.out_w = wd;
       if (split) {
         // strided and larger than 1x1: one stride-1 convolution per residue class of the dx
         // position, each with its own sub-filter
@@ -895,7 +916,6 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
         return igemm(cg, conv_flops);
       }
       if (l->stride == 1) {
-        cg.p = h; cg.q = wd; cg.pad = l->r - 1 - l->pad; cg.out_stride = 1;
         // the batch norm whose ReLU output was this convolution's input gets its backward sums
         // (and the masked gradient) from this launch, unless there are more 32-row blocks than
         // its finishing pass adds up
@@ -911,12 +931,9 @@ hipError_t run_step(acc_ctx* c, int j, float lr) {
             cg.bnb = BnBackwardSums{ptr(bb.x), ptr(s.x), stat, stat + l->cin, (float*)ptr(s.bnb), (int)stride};
           }
         }
-      } else {  // 1x1, pad 0: dense product on the strided positions, zeros elsewhere
-        cg.p = ho; cg.q = wo; cg.pad = 0; cg.out_stride = l->stride;
-        if (!s.dx_accumulate) {
-          e = fill_zero(ptr(s.dx), (size_t)k * h * wd * l->cin * es / 4, st);   // whole words: cin is even
-          if (e != hipSuccess) return e;
-        }
+      } else if (!s.dx_accumulate) {           // the positions between the strided ones
+        e = fill_zero(ptr(s.dx), (size_t)k * h * wd * l->cin * es / 4, st);   // whole words: cin is even
+        if (e != hipSuccess) return e;
       }
       return igemm(cg, conv_flops);
     }

@@ -47,7 +47,8 @@ int main(int argc, char** argv) {
   for (int i = 0; i < 4; ++i) st[i] = stub_make_stream(i);
   acc_resources res{pool, budget, host, arena, st[0], st[1], st[2], st[3]};
   acc_ctx* c = nullptr;
-  if (acc_create(layers.data(), (int)layers.size(), hdr[1], hdr[2], hdr[3], ACC_F32, &res, &c) != ACC_OK) return fail("create", nullptr);
+  const int dtype = scenario.compare(0, 4, "bf16") == 0 ? ACC_BF16 : ACC_F32;
+  if (acc_create(layers.data(), (int)layers.size(), hdr[1], hdr[2], hdr[3], dtype, &res, &c) != ACC_OK) return fail("create", nullptr);
   std::vector<int32_t> labels(512, 1);
   const float* images = (const float*)(uintptr_t)0x700000000000ull;   // never read by the stand-in
   float loss = 0.f;
@@ -130,6 +131,20 @@ int main(int argc, char** argv) {
     for (int k : {16, 96}) {
       if (acc_plan_swaps(c, k, budget, ACC_PLAN_DYNAMIC, &s) != ACC_OK) { rc = fail("plan", c); break; }
       steps(2, "step");
+    }
+  } else if (scenario == "bf16_filters") {
+    // data gradients that read the layer's own filter and others that read a flipped copy, in one network: whoever flips,
+    // and whoever reads, has to go by the same decision, under every plan
+    for (int k : {1, 16, 37}) {
+      if (acc_plan_swaps(c, k, budget, ACC_PLAN_DYNAMIC, &s) != ACC_OK) { rc = fail("plan", c); break; }
+      stub_set_static(s.static_bytes);
+      const long l0 = stub_counters().launches;
+      steps(2, "step");
+      acc_set_wgrad_overlap(c, 0);
+      steps(1, "serial step");
+      acc_set_wgrad_overlap(c, 1);
+      stub_new_epoch();
+      printf("k=%d: %ld launches\n", k, stub_counters().launches - l0);
     }
   } else if (scenario == "selftest") {
     // the stand-in must see planted mistakes: a wait on an event nobody recorded, a wait on last

@@ -31,6 +31,8 @@ char* g_pool = nullptr; size_t g_pool_bytes = 0;
 char* g_arena = nullptr; size_t g_arena_bytes = 0;
 int g_epoch = 1;
 bool g_capture = false;
+char* g_dynamic = nullptr;                // where the pool's planned part starts: filters that lie there are copies
+std::set<const void*> g_flipped;          // copies that a launch has written and no data gradient has read yet
 
 bool in_pool(const void* p, size_t bytes) {
   const char* q = static_cast<const char*>(p);
@@ -66,7 +68,12 @@ void stub_set_regions(void* pool, size_t pool_bytes, void* arena, size_t arena_b
   g_pool = static_cast<char*>(pool); g_pool_bytes = pool_bytes;
   g_arena = static_cast<char*>(arena); g_arena_bytes = arena_bytes;
 }
-void stub_new_epoch() { ++g_epoch; }
+void stub_set_static(size_t bytes) { g_dynamic = g_pool + bytes; }
+void stub_new_epoch() {
+  ++g_epoch;
+  if (g_dynamic && !g_flipped.empty()) { g.filters_for_nobody += (long)g_flipped.size(); complain("a flipped filter that nobody has read"); }
+  g_flipped.clear();
+}
 hipStream_t stub_make_stream(int id) { return new stub_stream{id, 0}; }
 void stub_free_stream(hipStream_t s) { delete s; }
 long stub_live_events() { return (long)g_events.size(); }
@@ -186,7 +193,11 @@ static void probe_events(LaunchProbe* probe, hipStream_t st, int variant) {
   if (probe->after) (void)hipEventRecord(probe->after, st);
 }
 
-bool conv_igemm_bf16_takes(const ConvGeom&, long, long) { return false; }
+// A line that moves with everything the choice of kernel may depend on: plan and launch have to ask about the same convolution.
+bool conv_igemm_bf16_takes(const ConvGeom& g_, long M, long K) {
+  if (g_.dtype != DT_BF16 || !g_.w_kn || g_.w || g_.bnb.sums || g_.stats) return false;
+  return (M + 3 * K + 5 * g_.n_out + 7 * g_.pad + 11 * g_.h + 13 * g_.wd + 17 * g_.stride + 19 * g_.out_stride + 23 * g_.out_h) % 3 != 0;
+}
 hipError_t conv_igemm_bf16(const ConvGeom&, int, int, hipStream_t, const LaunchProbe*) { return hipErrorInvalidValue; }
 const char* conv_variant_name(int v) { return v == V_WGRAD_DIRECT ? "wgrad_kernel<stub>" : "igemm_kernel<stub>"; }
 
@@ -196,7 +207,12 @@ bool conv_igemm_rows_takes(const ConvGeom& g_, long M, long K) {      // a line 
 static const void* g_transposed = nullptr;      // the filter that a weight gradient's launch has written last, until it is read
 hipError_t conv_igemm(const ConvGeom& g_, hipStream_t st, LaunchProbe* probe) {
   dev(g_.in, "conv_igemm: input"); dev(g_.w, "conv_igemm: filter"); dev(g_.w_kn, "conv_igemm: filter [k][n]"); dev(g_.out, "conv_igemm: output");
-  const void* reads = g_.w_kn && conv_igemm_rows_takes(g_, (long)g_.n_img * g_.p * g_.q, (long)g_.r * g_.s * g_.c) ? g_.w_kn : g_.w;
+  const long M = (long)g_.n_img * g_.p * g_.q, K = (long)g_.r * g_.s * g_.c;
+  const void* reads = g_.w_kn && (conv_igemm_rows_takes(g_, M, K) || conv_igemm_bf16_takes(g_, M, K)) ? g_.w_kn : g_.w;
+  if (reads && !g_.split && g_dynamic && static_cast<const char*>(reads) >= g_dynamic && !g_flipped.erase(reads)) {
+    ++g.filters_missing; complain("conv_igemm: reads a flipped filter that nobody has written");
+  }
+  if (g_.flip.wt) g_flipped.insert(g_.flip.wt);
   if (!reads && !g_.split) { ++g.filters_missing; complain("conv_igemm: no filter"); }
   if (g_transposed && reads != g_transposed) { ++g.filters_for_nobody; complain("conv_igemm: does not read the filter that was transposed for it"); }
   g_transposed = nullptr;
@@ -223,6 +239,7 @@ hipError_t conv_wgrad(const WgradGeom& g_, hipStream_t st, LaunchProbe* probe, R
   const size_t need = wgrad_workspace_least(g_.n_img, g_.p, g_.q, g_.cin, g_.cout, g_.r, g_.s, g_.dtype);
   if (need && (!g_.workspace || g_.workspace_bytes < need || !in_pool(g_.workspace, g_.workspace_bytes))) { ++g.pointers_outside_pool; complain("conv_wgrad: workspace runs past the pool"); }
   g_transposed = g_.flip_wt;
+  if (g_.flip_wt) g_flipped.insert(g_.flip_wt);
   if (deferred) *deferred = ReduceJob{nullptr, nullptr, 0, 0};
   if (need) {
     const ReduceJob job{g_.workspace, g_.dw, (size_t)g_.cout * g_.r * g_.s * g_.cin, (int)(need / ((size_t)g_.cout * g_.r * g_.s * g_.cin * 4))};
@@ -238,7 +255,7 @@ hipError_t reduce_parts(const ReduceJob& job, hipStream_t st) {
   return hipSuccess;
 }
 hipError_t filter_flip_transpose(const void* w, void* wt, int, int, int, int, int, hipStream_t st) {
-  dev(w, "flip: source"); dev(wt, "flip: target"); stub_count_launch("flip", st); return hipSuccess;
+  dev(w, "flip: source"); dev(wt, "flip: target"); g_flipped.insert(wt); stub_count_launch("flip", st); return hipSuccess;
 }
 hipError_t filter_gather_transpose(const void* w, void* wt, int, int, int, int, int, const DgradPart&, int, hipStream_t st) {
   dev(w, "gather: source"); dev(wt, "gather: target"); stub_count_launch("gather", st); return hipSuccess;

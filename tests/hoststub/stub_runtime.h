@@ -16,6 +16,7 @@ struct StubCounters {
 };
 StubCounters& stub_counters();
 void stub_set_regions(void* pool, size_t pool_bytes, void* arena, size_t arena_bytes);
+void stub_set_static(size_t bytes);   // of the pool: from there on filters are copies, and somebody must have written them
 void stub_new_epoch();            // call before every iteration: waits must find records of this epoch
 hipStream_t stub_make_stream(int id);
 void stub_free_stream(hipStream_t s);

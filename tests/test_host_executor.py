@@ -95,3 +95,11 @@ def test_filters_are_transposed_for_data_gradients_that_read_them(binaries, net)
     rc, log = run(built["limit"], spec_file(out, getattr(S, net)()), "small_large")
     assert rc == 0 and "RESULT: clean" in log and "ERROR" not in log, log[-3000:]
     assert "filters_for_nobody 0 filters_missing 0" in log
+
+
+@pytest.mark.parametrize("net", ["resnet50", "resnet34", "vgg16"])
+def test_flipped_filters_of_bf16_iterations_are_written_for_those_that_read_them(binaries, net):
+    built, out = binaries
+    rc, log = run(built["limit"], spec_file(out, getattr(S, net)()), "bf16_filters")
+    assert rc == 0 and "RESULT: clean" in log and "ERROR" not in log, log[-3000:]
+    assert "filters_for_nobody 0 filters_missing 0" in log
