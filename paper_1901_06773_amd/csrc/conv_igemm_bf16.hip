@@ -502,7 +502,7 @@ __device__ __forceinline__ void tile(const ConvGeom& g, int M, int K, int m0, in
     }
   }
 #else
-  (void)&mfma_bf16; (void)&decode_row; (void)&out_row_offset; (void)&load_lds16;
+  (void)&decode_row; (void)&out_row_offset;
 #endif
 }
 

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void wgrad_bf16_kernel(WgradGeo
       }
   }
 #else
-  (void)&mfma_bf16; (void)&row_xor<128>; (void)&load_lds16; (void)Yes::value; (void)No::value;
+  (void)Yes::value; (void)No::value;
 #endif
 }
 
