@@ -137,7 +137,8 @@ typedef struct {
   uint64_t touched_pool_bytes; /* ACC_DEBUG_POISON: bytes of the pool written at least once
                                during the iteration, static part included; else 0         */
   int32_t peak_is_measured; /* 1 if peak_pool_bytes comes from the poison scan            */
-  int32_t reserved;
+  int32_t copies_in_order;  /* last train_step: 1 if its offloads and prefetches ran in the
+                               compute stream (see acc_instr)                             */
   double host_wait_ms;      /* of host_issue_ms: time the host stood still because it was a full
                                window of steps or copies ahead of the GPU (it issues no further
                                ahead than that); host_issue_ms - host_wait_ms is what issuing
@@ -243,7 +244,11 @@ int acc_get_step_io(const acc_ctx* ctx, int step, int32_t* reads, int max_reads,
  * (swap-in stream).  arg: tensor id, or step index for op 1.  wait_*: the instruction first
  * waits for the event recorded after that compute step / after the offload resp. prefetch
  * (or input load) with that sequence number; -1 = none.  seq: own sequence number among
- * offloads resp. among prefetches and input loads.  record: op 1 records its step event. */
+ * offloads resp. among prefetches and input loads.  record: op 1 records its step event.
+ * A plan that swaps at least eight maps, of at most 1.25 MiB in all, is bound by the host
+ * that issues it: its offloads and prefetches run in the compute stream, in this order and
+ * without events (every wait is for something earlier in the list); input loads stay on the
+ * swap-in stream.  acc_stats.copies_in_order says so. */
 typedef struct {
   int32_t op, arg, wait_step, wait_d2h, wait_h2d, seq, record, reserved;
 } acc_instr;
@@ -252,7 +257,9 @@ int acc_get_instr(const acc_ctx* ctx, int index, acc_instr* out);
 
 /* One entry per instruction of the current plan, in issue order: when it runs on its own
  * stream, in seconds after the start of the iteration.  which = 0: as Algorithm 1's
- * simulation predicts with the current cost model; which = 1: as observed in the last
+ * simulation predicts with the current cost model, copies beside the kernels (also for plans
+ * whose copies run in the compute stream: the simulation knows no cost of issuing them, which
+ * is what decides there); which = 1: as observed in the last
  * train_step that ran with profiling level 1 or 3 (events around every step and copy, read
  * against the first event of the iteration on the compute stream; input loads are not timed
  * and report -1 / -1).  Returns the number of entries, ACC_EINVAL if max_entries is too small,
@@ -267,8 +274,9 @@ int acc_get_timeline(acc_ctx* ctx, int which, acc_timeline_entry* out, int max_e
 /* ---- execution (runtime memory manager, Sec. 5; the 2N steps of Sec. 3.1) ------------- */
 /* One iteration as Sec. 2 describes its last stage and Sec. 5 its runtime: the 2N steps in
  * order on the compute stream, offloads (then release) on the swap-out stream, allocate and
- * prefetch on the swap-in stream, the input batch being the first layer's prefetch
- * (Algorithm 1, j = 1); then the weight update.
+ * prefetch on the swap-in stream (both in the compute stream where there is little to swap:
+ * acc_instr), the input batch being the first layer's prefetch (Algorithm 1, j = 1), on the
+ * swap-in stream always; then the weight update.
  * One forward / backward / SGD step at the planned minibatch.  images: fp32 NCHW,
  * pinned host (ACC_LOC_HOST) or device (ACC_LOC_DEVICE); labels: int32, host.  Blocks
  * until the step is done; *loss_out is the mean cross-entropy at the pre-update weights. */
@@ -281,7 +289,7 @@ int acc_get_stats(acc_ctx* ctx, acc_stats* out);
  * ACC_DEBUG_POISON: before every iteration the dynamic part of the pool and the used part of
  * the host arena are filled with a NaN pattern; every block is filled with a second NaN
  * pattern at the moment the plan releases it (after the last step that uses its tensor, on
- * the compute stream; after the offload copy of a swapped map, on the swap-out stream).  A
+ * the compute stream; after the offload copy of a swapped map, on the stream of that copy).  A
  * kernel or copy that runs before the data it needs has arrived, or after its block has been
  * given away, then reads NaNs, and the loss or some gradient is not finite; a correct plan
  * gives the same bits as without the mode.  After the iteration the pool is scanned:

@@ -98,6 +98,7 @@ struct acc_ctx {
   struct Block { size_t off, bytes; };
   std::vector<std::vector<Block>> poison_after_step;   // per step: blocks released once it has run
   std::vector<Block> poison_after_d2h;                 // per offload: the block its map leaves behind
+  bool copies_in_order = false;                        // the plan's offloads and prefetches run in the compute stream
 
   int fail(int code, const std::string& what) { err = what; return code; }
   int hipfail(hipError_t e, const char* what) {
@@ -137,12 +138,19 @@ struct acc_ctx {
 // stream: it waits on an event of older work first.  The windows are far deeper than any
 // dependency between the streams (the pool holds a few dozen maps at a time).
 constexpr int kStepWindow = 32, kWindows = 3, kCopyWindow = 64;
-// Iterations that swap up to this many bytes each way are bound by the host that issues them: a copy on a stream of its own costs it two
-// event records and two waits, 13 us with the copy, and hides a copy of a few microseconds.  Their copies go to the compute stream.  One
-// bottleneck block, all nine maps swapped, fp32 / bf16, us per iteration with the copies on their own streams -> in the compute stream:
-// 256 KB 439 -> 281 / 469 -> 340, 512 KB 457 -> 381 / 475 -> 431, 1 MB 467 -> 400 / 484 -> 450, 1.5 MB 480 -> 423 / 486 -> 471, 3 MB
-// 511 -> 479 / -, from 4 MB on copies beside the kernels are the faster way (541 against 547).
+// Plans that swap eight maps or more, of at most 1.25 MiB in all, have their copies in the compute stream.  A copy on a stream of its own costs
+// the host two event records and two waits, about 20 us a map with the copies, and hides behind the kernels; in the compute stream
+// it costs the GPU 10 to 20 us each way.  So many maps are bound by the host that issues them and few are not: a bottleneck block that
+// swaps two maps of 64 KiB took 258 us per iteration with streams of their own and 296 in the compute stream, one that swaps all nine 493 and 386.
+// Measured both ways on 1019 plans of at most 1.25 MiB (bottleneck blocks of 12x12 to 56x56, ResNet-18 and -50 at 64x64 and 224x224, 1 to
+// 64 images, fp32 and bf16: the smallest, the largest, the first and random sets of maps; iterations of 0.2 to 10 ms): eight maps or more
+// are 1.07 times as fast in the compute stream in the middle (0.98 to 1.64; 2 of 172 plans more than 1 % slower), four to seven 1.06 (0.88
+// to 1.53; 39 of 477), fewer 1.01 (0.86 to 1.41; 66 of 370).  Eight maps and more of 1.25 to 3 MiB gain as much (37 plans, 1.00 to
+// 1.61), a few large ones lose; from 4 MB on a bottleneck block's copies beside the kernels are the faster way.  Nothing depends on the
+// choice but the time.
 constexpr size_t kOneStreamBytes = 5u << 18;
+constexpr int kOneStreamMaps = 8;
+bool copies_in_compute_stream(const Plan& p) { return p.n_swapped >= kOneStreamMaps && p.bytes_swapped <= kOneStreamBytes; }
 // Event timing of steps and copies is refused for plans that swap more than this per
 // iteration: such runs (ResNet-152, minibatch 224 and 256, all maps swapped, 36-41 GiB each
 // way) ended in a crash of the process at its next HIP call, cause unknown; the same
@@ -459,6 +467,7 @@ int install_plan(acc_ctx* c, Plan&& p, acc_plan_summary* out, double t0) {
     for (auto& e : c->ev_window) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
   c->plan = std::move(p);
+  c->copies_in_order = copies_in_compute_stream(c->plan);
   c->as_it_lies.assign(c->g.steps.size(), 0);
   if (c->have_res) c->as_it_lies = reads_as_it_lies(c, c->plan.k);
   c->obs_start.clear(); c->obs_end.clear();   // observations belong to the plan they ran under
@@ -1025,10 +1034,11 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
     c->drop_graph();
     (void)hipGetLastError();
   };
-  // Few small maps: the copies in the compute stream, in the order of the list (whose every wait is for something
-  // before it), without an event for each.
-  const bool one_stream = P.n_swapped > 0 && P.host_bytes <= kOneStreamBytes && !c->profiling && !c->calibrating;
+  // Little to swap: offloads and prefetches in the compute stream, in the order of the list (whose every wait is for something before
+  // it), without an event for each.  The input comes on the swap-in stream either way: a caller may have prepared it there.
+  const bool one_stream = c->copies_in_order;
   const hipStream_t s_out = one_stream ? c->s_c : c->s_o, s_in = one_stream ? c->s_c : c->s_i;
+  int load_issued = -1;      // one_stream: the last input load that the compute stream does not wait for yet
   int n_compute = 0;
   double t_waited = 0.0;     // host time spent blocked on the flow-control windows (the GPU is behind, not the host)
   auto window_wait = [&](hipEvent_t e) {
@@ -1052,20 +1062,26 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
             hipError_t e = fill_pseudo_input(c, (float*)dst, (size_t)P.k * g.in_c * g.in_h * g.in_w);
             if (e != hipSuccess) return c->hipfail(e, "fill_pseudo_input");
           } else {
-            hipError_t e = fill_zero((float*)dst, (size_t)P.k, s_in);
+            hipError_t e = fill_zero((float*)dst, (size_t)P.k, c->s_i);
             if (e != hipSuccess) return c->hipfail(e, "fill_zero(labels)");
           }
         } else if (in.arg == g.t_stage) {
           const size_t bytes = (size_t)P.k * g.in_c * g.in_h * g.in_w * sizeof(float);
           HIPCHK(c, hipMemcpyAsync(dst, images, bytes,
-                                   images_loc == ACC_LOC_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s_in));
+                                   images_loc == ACC_LOC_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, c->s_i));
         } else {
-          HIPCHK(c, hipMemcpyAsync(dst, labels, (size_t)P.k * sizeof(int32_t), hipMemcpyHostToDevice, s_in));
+          HIPCHK(c, hipMemcpyAsync(dst, labels, (size_t)P.k * sizeof(int32_t), hipMemcpyHostToDevice, c->s_i));
         }
-        if (!one_stream) HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
+        if (one_stream) load_issued = in.seq;
+        else HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
         break;
       }
       case I_COMPUTE: {
+        if (load_issued >= 0) {
+          HIPCHK(c, hipEventRecord(c->ev_h2d[load_issued], c->s_i));
+          HIPCHK(c, hipStreamWaitEvent(c->s_c, c->ev_h2d[load_issued], 0));
+          load_issued = -1;
+        }
         if (graph_mode) {
           if (!graph_started) {
             graph_started = true;
@@ -1133,10 +1149,10 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
       }
       case I_OFFLOAD: {
         if (!one_stream) HIPCHK(c, hipStreamWaitEvent(c->s_o, c->ev_step[in.wait_step], 0));
-        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_a[in.seq], c->s_o));
+        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_a[in.seq], s_out));
         HIPCHK(c, hipMemcpyAsync((char*)c->res.host + P.host_off[in.arg], c->dyn + P.off1[in.arg], P.tbytes[in.arg],
                                  hipMemcpyDeviceToHost, s_out));
-        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_b[in.seq], c->s_o));
+        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_b[in.seq], s_out));
         if (poison) {
           const acc_ctx::Block& b = c->poison_after_d2h[in.seq];
           const hipError_t ep = fill_words(c->dyn + b.off, b.bytes, kReleased, s_out);
@@ -1149,10 +1165,10 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
       case I_PREFETCH: {
         if (!one_stream && in.wait_step >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_i, c->ev_step[in.wait_step], 0));
         if (!one_stream && in.wait_d2h >= 0) HIPCHK(c, hipStreamWaitEvent(c->s_i, c->ev_d2h[in.wait_d2h], 0));
-        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_a[P.n_d2h + in.seq], c->s_i));
+        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_a[P.n_d2h + in.seq], s_in));
         HIPCHK(c, hipMemcpyAsync(c->dyn + P.off2[in.arg], (char*)c->res.host + P.host_off[in.arg], P.tbytes[in.arg],
                                  hipMemcpyHostToDevice, s_in));
-        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_b[P.n_d2h + in.seq], c->s_i));
+        if (c->profiling) HIPCHK(c, hipEventRecord(c->prof_copy_b[P.n_d2h + in.seq], s_in));
         if (!one_stream) HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
         c->cur_off[in.arg] = P.off2[in.arg];
         bytes_in += P.tbytes[in.arg];
@@ -1209,6 +1225,7 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
     if (c->stats.peak_pool_bytes > P.budget)
       return c->fail(ACC_EPOOL, "the iteration wrote beyond the budget (found by the poison scan)");
   }
+  c->stats.copies_in_order = one_stream ? 1 : 0;
   c->stats.bytes_out = bytes_out;
   c->stats.bytes_in = bytes_in;
   c->stats.steps_run += 1;

@@ -94,9 +94,11 @@ def timeline_summary(tl):
 def dependency_violations(ctx, tl, slack=20e-6):
     """Instructions whose observed start precedes the observed end of something the plan makes
     them wait for (the step, offload or prefetch named by wait_step / wait_d2h / wait_h2d), or
-    of the previous instruction on their own stream.  Empty when the streams and events of the
+    of the previous instruction on their own stream (all but the input loads on one, where the
+    copies run in the compute stream).  Empty when the streams and events of the
     executor order the work as planned.  slack: resolution of the event clock."""
     ins = ctx.instructions()
+    in_order = ctx.stats()["copies_in_order"]
     end_step, end_d2h, end_h2d = {}, {}, {}
     last_on_stream = {}
     bad = []
@@ -110,7 +112,7 @@ def dependency_violations(ctx, tl, slack=20e-6):
             deps.append(("offload", a["wait_d2h"], end_d2h[a["wait_d2h"]]))
         if a["wait_h2d"] >= 0 and a["wait_h2d"] in end_h2d:
             deps.append(("prefetch", a["wait_h2d"], end_h2d[a["wait_h2d"]]))
-        stream = {OP_COMPUTE: "c", OP_OFFLOAD: "o", OP_PREFETCH: "i", OP_LOAD: "i"}[a["op"]]
+        stream = "c" if in_order and a["op"] != OP_LOAD else {OP_COMPUTE: "c", OP_OFFLOAD: "o", OP_PREFETCH: "i", OP_LOAD: "i"}[a["op"]]
         if stream in last_on_stream:
             deps.append(("stream", stream, last_on_stream[stream]))
         for what, which, t in deps:

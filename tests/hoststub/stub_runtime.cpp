@@ -134,7 +134,7 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
 }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t s) {
   if (!s) { ++g.null_streams; complain("hipMemcpyAsync on the null stream"); }
-  else s->ops++;
+  else { s->ops++; ++g.copies_on[s->id & 3]; }
   ++g.copies;
   g.copy_bytes += bytes;
   const bool dst_dev = kind == hipMemcpyHostToDevice || kind == hipMemcpyDeviceToDevice;

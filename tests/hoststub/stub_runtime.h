@@ -7,6 +7,7 @@ struct StubCounters {
   long records = 0, stream_waits = 0, host_waits = 0, elapsed_reads = 0;
   long copies = 0, launches = 0, graph_launches = 0;
   unsigned long long copy_bytes = 0;
+  long copies_on[4] = {0, 0, 0, 0};               // by the stream's id
   // what must stay zero
   long dead_event_uses = 0, waits_on_unrecorded = 0, waits_on_stale = 0, elapsed_on_untimed = 0;
   long copies_out_of_range = 0, pointers_outside_pool = 0, null_streams = 0, sync_in_capture = 0;

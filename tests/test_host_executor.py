@@ -97,6 +97,12 @@ def test_filters_are_transposed_for_data_gradients_that_read_them(binaries, net)
     assert "filters_for_nobody 0 filters_missing 0" in log
 
 
+def test_copies_of_small_plans_run_in_the_compute_stream_timed_or_not(binaries):
+    built, out = binaries
+    rc, log = run(built["limit"], spec_file(out, S.bottleneck_unit()), "small_swaps")
+    assert rc == 0 and "RESULT: clean" in log and "ERROR" not in log and "WRONG" not in log, log[-3000:]
+
+
 @pytest.mark.parametrize("net", ["resnet50", "resnet34", "vgg16"])
 def test_flipped_filters_of_bf16_iterations_are_written_for_those_that_read_them(binaries, net):
     built, out = binaries
