@@ -7,9 +7,13 @@ namespace acc {
 constexpr int kBnThreads = 256;              // threads of a workgroup
 constexpr int kBnMaxSlabs = 1024;            // largest number of row slabs that a statistics pass adds up
 // Workgroups of a pass that sums, over all column slices: three per compute unit, all of them at once, and a quarter fewer partial sums for the
-// finishing kernel than four.  768 against 1024, 1/512 in brackets, over 36 shapes of each storage type, forward / backward / storing the masked
-// gradient: bf16 1.01 / 1.01 / 1.01 times as fast (0.99 / 0.99 / 0.95), 4 to 16 million elements 1.03 / 1.02 / 1.01 (1.05 / 1.03 / 0.99), fp32
-// 1.01 / 1.01 / 1.01 (1.01 / 0.99 / 0.98), no shape more than 3 % slower; 512 channels, 256 images of 28x28 bf16, storing, 276.5 -> 268 us (293).
+// finishing kernel than four (1024).  768 against 1024 on 38 shapes of each storage type that it changes (forward, backward, storing the masked
+// gradient; replayed from a graph, equal shapes differ by 0.3 %), by how many would give every thread its rows:
+//   up to 896 (a fifth trip for what are four): sums alone 1.03 times as fast (0.98 to 1.09), sums that store 0.99 (0.93 to 1.05; 1568
+//     rows of 2048 fp32 26.0 -> 27.8 us, 25088 of 256 bf16 28.1 -> 29.4): those stay as wanted;
+//   up to 2048: 1.02 (0.97 to 1.07);
+//   more: fp32 1.01 (0.99 to 1.05), bf16 storing 1.02 (1.00 to 1.04; 200704 rows of 512 276 -> 268 us), but bf16 sums alone 0.99 (0.95
+//     to 1.01; 12544 rows of 2048 67.8 -> 70.5 us, 135424 of 100 30.3 -> 31.7): those take 1024.
 constexpr int kBnWorkgroups = 768;
 constexpr int kBnRowsPerThread = 4;          // rows a thread of the reduction sums at least (else fewer slabs)
 constexpr int kSliceMaxSlabs = 512;          // finish and apply in one launch up to here; beyond, the separate finishing launch
@@ -60,7 +64,10 @@ inline SumShape bn_sum_shape(long rows, int c, int v, int elem_size, bool backwa
   s.rpi = kBnThreads / s.tpr;
   // at least kBnRowsPerThread rows per thread and slab (the partials the finishing kernel has to read grow with slabs * c)
   long n = slabs_wanted(rows, s.rpi);
-  const long cap = kBnWorkgroups / s.col_slices > 0 ? kBnWorkgroups / s.col_slices : 1;
+  const long wanted = n * s.col_slices;
+  const bool four = stores ? wanted <= kBnWorkgroups / 6 * 7 : elem_size == 2 && wanted > 2 * kBnMaxSlabs;
+  const int most = four ? kBnMaxSlabs : kBnWorkgroups;
+  const long cap = most / s.col_slices > 0 ? most / s.col_slices : 1;
   if (n > cap) n = cap;
   // few enough for the slice kernels: then as few as one batch of their partial loads
   // (128 slabs of doubles), as long as that leaves a workgroup per compute unit

@@ -55,6 +55,17 @@ def test_slices_of_like_width_where_gradients_are_stored(shapes, rows, c, es, tp
     assert shapes([(rows, c, 4, es, 1, 0)])[0][0] == 64
 
 
+# rows, channels, channels per thread, bytes of a value, backward (2: storing the masked gradient), slabs
+@pytest.mark.parametrize("rows,c,v,es,back,slabs", [
+    (1568, 2048, 4, 4, 2, 98), (1568, 2048, 4, 4, 1, 96), (25088, 256, 8, 2, 2, 784), (25088, 256, 8, 2, 1, 768), (25088, 256, 8, 2, 0, 768),
+    (28672, 256, 8, 2, 2, 896), (28673, 256, 8, 2, 2, 768), (65536, 256, 8, 2, 0, 768), (65537, 256, 8, 2, 0, 1024), (65537, 256, 8, 2, 1, 1024),
+    (200704, 512, 8, 2, 2, 768), (200704, 512, 8, 2, 0, 1024), (12544, 2048, 4, 2, 0, 128), (12544, 2048, 4, 2, 2, 96),
+    (200704, 64, 4, 4, 0, 768), (200704, 64, 4, 4, 1, 768), (200704, 64, 4, 4, 2, 768),
+])
+def test_three_or_four_workgroups_per_compute_unit(shapes, rows, c, v, es, back, slabs):
+    assert shapes([(rows, c, v, es, back > 0, back == 2)])[0][3] == slabs
+
+
 # alone / in an iteration
 @pytest.mark.parametrize("rows,c,es,alone,step", [
     (8036, 1024, 4, True, False), (32144, 512, 4, True, False), (128576, 256, 4, True, True), (25088, 1024, 4, True, True),
