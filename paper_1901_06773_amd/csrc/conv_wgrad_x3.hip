@@ -176,7 +176,14 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
       ch_off[b] = m_lim[b] ? ch_of[b] : OUTSIDE;
     }
   }
-  auto fill = [&]() {              // the offsets of the next 64 positions
+  // The offsets of the next 64 positions.  A lane reads what other lanes of its wave store here: LDS accesses of a wave happen in the order in
+  // which they are issued, and the fences keep the compiler from issuing a read on the wrong side of the stores (they cost no instruction).
+  auto same_order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto fill = [&]() {
+    same_order();                  // the reads of the 64 before
 #pragma unroll
     for (int b = 0; b < NTB; ++b) {
       const bool in = ((unsigned)ty[b] < (unsigned)gh[b]) & ((unsigned)tx[b] < (unsigned)gwd[b]) & (tm < Mrows);
@@ -190,6 +197,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_x3_kernel(WgradGeom g, int Mrows
       toff[b] += (uint32_t)((d_img * gh[b] + d_p * gs[b]) * gwd[b] + d_q * gs[b]) * row_b[b] + (wx ? wrap_q[b] : 0u) + (wy ? wrap_p[b] : 0u);
     }
     tm += 64;
+    same_order();                  // the reads of these
   };
   constexpr int NR = BPW == 2 ? 1 : 2;                   // register sets of loads in flight
   struct Regs { x3_v4u v[BPW][4]; } R0, R1_;
