@@ -247,8 +247,9 @@ int acc_get_step_io(const acc_ctx* ctx, int step, int32_t* reads, int max_reads,
  * offloads resp. among prefetches and input loads.  record: op 1 records its step event.
  * A plan that swaps at least eight maps, of at most 1.25 MiB in all, is bound by the host
  * that issues it: its offloads and prefetches run in the compute stream, in this order and
- * without events (every wait is for something earlier in the list); input loads stay on the
- * swap-in stream.  acc_stats.copies_in_order says so. */
+ * without events (every wait is for something earlier in the list).  So do its input loads
+ * where the swap-in stream is idle; where the caller has queued work there they come behind
+ * it, on that stream.  acc_stats.copies_in_order says so. */
 typedef struct {
   int32_t op, arg, wait_step, wait_d2h, wait_h2d, seq, record, reserved;
 } acc_instr;
@@ -275,8 +276,8 @@ int acc_get_timeline(acc_ctx* ctx, int which, acc_timeline_entry* out, int max_e
 /* One iteration as Sec. 2 describes its last stage and Sec. 5 its runtime: the 2N steps in
  * order on the compute stream, offloads (then release) on the swap-out stream, allocate and
  * prefetch on the swap-in stream (both in the compute stream where there is little to swap:
- * acc_instr), the input batch being the first layer's prefetch (Algorithm 1, j = 1), on the
- * swap-in stream always; then the weight update.
+ * acc_instr), the input batch being the first layer's prefetch (Algorithm 1, j = 1), behind
+ * whatever the caller has queued on the swap-in stream; then the weight update.
  * One forward / backward / SGD step at the planned minibatch.  images: fp32 NCHW,
  * pinned host (ACC_LOC_HOST) or device (ACC_LOC_DEVICE); labels: int32, host.  Blocks
  * until the step is done; *loss_out is the mean cross-entropy at the pre-update weights. */

@@ -9,10 +9,10 @@
 //
 // What bounds it.  A wave of 64 x 64 asks for twice the LDS bytes per product that its matrix instructions can wait for, so the large tiles are 128 x 64 a
 // wave; a compute unit runs eight such waves, and as the parts of a gradient (and the scratch memory that holds them) are limited,
-// they share one 256 x 128 tile, two groups of four waves that multiply every second 32 positions and add their sums at the end.  Without
-// its loads the kernel takes 104 us of the 130 that 256->256 3x3 at 14x14, 512 images, takes (8 of them the sum of the parts): the
-// matrix cores with the transposing reads, 1650 TFLOP/s at the clock they leave.  Address arithmetic and loads stand among the matrix
-// instructions (behind a barrier, before them: 148 us).
+// they share one 256 x 128 tile, two groups of four waves that multiply every second 32 positions and add their sums at the end.  256->256 3x3 at
+// 14x14, 512 images, takes 121 us with the sum of the parts (980 TFLOP/s), 96 (1230) where only the first chunks are loaded and then
+// multiplied again and again: the matrix cores with the transposing reads, the epilogue and the sum (matrix instructions alone, in a loop on such
+// data, hold 1650 to 1840).  Address arithmetic and loads stand among the matrix instructions (behind a barrier, before them: 148 us for 130).
 // Against 128 x 128 tiles of 64 x 64 a wave, transposed in registers on their way into LDS (us, with the sum of the parts):
 // 256->256 3x3 at 14x14, 512 images 192 -> 131; 512->512 3x3 at 7x7, 512 images 202 -> 133; 64->64 3x3 at 56x56, 128 images 106 -> 54;
 // 512->128 1x1 at 28x28, 256 images 64 -> 60 (56 at the copy rate); 512->512 3x3 at 7x7, 16 images 26.4 -> 12.3.

@@ -1035,8 +1035,17 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
     (void)hipGetLastError();
   };
   // Little to swap: offloads and prefetches in the compute stream, in the order of the list (whose every wait is for something before
-  // it), without an event for each.  The input comes on the swap-in stream either way: a caller may have prepared it there.
+  // it), without an event for each.  So does the input, unless the swap-in stream still has work of the caller's, who may be preparing it there:
+  // then it is loaded behind that work, and the compute stream waits (20 us of the 410 that a bottleneck block, two images, takes).
   const bool one_stream = c->copies_in_order;
+  bool load_in_order = false;
+  if (one_stream && !c->calibrating) {
+    const hipError_t idle = hipStreamQuery(c->s_i);
+    if (idle != hipSuccess && idle != hipErrorNotReady) return c->hipfail(idle, "hipStreamQuery(swap-in)");
+    load_in_order = idle == hipSuccess;
+    if (!load_in_order) (void)hipGetLastError();
+  }
+  const hipStream_t s_load = load_in_order ? c->s_c : c->s_i;
   const hipStream_t s_out = one_stream ? c->s_c : c->s_o, s_in = one_stream ? c->s_c : c->s_i;
   int load_issued = -1;      // one_stream: the last input load that the compute stream does not wait for yet
   int n_compute = 0;
@@ -1068,10 +1077,11 @@ extern "C" int acc_train_step(acc_ctx* c, const float* images, int images_loc, c
         } else if (in.arg == g.t_stage) {
           const size_t bytes = (size_t)P.k * g.in_c * g.in_h * g.in_w * sizeof(float);
           HIPCHK(c, hipMemcpyAsync(dst, images, bytes,
-                                   images_loc == ACC_LOC_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, c->s_i));
+                                   images_loc == ACC_LOC_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s_load));
         } else {
-          HIPCHK(c, hipMemcpyAsync(dst, labels, (size_t)P.k * sizeof(int32_t), hipMemcpyHostToDevice, c->s_i));
+          HIPCHK(c, hipMemcpyAsync(dst, labels, (size_t)P.k * sizeof(int32_t), hipMemcpyHostToDevice, s_load));
         }
+        if (load_in_order) break;
         if (one_stream) load_issued = in.seq;
         else HIPCHK(c, hipEventRecord(c->ev_h2d[in.seq], c->s_i));
         break;

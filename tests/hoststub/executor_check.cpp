@@ -133,27 +133,30 @@ int main(int argc, char** argv) {
       steps(2, "step");
     }
   } else if (scenario == "small_swaps") {
-    // which stream carries the copies: on either side of the line, the same with and without event timing, the input always on
-    // the swap-in stream
+    // which stream carries the copies: on either side of the line, the same with and without event timing; the input in the compute stream
+    // only where that carries the rest, too, and the caller has nothing queued on the swap-in stream
     struct { int k, maps, in_order; } cases[] = {{2, 9, 1}, {2, 8, 1}, {2, 7, 0}, {2, 1, 0}, {4, 9, 1}, {8, 9, 0}, {8, 8, 0}, {2, 9, 1}, {2, 0, 0}};
     for (const auto& q : cases) {
       std::vector<uint8_t> swap(9, 0);
       for (int i = 0; i < q.maps; ++i) swap[i] = 1;
       if (acc_plan_explicit(c, q.k, budget, swap.data(), 9, &s) != ACC_OK) { rc = fail("plan", c); break; }
-      for (int level : {0, 1, 2, 3, 0}) {
+      for (int level : {0, 1, 2, 3, 0}) for (int busy : {0, 1}) {
         acc_set_profiling(c, level);
+        stub_set_busy(st[2], busy);
         const StubCounters before = stub_counters();
         steps(1, "step");
         const StubCounters& now = stub_counters();
         acc_stats st2;
         acc_get_stats(c, &st2);
         const long on_c = now.copies_on[0] - before.copies_on[0], on_o = now.copies_on[1] - before.copies_on[1], on_i = now.copies_on[2] - before.copies_on[2];
-        const long n = q.maps;
-        const bool ok = st2.copies_in_order == q.in_order && on_c == (q.in_order ? 2 * n + 1 : 1) && on_o == (q.in_order ? 0 : n) && on_i == (q.in_order ? 2 : n + 2);
-        printf("k=%d maps %d (%.3f MiB) level %d: in order %d, copies on compute %ld out %ld in %ld%s\n", q.k, q.maps, s.bytes_swapped / 1048576.0, level,
-               st2.copies_in_order, on_c, on_o, on_i, ok ? "" : "  WRONG");
+        const long n = q.maps, in_c = q.in_order && !busy ? 2 : 0;
+        const bool ok = st2.copies_in_order == q.in_order && on_c == (q.in_order ? 2 * n + 1 : 1) + in_c && on_o == (q.in_order ? 0 : n) &&
+                        on_i == (q.in_order ? 0 : n) + 2 - in_c;
+        printf("k=%d maps %d (%.3f MiB) level %d busy %d: in order %d, copies on compute %ld out %ld in %ld%s\n", q.k, q.maps, s.bytes_swapped / 1048576.0, level,
+               busy, st2.copies_in_order, on_c, on_o, on_i, ok ? "" : "  WRONG");
         if (!ok) rc = 1;
       }
+      stub_set_busy(st[2], false);
       acc_set_profiling(c, 0);
     }
   } else if (scenario == "bf16_filters") {

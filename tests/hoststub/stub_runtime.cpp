@@ -21,7 +21,7 @@
 #include "../../paper_1901_06773_amd/csrc/kernels.h"
 #include "stub_runtime.h"
 
-struct stub_stream { int id; long ops; };
+struct stub_stream { int id; long ops; bool busy = false; };
 struct stub_event { unsigned flags; int epoch; long records; stub_stream* on; };
 
 namespace {
@@ -76,6 +76,7 @@ void stub_new_epoch() {
 }
 hipStream_t stub_make_stream(int id) { return new stub_stream{id, 0}; }
 void stub_free_stream(hipStream_t s) { delete s; }
+void stub_set_busy(hipStream_t s, bool busy) { s->busy = busy; }
 long stub_live_events() { return (long)g_events.size(); }
 
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags) {
@@ -131,6 +132,11 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   if (!s) ++g.null_streams;
   if (g_capture) { ++g.sync_in_capture; complain("hipStreamSynchronize while a stream is capturing"); }
   return hipSuccess;
+}
+hipError_t hipStreamQuery(hipStream_t s) {
+  if (!s) ++g.null_streams;
+  if (g_capture) { ++g.sync_in_capture; complain("hipStreamQuery while a stream is capturing"); }
+  return s && s->busy ? hipErrorNotReady : hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t s) {
   if (!s) { ++g.null_streams; complain("hipMemcpyAsync on the null stream"); }

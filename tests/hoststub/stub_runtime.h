@@ -20,5 +20,6 @@ void stub_set_regions(void* pool, size_t pool_bytes, void* arena, size_t arena_b
 void stub_set_static(size_t bytes);   // of the pool: from there on filters are copies, and somebody must have written them
 void stub_new_epoch();            // call before every iteration: waits must find records of this epoch
 hipStream_t stub_make_stream(int id);
+void stub_set_busy(hipStream_t s, bool busy);   // hipStreamQuery finds work of the caller's on it
 void stub_free_stream(hipStream_t s);
 long stub_live_events();

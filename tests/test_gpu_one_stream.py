@@ -1,7 +1,7 @@
 """Iterations that swap eight maps or more, of at most 1.25 MiB in all, issue their copies in the compute stream, others on streams of their own
 with events: on both sides of both lines a swapped iteration has the bits of the resident one, also where every byte that is not alive holds a
 NaN pattern and where steps and copies are timed, with weight gradients on their own stream or not, and where plans of both kinds follow each
-other in one context.  The input comes on the swap-in stream either way."""
+other in one context.  The input comes behind what the caller has queued on the swap-in stream either way."""
 import pytest
 import torch
 
