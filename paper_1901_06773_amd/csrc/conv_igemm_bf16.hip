@@ -628,11 +628,16 @@ constexpr Kind kKinds[KINDS] = {
     {"igemm_bf16 32x32, eight waves", 32, 32, 8, 32, 1, 0.0, 3.255, 0.543, 1.221, 0.487, 0.520, 0.271, 2.084},
 };
 // Tiles of 256 x 256 take a compute unit each, and in their last round most units may have none (392 tiles: 256 and 136).  The rows that don't
-// fill a round run behind the others as tiles of 192 or 64 rows in the same launch, where that makes the rounds fewer, a round of 192 rows
+// fill a round run behind the others as tiles of 192 or 64 rows in the same launch, where that saves 3 % of the rounds or more, a round of 192 rows
 // counted as 0.8 of one of 256, one of 64 as 0.4 (the half of the chip that runs a part round runs it faster).  us, 256 x 256
-// alone -> with lower tiles: 256->256 3x3 at 14x14, 512 images (256 + 182 x 192) 123 -> 114, at 28x28, 200 images (256 + 476 x 192) 185 -> 170;
-// 128->256 3x3 at 28x28, 256 images (256 + 704 x 192) 140 -> 127; 1024->512 1x1 at 28x28, 128 images (768 + 64 x 64) 131 -> 123;
-// layers that wait for memory gain nothing and keep one height.
+// alone -> with lower tiles: 256->256 3x3 at 14x14, 512 images (256 + 182 x 192) 113 -> 106, at 28x28, 200 images (256 + 476 x 192) 173 -> 157;
+// 128->256 3x3 at 28x28, 256 images (768 + 64 x 64) 130 -> 118; 1024->512 1x1 at 28x28, 128 images (768 + 64 x 64) 127 -> 116.
+// Measured with every split of up to four rounds on 299 forward launches of 2 to 47 rounds (layers of the ResNets at minibatches of 32 to 512,
+// random 1x1 and 3x3 ones): 214 are split, 1.09 times as fast on average (0.96 once, else 1.001 to 1.26), and all within 0.7 % of the best split on
+// average, 6 % at most.  Splits that save less than 3 % gained 0.5 % on average and lost up to 4 (85 launches, 20 slower: long launches drift apart
+// and have no last round).  The weights may lie anywhere from 0.7 and 0.3 to 0.8 and 0.45; below 0.78, three rounds of 192 come before two
+// of 256 and one of 64: 51 launches differ, 0.95 to 1.06, by nothing on average.
+// Layers that wait for memory keep one height (22 of them would be 1.06 times as fast with lower tiles, 0.97 to 1.17).
 struct Heights {
   int low, rows;                                         // height of the lower tiles (0: none), rows of the higher ones
   double rounds;
@@ -647,7 +652,7 @@ Heights heights(long M, long N) {
     if (r192 <= 3 && full + 0.8 * r192 < best.rounds - 0.05) best = Heights{192, (int)rows, full + 0.8 * r192};
     if (r64 == 1 && full + 0.4 < best.rounds - 0.05) best = Heights{64, (int)rows, full + 0.4};
   }
-  return best;
+  return best.rounds > 0.97 * (double)plain ? Heights{0, 0, (double)plain} : best;
 }
 double memory_us(const Kind& k, const ConvGeom& g, long M, long K) {
   // pixels that are read: all of the input, or, by strided filters smaller than their stride, those under a tap; chunks of 32 values (half

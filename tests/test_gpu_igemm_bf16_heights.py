@@ -33,10 +33,18 @@ def test_routes(case):
 
 
 def test_routes_one_height():
-    # a round that is full, less than one round, results that wait for memory
-    for case in ((128, 16, 32, 128, 256, 3), (60, 32, 32, 128, 256, 3), (128, 56, 56, 64, 256, 1)):
+    # a round that is full, less than one round, results that wait for memory, fewer than 3 % of many rounds saved
+    for case in ((128, 16, 32, 128, 256, 3), (60, 32, 32, 128, 256, 3), (128, 56, 56, 64, 256, 1), (164, 54, 52, 1024, 768, 1),
+                 (164, 42, 44, 1024, 1208, 1)):
         n, h, w, c, m, r = case
         assert B().op_conv_kernel("fwd", n, h, w, c, m, r, 1, r // 2, B().BF16) == "igemm_bf16 256x256", case
+
+
+def test_routes_of_measured_layers():
+    for case, low in (((512, 14, 14, 256, 256, 3), 192), ((200, 28, 28, 256, 256, 3), 192), ((256, 28, 28, 128, 256, 3), 64),
+                      ((128, 28, 28, 1024, 512, 1), 64)):
+        n, h, w, c, m, r = case
+        assert B().op_conv_kernel("fwd", n, h, w, c, m, r, 1, r // 2, B().BF16) == name(low), case
 
 
 @pytest.mark.gpu
